@@ -210,7 +210,7 @@ static fate_status layer_decode_checked(void* stream, const fate_ffn_desc* d, co
     a.r = FusedRouteArgs{static_cast<const uint16_t*>(x_bf16), static_cast<const uint16_t*>(Wg_bf16), bias,
                          static_cast<const uint16_t*>(Wg_next_bf16), bias_next, d->N, d->H, d->E, d->k, m,
                          renorm != 0, out->topk_ids, out->topk_w, out->pred_ids, out->pred_w, out->pred_pop,
-                         out->counts, out->offsets, out->perm, out->inv_perm, out->expert_order, nullptr};
+                         out->counts, out->offsets, out->perm, out->inv_perm, out->expert_order};
     a.zq = reinterpret_cast<unsigned long long*>(base + w.zq);
     a.experts = experts_dev; a.shared = shared_dev; a.n_shared = d->n_shared;
     a.shared_gate = static_cast<const uint16_t*>(shared_gate_bf16);

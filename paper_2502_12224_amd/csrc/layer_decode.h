@@ -14,7 +14,7 @@ constexpr int kLayerMaxP = 64;                  // (token, expert) pairs per cal
 constexpr int kLayerMaxParts = 16;              // one-token kernel: down blocks per output row block
 
 struct LayerArgs {
-    FusedRouteArgs r;              // x, gates, sizes, routing outputs (its zbuf is not used)
+    FusedRouteArgs r;              // x, gates, sizes, routing outputs
     unsigned long long* zq;        // [2][N][E] logits, each tagged with the call's epoch in the high word
     const fate_qexpert* experts;
     const fate_qexpert* shared;

@@ -1,15 +1,10 @@
 // Gate routing, cross-layer prediction, permutation: kernels and C entry points.
 //
-// fate_gate_route / fate_cross_layer_predict: one wavefront per token row.
-// The wave keeps its token rows in LDS, streams the gate matrix (L2
-// resident) row by row, reduces each logit with wavefront shuffles, then
-// does the softmax and the top-m selection in registers.
+// fate_gate_route / fate_cross_layer_predict: a workgroup per token (decode-sized calls and
+// hidden sizes that are no multiple of 1024) or the gate as a GEMM on the matrix cores.
 //
-// fate_route_fused: decode-side variant.  With a handful of tokens the gate
-// matrices (2 x E rows) are the only sizeable data, so one wave takes one gate
-// row for all tokens and the rows are spread over the chip; the workgroup
-// that finishes last (ticket counter) does softmax, selection, popularity
-// and the permutation for all tokens.
+// fate_route_fused, up to 16 tokens: a workgroup per (token, gate), the last one to leave does
+// popularity and permutation; prefill sizes: both gates in one GEMM launch, then the permutation.
 #include "common.h"
 #include "route_device.h"
 
@@ -20,50 +15,86 @@ __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-// 4 waves per block, TPW token rows per wave.
+// Logits of TPW tokens (rows xr) for every expert into z [TPW][E] (LDS), by a whole workgroup of
+// kTokWaves waves; wave w takes experts w, w + kTokWaves, .., four at a time, so that up to 16 rows
+// of 1 KiB are requested before the first is used.  Rows past the last expert read row 0.
+// A lane sums columns lane*8 + 512*j in order, then the lanes add up: the same bits for a
+// (token, expert) whichever workgroup, batch size or call evaluates it.
+constexpr int kTokWaves = 16;
 template <int TPW>
-__global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restrict__ x,
-                                                         const uint16_t* __restrict__ Wg,
-                                                         const float* __restrict__ bias, int N, int H, int E,
-                                                         int m, int renorm, int32_t* __restrict__ ids,
-                                                         float* __restrict__ w, float* __restrict__ probs,
-                                                         int32_t* __restrict__ pop) {
-    extern __shared__ uint4 smem[];
+__device__ __forceinline__ void token_logits(const uint4* __restrict__ x, const uint4* __restrict__ Wg,
+                                             const float* __restrict__ bias, int ntok, int nvec, int E, float* z) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nvec = H >> 3;
-    const int tok0 = (blockIdx.x * 4 + wave) * TPW;
-    uint4* xw = smem + (size_t)wave * TPW * nvec;
-    float* zw = reinterpret_cast<float*>(smem + (size_t)4 * TPW * nvec) + (size_t)wave * TPW * E;
+    constexpr int NE = 4, NJ = TPW == 1 ? 4 : 2;       // operands of one batch: within the 128 registers of 16 waves
+    for (int e0 = wave; e0 < E; e0 += kTokWaves * NE) {
+        float acc[NE][TPW];
+        const uint4* wr[NE];
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int e = e0 + kTokWaves * i;
+            wr[i] = Wg + (size_t)(e < E ? e : 0) * nvec;
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) acc[i][t] = 0.f;
+        }
+        for (int c0 = lane; c0 < nvec; c0 += 64 * NJ) {
+            uint4 wv[NJ][NE], xv[NJ][TPW];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int c = c0 + 64 * j;
+                const bool in = c < nvec;
+                const int cc = in ? c : lane;
+#pragma unroll
+                for (int i = 0; i < NE; ++i) wv[j][i] = wr[i][cc];
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    // columns past the row: the activations are zero there, which leaves the sums as they are
+                    const uint4 v = x[(size_t)(t < ntok ? t : 0) * nvec + cc];
+                    xv[j][t] = in ? v : make_uint4(0, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int i = 0; i < NE; ++i)
+#pragma unroll
+                    for (int t = 0; t < TPW; ++t) acc[i][t] = dot8_bf16(xv[j][t], wv[j][i], acc[i][t]);
+        }
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int e = e0 + kTokWaves * i;
+            if (e < E) {
+                const float b = bias ? bias[e] : 0.f;
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    const float s = wave_sum(acc[i][t]);
+                    if (lane == 0) z[t * E + e] = s + b;
+                }
+            }
+        }
+    }
+}
 
-    for (int t = 0; t < TPW; ++t) {
-        int tok = tok0 + t;
-        const uint4* xr = reinterpret_cast<const uint4*>(x) + (size_t)tok * nvec;
-        for (int c = lane; c < nvec; c += 64) xw[t * nvec + c] = (tok < N) ? xr[c] : make_uint4(0, 0, 0, 0);
-    }
+// A workgroup of 16 waves per TPW tokens.  A decode-sized call is a handful of dependent memory
+// round trips, so a token gets a whole compute unit: the gate matrix (a few hundred KB, from L2
+// after the first workgroup) is requested at once by 16 waves.  48 tokens, E = 64, H = 2048:
+// 9.5 us (one wave per token, rows one after the other: 109 us).
+template <int TPW>
+__global__ __launch_bounds__(64 * kTokWaves) void route_rows_kernel(const uint16_t* __restrict__ x,
+                                                                    const uint16_t* __restrict__ Wg,
+                                                                    const float* __restrict__ bias, int N, int H, int E,
+                                                                    int m, int renorm, int32_t* __restrict__ ids,
+                                                                    float* __restrict__ w, float* __restrict__ probs,
+                                                                    int32_t* __restrict__ pop) {
+    __shared__ float z[TPW * kMaxE];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nvec = H >> 3, tok0 = blockIdx.x * TPW, ntok = min(TPW, N - tok0);
+    token_logits<TPW>(reinterpret_cast<const uint4*>(x) + (size_t)tok0 * nvec, reinterpret_cast<const uint4*>(Wg), bias,
+                      ntok, nvec, E, z);
     __syncthreads();
-    for (int e = 0; e < E; ++e) {
-        float acc[TPW];
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) acc[t] = 0.f;
-        const uint4* wr = reinterpret_cast<const uint4*>(Wg) + (size_t)e * nvec;
-        for (int c = lane; c < nvec; c += 64) {
-            uint4 wv = wr[c];
-#pragma unroll
-            for (int t = 0; t < TPW; ++t) acc[t] = dot8_bf16(xw[t * nvec + c], wv, acc[t]);
-        }
-        float b = bias ? bias[e] : 0.f;
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-            float s = wave_sum(acc[t]);
-            if (lane == 0) zw[t * E + e] = s + b;
-        }
-    }
-    __syncthreads();
-    for (int t = 0; t < TPW; ++t) {
-        int tok = tok0 + t;
-        if (tok < N)
-            wave_softmax_topm(zw + t * E, E, m, renorm, ids + (size_t)tok * m, w + (size_t)tok * m,
-                              probs ? probs + (size_t)tok * E : nullptr, pop);
+    if (wave < ntok) {
+        const int tok = tok0 + wave;
+        wave_softmax_topm(z + wave * E, E, m, renorm, ids + (size_t)tok * m, w + (size_t)tok * m,
+                          probs ? probs + (size_t)tok * E : nullptr, pop);
     }
 }
 
@@ -206,20 +237,53 @@ __global__ __launch_bounds__(1024) void permute_kernel(const int32_t* __restrict
 }
 
 // ---- fused decode-side routing --------------------------------------------
-// workspace: [0] ticket counter (int32, zero between calls), then at byte 256
-// the logits zbuf[2][N][E] fp32.
-__global__ __launch_bounds__(256) void route_fused_kernel(FusedRouteArgs a, int32_t* ticket) {
-    __shared__ FusedRouteSmem sm;
+// grid (N, gates): a workgroup evaluates one gate for one token as route_rows_kernel does (same
+// bits) and selects; what the permutation and the popularity need goes out with device-scope
+// stores, and the workgroup that leaves last (ticket counter at the start of the workspace, zero
+// between calls) adds them up.  13 tokens, E = 60, H = 2048: 16 us (a wave per gate row for all
+// tokens, then every selection in the last workgroup: 52 us).
+__global__ __launch_bounds__(64 * kTokWaves) void route_fused_kernel(FusedRouteArgs a, int32_t* ticket) {
+    __shared__ float z[kMaxE];
+    __shared__ int32_t sel[kMaxM];
+    __shared__ float selw[kMaxM];
+    __shared__ int32_t all[kFusedMaxN * kMaxM];
+    __shared__ int32_t pop[kMaxE];
     __shared__ int32_t sm_perm[kPermSmemInts];
     __shared__ int sm_last;
-    fused_gate_rows(a, blockIdx.x, ZbufStore{a.zbuf, a.N, a.E});
-    wait_own_stores();      // this wave's device-scope logit stores have been acknowledged
-    __syncthreads();        // ... and so have every other wave's
-    if (threadIdx.x == 0) sm_last = (atomicAdd(ticket, 1) == (int)gridDim.x - 1);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t = blockIdx.x, g = blockIdx.y, nvec = a.H >> 3, E = a.E;
+    token_logits<1>(reinterpret_cast<const uint4*>(a.x) + (size_t)t * nvec, reinterpret_cast<const uint4*>(g ? a.Wg2 : a.Wg),
+                    g ? a.bias2 : a.bias, 1, nvec, E, z);
+    __syncthreads();
+    const int m = g ? a.m : a.k;
+    if (wave == 0) {
+        wave_softmax_topm(z, E, m, g ? 0 : a.renorm, sel, selw, nullptr, nullptr);
+        __builtin_amdgcn_wave_barrier();
+        if (tid < m) {
+            st_dev((g ? a.pids : a.ids) + (size_t)t * m + tid, sel[tid]);
+            (g ? a.pw : a.w)[(size_t)t * m + tid] = selw[tid];
+        }
+        wait_own_stores();      // the ids have been acknowledged before the ticket counts this workgroup
+        if (tid == 0) sm_last = (atomicAdd(ticket, 1) == (int)(gridDim.x * gridDim.y) - 1);
+    }
     __syncthreads();
     if (!sm_last) return;
-    fused_select(a, sm, sm_perm, ZbufLoad{a.zbuf, a.N, a.E});
-    if (threadIdx.x == 0) *ticket = 0;
+    const int P = a.N * a.k;
+    if (a.Wg2) {
+        for (int i = tid; i < E; i += 64 * kTokWaves) pop[i] = 0;
+        __syncthreads();
+        for (int i = tid; i < a.N * a.m; i += 64 * kTokWaves) atomicAdd(&pop[ld_dev(a.pids + i)], 1);
+    }
+    for (int i = tid; i < P; i += 64 * kTokWaves) all[i] = ld_dev(a.ids + i);
+    __syncthreads();
+    if (a.Wg2)
+        for (int i = tid; i < E; i += 64 * kTokWaves) a.pop[i] = pop[i];
+    if (P <= 64) {
+        if (wave == 0) wave_permute_small(all, P, E, a.counts, a.offsets, a.perm, a.inv_perm, a.order);
+    } else {
+        block_permute(all, P, E, a.counts, a.offsets, a.perm, a.inv_perm, a.order, sm_perm);
+    }
+    if (tid == 0) *ticket = 0;
 }
 
 static fate_status check_route_args(const void* x, const void* Wg, const float* bias, int N, int H, int E, int k,
@@ -236,13 +300,6 @@ static fate_status check_route_args(const void* x, const void* Wg, const float* 
     FATE_CHECK_PTR(ids);
     FATE_CHECK_PTR(w);
     return FATE_OK;
-}
-
-static int pick_tpw(int N, int H, int E) {
-    if (N < 256) return 1;
-    for (int tpw = 4; tpw > 1; tpw >>= 1)
-        if ((size_t)4 * tpw * (2 * (size_t)H + 4 * (size_t)E) <= 65536) return tpw;
-    return 1;
 }
 
 // tokens per workgroup of the gate GEMM: enough workgroups for the device before the tile is
@@ -274,15 +331,11 @@ static fate_status launch_route_rows(hipStream_t st, const void* x, const void* 
     auto ws = static_cast<const uint16_t*>(Wg);
     if (N >= 64 && H % 1024 == 0)     // prefill-sized batches: gate GEMM on the matrix cores
         return launch_route_mfma(st, x, Wg, bias, N, H, E, m, renorm, ids, w, probs, pop, RouteSecond{}, 1);
-    const int tpw = pick_tpw(N, H, E);
-    const size_t lds = (size_t)4 * tpw * (2 * (size_t)H + 4 * (size_t)E);
-    if (lds > 65536) FATE_FAIL(FATE_ESHAPE, "H = %d, E = %d need %zu bytes of LDS (> 64 KiB)", H, E, lds);
-    const int grid = (N + 4 * tpw - 1) / (4 * tpw);
-    switch (tpw) {
-        case 4: route_rows_kernel<4><<<grid, 256, lds, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop); break;
-        case 2: route_rows_kernel<2><<<grid, 256, lds, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop); break;
-        default: route_rows_kernel<1><<<grid, 256, lds, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop); break;
-    }
+    // four tokens per workgroup share the gate rows once one token each would be several rounds of workgroups
+    if (N >= 1024)
+        route_rows_kernel<4><<<(N + 3) / 4, 64 * kTokWaves, 0, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop);
+    else
+        route_rows_kernel<1><<<N, 64 * kTokWaves, 0, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop);
     FATE_HIP(hipGetLastError());
     return FATE_OK;
 }
@@ -378,13 +431,11 @@ extern "C" fate_status fate_route_fused(void* stream, const void* x_bf16, const 
         FATE_HIP(hipGetLastError());
         return FATE_OK;
     }
-    const int nrows = Wg_next_bf16 ? 2 * E : E;
-    const int grid = (nrows + 3) / 4;
     FusedRouteArgs a{static_cast<const uint16_t*>(x_bf16), static_cast<const uint16_t*>(Wg_bf16), bias,
                      static_cast<const uint16_t*>(Wg_next_bf16), bias_next, N, H, E, k, m, renorm != 0,
-                     topk_ids, topk_w, pred_ids, pred_w, pred_pop, counts, offsets, perm, inv_perm, expert_order,
-                     reinterpret_cast<float*>(static_cast<char*>(workspace) + 256)};
-    route_fused_kernel<<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a, static_cast<int32_t*>(workspace));
+                     topk_ids, topk_w, pred_ids, pred_w, pred_pop, counts, offsets, perm, inv_perm, expert_order};
+    route_fused_kernel<<<dim3(N, Wg_next_bf16 ? 2 : 1), 64 * kTokWaves, 0, static_cast<hipStream_t>(stream)>>>(
+        a, static_cast<int32_t*>(workspace));
     FATE_HIP(hipGetLastError());
     return FATE_OK;
 }

@@ -529,28 +529,12 @@ struct FusedRouteArgs {
     int N, H, E, k, m, renorm;
     int32_t* ids; float* w; int32_t* pids; float* pw; int32_t* pop;
     int32_t* counts; int32_t* offsets; int32_t* perm; int32_t* inv_perm; int32_t* order;
-    float* zbuf;                                  // [2][N][E] logits
 };
 
 struct FusedRouteSmem {
     float z[8][kMaxE];                            // one row per wave of the workgroup (at most 8)
     int32_t ids[kFusedMaxN * kMaxM];
     int32_t pop[kMaxE];
-};
-
-// Logits go through device-scope stores / loads: the selecting workgroup may
-// sit on another compute die than the one that produced a logit.
-struct ZbufStore {
-    float* zbuf; int N, E;
-    __device__ __forceinline__ void operator()(int g, int t, int e, float v) const {
-        st_dev(zbuf + ((size_t)g * N + t) * E + e, v);
-    }
-};
-struct ZbufLoad {
-    const float* zbuf; int N, E;
-    __device__ __forceinline__ float operator()(int g, int t, int e) const {
-        return ld_dev(zbuf + ((size_t)g * N + t) * E + e);
-    }
 };
 
 // Workgroup `rblock` of ceil(rows / waves-per-workgroup): each of its waves
