@@ -516,7 +516,7 @@ def bench_prefill(args, emit=True):
                    "experts_active_per_layer": active, "prefill_set_accuracy": set_acc,
                    "prediction_accuracy_topk_per_token": tok_acc, "near_tie_rows": near_ties, "routed_rows": N * L,
                    "cache_hit_rate": hits / max(1, hits + misses)},
-        "roofline": {"bound": "mfma", "kernel": "prefill_prep_kernel + grouped_gemm_kernel<2>", "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": "prefill_prep_kernel + grouped_gemm_kernel<true>", "achieved": achieved,
                      "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MFMA_PEAK_TFLOPS,
                      "traffic": measured_traffic(f"prefill_{args.workload}_traffic.txt"),
                      "flops_per_launch": up_flops, "us_per_launch": up_us,

@@ -57,8 +57,10 @@ static void carve(const fate_ffn_desc& d, void* base, FfnWorkspace* w) {
         w->ms.sgate = reinterpret_cast<float*>(p + off); off += align_up((size_t)d.N * 4, 256);
         w->ms.tab_up = reinterpret_cast<int32_t*>(p + off); off += align_up(nseg1 * 4, 256);
         w->ms.tab_down = reinterpret_cast<int32_t*>(p + off); off += align_up(nseg1 * 4, 256);
-        w->ms.yp_r = reinterpret_cast<__half*>(p + off); off += align_up((size_t)d.N * d.k * d.H * 2, 256);
-        w->ms.yp_s = reinterpret_cast<__half*>(p + off); off += align_up((size_t)d.n_shared * d.N * d.H * 2, 256);
+        int kp_r = 1, kp_s = 1;
+        mfma_k_parts(d, &kp_r, &kp_s);
+        w->ms.yp_r = reinterpret_cast<__half*>(p + off); off += align_up((size_t)kp_r * d.N * d.k * d.H * 2, 256);
+        w->ms.yp_s = reinterpret_cast<__half*>(p + off); off += align_up((size_t)kp_s * d.n_shared * d.N * d.H * 2, 256);
     }
     w->bytes = off + 256;
 }

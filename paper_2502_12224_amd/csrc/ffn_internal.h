@@ -35,8 +35,8 @@ struct MfmaScratch {
     float* sgate;      // [N] shared gate values
     int32_t* tab_up;   // [E + n_shared + 1] tile prefix sums of the up GEMM
     int32_t* tab_down; // same for the down GEMM
-    __half* yp_r;      // [P,H] per-pair outputs of the down GEMM
-    __half* yp_s;      // [n_shared*N,H]
+    __half* yp_r;      // [kp_r][P,H] per-pair outputs of the down GEMM
+    __half* yp_s;      // [kp_s][n_shared*N,H]
 };
 
 struct FfnWorkspace {
@@ -60,6 +60,8 @@ struct PartSel {
 };
 inline PartSel part_all() { return PartSel{{~0ull, ~0ull, ~0ull, ~0ull}, 1, 1}; }
 
+// parts of the reduction dimension of the down GEMM of routed / shared experts
+void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s);
 // phase: 0 = whole FFN, 1 = prep + up/gate GEMM only, 2 = down GEMM + combine only (timing aid)
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs a, const MfmaScratch& ms,
                             void* y_out, int phase, const PartSel& sel);

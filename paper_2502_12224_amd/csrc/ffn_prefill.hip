@@ -4,71 +4,74 @@
 //   prep     x (bf16) -> fp16 copy, shared-expert gate values, and the tile
 //            tables (prefix sums of tiles per expert segment) of both GEMMs;
 //   up       grouped GEMM  h = silu(X W1^T) * (X W3^T)   -> fp16 [rows, I]
-//   down     grouped GEMM  Yp = h W2^T                     -> fp16 [rows, H]
+//   down     grouped GEMM  Yp = h W2^T                     -> fp16 [K parts][rows, H]
 //   combine  y[t] = sum_j w[t,j] Yp[inv_perm[t*k+j]] + sum_s g_s(t) Yp_s[t]
 // Rows are (token, expert) pairs in the sorted order of the permutation, so
 // an expert's rows are contiguous; shared experts are extra segments of N rows.
 //
-// GEMM tile: a workgroup of four waves owns 64 rows x 128 weight rows; each
-// wave owns 32 weight rows (one device-native tile row-block) and all 64
-// rows; two workgroups share a compute unit (two waves per SIMD), so that one
-// wave's dequantisation and LDS reads run under the other's matrix products
-// (128-row tiles at one wave per SIMD left the matrix pipe idle 78 % of the time).  Activations go through LDS in chunks of 128 columns; weights go
-// straight from global memory into registers in their tile layout (one
-// contiguous KiB per wave load) and are dequantised there to fp16
-// (exact code, one rounding in code*scale), which is the B operand of
-// v_mfma_f32_32x32x16_f16.  Accumulation is fp32.
+// GEMM tile: a workgroup of four waves owns up to 128 rows and, per wave, two
+// 32-row blocks of weights (the same block of W1 and W3, or two neighbouring
+// blocks of W2): 8 accumulators of 32x32, so that a dequantised operand serves
+// four matrix products.  Two workgroups share a compute unit.
+// Everything the loop reads - activations, raw codes, scales - travels from
+// memory to LDS without passing through registers (global_load_lds), in a
+// ring of stages of 64 columns (128 for int2); the waits count the loads that
+// may still be in flight, so the stages ahead are never drained.  A wave
+// dequantises its own codes from LDS into the A operand of
+// v_mfma_f32_32x32x16_f16 (exact code, one rounding in code*scale) and
+// multiplies them with the workgroup's activation rows; accumulation is fp32.
+// Full tiles (128 rows) run at what the chip's power limit leaves of the matrix pipe: products
+// issue every 22 ns per SIMD (1.5 PFLOP/s at 1.5 to 1.6 GHz), and a stage of two paired waves is 87 %
+// products.  Measured (before: 64-row tiles, codes in registers): up 1125 -> 835 us and down
+// 645 -> 479 us at 2048 rows of the Mixtral shape (E = 8, H = 4096, I = 14336), 271 -> 200 and
+// 148 -> 119 us at 2048 tokens of the Qwen shape.  Tiles of at most 32 rows are bounded by the
+// wave's own vector instructions (about 1250 cycles per stage).
 #include <hip/hip_fp16.h>
 #include <algorithm>
+#include <type_traits>
 #include "common.h"
 #include "qformat.h"
 #include "ffn_internal.h"
 
 namespace fate {
 
-typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2v_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kBMUp = 64;           // rows per workgroup tile of the up GEMM (two matrices)
-constexpr int kBMDown = 64;         // rows per workgroup tile of the down GEMM
-constexpr int kBN = 128;            // weight rows per workgroup tile (4 waves x 32)
-constexpr int kKC = 128;            // columns per LDS chunk
-constexpr int kLdsRow = kKC + 8;    // halves per LDS row (16-byte pad against bank conflicts)
-constexpr int kWRing = 2;           // chunks of weights in flight per wave
-
-// Workgroup barrier that orders LDS traffic only: __syncthreads() would also wait for the
-// weight tiles that are meant to stay in flight across it.
-__device__ __forceinline__ void lds_only_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-#if defined(__HIP_DEVICE_COMPILE__)
-#define FATE_GLOBAL __attribute__((address_space(1)))
-#else
-#define FATE_GLOBAL
-#endif
-typedef const FATE_GLOBAL uint4* gu4p_t;
-typedef const FATE_GLOBAL uint16_t* gu16p_t;
+constexpr int kBM = 128;            // most rows of a workgroup tile
+constexpr int kBNUp = 128;          // weight rows per workgroup tile of the up GEMM (of each matrix)
+constexpr int kBNDown = 256;        // weight rows per workgroup tile of the down GEMM
+constexpr int kKQ = 128;            // H and I must be multiples of this
+constexpr int kGemmLds = 80 * 1024; // two workgroups per compute unit
+constexpr int kGemmSlots = 2 * 256; // workgroups the device holds at once
 
 struct GemmArgs {
     const __half* A_r; int lda_r;      // activations fp16 of routed segments
     const __half* A_s; int lda_s;      // activations fp16 of shared segments
     int H;                             // hidden size
-    int mode;                          // 0 = up (two matrices + SwiGLU, K = H), 1 = down (K = I of the expert)
     const fate_qexpert* experts; const fate_qexpert* shared;
     int E, n_shared, N, k;
-    const int32_t* offsets; const int32_t* perm;
+    const int32_t* offsets; const int32_t* perm; const int32_t* order;
     const int32_t* tile_start;         // [E + n_shared + 1]
     __half* out_r; int ldo_r;          // routed rows, by sorted position
     __half* out_s; int ldo_s;          // shared rows, s*N + t
     int nb_r, nb_s;                    // column blocks per routed / shared segment
-    int bits_r, group_r, bits_s, group_s;
+    int kp_r, kp_s;                    // parts of the reduction dimension (down GEMM), each with an output of its own
+    size_t part_r, part_s;             // elements between those outputs
     int32_t* status;
 };
 
+// Rows of one tile: a segment's rows are cut into as few tiles as hold them, of equal size up to
+// a whole number of 32-row products.
+__device__ __forceinline__ int tile_rows(int T) {
+    const int nt = (T + kBM - 1) / kBM;
+    return ((T + nt - 1) / nt + 31) & ~31;
+}
+
 __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __restrict__ x, int N, int H, int E,
                                                            int n_shared, const int32_t* __restrict__ offsets,
+                                                           const int32_t* __restrict__ order,
                                                            const uint16_t* __restrict__ shared_gate,
                                                            __half* __restrict__ xh, float* __restrict__ sgate,
                                                            int32_t* __restrict__ tab_up,
@@ -118,11 +121,13 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
             const int s = s0 + lane;
             int cu = 0, cd = 0;
             if (s < nseg) {
-                // a piece holds the routed experts of its mask; the shared experts go with the first piece
-                const bool mine = s < E ? ((sel.mask[s >> 6] >> (s & 63)) & 1ull) != 0 : sel.first != 0;
-                const int T = !mine ? 0 : (s < E ? offsets[s + 1] - offsets[s] : N);
-                cu = ((T + kBMUp - 1) / kBMUp) * (s < E ? nb_r_up : nb_s_up);
-                cd = ((T + kBMDown - 1) / kBMDown) * (s < E ? nb_r_down : nb_s_down);
+                // a piece holds the routed experts of its mask; the shared experts go with the first piece.
+                // The table is read from its end: shared experts, then experts by falling number of rows
+                const int e = s < E ? order[E - 1 - s] : 0;
+                const bool mine = s < E ? ((sel.mask[e >> 6] >> (e & 63)) & 1ull) != 0 : sel.first != 0;
+                const int T = !mine ? 0 : (s < E ? offsets[e + 1] - offsets[e] : N);
+                cu = ((T + kBM - 1) / kBM) * (s < E ? nb_r_up : nb_s_up);
+                cd = ((T + kBM - 1) / kBM) * (s < E ? nb_r_down : nb_s_down);
             }
             int iu = cu, id = cd;
 #pragma unroll
@@ -144,368 +149,405 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
     }
 }
 
-// raw tile piece of one lane -> fp16 B operands (8 columns each)
-template <int BITS>
-__device__ __forceinline__ void dequant_tile(const uint4& raw, uint32_t scale_bits, f16x8_t* b) {
-    const f16x2v_t s2 = {__builtin_bit_cast(_Float16, (unsigned short)scale_bits),
-                         __builtin_bit_cast(_Float16, (unsigned short)scale_bits)};
-    const uint32_t r[4] = {raw.x, raw.y, raw.z, raw.w};
+// Two neighbouring columns of one lane: columns 2p, 2p + 1 (p = 0..3) of matrix-core step d of the
+// stage whose raw tile pieces are `raw`, dequantised to a pair of fp16.  The code becomes an exact
+// fp16 integer (its bits OR-ed into the mantissa of a power of two, which is subtracted again) and
+// is rounded once in code * scale; with a zero-point (u - z) * s is rounded twice.
+template <int BITS, bool ZP, int TPS>
+__device__ __forceinline__ uint32_t dequant_pair(const uint4 (&raw)[TPS], int d, int p, f16x2v_t s2, f16x2v_t z2) {
+    auto dword = [&](int tl, int i) { return i == 0 ? raw[tl].x : i == 1 ? raw[tl].y : i == 2 ? raw[tl].z : raw[tl].w; };
+    auto both = [](float v) { return f16x2v_t{(_Float16)v, (_Float16)v}; };
+    f16x2v_t w;
     if constexpr (BITS == 2) {
-        // sixteen fields per dword -> two operands of 8 columns; signed code 2u - 3 (exact), one rounding in code * scale
-        const f16x2v_t two = {(_Float16)2.f, (_Float16)2.f}, three = {(_Float16)3.f, (_Float16)3.f};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            f16x2_t f[8];
-            int2_fields_to_f16(r[d], f);
-            f16x2v_t w[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) w[i] = (__builtin_bit_cast(f16x2v_t, f[i]) * two - three) * s2;
-            b[2 * d] = f16x8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
-            b[2 * d + 1] = f16x8_t{w[4].x, w[4].y, w[5].x, w[5].y, w[6].x, w[6].y, w[7].x, w[7].y};
-        }
+        // sixteen fields per dword, two steps; signed code 2u - 3 without a zero-point
+        const uint32_t r = dword(0, d >> 1), x = d & 1 ? r >> 8 : r;
+        const uint32_t v = p == 0 ? and_or_b32(x, 0x00030003u, 0x64006400u) : p == 1 ? and_or_b32(x, 0x000c000cu, 0x5c005c00u)
+                         : p == 2 ? and_or_b32(x, 0x00300030u, 0x54005400u) : and_or_b32(x, 0x00c000c0u, 0x4c004c00u);
+        w = __builtin_bit_cast(f16x2v_t, v) - both(p == 0 ? 1024.f : p == 1 ? 256.f : p == 2 ? 64.f : 16.f);
+        w = ZP ? w - z2 : w * both(2.f) - both(3.f);
     } else if constexpr (BITS == 4) {
-        const f16x2v_t offA = {(_Float16)1032.f, (_Float16)1032.f};   // 1024 + 8
-        const f16x2v_t offB = {(_Float16)72.f, (_Float16)72.f};       // 64 + 8
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const uint32_t hi = r[d] >> 8;
-            uint32_t u[4];
-            u[0] = and_or_b32(r[d], 0x000f000fu, 0x64006400u);   // columns 0,1: 1024 + u
-            u[1] = and_or_b32(r[d], 0x00f000f0u, 0x54005400u);   // columns 2,3: 64 + u
-            u[2] = and_or_b32(hi, 0x000f000fu, 0x64006400u);     // columns 4,5
-            u[3] = and_or_b32(hi, 0x00f000f0u, 0x54005400u);     // columns 6,7
-            f16x2v_t w[4];
-            w[0] = (__builtin_bit_cast(f16x2v_t, u[0]) - offA) * s2;
-            w[1] = (__builtin_bit_cast(f16x2v_t, u[1]) - offB) * s2;
-            w[2] = (__builtin_bit_cast(f16x2v_t, u[2]) - offA) * s2;
-            w[3] = (__builtin_bit_cast(f16x2v_t, u[3]) - offB) * s2;
-            b[d] = f16x8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
-        }
+        const uint32_t r = dword(0, d), x = p < 2 ? r : r >> 8;
+        const uint32_t v = p & 1 ? and_or_b32(x, 0x00f000f0u, 0x54005400u) : and_or_b32(x, 0x000f000fu, 0x64006400u);
+        w = __builtin_bit_cast(f16x2v_t, v) - both((p & 1 ? 64.f : 1024.f) + (ZP ? 0.f : 8.f));
+        if constexpr (ZP) w = w - z2;
     } else {
-        const f16x2v_t off = {(_Float16)1152.f, (_Float16)1152.f};    // 1024 + 128
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            f16x2v_t w[4];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const uint32_t v = r[2 * h + j];
-                const uint32_t p0 = __builtin_amdgcn_perm(0x64646464u, v, 0x04010400u);
-                const uint32_t p1 = __builtin_amdgcn_perm(0x64646464u, v, 0x04030402u);
-                w[2 * j] = (__builtin_bit_cast(f16x2v_t, p0) - off) * s2;
-                w[2 * j + 1] = (__builtin_bit_cast(f16x2v_t, p1) - off) * s2;
-            }
-            b[h] = f16x8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
-        }
+        const uint32_t v = __builtin_amdgcn_perm(0x64646464u, dword(d >> 1, 2 * (d & 1) + (p >> 1)), p & 1 ? 0x04030402u : 0x04010400u);
+        w = __builtin_bit_cast(f16x2v_t, v) - both(1152.f);       // 1024 + 128
     }
+    return __builtin_bit_cast(uint32_t, w * s2);
 }
 
-// the same with a zero-point: w = (u - z) * s on the unsigned field u (exact), two roundings
+// 16 (4) bytes per lane from sbase + voff (vaddr) to lds + lane*16 (*4).  The loads are outside the
+// compiler's sight: it must not wait for them (it would wait for all of them), the pipeline's
+// own counted waits do.
+__device__ __forceinline__ void lds_load16(uint32_t lds, const void* sbase, uint32_t voff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds), "v"(voff), "s"(sbase) : "memory");
+}
+__device__ __forceinline__ void lds_load4(uint32_t lds, const void* vaddr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+                 :: "s"(lds), "v"(vaddr) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+// Waits until at most `left` stages of LPS loads are outstanding (left <= MOST).
+template <int LPS, int MOST>
+__device__ __forceinline__ void wait_stages(int left) {
+    if constexpr (MOST == 0) wait_loads<0>();
+    else if (left >= MOST) wait_loads<MOST * LPS>();
+    else wait_stages<LPS, MOST - 1>(left);
+}
+// Workgroup barrier that orders LDS traffic only: the stages in flight stay in flight.
+__device__ __forceinline__ void lds_only_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
+// A value that is the same in all lanes, told to the compiler (it keeps what it loaded from memory
+// in vector registers otherwise).
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <class T>
+__device__ __forceinline__ T* uniform(T* p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+    return reinterpret_cast<T*>((uint64_t)hi << 32 | lo);
+}
+
+// What one tile needs; everything is the same in all lanes of a wave unless said otherwise.
+struct TileCtx {
+    const fate_qexpert* ex;
+    const __half* A; int lda;
+    const int32_t* rows; int div;      // activation row of tile row r: rows[r] / div, or r itself when rows is NULL
+    int nrows;                         // live rows of the tile (the rest read the first one and are not stored)
+    int wrow[2];                       // first weight row of the wave's two blocks
+    bool wlive[2];                     // whether they exist (a wave without weights still stages activations)
+    int Nout, K, col0, ncol;           // weight rows of the matrix, its columns, this part's columns
+    int group;
+    __half* out; int ldo;              // output row 0 of the tile
+};
+
 template <int BITS>
-__device__ __forceinline__ void dequant_tile_zp(const uint4& raw, uint32_t scale_bits, uint32_t zero_bits, f16x8_t* b) {
-    static_assert(BITS == 4 || BITS == 2, "zero-points come with the 4- and 2-bit formats");
-    const f16x2v_t s2 = {__builtin_bit_cast(_Float16, (unsigned short)scale_bits),
-                         __builtin_bit_cast(_Float16, (unsigned short)scale_bits)};
-    const f16x2v_t z2 = {__builtin_bit_cast(_Float16, (unsigned short)zero_bits),
-                         __builtin_bit_cast(_Float16, (unsigned short)zero_bits)};
-    const uint32_t r[4] = {raw.x, raw.y, raw.z, raw.w};
-    if constexpr (BITS == 2) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            f16x2_t f[8];
-            int2_fields_to_f16(r[d], f);
-            f16x2v_t w[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) w[i] = (__builtin_bit_cast(f16x2v_t, f[i]) - z2) * s2;
-            b[2 * d] = f16x8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
-            b[2 * d + 1] = f16x8_t{w[4].x, w[4].y, w[5].x, w[5].y, w[6].x, w[6].y, w[7].x, w[7].y};
-        }
-    } else {
-        const f16x2v_t cA = {(_Float16)1024.f, (_Float16)1024.f}, cB = {(_Float16)64.f, (_Float16)64.f};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const uint32_t hi = r[d] >> 8;
-            f16x2v_t w[4];
-            w[0] = ((__builtin_bit_cast(f16x2v_t, and_or_b32(r[d], 0x000f000fu, 0x64006400u)) - cA) - z2) * s2;
-            w[1] = ((__builtin_bit_cast(f16x2v_t, and_or_b32(r[d], 0x00f000f0u, 0x54005400u)) - cB) - z2) * s2;
-            w[2] = ((__builtin_bit_cast(f16x2v_t, and_or_b32(hi, 0x000f000fu, 0x64006400u)) - cA) - z2) * s2;
-            w[3] = ((__builtin_bit_cast(f16x2v_t, and_or_b32(hi, 0x00f000f0u, 0x54005400u)) - cB) - z2) * s2;
-            b[d] = f16x8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
-        }
-    }
-}
+struct GemmFmt {
+    static constexpr int KT = QFmt<BITS>::KT;
+    static constexpr int BK = KT < 64 ? 64 : KT;          // columns per stage
+    static constexpr int TPS = BK / KT;                   // weight tiles per stage and block
+    static constexpr int XROW = BK * 2;                   // bytes per activation row of a stage
+    static constexpr int xbytes(int nmt) { return nmt * 32 * XROW; }
+    static constexpr int stage(int nmt) { return xbytes(nmt) + 4 * 2 * TPS * 1024 + 4 * 256; }
+    static constexpr int depth(int nmt) { return kGemmLds / stage(nmt) < 6 ? kGemmLds / stage(nmt) : 6; }
+};
 
-template <int BITS, int NMAT, int kBM, bool ZP = false>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& a, const fate_qexpert* ex, int group, int row0, int T,
-                                          int nblk, const int* arow, __half* xt, __half* out, int ldo,
-                                          int out_row0, int Nout, int K, const __half* A, int lda) {
-    constexpr int KT = QFmt<BITS>::KT;
-    constexpr int TPC = kKC / KT;          // weight tiles per chunk (1 | 2 | 4)
-    constexpr int SPT = KT / 16;           // MFMA k-slots per tile (8 | 4 | 2)
+// One tile with NMT 32-row products.  UP: two matrices and SwiGLU; else one matrix, two row blocks.
+// Stage layout: activation rows (16-byte pieces of row r permuted by r & 7: conflict-free
+// ds_read_b128), then per wave the raw weight tiles of both blocks, then per wave 256 bytes of
+// scales and zero-points (lanes 0-15 / 16-31: scales of block 0 / 1, 32-47 / 48-63: zero-points).
+template <int BITS, bool ZP, bool UP, int NMT>
+__device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
+    typedef GemmFmt<BITS> F;
+    constexpr int KT = F::KT, BK = F::BK, TPS = F::TPS, XROW = F::XROW;
+    constexpr int SPT = KT / 16;                          // matrix-core steps per weight tile
+    constexpr int NX = NMT * 32 * XROW / 4096;            // activation loads per wave and stage
+    constexpr int RPL = 1024 / XROW;                      // activation rows per load
+    constexpr int S = F::depth(NMT), SB = F::stage(NMT);
+    constexpr int LPS = NX + 2 * TPS + 1;
+    static_assert(S >= 2, "at least one stage ahead");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, half = lane >> 5;
-    const int G = K / group, tiles_k = K / KT, nchunk = K / kKC;
-    const int wrow0 = nblk * kBN + wave * 32;              // first weight row of this wave
-    const bool wlive = wrow0 < Nout;
-    const int nmt = (min(kBM, T - row0) + 31) >> 5;        // 32-row tiles of this block that hold rows
-    gu4p_t wt[NMAT];
-    gu16p_t sc[NMAT];
-    gu16p_t zp[NMAT];
+    const int nstage = c.ncol / BK, tiles_k = c.K / KT;
+    const uint32_t lds0 = lds_offset(smem);
+
+    // activation loads: load i of this wave fills rows (i*4 + wave)*RPL + lane / (64 / RPL)
+    uint32_t xoff[NX];
     {
-        const void* wp[2] = {a.mode == 0 ? ex->w1 : ex->w2, ex->w3};
-        const void* sp[2] = {a.mode == 0 ? ex->s1 : ex->s2, ex->s3};
-        const void* zq[2] = {a.mode == 0 ? ex->z1 : ex->z2, ex->z3};
+        constexpr int LPR = XROW / 16;                    // lanes (16-byte pieces) per row
+        const int rl = lane / LPR, q = lane % LPR;
 #pragma unroll
-        for (int i = 0; i < NMAT; ++i) {
-            wt[i] = (gu4p_t)(uintptr_t)wp[i] + (size_t)(wrow0 >> 5) * tiles_k * 64 + lane;
-            sc[i] = (gu16p_t)(uintptr_t)sp[i] + wrow0 + n;          // group-major scales: [G][Nout]
-            zp[i] = (gu16p_t)(uintptr_t)(ZP ? zq[i] : sp[i]) + wrow0 + n;     // zero-points, same layout
+        for (int i = 0; i < NX; ++i) {
+            const int r = (i * 4 + wave) * RPL + rl;
+            const int rr = r < c.nrows ? r : 0;
+            const int ar = c.rows ? c.rows[rr] / c.div : rr;
+            xoff[i] = ((uint32_t)ar * (uint32_t)c.lda + (uint32_t)c.col0) * 2u + (uint32_t)((q ^ (r & 7)) * 16);
         }
     }
-    f32x16_t acc[NMAT][kBM / 32];
+    // weights: tile (row block, column tile) is 1 KiB; scales: group-major [groups][Nout]
+    const char* wbase[2];
+    const char* sbase;                                    // this lane's scale (or zero-point) address at group 0
+    {
+        const void* wp[2] = {UP ? c.ex->w1 : c.ex->w2, UP ? c.ex->w3 : c.ex->w2};
+        const void* sp[2] = {UP ? c.ex->s1 : c.ex->s2, UP ? c.ex->s3 : c.ex->s2};
+        const void* zp[2] = {UP ? c.ex->z1 : c.ex->z2, UP ? c.ex->z3 : c.ex->z2};
 #pragma unroll
-    for (int i = 0; i < NMAT; ++i)
+        for (int i = 0; i < 2; ++i)
+            wbase[i] = static_cast<const char*>(uniform(wp[i])) + ((size_t)(c.wrow[i] >> 5) * tiles_k + c.col0 / KT) * 1024;
+        const int b = (lane >> 4) & 1;
+        const void* p0 = ZP && half ? zp[0] : sp[0];          // (these differ between lanes)
+        const void* p1 = ZP && half ? zp[1] : sp[1];
+        sbase = static_cast<const char*>(b ? p1 : p0) + (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4;
+    }
+    const uint32_t lane16 = lane * 16;
+    // the next stage to be requested: stages are requested in order (group = 64 columns at least)
+    int gcol = c.col0 % c.group;
+    sbase += (size_t)(c.col0 / c.group) * c.Nout * 2;
+    // load l (0 .. LPS - 1) of stage st into ring slot `slot`
+    auto issue_one = [&](int st, int slot, int l) {
+        const uint32_t base = lds0 + slot * SB;
+        if (l < NX) {
+            lds_load16(base + (l * 4 + wave) * 1024, reinterpret_cast<const char*>(c.A) + (size_t)st * XROW, xoff[l]);
+        } else if (l < NX + 2 * TPS) {
+            const int i = (l - NX) / TPS, tl = (l - NX) % TPS;
+            lds_load16(base + F::xbytes(NMT) + (wave * 2 * TPS + i * TPS + tl) * 1024, wbase[i] + (size_t)(st * TPS + tl) * 1024,
+                       lane16);
+        } else {
+            lds_load4(base + F::xbytes(NMT) + 4 * 2 * TPS * 1024 + wave * 256, sbase);
+            gcol += BK;
+            if (gcol >= c.group) {
+                gcol -= c.group;
+                sbase += (size_t)c.Nout * 2;
+            }
+        }
+    };
+    auto issue = [&](int st, int slot) {
 #pragma unroll
-        for (int mt = 0; mt < kBM / 32; ++mt)
+        for (int l = 0; l < LPS; ++l) issue_one(st, slot, l);
+    };
+
+    f32x16_t acc[2][NMT];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[i][mt][j] = 0.f;
+    // this lane's activation pieces of a stage, in the order of the weight operands
+    uint32_t aoff[TPS * SPT];
+#pragma unroll
+    for (int tl = 0; tl < TPS; ++tl)
+#pragma unroll
+        for (int d = 0; d < SPT; ++d) {
+            const int piece = (tl * KT + half * (KT / 2)) / 8 + d;
+            aoff[tl * SPT + d] = n * XROW + (piece ^ (n & 7)) * 16;
+        }
 
-    // staging assignment: thread -> (row r0 + 16*i, 16-byte column piece cp)
-    const int cp = tid & 15, r0 = tid >> 4;
-    uint4 xr[kBM / 16];
-    uint4 raw[kWRing][NMAT][TPC];
-    uint32_t sbits[kWRing][NMAT][TPC];
-    uint32_t zbits[ZP ? kWRing : 1][NMAT][TPC];
-    // (the load is unconditional and the row is clamped: a branch around a load makes the
-    // compiler wait for every outstanding load at the next use, which empties the weight ring)
-    // the rows this thread stages do not change from chunk to chunk; a missing row reads row 0
-    // and is masked to zero (an AND, not a select: a select lets the compiler put the load
-    // back under a branch)
-    uint32_t xoff[kBM / 16];       // element offsets (rows * lda < 2^31: checked by the entry point)
-    uint32_t xmask[kBM / 16];
+    constexpr int KS = TPS * SPT;                         // matrix-core steps per stage
+    int slot = 0, slot_in = S - 1;                        // stage being multiplied, stage being filled
+    auto next = [](int i) { return i + 1 == S ? 0 : i + 1; };
 #pragma unroll
-    for (int i = 0; i < kBM / 16; ++i) {
-        const int ar = arow[r0 + 16 * i];
-        xoff[i] = (uint32_t)(ar >= 0 ? ar : 0) * (uint32_t)lda + cp * 8;
-        xmask[i] = ar >= 0 ? 0xffffffffu : 0u;
-    }
-    auto load_x = [&](int kc) {
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nstage) issue(s, s);
+    auto step = [&](int st, auto more) {                  // more: whether stage st + S - 1 exists
+        if constexpr (more) wait_loads<(S - 2) * LPS>();
+        else wait_stages<LPS, S - 2>(nstage - 1 - st);
+        lds_only_barrier();                               // stage st is in LDS, everyone is done with stage st - 1
+        const char* base = smem + slot * SB;
+        const char* wl = base + F::xbytes(NMT) + wave * (2 * TPS * 1024) + lane16;
+        const char* sl = base + F::xbytes(NMT) + 4 * 2 * TPS * 1024 + wave * 256 + n * 2;
+        uint4 raw[2][TPS];
+        f16x2v_t s2[2], z2[2];
+        f16x8_t av[2][NMT];                               // activations of the current and the next step
+        u32x4_t b[2][2];                                  // dequantised codes: [step parity][block]
+        auto read_av = [&](int d, int mt) {
+            av[d & 1][mt] = *reinterpret_cast<const f16x8_t*>(base + aoff[d] + mt * 32 * XROW);
+        };
+        // the e-th of the 8 pairs of a step: 4 of each block
+        auto dequant = [&](int d, int e) { b[d & 1][e >> 2][e & 3] = dequant_pair<BITS, ZP>(raw[e >> 2], d, e & 3, s2[e >> 2], z2[e >> 2]); };
 #pragma unroll
-        for (int i = 0; i < kBM / 16; ++i) {
-            const uint4 v = *reinterpret_cast<const uint4*>(A + xoff[i] + kc * kKC);
-            xr[i] = make_uint4(v.x & xmask[i], v.y & xmask[i], v.z & xmask[i], v.w & xmask[i]);
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int tl = 0; tl < TPS; ++tl) raw[i][tl] = *reinterpret_cast<const uint4*>(wl + (i * TPS + tl) * 1024);
+            const _Float16 sv = *reinterpret_cast<const _Float16*>(sl + i * 64);
+            const _Float16 zv = ZP ? *reinterpret_cast<const _Float16*>(sl + 128 + i * 64) : (_Float16)0.f;
+            s2[i] = f16x2v_t{sv, sv};
+            z2[i] = f16x2v_t{zv, zv};
         }
-    };
-    auto request_w = [&](int u, int kc) {
 #pragma unroll
-        for (int i = 0; i < NMAT; ++i)
+        for (int mt = 0; mt < NMT; ++mt) read_av(0, mt);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int tl = 0; tl < TPC; ++tl) {
-                const int tile = kc * TPC + tl;
-                raw[u][i][tl] = wt[i][(size_t)tile * 64];
-                sbits[u][i][tl] = sc[i][(size_t)((tile * KT) / group) * Nout];
-                if constexpr (ZP) zbits[u][i][tl] = zp[i][(size_t)((tile * KT) / group) * Nout];
+        for (int e = 0; e < 8; ++e) dequant(0, e);
+        // Matrix products of a step with the next step's dequantisation and LDS reads between them: a
+        // wave issues a vector instruction every 5 to 6 cycles and a product occupies the matrix pipe
+        // for 32, so the dequantisation of a step runs beside the products of four row blocks.  (The
+        // fences keep the compiler from collecting the vector instructions in front of the products.)
+#pragma unroll
+        for (int d = 0; d < KS; ++d) {
+#pragma unroll
+            for (int mt = 0; mt < NMT; ++mt) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    acc[i][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, b[d & 1][i]), av[d & 1][mt],
+                                                                        acc[i][mt], 0, 0, 0);
+                // (the next stage's loads go out one at a time: the memory path of a compute unit takes 64 bytes
+                // per cycle, and a wave that asks for a whole stage at once waits for it)
+                if constexpr (more) {
+                    constexpr int G = KS * NMT;
+#pragma unroll
+                    for (int l = LPS * (d * NMT + mt) / G; l < LPS * (d * NMT + mt + 1) / G; ++l) issue_one(st + S - 1, slot_in, l);
+                }
+                if (d + 1 < KS) {
+                    read_av(d + 1, mt);
+#pragma unroll
+                    for (int e = 8 * mt / NMT; e < 8 * (mt + 1) / NMT; ++e) dequant(d + 1, e);
+                }
             }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        slot = next(slot);
+        slot_in = next(slot_in);
     };
-    auto dequant = [&](int u, int i, int tl, f16x8_t* b) {
-        if constexpr (ZP) dequant_tile_zp<BITS>(raw[u][i][tl], sbits[u][i][tl], zbits[u][i][tl], b);
-        else dequant_tile<BITS>(raw[u][i][tl], sbits[u][i][tl], b);
-    };
-    // two activation tiles in LDS: chunk kc is multiplied from tile kc & 1 while chunk kc + 1 is
-    // written into the other one, so a chunk costs one barrier and a wave's dequantisation is
-    // not fenced off from its matrix products
-    auto stage_x = [&](int buf) {
+    int st = 0;
+    for (; st + S - 1 < nstage; ++st) step(st, std::true_type{});
+    for (; st < nstage; ++st) step(st, std::false_type{});
+    // epilogue: lane holds tile row mt*32 + n, weight rows 8*(j/4) + 4*half + j%4 of each block
 #pragma unroll
-        for (int i = 0; i < kBM / 16; ++i)
-            *reinterpret_cast<uint4*>(xt + buf * (kBM * kLdsRow) + (r0 + 16 * i) * kLdsRow + cp * 8) = xr[i];
-    };
-    auto multiply = [&](f16x8_t (&b)[NMAT][kKC / 16], int buf) {
-        const __half* xb = xt + buf * (kBM * kLdsRow);
+    for (int mt = 0; mt < NMT; ++mt) {
+        const int r = mt * 32 + n;
+        if (r < c.nrows) {
+            __half* o = c.out + (size_t)r * c.ldo + 4 * half;
 #pragma unroll
-        for (int mt = 0; mt < kBM / 32; ++mt) {
-            if (mt < nmt) {
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (UP) {
+                    __half h[4];
 #pragma unroll
-                for (int tl = 0; tl < TPC; ++tl)
-#pragma unroll
-                    for (int d = 0; d < SPT; ++d) {
-                        const int kl = tl * KT + half * (KT / 2) + 8 * d;
-                        const f16x8_t av = *reinterpret_cast<const f16x8_t*>(xb + (mt * 32 + n) * kLdsRow + kl);
-#pragma unroll
-                        for (int i = 0; i < NMAT; ++i)
-                            acc[i][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, b[i][tl * SPT + d], acc[i][mt], 0, 0, 0);
+                    for (int j = 0; j < 4; ++j) {
+                        const float g = acc[0][mt][4 * q + j];
+                        h[j] = __float2half(g / (1.0f + __expf(-g)) * acc[1][mt][4 * q + j]);
                     }
-            }
-        }
-    };
-    // At the top of iteration kc: tile kc & 1 holds chunk kc (a barrier has passed since it was
-    // written), xr holds chunk kc + 1, the weights of chunks kc .. kc + kWRing - 1 are requested.
-    static_assert(kWRing == 2, "ring slot and LDS tile of a chunk are both kc & 1");
-    int kc_done = 0;
-    const bool steady = BITS == 4 && wlive && nchunk >= kWRing;
-    // (int4 only: the int8 instantiation holds twice the tiles per chunk and has no registers
-    // left for a second copy of the loop)
-    if (steady) {
-#pragma unroll
-        for (int u = 0; u < kWRing; ++u) request_w(u, u);
-    } else {
-#pragma unroll
-        for (int u = 0; u < kWRing; ++u)
-            if (wlive && u < nchunk) request_w(u, u);
-    }
-    load_x(0);
-    stage_x(0);
-    load_x(min(1, nchunk - 1));
-    lds_only_barrier();
-    if (steady) {
-        // Steady state without a branch around any load: weights kWRing chunks ahead, the
-        // activations after next requested before the refill (loads return in order, and the
-        // next iteration must not wait for that refill).  Near the end the requests are clamped
-        // to the last chunk instead of being skipped: a few redundant loads, no branch.
-        const int nfull = nchunk / kWRing * kWRing;
-        for (int kc0 = 0; kc0 < nfull; kc0 += kWRing) {
-#pragma unroll
-            for (int u = 0; u < kWRing; ++u) {
-                const int kc = kc0 + u;
-                stage_x(u ^ 1);
-                load_x(min(kc + 2, nchunk - 1));
-                f16x8_t b[NMAT][kKC / 16];
-#pragma unroll
-                for (int i = 0; i < NMAT; ++i)
-#pragma unroll
-                    for (int tl = 0; tl < TPC; ++tl) dequant(u, i, tl, &b[i][tl * SPT]);
-                request_w(u, min(kc + kWRing, nchunk - 1));
-                multiply(b, u);
-                lds_only_barrier();   // chunk kc + 1 is visible, everyone is done reading chunk kc
-            }
-        }
-        kc_done = nfull;
-    }
-    // the last chunks (and shapes with a short K, or a wave without weight rows)
-    for (int kc0 = kc_done; kc0 < nchunk; kc0 += kWRing) {
-#pragma unroll
-        for (int u = 0; u < kWRing; ++u) {
-            const int kc = kc0 + u;
-            if (kc < nchunk) {
-                if (kc + 1 < nchunk) stage_x(u ^ 1);
-                if (kc + 2 < nchunk) load_x(kc + 2);
-                f16x8_t b[NMAT][kKC / 16];
-                if (wlive) {
-#pragma unroll
-                    for (int i = 0; i < NMAT; ++i)
-#pragma unroll
-                        for (int tl = 0; tl < TPC; ++tl)
-                            dequant(u, i, tl, &b[i][tl * SPT]);
-                    if (kc + kWRing < nchunk) request_w(u, kc + kWRing);
-                    multiply(b, u);
-                }
-                lds_only_barrier();
-            }
-        }
-    }
-    if (!wlive) return;
-    // epilogue: lane holds column wrow0 + n, rows (j/4)*8 + half*4 + (j%4) of each 32-row tile
-#pragma unroll
-    for (int mt = 0; mt < kBM / 32; ++mt)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int r = mt * 32 + (j >> 2) * 8 + half * 4 + (j & 3);
-            if (row0 + r < T) {
-                float v;
-                if constexpr (NMAT == 2) {
-                    const float g = acc[0][mt][j];
-                    v = g / (1.0f + __expf(-g)) * acc[1][mt][j];
+                    if (c.wlive[0]) *reinterpret_cast<uint2*>(o + c.wrow[0] + 8 * q) = *reinterpret_cast<uint2*>(h);
                 } else {
-                    v = acc[0][mt][j];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        __half h[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) h[j] = __float2half(acc[i][mt][4 * q + j]);
+                        if (c.wlive[i]) *reinterpret_cast<uint2*>(o + c.wrow[i] + 8 * q) = *reinterpret_cast<uint2*>(h);
+                    }
                 }
-                out[(size_t)(out_row0 + r) * ldo + wrow0 + n] = __float2half(v);
             }
         }
+    }
 }
 
-template <int NMAT>
+// A tile of any number of rows (at most kBM): as many 32-row products as it has rows, in one pass if
+// the stages of that many rows fit into LDS twice (int4), else in passes of 64 rows.
+template <int BITS, bool ZP, bool UP>
+__device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
+    if constexpr (BITS == 4) {
+        if (c.nrows <= 32) gemm_pipe<BITS, ZP, UP, 1>(c, smem);
+        else if (c.nrows <= 64) gemm_pipe<BITS, ZP, UP, 2>(c, smem);
+        else if (c.nrows <= 96) gemm_pipe<BITS, ZP, UP, 3>(c, smem);
+        else gemm_pipe<BITS, ZP, UP, 4>(c, smem);
+    } else {
+        TileCtx p = c;
+        for (int r0 = 0; r0 < c.nrows; r0 += 64) {
+            if (r0) {
+                lds_only_barrier();
+                if (c.rows) p.rows = c.rows + r0;
+                else p.A = c.A + (size_t)r0 * c.lda;
+                p.out = c.out + (size_t)r0 * c.ldo;
+            }
+            p.nrows = min(64, c.nrows - r0);
+            if (p.nrows <= 32) gemm_pipe<BITS, ZP, UP, 1>(p, smem);
+            else gemm_pipe<BITS, ZP, UP, 2>(p, smem);
+        }
+    }
+}
+
+template <bool UP>
 __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
-    constexpr int kBM = NMAT == 2 ? kBMUp : kBMDown;
-    __shared__ __align__(16) __half xt[2 * kBM * kLdsRow];
-    __shared__ int arow[kBM];
+    extern __shared__ uint4 gemm_smem[];
+    char* smem = reinterpret_cast<char*>(gemm_smem);
     const int nseg = a.E + a.n_shared;
     // the shared experts' segments come last in the table and hold the fullest tiles: they go first
-    const int ntile = a.tile_start[nseg];
+    const int ntile = uniform(a.tile_start[nseg]);
     if ((int)blockIdx.x >= ntile) return;
     const int b = ntile - 1 - (int)blockIdx.x;
     int lo = 0, hi = nseg;                 // last seg with tile_start[seg] <= b
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (a.tile_start[mid] <= b) lo = mid; else hi = mid;
+        if (uniform(a.tile_start[mid]) <= b) lo = mid; else hi = mid;
     }
     const int seg = lo;
     const bool is_shared = seg >= a.E;
-    const int local = b - a.tile_start[seg];
-    const int nb = is_shared ? a.nb_s : a.nb_r;
-    const int mb = local / nb, nblk = local - mb * nb;
-    const fate_qexpert* ex = is_shared ? a.shared + (seg - a.E) : a.experts + seg;
-    const int sbeg = is_shared ? 0 : a.offsets[seg];
-    const int T = is_shared ? a.N : a.offsets[seg + 1] - sbeg;
-    const int row0 = mb * kBM;
-    const int Nout = a.mode == 0 ? ex->I : a.H;
-    const int K = a.mode == 0 ? a.H : ex->I;
-    const __half* A = is_shared ? a.A_s : a.A_r;
-    const int lda = is_shared ? a.lda_s : a.lda_r;
-    if (nblk * kBN >= Nout) return;
-    if ((a.mode == 0 ? ex->w1 : ex->w2) == nullptr) {
+    int local = b - uniform(a.tile_start[seg]);
+    const int nb = is_shared ? a.nb_s : a.nb_r, kp = UP ? 1 : (is_shared ? a.kp_s : a.kp_r);
+    const int mb = local / (nb * kp);
+    local -= mb * (nb * kp);
+    const int part = local / nb, nblk = local - part * nb;
+    const int e = is_shared ? seg - a.E : uniform(a.order[a.E - 1 - seg]);
+    const fate_qexpert* ex = (is_shared ? a.shared : a.experts) + e;
+    const int sbeg = is_shared ? 0 : uniform(a.offsets[e]);
+    const int T = is_shared ? a.N : uniform(a.offsets[e + 1]) - sbeg;
+    const int row0 = mb * tile_rows(T);
+    TileCtx c;
+    c.ex = ex;
+    c.nrows = min(tile_rows(T), T - row0);
+    c.Nout = UP ? uniform(ex->I) : a.H;
+    c.K = UP ? a.H : uniform(ex->I);
+    if (nblk * (UP ? kBNUp : kBNDown) >= c.Nout || c.nrows <= 0) return;
+    if ((UP ? ex->w1 : ex->w2) == nullptr) {
         if (threadIdx.x == 0) atomicOr(a.status, 1);
         return;
     }
-    for (int r = threadIdx.x; r < kBM; r += 256) {
-        const int rr = row0 + r < T ? row0 + r : row0;
-        int ar;
-        if (a.mode == 0) ar = is_shared ? rr : a.perm[sbeg + rr] / a.k;
-        else ar = is_shared ? (seg - a.E) * a.N + rr : sbeg + rr;
-        arow[r] = ar;
-    }
-    __syncthreads();
-    __half* out = is_shared ? a.out_s : a.out_r;
-    const int ldo = is_shared ? a.ldo_s : a.ldo_r;
-    const int out_row0 = (is_shared ? (seg - a.E) * a.N : sbeg) + row0;
     // width and group of THIS expert's copy: a layer may hold copies of several widths (the
     // popularity-aware hybrid of section 4.5 moves the least popular experts at 2 bits)
-    const int bits = ex->bits, group = ex->group;
+    const int bits = uniform(ex->bits);
+    c.group = uniform(ex->group);
     const int kt = bits == 4 ? 64 : (bits == 8 ? 32 : 128);
-    if ((bits != 2 && bits != 4 && bits != 8) || group < kt || group % kt || K % group) {
-        if (threadIdx.x == 0) atomicOr(a.status, 4);
-        return;
-    }
     const bool has_z = ex->z1 != nullptr;
-    if (has_z && (bits == 8 || ex->z2 == nullptr || ex->z3 == nullptr)) {     // zero-points: 4- and 2-bit formats
+    if ((bits != 2 && bits != 4 && bits != 8) || c.group < kt || c.group % kt || c.group % 64 || c.K % c.group ||
+        (has_z && (bits == 8 || ex->z2 == nullptr || ex->z3 == nullptr))) {     // zero-points: 4- and 2-bit formats
         if (threadIdx.x == 0) atomicOr(a.status, 4);
         return;
     }
-    if (has_z && bits == 4)
-        gemm_tile<4, NMAT, kBM, true>(a, ex, group, row0, T, nblk, arow, xt, out, ldo, out_row0, Nout, K, A, lda);
-    else if (has_z)
-        gemm_tile<2, NMAT, kBM, true>(a, ex, group, row0, T, nblk, arow, xt, out, ldo, out_row0, Nout, K, A, lda);
-    else if (bits == 4)
-        gemm_tile<4, NMAT, kBM>(a, ex, group, row0, T, nblk, arow, xt, out, ldo, out_row0, Nout, K, A, lda);
-    else if (bits == 2)
-        gemm_tile<2, NMAT, kBM>(a, ex, group, row0, T, nblk, arow, xt, out, ldo, out_row0, Nout, K, A, lda);
-    else
-        gemm_tile<8, NMAT, kBM>(a, ex, group, row0, T, nblk, arow, xt, out, ldo, out_row0, Nout, K, A, lda);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int wr = UP ? nblk * kBNUp + wave * 32 : nblk * kBNDown + wave * 64 + i * 32;
+        c.wlive[i] = wr < c.Nout;
+        c.wrow[i] = c.wlive[i] ? wr : 0;
+    }
+    // columns of this part: a whole number of 128-column pieces
+    const int pieces = c.K / kKQ;
+    const int p0 = pieces * part / kp, p1 = pieces * (part + 1) / kp;
+    c.col0 = p0 * kKQ;
+    c.ncol = (p1 - p0) * kKQ;
+    c.lda = is_shared ? a.lda_s : a.lda_r;
+    c.A = is_shared ? a.A_s : a.A_r;
+    c.rows = nullptr;
+    c.div = 1;
+    if (UP) {
+        if (is_shared) c.A += (size_t)row0 * c.lda;
+        else { c.rows = a.perm + sbeg + row0; c.div = a.k; }
+    } else {
+        c.A += (size_t)((is_shared ? (seg - a.E) * a.N : sbeg) + row0) * c.lda;
+    }
+    const int out_row0 = (is_shared ? (seg - a.E) * a.N : sbeg) + row0;
+    c.ldo = is_shared ? a.ldo_s : a.ldo_r;
+    c.out = (is_shared ? a.out_s + part * a.part_s : a.out_r + part * a.part_r) + (size_t)out_row0 * c.ldo;
+    if (has_z && bits == 4) gemm_tile<4, true, UP>(c, smem);
+    else if (has_z) gemm_tile<2, true, UP>(c, smem);
+    else if (bits == 4) gemm_tile<4, false, UP>(c, smem);
+    else if (bits == 2) gemm_tile<2, false, UP>(c, smem);
+    else gemm_tile<8, false, UP>(c, smem);
 }
 
-// two waves per SIMD for the up GEMM (two matrices: 256 registers), three for the down GEMM
-template <int NMAT>
+template <bool UP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void grouped_gemm_kernel(GemmArgs a) {
-    grouped_gemm_body<NMAT>(a);
-}
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void grouped_gemm_down_kernel(GemmArgs a) {
-    grouped_gemm_body<1>(a);
+    grouped_gemm_body<UP>(a);
 }
 
-// y[t,:] = sum_j w[t,j] * Yp_r[inv_perm[t*k+j], :] + sum_s g_s(t) * Yp_s[s*N+t, :]
+// y[t,:] = sum_j w[t,j] * Yp_r[inv_perm[t*k+j], :] + sum_s g_s(t) * Yp_s[s*N+t, :], each Yp the sum of its K parts
 __global__ __launch_bounds__(256) void combine_kernel(const __half* __restrict__ yp_r,
                                                       const __half* __restrict__ yp_s,
                                                       const int32_t* __restrict__ inv_perm,
                                                       const float* __restrict__ topk_w,
                                                       const float* __restrict__ sgate, int N, int H, int k,
-                                                      int n_shared, float* __restrict__ y32,
+                                                      int n_shared, int kp_r, int kp_s, size_t part_r, size_t part_s, float* __restrict__ y32,
                                                       uint16_t* __restrict__ y16) {
     const int t = blockIdx.x;
     for (int c = threadIdx.x; c < (H >> 3); c += 256) {
@@ -513,6 +555,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const __half* __restrict__
         for (int j = 0; j < k + n_shared; ++j) {
             float wgt;
             const __half* src;
+            const int kp = j < k ? kp_r : kp_s;
+            const size_t stride = j < k ? part_r : part_s;
             if (j < k) {
                 const int pos = inv_perm[t * k + j];
                 if (pos < 0) continue;
@@ -522,12 +566,14 @@ __global__ __launch_bounds__(256) void combine_kernel(const __half* __restrict__
                 wgt = sgate ? sgate[t] : 1.0f;
                 src = yp_s + ((size_t)(j - k) * N + t) * H;
             }
-            const uint4 v = reinterpret_cast<const uint4*>(src)[c];
-            const __half2* h = reinterpret_cast<const __half2*>(&v);
+            for (int p = 0; p < kp; ++p) {
+                const uint4 v = reinterpret_cast<const uint4*>(src + p * stride)[c];
+                const __half2* h = reinterpret_cast<const __half2*>(&v);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                acc[2 * i] = fmaf(wgt, __low2float(h[i]), acc[2 * i]);
-                acc[2 * i + 1] = fmaf(wgt, __high2float(h[i]), acc[2 * i + 1]);
+                for (int i = 0; i < 4; ++i) {
+                    acc[2 * i] = fmaf(wgt, __low2float(h[i]), acc[2 * i]);
+                    acc[2 * i + 1] = fmaf(wgt, __high2float(h[i]), acc[2 * i + 1]);
+                }
             }
         }
         if (y32) {
@@ -544,56 +590,80 @@ __global__ __launch_bounds__(256) void combine_kernel(const __half* __restrict__
     }
 }
 
+// Parts of the reduction dimension of the down GEMM.  A tile's time is its K; with `tiles` of
+// length K over 2 workgroups per compute unit, a tile longer than the average load of a
+// workgroup would run on after everything else has ended, so it is cut into parts.  Every part
+// has an output of its own, which combine adds up (512 columns at least, 8 parts at most).
+void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s) {
+    const long long P = (long long)d.N * d.k, nb = (d.H + kBNDown - 1) / kBNDown;
+    const long long tr = (P / kBM + std::min<long long>(d.E, P)) * nb;
+    const long long ts = (long long)d.n_shared * ((d.N + kBM - 1) / kBM) * nb;
+    const long long load = std::max<long long>((tr * d.I_max + ts * (d.n_shared ? d.I_shared_max : 0)) / kGemmSlots, 512);
+    auto parts = [&](long long K) { return (int)std::min<long long>(std::max<long long>((K + load - 1) / load, 1), 8); };
+    *kp_r = parts(d.I_max);
+    *kp_s = d.n_shared ? parts(d.I_shared_max) : 1;
+}
+
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs da, const MfmaScratch& ms,
                             void* y_out, int phase, const PartSel& sel) {
-    if (d.H % kKC || d.I_max % kKC || (d.n_shared && d.I_shared_max % kKC))
-        FATE_FAIL(FATE_ESHAPE, "the MFMA path needs H and I to be multiples of %d", kKC);
+    if (d.H % kKQ || d.I_max % kKQ || (d.n_shared && d.I_shared_max % kKQ))
+        FATE_FAIL(FATE_ESHAPE, "the MFMA path needs H and I to be multiples of %d", kKQ);
     const int P = d.N * d.k;
     // the GEMM addresses activation rows with 32-bit element offsets
     const long long amax = std::max({(long long)d.N * d.H, (long long)P * da.ldh_r,
                                      (long long)d.n_shared * d.N * da.ldh_s});
     if (amax >= (1LL << 31))
         FATE_FAIL(FATE_ESHAPE, "the MFMA path needs activation matrices of fewer than 2^31 elements (%lld)", amax);
-    const int nseg = d.E + d.n_shared;
-    const int nb_r_up = (d.I_max + kBN - 1) / kBN, nb_s_up = d.n_shared ? (d.I_shared_max + kBN - 1) / kBN : 0;
-    const int nb_down = (d.H + kBN - 1) / kBN;
+    const int nb_r_up = (d.I_max + kBNUp - 1) / kBNUp, nb_s_up = d.n_shared ? (d.I_shared_max + kBNUp - 1) / kBNUp : 0;
+    const int nb_down = (d.H + kBNDown - 1) / kBNDown;
+    int kp_r = 1, kp_s = 1;
+    mfma_k_parts(d, &kp_r, &kp_s);
     const bool do_up = phase != 2, do_down = phase != 1;
-    (void)nseg;
+    static bool attr_done = false;
+    if (!attr_done) {
+        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<true>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<false>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        attr_done = true;
+    }
     if (do_up) {
         prefill_prep_kernel<<<sel.first ? d.N : 1, 256, 0, st>>>(da.x, d.N, d.H, d.E, d.n_shared, da.offsets,
-                                                                 da.shared_gate, ms.xh, ms.sgate, ms.tab_up, ms.tab_down,
-                                                                 nb_r_up, nb_s_up, nb_down, nb_down, sel);
+                                                                 da.order, da.shared_gate, ms.xh, ms.sgate, ms.tab_up, ms.tab_down,
+                                                                 nb_r_up, nb_s_up, nb_down * kp_r, nb_down * kp_s, sel);
         FATE_HIP(hipGetLastError());
     }
-    // upper bounds of the routed row blocks, and the shared experts' row blocks, per GEMM
-    const int mb_r_up = P / kBMUp + (d.E < P ? d.E : P), mb_s_up = (d.N + kBMUp - 1) / kBMUp;
-    const int mb_r_down = P / kBMDown + (d.E < P ? d.E : P), mb_s_down = (d.N + kBMDown - 1) / kBMDown;
+    // upper bounds of the routed row blocks, and the shared experts' row blocks
+    const long long mb_r = P / kBM + (d.E < P ? d.E : P), mb_s = (d.N + kBM - 1) / kBM;
     GemmArgs g{};
     g.experts = da.experts; g.shared = da.shared; g.E = d.E; g.n_shared = d.n_shared; g.N = d.N; g.k = d.k;
-    g.offsets = da.offsets; g.perm = da.perm;
-    g.bits_r = da.bits_r; g.group_r = da.group_r; g.bits_s = da.bits_s; g.group_s = da.group_s;
+    g.offsets = da.offsets; g.perm = da.perm; g.order = da.order;
     g.status = da.status;
     g.H = d.H;
     if (do_up) {
-        g.A_r = ms.xh; g.lda_r = d.H; g.A_s = ms.xh; g.lda_s = d.H; g.mode = 0; g.tile_start = ms.tab_up;
+        g.A_r = ms.xh; g.lda_r = d.H; g.A_s = ms.xh; g.lda_s = d.H; g.tile_start = ms.tab_up;
         g.out_r = da.h_r; g.ldo_r = da.ldh_r; g.out_s = da.h_s; g.ldo_s = da.ldh_s;
         g.nb_r = nb_r_up; g.nb_s = nb_s_up;
-        const long long grid = (long long)mb_r_up * nb_r_up + (long long)d.n_shared * mb_s_up * nb_s_up;
+        g.kp_r = g.kp_s = 1;
+        const long long grid = mb_r * nb_r_up + d.n_shared * mb_s * nb_s_up;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
-        grouped_gemm_kernel<2><<<(unsigned)grid, 256, 0, st>>>(g);
+        grouped_gemm_kernel<true><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
     }
     if (do_down) {
-        g.A_r = da.h_r; g.lda_r = da.ldh_r; g.A_s = da.h_s; g.lda_s = da.ldh_s; g.mode = 1;
+        g.A_r = da.h_r; g.lda_r = da.ldh_r; g.A_s = da.h_s; g.lda_s = da.ldh_s;
         g.tile_start = ms.tab_down; g.nb_r = nb_down; g.nb_s = nb_down;
         g.out_r = ms.yp_r; g.ldo_r = d.H; g.out_s = ms.yp_s; g.ldo_s = d.H;
-        const long long grid = ((long long)mb_r_down + (long long)d.n_shared * mb_s_down) * nb_down;
+        g.kp_r = kp_r; g.kp_s = kp_s;
+        g.part_r = (size_t)P * d.H; g.part_s = (size_t)d.n_shared * d.N * d.H;
+        const long long grid = (mb_r * kp_r + d.n_shared * mb_s * kp_s) * nb_down;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
-        grouped_gemm_down_kernel<<<(unsigned)grid, 256, 0, st>>>(g);
+        grouped_gemm_kernel<false><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
         if (sel.last)
             combine_kernel<<<d.N, 256, 0, st>>>(ms.yp_r, ms.yp_s, da.inv_perm, da.topk_w,
-                                            da.shared_gate ? ms.sgate : nullptr, d.N, d.H, d.k, d.n_shared,
+                                            da.shared_gate ? ms.sgate : nullptr, d.N, d.H, d.k, d.n_shared, kp_r, kp_s,
+                                            g.part_r, g.part_s,
                                             d.y_is_fp32 ? static_cast<float*>(y_out) : nullptr,
                                             d.y_is_fp32 ? nullptr : static_cast<uint16_t*>(y_out));
         FATE_HIP(hipGetLastError());
