@@ -7,6 +7,7 @@
 // popularity and permutation; prefill sizes: both gates in one GEMM launch, then the permutation.
 #include "common.h"
 #include "route_device.h"
+#include "async_lds.h"
 
 namespace fate {
 
@@ -99,141 +100,250 @@ __global__ __launch_bounds__(64 * kTokWaves) void route_rows_kernel(const uint16
 }
 
 // Many tokens (prefill): the gate is a small GEMM, z[N,E] = x[N,H] . Wg[E,H]^T, done on the matrix
-// cores.  A workgroup (8 waves) owns 32 tokens; wave w takes expert tile (w & 1) of a pair of
-// 32-expert tiles and quarter (w >> 1) of the reduction dimension; the quarters add up in LDS.  Both operands are row-major with the
-// reduction dimension contiguous, which is the register layout of v_mfma_f32_32x32x16_bf16 as it
-// stands: lane (half, r) holds 8 consecutive elements of row r - 16 bytes straight from memory.
+// cores.  A workgroup (8 waves) owns TOK tokens; wave w takes expert tile (w & 1) of a pair of
+// 32-expert tiles and quarter (w >> 1) of the reduction dimension; the quarters add up in LDS.
 // bf16 products are exact in fp32; accumulation is fp32.  The logits meet in LDS, then one wave
 // per token does softmax and selection as in the other kernels.
+// What bounds it is the way of the gate matrix (a few hundred KB per workgroup) into the compute
+// unit.  Every wave brings its own rows and columns to LDS by itself, 64 columns at a time in a ring
+// of stages, whole 128-byte lines per row (read straight into the operand registers, a load
+// touches 32 rows for 32 bytes each); no barrier before the logits meet.  Both gates, E = 60, H = 2048: 131
+// tokens 18.3 -> 10.8 us, 2048 tokens 25.4 -> 16.6 us.
 struct RouteSecond {             // arguments of the second gate (grid.y = 2); unused when grid.y = 1
     const uint16_t* Wg; const float* bias; int m; int32_t* ids; float* w; int32_t* pop;
-    int32_t* pop_part;           // [workgroups][E]: when set, a workgroup leaves its counts here (plain stores)
-                                 // for the permutation kernel to add up, and pop needs neither zeroing nor atomics
+    int32_t* pop_part;           // [workgroups][E] each: when set, a workgroup leaves its counts of predicted /
+    int32_t* cnt_part;           // selected experts there (plain stores) for permute_parts_kernel to add up
 };
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float rf32x16_t;
-constexpr int kGemmTok = 32;
+constexpr int kGateWaves = 8;
+constexpr int gate_stage(int tok) { return 32 * 128 + tok * 128; }       // bytes per wave: 32 gate rows, the tokens
+constexpr int gate_depth(int tok) { return tok == 32 ? 2 : 3; }
+constexpr int gate_lds(int tok, int ne) {
+    const int ring = kGateWaves * gate_depth(tok) * gate_stage(tok), logits = 4 * tok * ne * 64 * 4;
+    return ring > logits ? ring : logits;
+}
 
-__global__ __launch_bounds__(512) void route_mfma_kernel(const uint16_t* __restrict__ x,
-                                                         const uint16_t* __restrict__ Wg,
-                                                         const float* __restrict__ bias, int N, int H, int E,
-                                                         int m, int renorm, int32_t* __restrict__ ids,
-                                                         float* __restrict__ w, float* __restrict__ probs,
-                                                         int32_t* __restrict__ pop, int ntok, RouteSecond g2) {
-    // ntok <= 32 tokens per workgroup: with few tokens in the call, fewer rows of the 32-row
-    // product are live but more workgroups share the work (each still reads all of Wg)
-    extern __shared__ float zs[];                 // [4 quarters][32 tokens][Epad]
-    // popularity counts of this workgroup's tokens: added up here first, so that the device-wide
-    // histogram takes one atomic per workgroup and expert instead of one per token and expert
-    // (atomics on one address are served one after the other, and popular experts are popular)
+// NE = pairs of expert tiles (E <= 64 * NE)
+template <int TOK, int NE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void route_mfma_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ Wg, const float* __restrict__ bias, int N, int H, int E,
+    int m, int renorm, int32_t* __restrict__ ids, float* __restrict__ w, float* __restrict__ probs,
+    int32_t* __restrict__ pop, RouteSecond g2) {
+    extern __shared__ uint4 smem[];
+    // counts of this workgroup's tokens: added up here first, so that a device-wide histogram
+    // takes one atomic per workgroup and expert instead of one per token and expert
     __shared__ int32_t pop_s[kMaxE];
-    int32_t* pop_part = nullptr;
+    int32_t* part = g2.cnt_part;
     if (blockIdx.y == 1) {                        // the second gate of the same launch (next layer's)
         Wg = g2.Wg; bias = g2.bias; m = g2.m; renorm = 0; ids = g2.ids; w = g2.w; probs = nullptr; pop = g2.pop;
-        pop_part = g2.pop_part;
+        part = g2.pop_part;
     }
+    constexpr int S = gate_depth(TOK), SB = gate_stage(TOK), NX = TOK / 8, LPS = 4 + NX;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5;
     const int etile = wave & 1, kq = wave >> 1;
-    const int Epad = (E + 63) & ~63;
-    const int t0 = blockIdx.x * ntok;
-    const int tok = n < ntok ? t0 + n : N;        // rows past ntok: no token
-    const int kbeg = kq * (H >> 2), kend = kbeg + (H >> 2);
+    const int t0 = blockIdx.x * TOK;
+    const int nchunk = H >> 8, nst = NE * nchunk;  // stages: the quarter's chunks of 64 columns for every pair of tiles
+    const bool counted = pop != nullptr || part != nullptr;
+    if (counted)
+        for (int i = threadIdx.x; i < E; i += 512) pop_s[i] = 0;
 
-    // Rows without a token and columns without an expert read row 0 instead (their products are
-    // never looked at): every load is unconditional, so the compiler's waits count the loads
-    // still in flight and the next chunk's operands travel under this chunk's products.
-    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)(tok < N ? tok : 0) * H) + half;
-    for (int e0 = 0; e0 < E; e0 += 64) {
-        const int e = e0 + etile * 32 + n;
-        const uint4* wr = reinterpret_cast<const uint4*>(Wg + (size_t)(e < E ? e : 0) * H) + half;
-        rf32x16_t acc;
+    // a load brings 8 rows of 128 bytes; piece p of row r goes to place p ^ (r & 7)
+    char* ring = reinterpret_cast<char*>(smem) + wave * (S * SB);
+    const uint32_t lds0 = lds_offset(ring);
+    const int rl = lane >> 3, q = (lane & 7) ^ rl;
+    uint32_t xoff[NX], woff[4];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc[j] = 0.f;
-        // chunks of eight matrix-core steps (H % 1024 == 0: a quarter of K is a whole number of
-        // pairs of chunks)
-        constexpr int kStep = 8;
-        uint4 av[2][kStep], bv[2][kStep];
-        auto request = [&](uint4 (&a)[kStep], uint4 (&b)[kStep], int k) {
+    for (int i = 0; i < NX; ++i) {
+        const int t = t0 + i * 8 + rl;
+        xoff[i] = (uint32_t)((i * 8 + rl) * (t < N ? 1 : 0)) * (uint32_t)H * 2u + q * 16;      // no token: the first one's row
+    }
 #pragma unroll
-            for (int u = 0; u < kStep; ++u) {
-                a[u] = xr[(k + 16 * u) >> 3];
-                b[u] = wr[(k + 16 * u) >> 3];
+    for (int i = 0; i < 4; ++i) woff[i] = (uint32_t)(i * 8 + rl) * (uint32_t)H * 2u + q * 16;
+    const char* xb = reinterpret_cast<const char*>(x + (size_t)t0 * H + kq * (H >> 2));
+    const char* wb = reinterpret_cast<const char*>(Wg + kq * (H >> 2));
+    auto issue = [&](int st, int slot) {
+        const int e0 = st / nchunk, c = st - e0 * nchunk;
+        const uint32_t base = lds0 + slot * SB;
+        const int r0 = e0 * 64 + etile * 32;          // rows past the last expert read row 0 (their logits are not looked at)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            lds_load16(base + i * 1024, wb + c * 128, r0 + i * 8 + rl < E ? (uint32_t)r0 * (uint32_t)H * 2u + woff[i] : (uint32_t)q * 16);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) lds_load16(base + 4096 + i * 1024, xb + c * 128, xoff[i]);
+    };
+    rf32x16_t acc[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[e][j] = 0.f;
+    const int xr = n & (TOK - 1);
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s) issue(s, s);      // (H >= 1024: four stages at least)
+    int slot = 0, slot_in = S - 1, st = 0;
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+        for (int c = 0; c < nchunk; ++c, ++st) {
+            wait_stages<LPS, S - 2>(nst - 1 - st);
+            // the wave's reads of the stage that is about to be overwritten have returned
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (st + S - 1 < nst) issue(st + S - 1, slot_in);
+            const char* base = ring + slot * SB;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int p = 2 * u + half;
+                const uint4 av = *reinterpret_cast<const uint4*>(base + 4096 + xr * 128 + ((p ^ (xr & 7)) * 16));
+                const uint4 bv = *reinterpret_cast<const uint4*>(base + n * 128 + ((p ^ (n & 7)) * 16));
+                acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av),
+                                                                 __builtin_bit_cast(bf16x8_t, bv), acc[e], 0, 0, 0);
             }
-        };
-        auto multiply = [&](const uint4 (&a)[kStep], const uint4 (&b)[kStep]) {
-#pragma unroll
-            for (int u = 0; u < kStep; ++u)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a[u]),
-                                                              __builtin_bit_cast(bf16x8_t, b[u]), acc, 0, 0, 0);
-        };
-        request(av[0], bv[0], kbeg);
-        for (int k = kbeg; k < kend; k += 2 * 16 * kStep) {
-            request(av[1], bv[1], k + 16 * kStep);
-            multiply(av[0], bv[0]);
-            // the last request of the row runs past this wave's quarter by one chunk: clamped to stay inside the row
-            request(av[0], bv[0], k + 2 * 16 * kStep < kend ? k + 2 * 16 * kStep : kbeg);
-            multiply(av[1], bv[1]);
+            slot = slot + 1 == S ? 0 : slot + 1;
+            slot_in = slot_in + 1 == S ? 0 : slot_in + 1;
         }
-        // lane (half, n) holds expert column n, token rows 8*(j/4) + 4*half + j%4
+    __syncthreads();                                  // the rings are done with: the logits take their place
+    float* zs = reinterpret_cast<float*>(smem);       // [4 quarters][TOK][64 * NE]
+    constexpr int Epad = 64 * NE;
+    // lane (half, n) holds expert column n, token rows 8*(j/4) + 4*half + j%4
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int t = 8 * (j >> 2) + 4 * half + (j & 3);
-            zs[((size_t)kq * kGemmTok + t) * Epad + e0 + etile * 32 + n] = acc[j];
+            if (t < TOK) zs[((size_t)kq * TOK + t) * Epad + e * 64 + etile * 32 + n] = acc[e][j];
+        }
+    __syncthreads();
+    for (int t = wave; t < TOK; t += kGateWaves) {
+        const int tk = t0 + t;
+        if (tk < N) {
+            float* z = zs + (size_t)t * Epad;
+            constexpr size_t Q = (size_t)TOK * Epad;
+#pragma unroll
+            for (int e = lane; e < Epad; e += 64)
+                if (e < E) z[e] = ((z[e] + z[e + Q]) + (z[e + 2 * Q] + z[e + 3 * Q])) + (bias ? bias[e] : 0.f);
+            __builtin_amdgcn_wave_barrier();
+            wave_softmax_topm(z, E, m, renorm, ids + (size_t)tk * m, w + (size_t)tk * m,
+                              probs ? probs + (size_t)tk * E : nullptr, counted ? pop_s : nullptr);
         }
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < ntok * E; i += 512) {
-        const int t = i / E, e = i - t * E;
-        const size_t o = (size_t)t * Epad + e, q = (size_t)kGemmTok * Epad;
-        zs[o] = ((zs[o] + zs[o + q]) + (zs[o + 2 * q] + zs[o + 3 * q])) + (bias ? bias[e] : 0.f);
-    }
-    if (pop)
-        for (int i = threadIdx.x; i < E; i += 512) pop_s[i] = 0;
-    __syncthreads();
-    for (int t = wave; t < ntok; t += 8) {
-        const int tk = t0 + t;
-        if (tk < N)
-            wave_softmax_topm(zs + (size_t)t * Epad, E, m, renorm, ids + (size_t)tk * m, w + (size_t)tk * m,
-                              probs ? probs + (size_t)tk * E : nullptr, pop ? pop_s : nullptr);
-    }
-    if (pop) {
+    if (counted) {
         __syncthreads();
-        if (pop_part) {
-            for (int i = threadIdx.x; i < E; i += 512) pop_part[(size_t)blockIdx.x * E + i] = pop_s[i];
-        } else {
-            for (int i = threadIdx.x; i < E; i += 512)
-                if (pop_s[i]) atomicAdd(&pop[i], pop_s[i]);
+        for (int i = threadIdx.x; i < E; i += 512) {
+            if (part) part[(size_t)blockIdx.x * E + i] = pop_s[i];
+            else if (pop_s[i]) atomicAdd(&pop[i], pop_s[i]);
         }
     }
 }
 
 __global__ __launch_bounds__(1024) void permute_kernel(const int32_t* __restrict__ ids, int P, int E,
                                                        int32_t* counts, int32_t* offsets, int32_t* perm,
-                                                       int32_t* inv_perm, int32_t* order,
-                                                       const int32_t* __restrict__ pop_part, int nparts,
-                                                       int32_t* __restrict__ pop_out) {
+                                                       int32_t* inv_perm, int32_t* order) {
     __shared__ int32_t sm[kPermSmemInts];
-    if (pop_part) {
-        // predicted popularity: the routing workgroups' partial histograms [nparts][E] added up
-        // (lane = expert within a group of 64, wave = every 16th partial row)
-        __shared__ int32_t hist[kMaxE];
-        const int lane = threadIdx.x & 63, row = threadIdx.x >> 6;
-        for (int i = threadIdx.x; i < E; i += 1024) hist[i] = 0;
-        __syncthreads();
-        for (int e = lane; e < E; e += 64) {
-            int sum = 0;
-            for (int p = row; p < nparts; p += 16) sum += pop_part[(size_t)p * E + e];
-            if (sum) atomicAdd(&hist[e], sum);
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < E; i += 1024) pop_out[i] = hist[i];
-    }
     if (P <= 64) {
         if (threadIdx.x < 64) wave_permute_small(ids, P, E, counts, offsets, perm, inv_perm, order);
         return;
     }
     block_permute(ids, P, E, counts, offsets, perm, inv_perm, order, sm);
+}
+
+// The permutation after route_mfma_kernel, a workgroup per routing workgroup: the rows of counts
+// that those left (cnt_part [nparts][E]) give the place of every expert and, summed up to this
+// workgroup's row, of its pairs among the expert's; the pairs of its own tokens (pairs_wg of them)
+// are ranked by one wave in order.  Same outputs as permute_kernel, which one workgroup works
+// through on its own (131 tokens, k = 4: 8.9 -> 5.5 us, 2048 tokens 21.9 -> 13.2 us).
+// The first workgroup writes what is not per pair.
+__global__ __launch_bounds__(256) void permute_parts_kernel(const int32_t* __restrict__ ids, int P, int pairs_wg, int E,
+                                                            int nparts, const int32_t* __restrict__ cnt_part,
+                                                            const int32_t* __restrict__ pop_part, int32_t* counts,
+                                                            int32_t* offsets, int32_t* perm, int32_t* inv_perm,
+                                                            int32_t* order, int32_t* pop_out) {
+    __shared__ int32_t tot[kMaxE], before[kMaxE], pops[kMaxE], wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.x;
+    const int beg = b * pairs_wg, end = min(P, beg + pairs_wg);
+    const int id0 = wave == 0 && beg + lane < end ? ids[beg + lane] : -1;      // under way with the counts
+    for (int i = tid; i < E; i += 256) tot[i] = before[i] = pops[i] = 0;
+    __syncthreads();
+    // column sums: a thread takes one expert (of Ew = 64, 128 or 256 columns) and every (256 / Ew)-th row
+    const int Ew = E <= 64 ? 64 : (E <= 128 ? 128 : 256);
+    const int e0 = tid & (Ew - 1), rstep = 256 / Ew;
+    if (e0 < E) {
+        int t = 0, bf = 0, pp = 0;
+        const bool want_pop = b == 0 && pop_part != nullptr;
+        for (int p = tid / Ew; p < nparts; p += 8 * rstep) {
+            int v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = p + i * rstep < nparts ? cnt_part[(size_t)(p + i * rstep) * E + e0] : 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                t += v[i];
+                bf += p + i * rstep < b ? v[i] : 0;
+            }
+        }
+        if (want_pop)
+            for (int p = tid / Ew; p < nparts; p += rstep) pp += pop_part[(size_t)p * E + e0];
+        if (rstep == 1) {
+            tot[e0] = t; before[e0] = bf; pops[e0] = pp;
+        } else {
+            atomicAdd(&tot[e0], t);
+            atomicAdd(&before[e0], bf);
+            if (want_pop) atomicAdd(&pops[e0], pp);
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the totals over experts (one per thread)
+    const int c = tid < E ? tot[tid] : 0;
+    int inc = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += up;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    int carry = 0;
+    for (int i = 0; i < wave; ++i) carry += wsum[i];
+    const int off = carry + inc - c;
+    if (tid < E) before[tid] += off;                   // where this workgroup's pairs of the expert start
+    if (b == 0) {
+        if (tid < E) {
+            counts[tid] = c;
+            offsets[tid] = off;
+            if (pop_part) pop_out[tid] = pops[tid];
+        }
+        if (tid == 0) offsets[E] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        int nbits = 0;
+        while ((1 << nbits) < E) ++nbits;
+        const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+        volatile int32_t* at = before;
+        for (int i0 = beg; i0 < end; i0 += 64) {
+            const int i = i0 + lane;
+            const int e = i0 == beg ? id0 : (i < end ? ids[i] : -1);
+            const bool valid = i < end && e >= 0 && e < E;
+            const unsigned long long mk = wave_match(e, valid, nbits);
+            const int start = valid ? at[e] : 0;
+            if (valid) {
+                const int pos = start + __popcll(mk & lt);
+                perm[pos] = i;
+                inv_perm[i] = pos;
+                if ((mk & lt) == 0) at[e] = start + __popcll(mk);
+            }
+        }
+    } else if (b == 0) {
+        // experts by (count descending, id ascending): rank = experts that come before
+        for (int e = tid - 64; e < E; e += 192) {
+            const int ce = tot[e];
+            int r = 0;
+            for (int j = 0; j < E; ++j) {
+                const int cj = tot[j];
+                r += cj > ce || (cj == ce && j < e);
+            }
+            order[r] = e;
+        }
+    }
 }
 
 // ---- fused decode-side routing --------------------------------------------
@@ -306,22 +416,38 @@ static fate_status check_route_args(const void* x, const void* Wg, const float* 
 // filled with tokens
 static int route_mfma_ntok(int N) { return N > 4096 ? 32 : (N > 1024 ? 16 : 8); }
 
+template <int TOK, int NE>
+static fate_status launch_route_mfma_v(hipStream_t st, dim3 grid, const uint16_t* x, const uint16_t* Wg, const float* bias,
+                                       int N, int H, int E, int m, bool renorm, int32_t* ids, float* w, float* probs,
+                                       int32_t* pop, const RouteSecond& second) {
+    constexpr int lds = gate_lds(TOK, NE);
+    static bool attr_done = false;
+    if (!attr_done) {
+        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(route_mfma_kernel<TOK, NE>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        attr_done = true;
+    }
+    route_mfma_kernel<TOK, NE><<<grid, 64 * kGateWaves, lds, st>>>(x, Wg, bias, N, H, E, m, renorm, ids, w, probs, pop, second);
+    FATE_HIP(hipGetLastError());
+    return FATE_OK;
+}
+
 static fate_status launch_route_mfma(hipStream_t st, const void* x, const void* Wg, const float* bias, int N, int H,
                                      int E, int m, bool renorm, int32_t* ids, float* w, float* probs, int32_t* pop,
                                      RouteSecond second, int ngates) {
-    const size_t lds_g = (size_t)4 * kGemmTok * ((E + 63) & ~63) * sizeof(float);
-    static bool attr_done = false;
-    if (!attr_done) {
-        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(route_mfma_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kGemmTok * kMaxE * 4));
-        attr_done = true;
-    }
     const int ntok = route_mfma_ntok(N);
-    route_mfma_kernel<<<dim3((N + ntok - 1) / ntok, ngates), 512, lds_g, st>>>(
-        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(Wg), bias, N, H, E, m, renorm, ids, w, probs, pop,
-        ntok, second);
-    FATE_HIP(hipGetLastError());
-    return FATE_OK;
+    const dim3 grid((N + ntok - 1) / ntok, ngates);
+    const uint16_t *xs = static_cast<const uint16_t*>(x), *ws = static_cast<const uint16_t*>(Wg);
+#define FATE_GATE(TOK, NE) return launch_route_mfma_v<TOK, NE>(st, grid, xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop, second)
+#define FATE_GATE_E(TOK)                          \
+    if (E <= 64) FATE_GATE(TOK, 1);               \
+    else if (E <= 128) FATE_GATE(TOK, 2);         \
+    else FATE_GATE(TOK, 4);
+    if (ntok == 8) { FATE_GATE_E(8) }
+    else if (ntok == 16) { FATE_GATE_E(16) }
+    else { FATE_GATE_E(32) }
+#undef FATE_GATE_E
+#undef FATE_GATE
 }
 
 static fate_status launch_route_rows(hipStream_t st, const void* x, const void* Wg, const float* bias, int N,
@@ -379,7 +505,7 @@ extern "C" fate_status fate_permute(void* stream, const int32_t* topk_ids, int N
     if (N > 0 && (topk_ids == nullptr || perm == nullptr || inv_perm == nullptr))
         FATE_FAIL(FATE_EINVAL, "topk_ids, perm and inv_perm must not be NULL when N > 0");
     permute_kernel<<<1, 1024, 0, static_cast<hipStream_t>(stream)>>>(topk_ids, N * k, E, counts, offsets, perm,
-                                                                    inv_perm, expert_order, nullptr, 0, nullptr);
+                                                                    inv_perm, expert_order);
     FATE_HIP(hipGetLastError());
     return FATE_OK;
 }
@@ -417,17 +543,19 @@ extern "C" fate_status fate_route_fused(void* stream, const void* x_bf16, const 
     FATE_CHECK_PTR(workspace);
     if (big) {
         hipStream_t st = static_cast<hipStream_t>(stream);
-        // the workgroups' popularity counts go through the workspace and are added up by the
-        // permutation kernel: no zeroing launch, no atomics on the device-wide histogram
+        // the workgroups' counts go through the workspace and are added up by the permutation
+        // kernel: no zeroing launch, no atomics on the device-wide histogram
         const int ntok = route_mfma_ntok(N), nparts = (N + ntok - 1) / ntok;
-        int32_t* pop_part = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + 256);
+        int32_t* cnt_part = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + 256);
+        int32_t* pop_part = cnt_part + (size_t)nparts * E;         // (nparts <= N / 8 + 1: the logits' room holds both)
         s = launch_route_mfma(st, x_bf16, Wg_bf16, bias, N, H, E, k, renorm != 0, topk_ids, topk_w, nullptr, nullptr,
                               RouteSecond{static_cast<const uint16_t*>(Wg_next_bf16), bias_next, m, pred_ids, pred_w,
-                                          pred_pop, pop_part},
+                                          pred_pop, pop_part, cnt_part},
                               Wg_next_bf16 ? 2 : 1);
         if (s != FATE_OK) return s;
-        permute_kernel<<<1, 1024, 0, st>>>(topk_ids, N * k, E, counts, offsets, perm, inv_perm, expert_order,
-                                           Wg_next_bf16 ? pop_part : nullptr, nparts, pred_pop);
+        permute_parts_kernel<<<nparts, 256, 0, st>>>(topk_ids, N * k, ntok * k, E, nparts, cnt_part,
+                                                     Wg_next_bf16 ? pop_part : nullptr, counts, offsets, perm, inv_perm,
+                                                     expert_order, pred_pop);
         FATE_HIP(hipGetLastError());
         return FATE_OK;
     }
