@@ -42,7 +42,8 @@ static void carve(const fate_ffn_desc& d, void* base, FfnWorkspace* w) {
     off += align_up((size_t)d.N * d.k * d.I_max * 2, 256);
     w->h_s = reinterpret_cast<__half*>(p + off);
     off += align_up((size_t)d.n_shared * d.N * (d.n_shared ? d.I_shared_max : 0) * 2, 256);
-    const bool mfma = d.mode == 2 || (d.mode == 0 && d.N > 16);
+    const bool exact = d.mode != 2 && decode_by_gemm(d);
+    const bool mfma = d.mode == 2 || (d.mode == 0 && d.N > 16) || exact;
     w->part_r = w->part_s = reinterpret_cast<float*>(p + off);
     if (!mfma) {
         const int ncr = decode_down_chunks(d.I_max / d.group);
@@ -55,12 +56,13 @@ static void carve(const fate_ffn_desc& d, void* base, FfnWorkspace* w) {
         const size_t nseg1 = (size_t)d.E + d.n_shared + 1;
         w->ms.xh = reinterpret_cast<__half*>(p + off); off += align_up((size_t)d.N * d.H * 2, 256);
         w->ms.sgate = reinterpret_cast<float*>(p + off); off += align_up((size_t)d.N * 4, 256);
-        w->ms.tab_up = reinterpret_cast<int32_t*>(p + off); off += align_up(nseg1 * 4, 256);
-        w->ms.tab_down = reinterpret_cast<int32_t*>(p + off); off += align_up(nseg1 * 4, 256);
+        w->ms.tab_up = reinterpret_cast<int4*>(p + off); off += align_up(nseg1 * sizeof(int4), 256);
+        w->ms.tab_down = reinterpret_cast<int4*>(p + off); off += align_up(nseg1 * sizeof(int4), 256);
         int kp_r = 1, kp_s = 1;
         mfma_k_parts(d, &kp_r, &kp_s);
-        w->ms.yp_r = reinterpret_cast<__half*>(p + off); off += align_up((size_t)kp_r * d.N * d.k * d.H * 2, 256);
-        w->ms.yp_s = reinterpret_cast<__half*>(p + off); off += align_up((size_t)kp_s * d.n_shared * d.N * d.H * 2, 256);
+        const size_t osz = exact ? 4 : 2;
+        w->ms.yp_r = p + off; off += align_up((size_t)kp_r * d.N * d.k * d.H * osz, 256);
+        w->ms.yp_s = p + off; off += align_up((size_t)kp_s * d.n_shared * d.N * d.H * osz, 256);
     }
     w->bytes = off + 256;
 }
@@ -117,9 +119,13 @@ static fate_status ffn_q_phase(int phase, const PartSel& sel, void* stream, cons
     if (mode == 1) {
         if (phase != 0 || !sel.first || !sel.last || ~sel.mask[0] || ~sel.mask[1] || ~sel.mask[2] || ~sel.mask[3])
             FATE_FAIL(FATE_EINVAL, "the decode kernels run the whole FFN only (no phases, no pieces)");
+        if (decode_by_gemm(*d)) {
+            fate_status s2 = check_decode_groups(*d);
+            return s2 != FATE_OK ? s2 : launch_ffn_mfma(st, *d, a, w.ms, y, 0, sel, true);
+        }
         return launch_ffn_decode(st, *d, a, y);
     }
-    return launch_ffn_mfma(st, *d, a, w.ms, y, phase, sel);
+    return launch_ffn_mfma(st, *d, a, w.ms, y, phase, sel, false);
 }
 
 extern "C" fate_status fate_moe_ffn_q(void* stream, const fate_ffn_desc* d, const void* x_bf16,

@@ -1,5 +1,6 @@
-// Decode-side expert FFN behind fate_moe_ffn_q: bandwidth-bound dequant-GEMV
-// kernels, three launches per layer.
+// Decode-side expert FFN behind fate_moe_ffn_q for small layers and for sizes
+// that are no multiple of 128 (decode_by_gemm says which calls take the GEMM's
+// decode-sized form instead): dequant-GEMV kernels, three launches per layer.
 //  up:   a workgroup owns 32 intermediate neurons of one activated expert (or
 //        of a shared expert): it streams the matching 32-row blocks of W1 and
 //        W3 (device-native 1 KiB tiles, one contiguous KiB per wave load),
@@ -329,9 +330,15 @@ __global__ __launch_bounds__(256) void ffn_sum_decode_kernel(DecodeArgs a, void*
 
 constexpr size_t kLdsMax = 96 * 1024;
 
-fate_status launch_ffn_decode(hipStream_t st, const fate_ffn_desc& d, DecodeArgs a, void* y_out) {
+fate_status check_decode_groups(const fate_ffn_desc& d) {
     if (!decode_group_ok(d.bits, d.group) || (d.n_shared && !decode_group_ok(d.shared_bits, d.shared_group)))
         FATE_FAIL(FATE_ESHAPE, "decode path: group must be 64, 128 or 256 (int4) / 64 or 128 (int8)");
+    return FATE_OK;
+}
+
+fate_status launch_ffn_decode(hipStream_t st, const fate_ffn_desc& d, DecodeArgs a, void* y_out) {
+    const fate_status gs = check_decode_groups(d);
+    if (gs != FATE_OK) return gs;
     const int Gr = d.I_max / d.group, Gs = d.n_shared ? d.I_shared_max / d.shared_group : 0;
     a.nchunk_r = decode_down_chunks(Gr); a.cg_r = (Gr + a.nchunk_r - 1) / a.nchunk_r;
     a.nchunk_s = decode_down_chunks(Gs); a.cg_s = Gs ? (Gs + a.nchunk_s - 1) / a.nchunk_s : 1;

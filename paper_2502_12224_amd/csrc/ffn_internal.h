@@ -33,10 +33,10 @@ struct DecodeArgs {
 struct MfmaScratch {
     __half* xh;        // [N,H] fp16 copy of x
     float* sgate;      // [N] shared gate values
-    int32_t* tab_up;   // [E + n_shared + 1] tile prefix sums of the up GEMM
-    int32_t* tab_down; // same for the down GEMM
-    __half* yp_r;      // [kp_r][P,H] per-pair outputs of the down GEMM
-    __half* yp_s;      // [kp_s][n_shared*N,H]
+    int4* tab_up;      // [E + n_shared + 1] segments of the up GEMM: first tile, expert, first row, rows
+    int4* tab_down;    // same for the down GEMM
+    void* yp_r;        // [kp_r][P,H] per-pair outputs of the down GEMM, fp16 (decode-sized calls: fp32)
+    void* yp_s;        // [kp_s][n_shared*N,H]
 };
 
 struct FfnWorkspace {
@@ -49,6 +49,7 @@ struct FfnWorkspace {
     size_t bytes;
 };
 
+fate_status check_decode_groups(const fate_ffn_desc& d);
 fate_status launch_ffn_decode(hipStream_t st, const fate_ffn_desc& d, DecodeArgs a, void* y_out);
 // reduction chunks (of at most 16 groups) of the decode down kernel for an intermediate size of G groups
 inline int decode_down_chunks(int G) { return G > 0 ? (G + 15) / 16 : 1; }
@@ -62,8 +63,17 @@ inline PartSel part_all() { return PartSel{{~0ull, ~0ull, ~0ull, ~0ull}, 1, 1}; 
 
 // parts of the reduction dimension of the down GEMM of routed / shared experts
 void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s);
-// phase: 0 = whole FFN, 1 = prep + up/gate GEMM only, 2 = down GEMM + combine only (timing aid)
+// exact: the decode-sized form of the GEMMs (at most 16 tokens).  phase: 0 = whole FFN, 1 = prep + up/gate GEMM only, 2 = down GEMM + combine only (timing aid)
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs a, const MfmaScratch& ms,
-                            void* y_out, int phase, const PartSel& sel);
+                            void* y_out, int phase, const PartSel& sel, bool exact);
+// The decode kernels' job done by the GEMM's decode-sized form (exact weights, fp32 per-pair outputs):
+// up to 16 tokens, sizes that are multiples of 128, and at least half a device of its 128-neuron
+// workgroups.  Below that the decode kernels' 32-neuron workgroups spread the weights further (two
+// int8 layers of H = 256, I = 512, E = 8 at 16 tokens: 49 us with them, 56 with the GEMMs).
+inline bool decode_by_gemm(const fate_ffn_desc& d) {
+    if (d.N > 16 || d.H % 128 || d.I_max % 128 || (d.n_shared && d.I_shared_max % 128)) return false;
+    const long long experts = (long long)d.N * d.k < d.E ? (long long)d.N * d.k : d.E;
+    return experts * (d.I_max / 128) + d.n_shared * ((d.n_shared ? d.I_shared_max : 0) / 128) >= 128;
+}
 
 }  // namespace fate

@@ -53,10 +53,10 @@ struct GemmArgs {
     int H;                             // hidden size
     const fate_qexpert* experts; const fate_qexpert* shared;
     int E, n_shared, N, k;
-    const int32_t* offsets; const int32_t* perm; const int32_t* order;
-    const int32_t* tile_start;         // [E + n_shared + 1]
-    __half* out_r; int ldo_r;          // routed rows, by sorted position
-    __half* out_s; int ldo_s;          // shared rows, s*N + t
+    const int32_t* perm;
+    const int4* segs;                  // [E + n_shared + 1]: first tile, expert, first row and rows of a segment
+    void* out_r; int ldo_r;            // routed rows, by sorted position (fp16; the exact down GEMM: fp32)
+    void* out_s; int ldo_s;            // shared rows, s*N + t
     int nb_r, nb_s;                    // column blocks per routed / shared segment
     int kp_r, kp_s;                    // parts of the reduction dimension (down GEMM), each with an output of its own
     size_t part_r, part_s;             // elements between those outputs
@@ -75,9 +75,9 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
                                                            const int32_t* __restrict__ order,
                                                            const uint16_t* __restrict__ shared_gate,
                                                            __half* __restrict__ xh, float* __restrict__ sgate,
-                                                           int32_t* __restrict__ tab_up,
-                                                           int32_t* __restrict__ tab_down, int nb_r_up,
-                                                           int nb_s_up, int nb_r_down, int nb_s_down, PartSel sel) {
+                                                           int4* __restrict__ tab_up, int4* __restrict__ tab_down,
+                                                           int nb_r_up, int nb_s_up, int nb_r_down, int nb_s_down,
+                                                           PartSel sel) {
     __shared__ float red[4];
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nvec = H >> 3;
@@ -120,13 +120,14 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
         int ru = 0, rd = 0;
         for (int s0 = 0; s0 < nseg; s0 += 64) {
             const int s = s0 + lane;
-            int cu = 0, cd = 0;
+            int cu = 0, cd = 0, e = 0, T = 0, row = 0;
             if (s < nseg) {
                 // a piece holds the routed experts of its mask; the shared experts go with the first piece.
                 // The table is read from its end: shared experts, then experts by falling number of rows
-                const int e = s < E ? order[E - 1 - s] : 0;
+                e = s < E ? order[E - 1 - s] : s - E;
                 const bool mine = s < E ? ((sel.mask[e >> 6] >> (e & 63)) & 1ull) != 0 : sel.first != 0;
-                const int T = !mine ? 0 : (s < E ? offsets[e + 1] - offsets[e] : N);
+                row = s < E ? offsets[e] : 0;
+                T = !mine ? 0 : (s < E ? offsets[e + 1] - row : N);
                 cu = ((T + kBM - 1) / kBM) * (s < E ? nb_r_up : nb_s_up);
                 cd = ((T + kBM - 1) / kBM) * (s < E ? nb_r_down : nb_s_down);
             }
@@ -137,15 +138,15 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
                 if (lane >= sh) { iu += pu; id += pd; }
             }
             if (s < nseg) {
-                tab_up[s] = ru + iu - cu;
-                tab_down[s] = rd + id - cd;
+                tab_up[s] = make_int4(ru + iu - cu, e, row, T);
+                tab_down[s] = make_int4(rd + id - cd, e, row, T);
             }
             ru += __shfl(iu, 63, 64);
             rd += __shfl(id, 63, 64);
         }
         if (lane == 0) {
-            tab_up[nseg] = ru;
-            tab_down[nseg] = rd;
+            tab_up[nseg] = make_int4(ru, 0, 0, 0);
+            tab_down[nseg] = make_int4(rd, 0, 0, 0);
         }
     }
 }
@@ -198,7 +199,7 @@ struct TileCtx {
     bool wlive[2];                     // whether they exist (a wave without weights still stages activations)
     int Nout, K, col0, ncol;           // weight rows of the matrix, its columns, this part's columns
     int group;
-    __half* out; int ldo;              // output row 0 of the tile
+    void* out; int ldo;                // output row 0 of the tile
 };
 
 template <int BITS>
@@ -378,7 +379,7 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
     for (int mt = 0; mt < NMT; ++mt) {
         const int r = mt * 32 + n;
         if (r < c.nrows) {
-            __half* o = c.out + (size_t)r * c.ldo + 4 * half;
+            __half* o = static_cast<__half*>(c.out) + (size_t)r * c.ldo + 4 * half;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if constexpr (UP) {
@@ -419,7 +420,7 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
                 lds_only_barrier();
                 if (c.rows) p.rows = c.rows + r0;
                 else p.A = c.A + (size_t)r0 * c.lda;
-                p.out = c.out + (size_t)r0 * c.ldo;
+                p.out = static_cast<__half*>(c.out) + (size_t)r0 * c.ldo;
             }
             p.nrows = min(64, c.nrows - r0);
             if (p.nrows <= 32) gemm_pipe<BITS, ZP, UP, 1>(p, smem);
@@ -428,41 +429,306 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
     }
 }
 
-template <bool UP>
+// ---- decode-sized form ---------------------------------------------------------------------------
+// At most 16 rows per expert: the codes stream once and everything else is small, so a tile is bounded
+// by the memory path and by the vector instructions of the widening.  The codes enter the matrix
+// cores as exact fp16 integers and a group's fp16 scale multiplies the group's fp32 sum: the weights
+// enter exactly, and a pair of codes takes two vector instructions instead of three.  With
+// zero-points the group's sum of activations comes from a third product with ones.
+// 13 tokens of the Qwen shape: up 45.3 -> 27.8 us (106 MB of codes and scales: 3.8 TB/s), down 45.7 -> 15.9 us
+// against the dequant-GEMV kernels, whose loads sit under branches.
+// D = activations x codes: lane n holds weight row n, rows 4*half + 0..3 and 8 + 4*half + 0..3.
+template <int BITS>
+struct ExactFmt {
+    static constexpr int KT = QFmt<BITS>::KT;
+    static constexpr int BK = BITS == 8 ? 64 : 128;       // columns per stage
+    static constexpr int TPS = BK / KT;
+    static constexpr int HS = BITS == 4 ? 2 : 1;          // scales per row and stage (groups of 64: two for int4)
+    static constexpr int XROW = BK * 2;
+    static constexpr int xbytes = 16 * XROW;
+    static constexpr int stage = xbytes + 4 * 2 * TPS * 1024 + 4 * HS * 256;
+    static constexpr int depth = kGemmLds / stage < 4 ? kGemmLds / stage : 4;
+};
+
+// codes of columns 2p, 2p + 1 of matrix-core step d as exact fp16 integers (int4: u - 8, int8: u - 128, int2: 2u - 3)
+template <int BITS, int TPS>
+__device__ __forceinline__ uint32_t code_pair(const uint4 (&raw)[TPS], int d, int p) {
+    auto dword = [&](int tl, int i) { return i == 0 ? raw[tl].x : i == 1 ? raw[tl].y : i == 2 ? raw[tl].z : raw[tl].w; };
+    auto both = [](float v) { return f16x2v_t{(_Float16)v, (_Float16)v}; };
+    f16x2v_t w;
+    if constexpr (BITS == 2) {
+        const uint32_t r = dword(0, d >> 1), x = d & 1 ? r >> 8 : r;
+        const uint32_t v = p == 0 ? and_or_b32(x, 0x00030003u, 0x64006400u) : p == 1 ? and_or_b32(x, 0x000c000cu, 0x5c005c00u)
+                         : p == 2 ? and_or_b32(x, 0x00300030u, 0x54005400u) : and_or_b32(x, 0x00c000c0u, 0x4c004c00u);
+        w = (__builtin_bit_cast(f16x2v_t, v) - both(p == 0 ? 1024.f : p == 1 ? 256.f : p == 2 ? 64.f : 16.f)) * both(2.f) - both(3.f);
+    } else if constexpr (BITS == 4) {
+        const uint32_t r = dword(d >> 2, d & 3), x = p < 2 ? r : r >> 8;
+        const uint32_t v = p & 1 ? and_or_b32(x, 0x00f000f0u, 0x54005400u) : and_or_b32(x, 0x000f000fu, 0x64006400u);
+        w = __builtin_bit_cast(f16x2v_t, v) - both(p & 1 ? 72.f : 1032.f);
+    } else {
+        const uint32_t v = __builtin_amdgcn_perm(0x64646464u, dword(d >> 1, 2 * (d & 1) + (p >> 1)), p & 1 ? 0x04030402u : 0x04010400u);
+        w = __builtin_bit_cast(f16x2v_t, v) - both(1152.f);
+    }
+    return __builtin_bit_cast(uint32_t, w);
+}
+
+// (u - z) x summed over a group = (sum of q x, q = a*u - c, plus (c - a z) times the sum of x) / a
+template <int BITS> struct ZpExact { static constexpr float inv_a = 1.0f, c_over_a = 8.0f; };
+template <> struct ZpExact<2> { static constexpr float inv_a = 0.5f, c_over_a = 1.5f; };
+
+template <int BITS, bool ZP, bool UP>
+__device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
+    typedef ExactFmt<BITS> F;
+    constexpr int KT = F::KT, BK = F::BK, TPS = F::TPS, HS = F::HS, XROW = F::XROW;
+    constexpr int SPT = KT / 16, KS = TPS * SPT, KH = KS / HS;
+    constexpr int NX = F::xbytes / 4096 > 0 ? F::xbytes / 4096 : 1;        // (2 KiB of activations: two waves load them)
+    constexpr int S = F::depth, SB = F::stage;
+    constexpr int LPS = NX + 2 * TPS + HS;
+    static_assert(S >= 2, "at least one stage ahead");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, half = lane >> 5;
+    const int nstage = c.ncol / BK, tiles_k = c.K / KT;
+    const uint32_t lds0 = lds_offset(smem);
+    constexpr int LPR = XROW / 16, RPL = 64 / LPR;        // lanes per row, rows per load
+    constexpr int XL = F::xbytes / 1024;                  // activation loads of a stage (4 or 2): one per wave, twice the same for int8
+    const int xl = wave % XL;
+    uint32_t xoff;
+    {
+        const int r = xl * RPL + lane / LPR, q = lane % LPR;
+        const int rr = r < c.nrows ? r : 0;
+        const int ar = c.rows ? c.rows[rr] / c.div : rr;
+        xoff = ((uint32_t)ar * (uint32_t)c.lda + (uint32_t)c.col0) * 2u + (uint32_t)((q ^ (r & 7)) * 16);
+    }
+    const char* wbase[2];
+    const char* sbase;
+    {
+        const void* wp[2] = {UP ? c.ex->w1 : c.ex->w2, UP ? c.ex->w3 : c.ex->w2};
+        const void* sp[2] = {UP ? c.ex->s1 : c.ex->s2, UP ? c.ex->s3 : c.ex->s2};
+        const void* zp[2] = {UP ? c.ex->z1 : c.ex->z2, UP ? c.ex->z3 : c.ex->z2};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            wbase[i] = static_cast<const char*>(uniform(wp[i])) + ((size_t)(c.wrow[i] >> 5) * tiles_k + c.col0 / KT) * 1024;
+        const int b = (lane >> 4) & 1;
+        const void* p0 = ZP && half ? zp[0] : sp[0];
+        const void* p1 = ZP && half ? zp[1] : sp[1];
+        sbase = static_cast<const char*>(b ? p1 : p0) + (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
+                (size_t)(c.col0 / c.group) * c.Nout * 2;
+    }
+    const uint32_t lane16 = lane * 16;
+    int gcol = c.col0 % c.group;                          // of the next piece of scales to be requested
+    auto issue_one = [&](int st, int slot, int l) {
+        const uint32_t base = lds0 + slot * SB;
+        if (l < NX) {
+            lds_load16(base + xl * 1024, reinterpret_cast<const char*>(c.A) + (size_t)st * XROW, xoff);
+        } else if (l < NX + 2 * TPS) {
+            const int i = (l - NX) / TPS, tl = (l - NX) % TPS;
+            lds_load16(base + F::xbytes + (wave * 2 * TPS + i * TPS + tl) * 1024, wbase[i] + (size_t)(st * TPS + tl) * 1024, lane16);
+        } else {
+            lds_load4(base + F::xbytes + 4 * 2 * TPS * 1024 + (wave * HS + (l - NX - 2 * TPS)) * 256, sbase);
+            gcol += BK / HS;
+            if (gcol >= c.group) {
+                gcol -= c.group;
+                sbase += (size_t)c.Nout * 2;
+            }
+        }
+    };
+    f32x16_t acc[2], sum;
+    // The up projection adds its groups up in quarters, as the one-call decode layer does (a wave per
+    // quarter there): h is rounded to fp16 and must not depend on which of the two computed it.
+    float out[2][8], tot[2][8];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc[0][j] = acc[1][j] = sum[j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) out[i][j] = tot[i][j] = 0.f;
+    const int ngroups = c.K / c.group;
+    int gidx = 0, quarter = ngroups / 4;                  // groups done, end of the current quarter
+    auto close_quarter = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                tot[i][j] += out[i][j];
+                out[i][j] = 0.f;
+            }
+    };
+    uint32_t aoff[KS];
+#pragma unroll
+    for (int d = 0; d < KS; ++d) {
+        const int piece = ((d / SPT) * KT + half * (KT / 2)) / 8 + d % SPT;
+        aoff[d] = (n & 15) * XROW + (piece ^ (n & 7)) * 16;
+    }
+    const f16x8_t ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
+    int gleft = c.group - c.col0 % c.group;               // columns left of the group being summed
+    int slot = 0, slot_in = S - 1;
+    auto next = [](int i) { return i + 1 == S ? 0 : i + 1; };
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nstage) {
+#pragma unroll
+            for (int l = 0; l < LPS; ++l) issue_one(s, s, l);
+        }
+    auto step = [&](int st, auto more) {                  // more: whether stage st + S - 1 exists
+        if constexpr (more) wait_loads<(S - 2) * LPS>();
+        else wait_stages<LPS, S - 2>(nstage - 1 - st);
+        lds_only_barrier();                               // stage st is in LDS, everyone is done with stage st - 1
+        const char* base = smem + slot * SB;
+        const char* wl = base + F::xbytes + wave * (2 * TPS * 1024) + lane16;
+        const char* sl = base + F::xbytes + 4 * 2 * TPS * 1024 + wave * (HS * 256) + n * 2;
+        uint4 raw[2][TPS];
+        _Float16 sv[HS][2], zv[HS][2];
+        f16x8_t av[2];
+        u32x4_t b[2][2];
+        auto widen = [&](int d, int e) { b[d & 1][e >> 2][e & 3] = code_pair<BITS>(raw[e >> 2], d, e & 3); };
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int tl = 0; tl < TPS; ++tl) raw[i][tl] = *reinterpret_cast<const uint4*>(wl + (i * TPS + tl) * 1024);
+#pragma unroll
+            for (int h = 0; h < HS; ++h) {
+                sv[h][i] = *reinterpret_cast<const _Float16*>(sl + h * 256 + i * 64);
+                zv[h][i] = ZP ? *reinterpret_cast<const _Float16*>(sl + h * 256 + 128 + i * 64) : (_Float16)0.f;
+            }
+        }
+        av[0] = *reinterpret_cast<const f16x8_t*>(base + aoff[0]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) widen(0, e);
+#pragma unroll
+        for (int d = 0; d < KS; ++d) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[d & 1], __builtin_bit_cast(f16x8_t, b[d & 1][i]), acc[i], 0, 0, 0);
+            if constexpr (ZP) sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[d & 1], ones, sum, 0, 0, 0);
+            if constexpr (more) {
+#pragma unroll
+                for (int l = LPS * d / KS; l < LPS * (d + 1) / KS; ++l) issue_one(st + S - 1, slot_in, l);
+            }
+            if (d + 1 < KS) {
+                av[(d + 1) & 1] = *reinterpret_cast<const f16x8_t*>(base + aoff[d + 1]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) widen(d + 1, e);
+            }
+            if ((d + 1) % KH == 0) {                      // the end of a scale's columns: the end of its group?
+                gleft -= BK / HS;
+                // (a part of the reduction dimension may end inside a group)
+                bool end = gleft == 0;
+                if constexpr (!more) end = end || (d + 1 == KS && st + 1 == nstage);
+                if (end) {
+                    gleft = c.group;
+                    const int h = d / KH;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const float s = (float)sv[h][i];
+                        const float dz = ZP ? (ZpExact<BITS>::c_over_a - (float)zv[h][i]) : 0.f;
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const float v = ZP ? fmaf(ZpExact<BITS>::inv_a, acc[i][j], dz * sum[j]) : acc[i][j];
+                            out[i][j] = fmaf(s, v, out[i][j]);
+                        }
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) sum[j] = 0.f;
+                    if constexpr (UP) {
+                        if (++gidx >= quarter) {
+                            close_quarter();
+                            // the next quarter that holds a group ends at ngroups * q / 4
+                            int qn = 4 * gidx / ngroups + 1;
+                            while (qn < 4 && ngroups * qn / 4 <= gidx) ++qn;
+                            quarter = ngroups * qn / 4;
+                        }
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        slot = next(slot);
+        slot_in = next(slot_in);
+    };
+    int st = 0;
+    for (; st + S - 1 < nstage; ++st) step(st, std::true_type{});
+    for (; st < nstage; ++st) step(st, std::false_type{});
+    if constexpr (UP) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) out[i][j] = tot[i][j];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int r = 8 * (j >> 2) + 4 * half + (j & 3);
+        if (r < c.nrows) {
+            if constexpr (UP) {
+                if (c.wlive[0])
+                    static_cast<__half*>(c.out)[(size_t)r * c.ldo + c.wrow[0] + n] =
+                        __float2half(out[0][j] / (1.0f + expf(-out[0][j])) * out[1][j]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (c.wlive[i]) static_cast<float*>(c.out)[(size_t)r * c.ldo + c.wrow[i] + n] = out[i][j];
+            }
+        }
+    }
+}
+
+// EXACT: the decode-sized form (at most 16 rows per expert), fp32 outputs of the down GEMM.
+template <bool UP, bool EXACT>
 __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     extern __shared__ uint4 gemm_smem[];
     char* smem = reinterpret_cast<char*>(gemm_smem);
+    const int lane = threadIdx.x & 63;
     const int nseg = a.E + a.n_shared;
-    // the shared experts' segments come last in the table and hold the fullest tiles: they go first
-    const int ntile = uniform(a.tile_start[nseg]);
+    // Which tile: the segments' first tiles, one per lane, all requested at once.  The shared experts'
+    // segments come last in the table and hold the fullest tiles: they go first.
+    constexpr int kSegRegs = (kMaxE + 16 + 1 + 63) / 64;
+    int4 seg[kSegRegs];
+#pragma unroll
+    for (int i = 0; i < kSegRegs; ++i)
+        if (64 * i <= nseg) seg[i] = a.segs[min(64 * i + lane, nseg)];
+    int ntile = 0;
+#pragma unroll
+    for (int i = 0; i < kSegRegs; ++i)
+        if ((nseg >> 6) == i) ntile = __builtin_amdgcn_readlane(seg[i].x, nseg & 63);
     if ((int)blockIdx.x >= ntile) return;
     const int b = ntile - 1 - (int)blockIdx.x;
-    int lo = 0, hi = nseg;                 // last seg with tile_start[seg] <= b
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (uniform(a.tile_start[mid]) <= b) lo = mid; else hi = mid;
-    }
-    const int seg = lo;
-    const bool is_shared = seg >= a.E;
-    int local = b - uniform(a.tile_start[seg]);
+    int sidx = 0, first = 0, e = 0, sbeg = 0, T = 0;       // last segment that starts at or before tile b
+#pragma unroll
+    for (int i = 0; i < kSegRegs; ++i)
+        if (64 * i < nseg) {
+            const unsigned long long m = __ballot(64 * i + lane < nseg && seg[i].x <= b);
+            if (m) {
+                const int l = 63 - __clzll((long long)m);
+                sidx = 64 * i + l;
+                first = __builtin_amdgcn_readlane(seg[i].x, l);
+                e = __builtin_amdgcn_readlane(seg[i].y, l);
+                sbeg = __builtin_amdgcn_readlane(seg[i].z, l);
+                T = __builtin_amdgcn_readlane(seg[i].w, l);
+            }
+        }
+    const bool is_shared = sidx >= a.E;
+    int local = b - first;
     const int nb = is_shared ? a.nb_s : a.nb_r, kp = UP ? 1 : (is_shared ? a.kp_s : a.kp_r);
     const int mb = local / (nb * kp);
     local -= mb * (nb * kp);
     const int part = local / nb, nblk = local - part * nb;
-    const int e = is_shared ? seg - a.E : uniform(a.order[a.E - 1 - seg]);
     const fate_qexpert* ex = (is_shared ? a.shared : a.experts) + e;
-    const int sbeg = is_shared ? 0 : uniform(a.offsets[e]);
-    const int T = is_shared ? a.N : uniform(a.offsets[e + 1]) - sbeg;
     const int row0 = mb * tile_rows(T);
     TileCtx c;
     c.ex = ex;
     c.nrows = min(tile_rows(T), T - row0);
     c.Nout = UP ? uniform(ex->I) : a.H;
     c.K = UP ? a.H : uniform(ex->I);
-    if (nblk * (UP ? kBNUp : kBNDown) >= c.Nout || c.nrows <= 0) return;
-    if ((UP ? ex->w1 : ex->w2) == nullptr) {
-        if (threadIdx.x == 0) atomicOr(a.status, 1);
-        return;
+    if (c.nrows <= 0 || (UP && nblk * kBNUp >= c.Nout)) return;
+    const int out_row0 = (is_shared ? e * a.N : sbeg) + row0;
+    c.ldo = is_shared ? a.ldo_s : a.ldo_r;
+    {
+        constexpr size_t osz = EXACT && !UP ? sizeof(float) : sizeof(__half);
+        c.out = static_cast<char*>(is_shared ? a.out_s : a.out_r) +
+                ((size_t)part * (is_shared ? a.part_s : a.part_r) + (size_t)out_row0 * c.ldo) * osz;
     }
     // width and group of THIS expert's copy: a layer may hold copies of several widths (the
     // popularity-aware hybrid of section 4.5 moves the least popular experts at 2 bits)
@@ -470,9 +736,22 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     c.group = uniform(ex->group);
     const int kt = bits == 4 ? 64 : (bits == 8 ? 32 : 128);
     const bool has_z = ex->z1 != nullptr;
-    if ((bits != 2 && bits != 4 && bits != 8) || c.group < kt || c.group % kt || c.group % 64 || c.K % c.group ||
-        (has_z && (bits == 8 || ex->z2 == nullptr || ex->z3 == nullptr))) {     // zero-points: 4- and 2-bit formats
-        if (threadIdx.x == 0) atomicOr(a.status, 4);
+    const bool absent = ex->w1 == nullptr || ex->w3 == nullptr || ex->w2 == nullptr;
+    const bool bad = (bits != 2 && bits != 4 && bits != 8) || c.group < kt || c.group % kt || c.group % 64 || a.H % c.group ||
+                     uniform(ex->I) % c.group || (has_z && (bits == 8 || ex->z2 == nullptr || ex->z3 == nullptr));   // zero-points: 4 and 2 bits
+    if (absent || bad) {
+        // nothing to multiply: the pairs of this expert contribute zeros
+        if (UP) {
+            if (threadIdx.x == 0) atomicOr(a.status, absent ? 1 : 4);
+        } else {
+            for (int i = threadIdx.x; i < c.nrows * (kBNDown / 4); i += 256) {
+                const int r = i / (kBNDown / 4), col = nblk * kBNDown + (i % (kBNDown / 4)) * 4;
+                if (col < a.H) {
+                    if (EXACT) reinterpret_cast<float4*>(static_cast<float*>(c.out) + (size_t)r * c.ldo + col)[0] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    else reinterpret_cast<uint2*>(static_cast<__half*>(c.out) + (size_t)r * c.ldo + col)[0] = make_uint2(0, 0);
+                }
+            }
+        }
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -482,7 +761,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         c.wlive[i] = wr < c.Nout;
         c.wrow[i] = c.wlive[i] ? wr : 0;
     }
-    // columns of this part: a whole number of 128-column pieces
+    // columns of this part: a whole number of 128-column pieces (none is possible: an expert smaller than I_max)
     const int pieces = c.K / kKQ;
     const int p0 = pieces * part / kp, p1 = pieces * (part + 1) / kp;
     c.col0 = p0 * kKQ;
@@ -495,69 +774,88 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         if (is_shared) c.A += (size_t)row0 * c.lda;
         else { c.rows = a.perm + sbeg + row0; c.div = a.k; }
     } else {
-        c.A += (size_t)((is_shared ? (seg - a.E) * a.N : sbeg) + row0) * c.lda;
+        c.A += (size_t)out_row0 * c.lda;
     }
-    const int out_row0 = (is_shared ? (seg - a.E) * a.N : sbeg) + row0;
-    c.ldo = is_shared ? a.ldo_s : a.ldo_r;
-    c.out = (is_shared ? a.out_s + part * a.part_s : a.out_r + part * a.part_r) + (size_t)out_row0 * c.ldo;
-    if (has_z && bits == 4) gemm_tile<4, true, UP>(c, smem);
-    else if (has_z) gemm_tile<2, true, UP>(c, smem);
-    else if (bits == 4) gemm_tile<4, false, UP>(c, smem);
-    else if (bits == 2) gemm_tile<2, false, UP>(c, smem);
-    else gemm_tile<8, false, UP>(c, smem);
+    if constexpr (EXACT) {
+        if (has_z && bits == 4) gemm_exact<4, true, UP>(c, smem);
+        else if (has_z) gemm_exact<2, true, UP>(c, smem);
+        else if (bits == 4) gemm_exact<4, false, UP>(c, smem);
+        else if (bits == 2) gemm_exact<2, false, UP>(c, smem);
+        else gemm_exact<8, false, UP>(c, smem);
+    } else {
+        if (has_z && bits == 4) gemm_tile<4, true, UP>(c, smem);
+        else if (has_z) gemm_tile<2, true, UP>(c, smem);
+        else if (bits == 4) gemm_tile<4, false, UP>(c, smem);
+        else if (bits == 2) gemm_tile<2, false, UP>(c, smem);
+        else gemm_tile<8, false, UP>(c, smem);
+    }
 }
 
 template <bool UP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void grouped_gemm_kernel(GemmArgs a) {
-    grouped_gemm_body<UP>(a);
+    grouped_gemm_body<UP, false>(a);
+}
+template <bool UP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void grouped_gemm_exact_kernel(GemmArgs a) {
+    grouped_gemm_body<UP, true>(a);
 }
 
 // y[t,:] = sum_j w[t,j] * Yp_r[inv_perm[t*k+j], :] + sum_s g_s(t) * Yp_s[s*N+t, :], each Yp the sum of its K parts
-__global__ __launch_bounds__(256) void combine_kernel(const __half* __restrict__ yp_r,
-                                                      const __half* __restrict__ yp_s,
+template <class T>
+__global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ yp_r, const T* __restrict__ yp_s,
                                                       const int32_t* __restrict__ inv_perm,
                                                       const float* __restrict__ topk_w,
-                                                      const float* __restrict__ sgate, int N, int H, int k,
-                                                      int n_shared, int kp_r, int kp_s, size_t part_r, size_t part_s, float* __restrict__ y32,
-                                                      uint16_t* __restrict__ y16) {
+                                                      const float* __restrict__ sgate, int H, int k, int n_shared, int N,
+                                                      int kp_r, int kp_s, size_t part_r, size_t part_s,
+                                                      float* __restrict__ y32, uint16_t* __restrict__ y16) {
+    constexpr int V = 16 / sizeof(T);                     // outputs per thread: one 16-byte load of every row
     const int t = blockIdx.x;
-    for (int c = threadIdx.x; c < (H >> 3); c += 256) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int j = 0; j < k + n_shared; ++j) {
-            float wgt;
-            const __half* src;
-            const int kp = j < k ? kp_r : kp_s;
-            const size_t stride = j < k ? part_r : part_s;
-            if (j < k) {
-                const int pos = inv_perm[t * k + j];
-                if (pos < 0) continue;
-                wgt = topk_w[t * k + j];
-                src = yp_r + (size_t)pos * H;
-            } else {
-                wgt = sgate ? sgate[t] : 1.0f;
-                src = yp_s + ((size_t)(j - k) * N + t) * H;
-            }
-            for (int p = 0; p < kp; ++p) {
-                const uint4 v = reinterpret_cast<const uint4*>(src + p * stride)[c];
+    const int c = blockIdx.y * 256 + threadIdx.x;
+    if (c * V >= H) return;
+    float acc[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) acc[i] = 0.f;
+    for (int j = 0; j < k + n_shared; ++j) {
+        float wgt;
+        const T* src;
+        const int kp = j < k ? kp_r : kp_s;
+        const size_t stride = j < k ? part_r : part_s;
+        if (j < k) {
+            const int pos = inv_perm[t * k + j];
+            if (pos < 0) continue;
+            wgt = topk_w[t * k + j];
+            src = yp_r + (size_t)pos * H;
+        } else {
+            wgt = sgate ? sgate[t] : 1.0f;
+            src = yp_s + ((size_t)(j - k) * N + t) * H;
+        }
+        for (int p = 0; p < kp; ++p) {
+            const uint4 v = reinterpret_cast<const uint4*>(src + p * stride)[c];
+            if constexpr (sizeof(T) == 2) {
                 const __half2* h = reinterpret_cast<const __half2*>(&v);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     acc[2 * i] = fmaf(wgt, __low2float(h[i]), acc[2 * i]);
                     acc[2 * i + 1] = fmaf(wgt, __high2float(h[i]), acc[2 * i + 1]);
                 }
+            } else {
+                acc[0] = fmaf(wgt, __uint_as_float(v.x), acc[0]);
+                acc[1] = fmaf(wgt, __uint_as_float(v.y), acc[1]);
+                acc[2] = fmaf(wgt, __uint_as_float(v.z), acc[2]);
+                acc[3] = fmaf(wgt, __uint_as_float(v.w), acc[3]);
             }
         }
-        if (y32) {
-            float4* o = reinterpret_cast<float4*>(y32 + (size_t)t * H + c * 8);
-            o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-            o[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-        } else {
-            uint32_t o[4];
+    }
+    if (y32) {
+        float4* o = reinterpret_cast<float4*>(y32 + (size_t)t * H + c * V);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                o[i] = f32_to_bf16_bits(acc[2 * i]) | (f32_to_bf16_bits(acc[2 * i + 1]) << 16);
-            reinterpret_cast<uint4*>(y16 + (size_t)t * H)[c] = make_uint4(o[0], o[1], o[2], o[3]);
-        }
+        for (int i = 0; i < V / 4; ++i) o[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+    } else {
+        uint2* o = reinterpret_cast<uint2*>(y16 + (size_t)t * H + c * V);
+#pragma unroll
+        for (int i = 0; i < V / 4; ++i)
+            o[i] = make_uint2(f32_to_bf16_bits(acc[4 * i]) | (f32_to_bf16_bits(acc[4 * i + 1]) << 16),
+                              f32_to_bf16_bits(acc[4 * i + 2]) | (f32_to_bf16_bits(acc[4 * i + 3]) << 16));
     }
 }
 
@@ -576,7 +874,7 @@ void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s) {
 }
 
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs da, const MfmaScratch& ms,
-                            void* y_out, int phase, const PartSel& sel) {
+                            void* y_out, int phase, const PartSel& sel, bool exact) {
     if (d.H % kKQ || d.I_max % kKQ || (d.n_shared && d.I_shared_max % kKQ))
         FATE_FAIL(FATE_ESHAPE, "the MFMA path needs H and I to be multiples of %d", kKQ);
     const int P = d.N * d.k;
@@ -596,6 +894,10 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<false>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_exact_kernel<true>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_exact_kernel<false>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         attr_done = true;
     }
     if (do_up) {
@@ -608,35 +910,44 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
     const long long mb_r = P / kBM + (d.E < P ? d.E : P), mb_s = (d.N + kBM - 1) / kBM;
     GemmArgs g{};
     g.experts = da.experts; g.shared = da.shared; g.E = d.E; g.n_shared = d.n_shared; g.N = d.N; g.k = d.k;
-    g.offsets = da.offsets; g.perm = da.perm; g.order = da.order;
+    g.perm = da.perm;
     g.status = da.status;
     g.H = d.H;
     if (do_up) {
-        g.A_r = ms.xh; g.lda_r = d.H; g.A_s = ms.xh; g.lda_s = d.H; g.tile_start = ms.tab_up;
+        g.A_r = ms.xh; g.lda_r = d.H; g.A_s = ms.xh; g.lda_s = d.H; g.segs = ms.tab_up;
         g.out_r = da.h_r; g.ldo_r = da.ldh_r; g.out_s = da.h_s; g.ldo_s = da.ldh_s;
         g.nb_r = nb_r_up; g.nb_s = nb_s_up;
         g.kp_r = g.kp_s = 1;
         const long long grid = mb_r * nb_r_up + d.n_shared * mb_s * nb_s_up;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
-        grouped_gemm_kernel<true><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
+        if (exact) grouped_gemm_exact_kernel<true><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<true><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
     }
     if (do_down) {
         g.A_r = da.h_r; g.lda_r = da.ldh_r; g.A_s = da.h_s; g.lda_s = da.ldh_s;
-        g.tile_start = ms.tab_down; g.nb_r = nb_down; g.nb_s = nb_down;
+        g.segs = ms.tab_down; g.nb_r = nb_down; g.nb_s = nb_down;
         g.out_r = ms.yp_r; g.ldo_r = d.H; g.out_s = ms.yp_s; g.ldo_s = d.H;
         g.kp_r = kp_r; g.kp_s = kp_s;
         g.part_r = (size_t)P * d.H; g.part_s = (size_t)d.n_shared * d.N * d.H;
         const long long grid = (mb_r * kp_r + d.n_shared * mb_s * kp_s) * nb_down;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
-        grouped_gemm_kernel<false><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
+        if (exact) grouped_gemm_exact_kernel<false><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<false><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
-        if (sel.last)
-            combine_kernel<<<d.N, 256, 0, st>>>(ms.yp_r, ms.yp_s, da.inv_perm, da.topk_w,
-                                            da.shared_gate ? ms.sgate : nullptr, d.N, d.H, d.k, d.n_shared, kp_r, kp_s,
-                                            g.part_r, g.part_s,
-                                            d.y_is_fp32 ? static_cast<float*>(y_out) : nullptr,
-                                            d.y_is_fp32 ? nullptr : static_cast<uint16_t*>(y_out));
+        if (sel.last) {
+            float* y32 = d.y_is_fp32 ? static_cast<float*>(y_out) : nullptr;
+            uint16_t* y16 = d.y_is_fp32 ? nullptr : static_cast<uint16_t*>(y_out);
+            const float* gate = da.shared_gate ? ms.sgate : nullptr;
+            if (exact)
+                combine_kernel<float><<<dim3(d.N, (d.H / 4 + 255) / 256), 256, 0, st>>>(
+                    static_cast<const float*>(ms.yp_r), static_cast<const float*>(ms.yp_s), da.inv_perm, da.topk_w, gate, d.H,
+                    d.k, d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
+            else
+                combine_kernel<__half><<<dim3(d.N, (d.H / 8 + 255) / 256), 256, 0, st>>>(
+                    static_cast<const __half*>(ms.yp_r), static_cast<const __half*>(ms.yp_s), da.inv_perm, da.topk_w, gate, d.H,
+                    d.k, d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
+        }
         FATE_HIP(hipGetLastError());
     }
     return FATE_OK;
