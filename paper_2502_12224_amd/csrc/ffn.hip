@@ -121,11 +121,15 @@ static fate_status ffn_q_phase(int phase, const PartSel& sel, void* stream, cons
             FATE_FAIL(FATE_EINVAL, "the decode kernels run the whole FFN only (no phases, no pieces)");
         if (decode_by_gemm(*d)) {
             fate_status s2 = check_decode_groups(*d);
-            return s2 != FATE_OK ? s2 : launch_ffn_mfma(st, *d, a, w.ms, y, 0, sel, true);
+            MfmaMode m;
+            m.exact = true;
+            return s2 != FATE_OK ? s2 : launch_ffn_mfma(st, *d, a, w.ms, y, sel, m);
         }
         return launch_ffn_decode(st, *d, a, y);
     }
-    return launch_ffn_mfma(st, *d, a, w.ms, y, phase, sel, false);
+    MfmaMode m;
+    m.phase = phase;
+    return launch_ffn_mfma(st, *d, a, w.ms, y, sel, m);
 }
 
 extern "C" fate_status fate_moe_ffn_q(void* stream, const fate_ffn_desc* d, const void* x_bf16,
@@ -233,6 +237,8 @@ static fate_status layer_decode_checked(void* stream, const fate_ffn_desc* d, co
     a.y_is_fp32 = d->y_is_fp32;
     a.status = status ? status : reinterpret_cast<int32_t*>(base + w.status);
     a.sync = reinterpret_cast<int32_t*>(base + w.sync);
+    a.scratch = base + w.part_r;
+    a.scratch_bytes = w.hq - w.part_r;
     return launch_layer_decode(static_cast<hipStream_t>(stream), *d, a);
 }
 

@@ -59,13 +59,40 @@ struct PartSel {
     unsigned long long mask[4];
     int first, last;
 };
-inline PartSel part_all() { return PartSel{{~0ull, ~0ull, ~0ull, ~0ull}, 1, 1}; }
+__host__ __device__ inline PartSel part_all() { return PartSel{{~0ull, ~0ull, ~0ull, ~0ull}, 1, 1}; }
 
 // parts of the reduction dimension of the down GEMM of routed / shared experts
 void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s);
-// exact: the decode-sized form of the GEMMs (at most 16 tokens).  phase: 0 = whole FFN, 1 = prep + up/gate GEMM only, 2 = down GEMM + combine only (timing aid)
-fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs a, const MfmaScratch& ms,
-                            void* y_out, int phase, const PartSel& sel, bool exact);
+// Routing of a decode layer inside its up GEMM's launch, from the logits (at most 64 pairs): every workgroup
+// selects for itself, the first one writes the outputs.
+struct LayerOut {
+    const float* z;                    // [gates][N][E] logits
+    int N, k, m, E, renorm;
+    int32_t* ids; float* w;
+    int32_t* pids; float* pw;          // pids NULL: no prediction
+    int32_t *counts, *offsets, *perm, *inv_perm, *order, *pop;
+    int32_t* calls;                    // counts the calls
+};
+
+// How launch_ffn_mfma runs: phase 0 = whole FFN, 1 = prep + up GEMM only, 2 = down GEMM + combine only (timing
+// aid); exact = the decode-sized form of the GEMMs (at most 16 tokens); layer = inside a decode layer (at most 8
+// tokens, exact): the logits, x and the shared gate are there, nothing else of the routing is, and entries of
+// another format than the descriptor's, or with zero-points, count as absent.
+struct MfmaMode {
+    int phase = 0;
+    bool exact = false;
+    const LayerOut* layer = nullptr;
+};
+fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs da, const MfmaScratch& ms,
+                            void* y_out, const PartSel& sel, const MfmaMode& mode);
+
+// Column blocks per segment of the two GEMMs' tile tables, K parts of the down GEMM included.
+struct TileBlocks {
+    int r_up, s_up, r_down, s_down;
+};
+TileBlocks mfma_tile_blocks(const fate_ffn_desc& d);
+constexpr int kTileRows = 128;      // most rows of a tile
+
 // The decode kernels' job done by the GEMM's decode-sized form (exact weights, fp32 per-pair outputs):
 // up to 16 tokens, sizes that are multiples of 128, and at least half a device of its 128-neuron
 // workgroups.  Below that the decode kernels' 32-neuron workgroups spread the weights further (two

@@ -33,6 +33,8 @@
 #include "qformat.h"
 #include "ffn_internal.h"
 #include "async_lds.h"
+#include "tile_table.h"
+#include "route_device.h"
 
 namespace fate {
 
@@ -40,11 +42,12 @@ typedef _Float16 f16x2v_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kBM = 128;            // most rows of a workgroup tile
+constexpr int kBM = kTileRows;      // most rows of a workgroup tile
 constexpr int kBNUp = 128;          // weight rows per workgroup tile of the up GEMM (of each matrix)
 constexpr int kBNDown = 256;        // weight rows per workgroup tile of the down GEMM
+constexpr int kCombineRows = 64;    // rows whose addresses and weights a combination block keeps in LDS
 constexpr int kKQ = 128;            // H and I must be multiples of this
-constexpr int kGemmLds = 80 * 1024; // two workgroups per compute unit
+constexpr int kGemmLds = 80 * 1024 - 128;   // two workgroups per compute unit
 constexpr int kGemmSlots = 2 * 256; // workgroups the device holds at once
 
 struct GemmArgs {
@@ -60,6 +63,8 @@ struct GemmArgs {
     int nb_r, nb_s;                    // column blocks per routed / shared segment
     int kp_r, kp_s;                    // parts of the reduction dimension (down GEMM), each with an output of its own
     size_t part_r, part_s;             // elements between those outputs
+    int bits_r, group_r, bits_s, group_s;              // decode layer: entries of another format, or with zero-points, count as absent
+    LayerOut lo;                       // decode layer only
     int32_t* status;
 };
 
@@ -76,8 +81,7 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
                                                            const uint16_t* __restrict__ shared_gate,
                                                            __half* __restrict__ xh, float* __restrict__ sgate,
                                                            int4* __restrict__ tab_up, int4* __restrict__ tab_down,
-                                                           int nb_r_up, int nb_s_up, int nb_r_down, int nb_s_down,
-                                                           PartSel sel) {
+                                                           TileBlocks nb, PartSel sel) {
     __shared__ float red[4];
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nvec = H >> 3;
@@ -115,39 +119,7 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
     }
     }
     if (t == 0 && wave == 0) {
-        // tile tables: exclusive prefix sums over the segments, 64 segments per step of one wave
-        const int nseg = E + n_shared;
-        int ru = 0, rd = 0;
-        for (int s0 = 0; s0 < nseg; s0 += 64) {
-            const int s = s0 + lane;
-            int cu = 0, cd = 0, e = 0, T = 0, row = 0;
-            if (s < nseg) {
-                // a piece holds the routed experts of its mask; the shared experts go with the first piece.
-                // The table is read from its end: shared experts, then experts by falling number of rows
-                e = s < E ? order[E - 1 - s] : s - E;
-                const bool mine = s < E ? ((sel.mask[e >> 6] >> (e & 63)) & 1ull) != 0 : sel.first != 0;
-                row = s < E ? offsets[e] : 0;
-                T = !mine ? 0 : (s < E ? offsets[e + 1] - row : N);
-                cu = ((T + kBM - 1) / kBM) * (s < E ? nb_r_up : nb_s_up);
-                cd = ((T + kBM - 1) / kBM) * (s < E ? nb_r_down : nb_s_down);
-            }
-            int iu = cu, id = cd;
-#pragma unroll
-            for (int sh = 1; sh < 64; sh <<= 1) {
-                const int pu = __shfl_up(iu, sh, 64), pd = __shfl_up(id, sh, 64);
-                if (lane >= sh) { iu += pu; id += pd; }
-            }
-            if (s < nseg) {
-                tab_up[s] = make_int4(ru + iu - cu, e, row, T);
-                tab_down[s] = make_int4(rd + id - cd, e, row, T);
-            }
-            ru += __shfl(iu, 63, 64);
-            rd += __shfl(id, 63, 64);
-        }
-        if (lane == 0) {
-            tab_up[nseg] = make_int4(ru, 0, 0, 0);
-            tab_down[nseg] = make_int4(rd, 0, 0, 0);
-        }
+        wave_tile_tables(offsets, order, E, n_shared, N, nb, sel, tab_up, tab_down);
     }
 }
 
@@ -200,6 +172,7 @@ struct TileCtx {
     int Nout, K, col0, ncol;           // weight rows of the matrix, its columns, this part's columns
     int group;
     void* out; int ldo;                // output row 0 of the tile
+    const int32_t* orows;              // decode-sized form: output row of tile row r, or NULL: r itself
 };
 
 template <int BITS>
@@ -438,16 +411,25 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
 // 13 tokens of the Qwen shape: up 45.3 -> 27.8 us (106 MB of codes and scales: 3.8 TB/s), down 45.7 -> 15.9 us
 // against the dequant-GEMV kernels, whose loads sit under branches.
 // D = activations x codes: lane n holds weight row n, rows 4*half + 0..3 and 8 + 4*half + 0..3.
-template <int BITS>
+// R: rows of the tile (8 or 16).  KW: waves over which the reduction dimension is split (up projection of a
+// decode layer: tiles of 64 neurons instead of 128; a wave issues an instruction every 5 to 6 cycles and no
+// more, so two waves per SIMD get through the widening twice as fast as one.  One token of the Mixtral shape:
+// 34 -> 26 us; four ranges gain nothing more).  A stage's scales are one load of 256 bytes per wave: for int4 both
+// blocks' scales of both 64-column halves (groups of 64, or a multiple of 128), with zero-points a second one
+// like it; for the other widths, whose stages lie inside a group, scales in the first half and zero-points in the other.
+template <int BITS, bool ZP, int R, int KW>
 struct ExactFmt {
     static constexpr int KT = QFmt<BITS>::KT;
     static constexpr int BK = BITS == 8 ? 64 : 128;       // columns per stage
     static constexpr int TPS = BK / KT;
-    static constexpr int HS = BITS == 4 ? 2 : 1;          // scales per row and stage (groups of 64: two for int4)
+    static constexpr int HS = BITS == 4 ? 2 : 1;          // scales per row and stage
+    static constexpr int SL = BITS == 4 && ZP ? 2 : 1;    // loads of scales and zero-points
     static constexpr int XROW = BK * 2;
-    static constexpr int xbytes = 16 * XROW;
-    static constexpr int stage = xbytes + 4 * 2 * TPS * 1024 + 4 * HS * 256;
-    static constexpr int depth = kGemmLds / stage < 4 ? kGemmLds / stage : 4;
+    static constexpr int xwave = R * XROW;                // of the waves that share a range of columns
+    static constexpr int xbytes = KW * xwave;
+    static constexpr int sc0 = xbytes + 4 * 2 * TPS * 1024;
+    static constexpr int stage = sc0 + 4 * SL * 256;
+    static constexpr int depth = kGemmLds / stage < 8 ? kGemmLds / stage : 8;
 };
 
 // codes of columns 2p, 2p + 1 of matrix-core step d as exact fp16 integers (int4: u - 8, int8: u - 128, int2: 2u - 3)
@@ -476,79 +458,87 @@ __device__ __forceinline__ uint32_t code_pair(const uint4 (&raw)[TPS], int d, in
 template <int BITS> struct ZpExact { static constexpr float inv_a = 1.0f, c_over_a = 8.0f; };
 template <> struct ZpExact<2> { static constexpr float inv_a = 0.5f, c_over_a = 1.5f; };
 
-template <int BITS, bool ZP, bool UP>
+template <int BITS, bool ZP, bool UP, int R, int KW>
 __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
-    typedef ExactFmt<BITS> F;
-    constexpr int KT = F::KT, BK = F::BK, TPS = F::TPS, HS = F::HS, XROW = F::XROW;
+    typedef ExactFmt<BITS, ZP, R, KW> F;
+    constexpr int KT = F::KT, BK = F::BK, TPS = F::TPS, HS = F::HS, SL = F::SL, XROW = F::XROW, RJ = R / 2;
     constexpr int SPT = KT / 16, KS = TPS * SPT, KH = KS / HS;
-    constexpr int NX = F::xbytes / 4096 > 0 ? F::xbytes / 4096 : 1;        // (2 KiB of activations: two waves load them)
     constexpr int S = F::depth, SB = F::stage;
-    constexpr int LPS = NX + 2 * TPS + HS;
+    constexpr int NX = (F::xwave / 1024 + 4 / KW - 1) / (4 / KW);          // activation loads per wave and stage
+    constexpr int LPS = NX + 2 * TPS + SL;
     static_assert(S >= 2, "at least one stage ahead");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5;
-    const int nstage = c.ncol / BK, tiles_k = c.K / KT;
+    const int kw = wave & (KW - 1);                       // this wave's range of columns
+    const int ncol = c.ncol / KW, col0 = c.col0 + kw * ncol;
+    const int nstage = ncol / BK, tiles_k = c.K / KT;
     const uint32_t lds0 = lds_offset(smem);
     constexpr int LPR = XROW / 16, RPL = 64 / LPR;        // lanes per row, rows per load
-    constexpr int XL = F::xbytes / 1024;                  // activation loads of a stage (4 or 2): one per wave, twice the same for int8
-    const int xl = wave % XL;
-    uint32_t xoff;
-    {
-        const int r = xl * RPL + lane / LPR, q = lane % LPR;
+    constexpr int XL = F::xwave / 1024;                   // activation loads of a range; waves beyond them repeat one
+    uint32_t xoff[NX];
+    auto xpiece = [&](int i) { return (i * (4 / KW) + wave / KW) % XL; };
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int r = xpiece(i) * RPL + lane / LPR, q = lane % LPR;
         const int rr = r < c.nrows ? r : 0;
         const int ar = c.rows ? c.rows[rr] / c.div : rr;
-        xoff = ((uint32_t)ar * (uint32_t)c.lda + (uint32_t)c.col0) * 2u + (uint32_t)((q ^ (r & 7)) * 16);
+        xoff[i] = ((uint32_t)ar * (uint32_t)c.lda + (uint32_t)col0) * 2u + (uint32_t)((q ^ (r & 7)) * 16);
     }
     const char* wbase[2];
-    const char* sbase;
+    const char *sbase, *zbase;                            // this lane's scale / zero-point address (int4 with zero-points: zbase)
     {
         const void* wp[2] = {UP ? c.ex->w1 : c.ex->w2, UP ? c.ex->w3 : c.ex->w2};
         const void* sp[2] = {UP ? c.ex->s1 : c.ex->s2, UP ? c.ex->s3 : c.ex->s2};
         const void* zp[2] = {UP ? c.ex->z1 : c.ex->z2, UP ? c.ex->z3 : c.ex->z2};
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            wbase[i] = static_cast<const char*>(uniform(wp[i])) + ((size_t)(c.wrow[i] >> 5) * tiles_k + c.col0 / KT) * 1024;
+            wbase[i] = static_cast<const char*>(uniform(wp[i])) + ((size_t)(c.wrow[i] >> 5) * tiles_k + col0 / KT) * 1024;
         const int b = (lane >> 4) & 1;
-        const void* p0 = ZP && half ? zp[0] : sp[0];
-        const void* p1 = ZP && half ? zp[1] : sp[1];
-        sbase = static_cast<const char*>(b ? p1 : p0) + (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
-                (size_t)(c.col0 / c.group) * c.Nout * 2;
+        const size_t off = (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
+                           (size_t)((col0 + (BITS == 4 ? 64 * half : 0)) / c.group) * c.Nout * 2;
+        const bool zs = ZP && BITS != 4 && half;
+        sbase = static_cast<const char*>(b ? (zs ? zp[1] : sp[1]) : (zs ? zp[0] : sp[0])) + off;
+        zbase = ZP && BITS == 4 ? static_cast<const char*>(b ? zp[1] : zp[0]) + off : nullptr;
     }
     const uint32_t lane16 = lane * 16;
-    int gcol = c.col0 % c.group;                          // of the next piece of scales to be requested
+    int gcol = col0 % c.group;                          // of the next stage to be requested
     auto issue_one = [&](int st, int slot, int l) {
         const uint32_t base = lds0 + slot * SB;
         if (l < NX) {
-            lds_load16(base + xl * 1024, reinterpret_cast<const char*>(c.A) + (size_t)st * XROW, xoff);
+            lds_load16(base + kw * F::xwave + xpiece(l) * 1024, reinterpret_cast<const char*>(c.A) + (size_t)st * XROW, xoff[l]);
         } else if (l < NX + 2 * TPS) {
             const int i = (l - NX) / TPS, tl = (l - NX) % TPS;
             lds_load16(base + F::xbytes + (wave * 2 * TPS + i * TPS + tl) * 1024, wbase[i] + (size_t)(st * TPS + tl) * 1024, lane16);
+        } else if (l == NX + 2 * TPS) {
+            lds_load4(base + F::sc0 + wave * SL * 256, sbase);
         } else {
-            lds_load4(base + F::xbytes + 4 * 2 * TPS * 1024 + (wave * HS + (l - NX - 2 * TPS)) * 256, sbase);
-            gcol += BK / HS;
-            if (gcol >= c.group) {
-                gcol -= c.group;
-                sbase += (size_t)c.Nout * 2;
-            }
+            lds_load4(base + F::sc0 + (wave * SL + 1) * 256, zbase);
+        }
+        if (l == LPS - 1) {                               // on to the next stage's groups (two of them for int4 groups of 64)
+            gcol += BK;
+            const size_t adv = gcol >= c.group ? (size_t)(BITS == 4 && c.group == 64 ? 2 : 1) * c.Nout * 2 : 0;
+            if (gcol >= c.group) gcol = 0;
+            sbase += adv;
+            if (ZP && BITS == 4) zbase += adv;
         }
     };
     f32x16_t acc[2], sum;
     // The up projection adds its groups up in quarters, as the one-call decode layer does (a wave per
     // quarter there): h is rounded to fp16 and must not depend on which of the two computed it.
-    float out[2][8], tot[2][8];
+    float out[2][RJ], tot[2][RJ];
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[0][j] = acc[1][j] = sum[j] = 0.f;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) out[i][j] = tot[i][j] = 0.f;
+        for (int j = 0; j < RJ; ++j) out[i][j] = tot[i][j] = 0.f;
     const int ngroups = c.K / c.group;
     int gidx = 0, quarter = ngroups / 4;                  // groups done, end of the current quarter
     auto close_quarter = [&]() {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < RJ; ++j) {
                 tot[i][j] += out[i][j];
                 out[i][j] = 0.f;
             }
@@ -557,10 +547,10 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
 #pragma unroll
     for (int d = 0; d < KS; ++d) {
         const int piece = ((d / SPT) * KT + half * (KT / 2)) / 8 + d % SPT;
-        aoff[d] = (n & 15) * XROW + (piece ^ (n & 7)) * 16;
+        aoff[d] = kw * F::xwave + (n & (R - 1)) * XROW + (piece ^ (n & 7)) * 16;
     }
     const f16x8_t ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
-    int gleft = c.group - c.col0 % c.group;               // columns left of the group being summed
+    int gleft = c.group - col0 % c.group;               // columns left of the group being summed
     int slot = 0, slot_in = S - 1;
     auto next = [](int i) { return i + 1 == S ? 0 : i + 1; };
 #pragma unroll
@@ -575,7 +565,7 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
         lds_only_barrier();                               // stage st is in LDS, everyone is done with stage st - 1
         const char* base = smem + slot * SB;
         const char* wl = base + F::xbytes + wave * (2 * TPS * 1024) + lane16;
-        const char* sl = base + F::xbytes + 4 * 2 * TPS * 1024 + wave * (HS * 256) + n * 2;
+        const char* sl = base + F::sc0 + wave * SL * 256 + n * 2;
         uint4 raw[2][TPS];
         _Float16 sv[HS][2], zv[HS][2];
         f16x8_t av[2];
@@ -587,8 +577,8 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
             for (int tl = 0; tl < TPS; ++tl) raw[i][tl] = *reinterpret_cast<const uint4*>(wl + (i * TPS + tl) * 1024);
 #pragma unroll
             for (int h = 0; h < HS; ++h) {
-                sv[h][i] = *reinterpret_cast<const _Float16*>(sl + h * 256 + i * 64);
-                zv[h][i] = ZP ? *reinterpret_cast<const _Float16*>(sl + h * 256 + 128 + i * 64) : (_Float16)0.f;
+                sv[h][i] = *reinterpret_cast<const _Float16*>(sl + (h * 2 + i) * 64);
+                zv[h][i] = ZP ? *reinterpret_cast<const _Float16*>(sl + (BITS == 4 ? 256 + (h * 2 + i) * 64 : 128 + i * 64)) : (_Float16)0.f;
             }
         }
         av[0] = *reinterpret_cast<const f16x8_t*>(base + aoff[0]);
@@ -624,7 +614,7 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
                         const float s = (float)sv[h][i];
                         const float dz = ZP ? (ZpExact<BITS>::c_over_a - (float)zv[h][i]) : 0.f;
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) {
+                        for (int j = 0; j < RJ; ++j) {
                             const float v = ZP ? fmaf(ZpExact<BITS>::inv_a, acc[i][j], dz * sum[j]) : acc[i][j];
                             out[i][j] = fmaf(s, v, out[i][j]);
                         }
@@ -633,7 +623,7 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
                     }
 #pragma unroll
                     for (int j = 0; j < 16; ++j) sum[j] = 0.f;
-                    if constexpr (UP) {
+                    if constexpr (UP && KW == 1) {
                         if (++gidx >= quarter) {
                             close_quarter();
                             // the next quarter that holds a group ends at ngroups * q / 4
@@ -652,65 +642,172 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
     int st = 0;
     for (; st + S - 1 < nstage; ++st) step(st, std::true_type{});
     for (; st < nstage; ++st) step(st, std::false_type{});
-    if constexpr (UP) {
+    if constexpr (UP && KW == 1) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) out[i][j] = tot[i][j];
+            for (int j = 0; j < RJ; ++j) out[i][j] = tot[i][j];
+    }
+    if constexpr (KW > 1) {
+        // the ranges' sums meet in LDS: the first range's wave of every block adds the others in order
+        static_assert(UP, "the split of the reduction dimension belongs to the up projection");
+        float* red = reinterpret_cast<float*>(smem);      // [range - 1][block of the tile][matrix][row][32]
+        lds_only_barrier();                               // the rings are done with
+        const int blk = wave / KW;
+        auto at = [&](int range, int i, int j) {
+            return red + (((range * (4 / KW) + blk) * 2 + i) * RJ * 2 + (j >> 2) * 8 + 4 * half + (j & 3)) * 32 + n;
+        };
+        if (kw > 0) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < RJ; ++j) *at(kw - 1, i, j) = out[i][j];
+        }
+        lds_only_barrier();
+        if (kw > 0) return;
+#pragma unroll
+        for (int q = 0; q < KW - 1; ++q)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < RJ; ++j) out[i][j] += *at(q, i, j);
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < RJ; ++j) {
         const int r = 8 * (j >> 2) + 4 * half + (j & 3);
         if (r < c.nrows) {
+            const int ro = c.orows ? c.orows[r] : r;
             if constexpr (UP) {
                 if (c.wlive[0])
-                    static_cast<__half*>(c.out)[(size_t)r * c.ldo + c.wrow[0] + n] =
+                    static_cast<__half*>(c.out)[(size_t)ro * c.ldo + c.wrow[0] + n] =
                         __float2half(out[0][j] / (1.0f + expf(-out[0][j])) * out[1][j]);
             } else {
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    if (c.wlive[i]) static_cast<float*>(c.out)[(size_t)r * c.ldo + c.wrow[i] + n] = out[i][j];
+                    if (c.wlive[i]) static_cast<float*>(c.out)[(size_t)ro * c.ldo + c.wrow[i] + n] = out[i][j];
             }
         }
     }
 }
 
-// EXACT: the decode-sized form (at most 16 rows per expert), fp32 outputs of the down GEMM.
-template <bool UP, bool EXACT>
+// The routing outputs of a decode layer, by one workgroup beside the layer's up GEMM: selection, prediction,
+// permutation and popularity (at most 64 pairs).
+__device__ __forceinline__ void layer_outputs(const LayerOut& o, char* smem) {
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), P = o.N * o.k;
+    float* z = reinterpret_cast<float*>(smem);            // [gates][N][E]
+    int32_t* ids = reinterpret_cast<int32_t*>(z + 2 * o.N * o.E);
+    int32_t* pop = ids + 64;
+    const int njobs = (o.pids ? 2 : 1) * o.N;
+    for (int i = tid; i < njobs * o.E; i += 256) z[i] = o.z[i];
+    for (int i = tid; i < o.E; i += 256) pop[i] = 0;
+    __syncthreads();
+    for (int j = wave; j < njobs; j += 4) {
+        const int t = j < o.N ? j : j - o.N;
+        if (j < o.N) wave_softmax_topm(z + (size_t)j * o.E, o.E, o.k, o.renorm, ids + t * o.k, o.w + (size_t)t * o.k, nullptr, nullptr);
+        else wave_softmax_topm(z + (size_t)j * o.E, o.E, o.m, 0, o.pids + (size_t)t * o.m, o.pw + (size_t)t * o.m, nullptr, pop);
+    }
+    __syncthreads();
+    if (tid < P) o.ids[tid] = ids[tid];
+    if (o.pids)
+        for (int i = tid; i < o.E; i += 256) o.pop[i] = pop[i];
+    if (wave == 0) wave_permute_small(ids, P, o.E, o.counts, o.offsets, o.perm, o.inv_perm, o.order);
+    if (tid == 0) *o.calls += 1;
+}
+
+// MODE 0: prefill.  MODE 1: decode-sized (at most 16 rows per expert), fp32 outputs of the down GEMM.
+// MODE 2: the same inside a decode layer (at most 8 tokens, 64 pairs): no tile table; a workgroup finds its
+// expert and rows by itself, the up GEMM's from the logits and the down GEMM's from the selection; rows of h
+// and of the outputs are pairs.  The up GEMM's first workgroup writes the layer's routing outputs.
+template <bool UP, int MODE, int KW>
 __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     extern __shared__ uint4 gemm_smem[];
     char* smem = reinterpret_cast<char*>(gemm_smem);
+    __shared__ int32_t rowlist[MODE == 2 ? 8 : 1];
+    constexpr bool EXACT = MODE != 0;
     const int lane = threadIdx.x & 63;
-    const int nseg = a.E + a.n_shared;
-    // Which tile: the segments' first tiles, one per lane, all requested at once.  The shared experts'
-    // segments come last in the table and hold the fullest tiles: they go first.
-    constexpr int kSegRegs = (kMaxE + 16 + 1 + 63) / 64;
-    int4 seg[kSegRegs];
-#pragma unroll
-    for (int i = 0; i < kSegRegs; ++i)
-        if (64 * i <= nseg) seg[i] = a.segs[min(64 * i + lane, nseg)];
-    int ntile = 0;
-#pragma unroll
-    for (int i = 0; i < kSegRegs; ++i)
-        if ((nseg >> 6) == i) ntile = __builtin_amdgcn_readlane(seg[i].x, nseg & 63);
-    if ((int)blockIdx.x >= ntile) return;
-    const int b = ntile - 1 - (int)blockIdx.x;
-    int sidx = 0, first = 0, e = 0, sbeg = 0, T = 0;       // last segment that starts at or before tile b
-#pragma unroll
-    for (int i = 0; i < kSegRegs; ++i)
-        if (64 * i < nseg) {
-            const unsigned long long m = __ballot(64 * i + lane < nseg && seg[i].x <= b);
-            if (m) {
-                const int l = 63 - __clzll((long long)m);
-                sidx = 64 * i + l;
-                first = __builtin_amdgcn_readlane(seg[i].x, l);
-                e = __builtin_amdgcn_readlane(seg[i].y, l);
-                sbeg = __builtin_amdgcn_readlane(seg[i].z, l);
-                T = __builtin_amdgcn_readlane(seg[i].w, l);
-            }
+    bool is_shared;
+    int local, e = 0, sbeg = 0, T = 0;
+    if constexpr (MODE == 2) {
+        int b = (int)blockIdx.x;
+        if (UP && b-- == 0) {
+            layer_outputs(a.lo, smem);
+            return;
         }
-    const bool is_shared = sidx >= a.E;
-    int local = b - first;
+        const int kr = a.nb_r * (UP ? 1 : a.kp_r), ks = a.nb_s * (UP ? 1 : a.kp_s);
+        is_shared = b < a.n_shared * ks;
+        if (is_shared) {
+            e = b / ks;
+            local = b - e * ks;
+            T = a.N;
+        } else {
+            b -= a.n_shared * ks;
+            const int slot = b / kr;
+            local = b - slot * kr;
+            // slot s is the s-th pair, in pair order, whose expert no earlier pair has
+            const int P = a.N * a.k;
+            int key;
+            if constexpr (UP) {
+                float* z = reinterpret_cast<float*>(smem);
+                int32_t* ids = reinterpret_cast<int32_t*>(z + a.N * a.E);
+                for (int i = threadIdx.x; i < a.N * a.E; i += 256) z[i] = a.lo.z[i];
+                __syncthreads();
+                for (int t = threadIdx.x >> 6; t < a.N; t += 4) wave_topk_ids(z + t * a.E, a.E, a.k, ids + t * a.k);
+                __syncthreads();
+                key = lane < P ? ids[lane] : -1;
+            } else {
+                key = lane < P ? a.lo.ids[lane] : -1;
+            }
+            unsigned long long same = __ballot(key >= 0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {                 // E <= 256
+                const unsigned long long m = __ballot((key >> i) & 1);
+                same &= (key >> i) & 1 ? m : ~m;
+            }
+            const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+            const bool lead = key >= 0 && (same & lt) == 0;
+            const unsigned long long leads = __ballot(lead);
+            const unsigned long long mine = __ballot(lead && __popcll(leads & lt) == slot);
+            if (mine == 0) return;                        // fewer activated experts than slots
+            const int l = __ffsll((long long)mine) - 1;
+            e = __builtin_amdgcn_readlane(key, l);
+            const unsigned long long rows = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(same >> 32), l) << 32) |
+                                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)same, l);
+            T = __popcll(rows);
+            if (threadIdx.x < 64 && ((rows >> lane) & 1)) rowlist[__popcll(rows & lt)] = lane;
+            __syncthreads();                              // (and the selection's LDS is free for the ring)
+        }
+    } else {
+        const int nseg = a.E + a.n_shared;
+        // Which tile: the segments' first tiles, one per lane, all requested at once.  The shared experts'
+        // segments come last in the table and hold the fullest tiles: they go first.
+        constexpr int kSegRegs = (kMaxE + 16 + 1 + 63) / 64;
+        int4 seg[kSegRegs];
+#pragma unroll
+        for (int i = 0; i < kSegRegs; ++i)
+            if (64 * i <= nseg) seg[i] = a.segs[min(64 * i + lane, nseg)];
+        int ntile = 0;
+#pragma unroll
+        for (int i = 0; i < kSegRegs; ++i)
+            if ((nseg >> 6) == i) ntile = __builtin_amdgcn_readlane(seg[i].x, nseg & 63);
+        if ((int)blockIdx.x >= ntile) return;
+        const int b = ntile - 1 - (int)blockIdx.x;
+        int sidx = 0, first = 0;                           // last segment that starts at or before tile b
+#pragma unroll
+        for (int i = 0; i < kSegRegs; ++i)
+            if (64 * i < nseg) {
+                const unsigned long long m = __ballot(64 * i + lane < nseg && seg[i].x <= b);
+                if (m) {
+                    const int l = 63 - __clzll((long long)m);
+                    sidx = 64 * i + l;
+                    first = __builtin_amdgcn_readlane(seg[i].x, l);
+                    e = __builtin_amdgcn_readlane(seg[i].y, l);
+                    sbeg = __builtin_amdgcn_readlane(seg[i].z, l);
+                    T = __builtin_amdgcn_readlane(seg[i].w, l);
+                }
+            }
+        is_shared = sidx >= a.E;
+        local = b - first;
+    }
     const int nb = is_shared ? a.nb_s : a.nb_r, kp = UP ? 1 : (is_shared ? a.kp_s : a.kp_r);
     const int mb = local / (nb * kp);
     local -= mb * (nb * kp);
@@ -720,10 +817,11 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     TileCtx c;
     c.ex = ex;
     c.nrows = min(tile_rows(T), T - row0);
+    constexpr int kBN = UP ? kBNUp / KW : kBNDown;
     c.Nout = UP ? uniform(ex->I) : a.H;
     c.K = UP ? a.H : uniform(ex->I);
-    if (c.nrows <= 0 || (UP && nblk * kBNUp >= c.Nout)) return;
-    const int out_row0 = (is_shared ? e * a.N : sbeg) + row0;
+    if (c.nrows <= 0) return;
+    const int out_row0 = (is_shared ? e * a.N : sbeg) + row0;      // (MODE 2, routed: 0, rows are pairs)
     c.ldo = is_shared ? a.ldo_s : a.ldo_r;
     {
         constexpr size_t osz = EXACT && !UP ? sizeof(float) : sizeof(__half);
@@ -736,8 +834,10 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     c.group = uniform(ex->group);
     const int kt = bits == 4 ? 64 : (bits == 8 ? 32 : 128);
     const bool has_z = ex->z1 != nullptr;
-    const bool absent = ex->w1 == nullptr || ex->w3 == nullptr || ex->w2 == nullptr;
-    const bool bad = (bits != 2 && bits != 4 && bits != 8) || c.group < kt || c.group % kt || c.group % 64 || a.H % c.group ||
+    const bool absent = ex->w1 == nullptr || ex->w3 == nullptr || ex->w2 == nullptr ||
+                        (MODE == 2 && (has_z || bits != (is_shared ? a.bits_s : a.bits_r) ||
+                                               c.group != (is_shared ? a.group_s : a.group_r)));
+    const bool bad = (bits != 2 && bits != 4 && bits != 8) || c.group < kt || c.group % kt || c.group % 64 || (EXACT && c.group != 64 && c.group % 128) || a.H % c.group ||
                      uniform(ex->I) % c.group || (has_z && (bits == 8 || ex->z2 == nullptr || ex->z3 == nullptr));   // zero-points: 4 and 2 bits
     if (absent || bad) {
         // nothing to multiply: the pairs of this expert contribute zeros
@@ -745,7 +845,9 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
             if (threadIdx.x == 0) atomicOr(a.status, absent ? 1 : 4);
         } else {
             for (int i = threadIdx.x; i < c.nrows * (kBNDown / 4); i += 256) {
-                const int r = i / (kBNDown / 4), col = nblk * kBNDown + (i % (kBNDown / 4)) * 4;
+                int r = i / (kBNDown / 4);
+                const int col = nblk * kBNDown + (i % (kBNDown / 4)) * 4;
+                if (MODE == 2 && !is_shared) r = rowlist[r];
                 if (col < a.H) {
                     if (EXACT) reinterpret_cast<float4*>(static_cast<float*>(c.out) + (size_t)r * c.ldo + col)[0] = make_float4(0.f, 0.f, 0.f, 0.f);
                     else reinterpret_cast<uint2*>(static_cast<__half*>(c.out) + (size_t)r * c.ldo + col)[0] = make_uint2(0, 0);
@@ -754,10 +856,11 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         }
         return;
     }
+    if (UP && nblk * kBN >= c.Nout) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int wr = UP ? nblk * kBNUp + wave * 32 : nblk * kBNDown + wave * 64 + i * 32;
+        const int wr = UP ? nblk * kBN + wave / KW * 32 : nblk * kBNDown + wave * 64 + i * 32;
         c.wlive[i] = wr < c.Nout;
         c.wrow[i] = c.wlive[i] ? wr : 0;
     }
@@ -768,20 +871,26 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     c.ncol = (p1 - p0) * kKQ;
     c.lda = is_shared ? a.lda_s : a.lda_r;
     c.A = is_shared ? a.A_s : a.A_r;
-    c.rows = nullptr;
+    c.rows = c.orows = nullptr;
     c.div = 1;
-    if (UP) {
+    if (MODE == 2 && !is_shared) {
+        c.rows = c.orows = rowlist;
+        if (UP) c.div = a.k;
+    } else if (UP) {
         if (is_shared) c.A += (size_t)row0 * c.lda;
         else { c.rows = a.perm + sbeg + row0; c.div = a.k; }
     } else {
         c.A += (size_t)out_row0 * c.lda;
     }
-    if constexpr (EXACT) {
-        if (has_z && bits == 4) gemm_exact<4, true, UP>(c, smem);
-        else if (has_z) gemm_exact<2, true, UP>(c, smem);
-        else if (bits == 4) gemm_exact<4, false, UP>(c, smem);
-        else if (bits == 2) gemm_exact<2, false, UP>(c, smem);
-        else gemm_exact<8, false, UP>(c, smem);
+    if constexpr (MODE == 2) {
+        if (bits == 4) gemm_exact<4, false, UP, 8, KW>(c, smem);
+        else gemm_exact<8, false, UP, 8, KW>(c, smem);
+    } else if constexpr (MODE == 1) {
+        if (has_z && bits == 4) gemm_exact<4, true, UP, 16, 1>(c, smem);
+        else if (has_z) gemm_exact<2, true, UP, 16, 1>(c, smem);
+        else if (bits == 4) gemm_exact<4, false, UP, 16, 1>(c, smem);
+        else if (bits == 2) gemm_exact<2, false, UP, 16, 1>(c, smem);
+        else gemm_exact<8, false, UP, 16, 1>(c, smem);
     } else {
         if (has_z && bits == 4) gemm_tile<4, true, UP>(c, smem);
         else if (has_z) gemm_tile<2, true, UP>(c, smem);
@@ -791,61 +900,76 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     }
 }
 
-template <bool UP>
+template <bool UP, int MODE, int KW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void grouped_gemm_kernel(GemmArgs a) {
-    grouped_gemm_body<UP, false>(a);
-}
-template <bool UP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void grouped_gemm_exact_kernel(GemmArgs a) {
-    grouped_gemm_body<UP, true>(a);
+    grouped_gemm_body<UP, MODE, KW>(a);
 }
 
-// y[t,:] = sum_j w[t,j] * Yp_r[inv_perm[t*k+j], :] + sum_s g_s(t) * Yp_s[s*N+t, :], each Yp the sum of its K parts
+// y[t,:] = sum_j w[t,j] * Yp_r[pos(t,j), :] + sum_s g_s(t) * Yp_s[s*N+t, :], each Yp the sum of its K parts;
+// pos = inv_perm, or the pair itself when that is NULL.  A block of 64 to 256 threads per token and slice of
+// H: with few tokens the rows' latency is all there is, so a thread asks for eight rows at once.
 template <class T>
-__global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ yp_r, const T* __restrict__ yp_s,
-                                                      const int32_t* __restrict__ inv_perm,
-                                                      const float* __restrict__ topk_w,
-                                                      const float* __restrict__ sgate, int H, int k, int n_shared, int N,
-                                                      int kp_r, int kp_s, size_t part_r, size_t part_s,
-                                                      float* __restrict__ y32, uint16_t* __restrict__ y16) {
+__global__ void combine_kernel(const T* __restrict__ yp_r, const T* __restrict__ yp_s, const int32_t* __restrict__ inv_perm,
+                               const float* __restrict__ topk_w, const float* __restrict__ sgate, int H, int k, int n_shared,
+                               int N, int kp_r, int kp_s, size_t part_r, size_t part_s, float* __restrict__ y32,
+                               uint16_t* __restrict__ y16) {
     constexpr int V = 16 / sizeof(T);                     // outputs per thread: one 16-byte load of every row
+    __shared__ const T* src[kCombineRows];
+    __shared__ float wgt[kCombineRows];
     const int t = blockIdx.x;
-    const int c = blockIdx.y * 256 + threadIdx.x;
-    if (c * V >= H) return;
+    const int c = blockIdx.y * blockDim.x + threadIdx.x;
+    const int nr = k * kp_r, nrows = nr + n_shared * kp_s;
     float acc[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) acc[i] = 0.f;
-    for (int j = 0; j < k + n_shared; ++j) {
-        float wgt;
-        const T* src;
-        const int kp = j < k ? kp_r : kp_s;
-        const size_t stride = j < k ? part_r : part_s;
-        if (j < k) {
-            const int pos = inv_perm[t * k + j];
-            if (pos < 0) continue;
-            wgt = topk_w[t * k + j];
-            src = yp_r + (size_t)pos * H;
-        } else {
-            wgt = sgate ? sgate[t] : 1.0f;
-            src = yp_s + ((size_t)(j - k) * N + t) * H;
-        }
-        for (int p = 0; p < kp; ++p) {
-            const uint4 v = reinterpret_cast<const uint4*>(src + p * stride)[c];
-            if constexpr (sizeof(T) == 2) {
-                const __half2* h = reinterpret_cast<const __half2*>(&v);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[2 * i] = fmaf(wgt, __low2float(h[i]), acc[2 * i]);
-                    acc[2 * i + 1] = fmaf(wgt, __high2float(h[i]), acc[2 * i + 1]);
-                }
+    for (int r0 = 0; r0 < nrows; r0 += kCombineRows) {
+        const int lim = min(kCombineRows, nrows - r0);
+        if (r0) __syncthreads();
+        for (int i = threadIdx.x; i < lim; i += blockDim.x) {
+            const int r = r0 + i;
+            if (r < nr) {
+                const int j = r / kp_r, p = r - j * kp_r;
+                const int pos = inv_perm ? inv_perm[t * k + j] : t * k + j;
+                src[i] = yp_r + p * part_r + (size_t)max(pos, 0) * H;
+                wgt[i] = pos < 0 ? 0.f : topk_w[t * k + j];        // (a pair whose expert id was out of range: no row of its own)
+                if (pos < 0) src[i] = nullptr;
             } else {
-                acc[0] = fmaf(wgt, __uint_as_float(v.x), acc[0]);
-                acc[1] = fmaf(wgt, __uint_as_float(v.y), acc[1]);
-                acc[2] = fmaf(wgt, __uint_as_float(v.z), acc[2]);
-                acc[3] = fmaf(wgt, __uint_as_float(v.w), acc[3]);
+                const int s = (r - nr) / kp_s, p = r - nr - s * kp_s;
+                src[i] = yp_s + p * part_s + ((size_t)s * N + t) * H;
+                wgt[i] = sgate ? sgate[t] : 1.0f;
+            }
+        }
+        __syncthreads();
+        if (c * V < H) {
+            for (int i0 = 0; i0 < lim; i0 += 8) {
+                uint4 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const T* q = src[min(i0 + u, lim - 1)];
+                    v[u] = q ? reinterpret_cast<const uint4*>(q)[c] : make_uint4(0, 0, 0, 0);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (i0 + u >= lim) break;
+                    const float w = wgt[i0 + u];
+                    if constexpr (sizeof(T) == 2) {
+                        const __half2* h = reinterpret_cast<const __half2*>(&v[u]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            acc[2 * i] = fmaf(w, __low2float(h[i]), acc[2 * i]);
+                            acc[2 * i + 1] = fmaf(w, __high2float(h[i]), acc[2 * i + 1]);
+                        }
+                    } else {
+                        acc[0] = fmaf(w, __uint_as_float(v[u].x), acc[0]);
+                        acc[1] = fmaf(w, __uint_as_float(v[u].y), acc[1]);
+                        acc[2] = fmaf(w, __uint_as_float(v[u].z), acc[2]);
+                        acc[3] = fmaf(w, __uint_as_float(v[u].w), acc[3]);
+                    }
+                }
             }
         }
     }
+    if (c * V >= H) return;
     if (y32) {
         float4* o = reinterpret_cast<float4*>(y32 + (size_t)t * H + c * V);
 #pragma unroll
@@ -873,8 +997,18 @@ void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s) {
     *kp_s = d.n_shared ? parts(d.I_shared_max) : 1;
 }
 
+TileBlocks mfma_tile_blocks(const fate_ffn_desc& d) {
+    int kp_r = 1, kp_s = 1;
+    mfma_k_parts(d, &kp_r, &kp_s);
+    const int nb_down = (d.H + kBNDown - 1) / kBNDown;
+    return TileBlocks{(d.I_max + kBNUp - 1) / kBNUp, d.n_shared ? (d.I_shared_max + kBNUp - 1) / kBNUp : 0, nb_down * kp_r,
+                      nb_down * kp_s};
+}
+
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs da, const MfmaScratch& ms,
-                            void* y_out, int phase, const PartSel& sel, bool exact) {
+                            void* y_out, const PartSel& sel, const MfmaMode& mode) {
+    const int phase = mode.phase;
+    const bool exact = mode.exact;
     if (d.H % kKQ || d.I_max % kKQ || (d.n_shared && d.I_shared_max % kKQ))
         FATE_FAIL(FATE_ESHAPE, "the MFMA path needs H and I to be multiples of %d", kKQ);
     const int P = d.N * d.k;
@@ -883,45 +1017,52 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
                                      (long long)d.n_shared * d.N * da.ldh_s});
     if (amax >= (1LL << 31))
         FATE_FAIL(FATE_ESHAPE, "the MFMA path needs activation matrices of fewer than 2^31 elements (%lld)", amax);
-    const int nb_r_up = (d.I_max + kBNUp - 1) / kBNUp, nb_s_up = d.n_shared ? (d.I_shared_max + kBNUp - 1) / kBNUp : 0;
-    const int nb_down = (d.H + kBNDown - 1) / kBNDown;
+    const TileBlocks nb = mfma_tile_blocks(d);
     int kp_r = 1, kp_s = 1;
     mfma_k_parts(d, &kp_r, &kp_s);
+    const int nb_down = nb.r_down / kp_r;
+    // upper bounds of the routed row blocks, and the shared experts' row blocks
+    const long long mb_r = (mode.exact ? 0 : P / kBM) + (d.E < P ? d.E : P), mb_s = (d.N + kBM - 1) / kBM;
     const bool do_up = phase != 2, do_down = phase != 1;
     static bool attr_done = false;
     if (!attr_done) {
-        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_exact_kernel<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_exact_kernel<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+#define FATE_GEMM_ATTR(UP, MODE, KW)                                                                 \
+    FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<UP, MODE, KW>),   \
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        FATE_GEMM_ATTR(true, 0, 1) FATE_GEMM_ATTR(false, 0, 1)
+        FATE_GEMM_ATTR(true, 1, 1) FATE_GEMM_ATTR(false, 1, 1)
+        FATE_GEMM_ATTR(true, 2, 1) FATE_GEMM_ATTR(false, 2, 1)
+        FATE_GEMM_ATTR(true, 2, 2)
+#undef FATE_GEMM_ATTR
         attr_done = true;
     }
-    if (do_up) {
+    // Decode layer: the columns of the up projection are split over pairs of waves if they can be (whole stages of 128)
+    const int kw = mode.layer && d.H % 256 == 0 ? 2 : 1;
+    if (do_up && !mode.layer) {
         prefill_prep_kernel<<<sel.first ? d.N : 1, 256, 0, st>>>(da.x, d.N, d.H, d.E, d.n_shared, da.offsets,
                                                                  da.order, da.shared_gate, ms.xh, ms.sgate, ms.tab_up, ms.tab_down,
-                                                                 nb_r_up, nb_s_up, nb_down * kp_r, nb_down * kp_s, sel);
+                                                                 nb, sel);
         FATE_HIP(hipGetLastError());
     }
-    // upper bounds of the routed row blocks, and the shared experts' row blocks
-    const long long mb_r = P / kBM + (d.E < P ? d.E : P), mb_s = (d.N + kBM - 1) / kBM;
     GemmArgs g{};
     g.experts = da.experts; g.shared = da.shared; g.E = d.E; g.n_shared = d.n_shared; g.N = d.N; g.k = d.k;
     g.perm = da.perm;
     g.status = da.status;
+    if (mode.layer) g.lo = *mode.layer;
+    g.bits_r = da.bits_r; g.group_r = da.group_r; g.bits_s = da.bits_s; g.group_s = da.group_s;
     g.H = d.H;
     if (do_up) {
         g.A_r = ms.xh; g.lda_r = d.H; g.A_s = ms.xh; g.lda_s = d.H; g.segs = ms.tab_up;
         g.out_r = da.h_r; g.ldo_r = da.ldh_r; g.out_s = da.h_s; g.ldo_s = da.ldh_s;
-        g.nb_r = nb_r_up; g.nb_s = nb_s_up;
+        g.nb_r = nb.r_up * kw; g.nb_s = nb.s_up * kw;
         g.kp_r = g.kp_s = 1;
-        const long long grid = mb_r * nb_r_up + d.n_shared * mb_s * nb_s_up;
+        const long long grid = (mb_r * nb.r_up + d.n_shared * mb_s * nb.s_up) * kw + (mode.layer ? 1 : 0);
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
-        if (exact) grouped_gemm_exact_kernel<true><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
-        else grouped_gemm_kernel<true><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
+        const unsigned ng = (unsigned)grid;
+        if (mode.layer && kw == 2) grouped_gemm_kernel<true, 2, 2><<<ng, 256, kGemmLds, st>>>(g);
+        else if (mode.layer) grouped_gemm_kernel<true, 2, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else if (exact) grouped_gemm_kernel<true, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<true, 0, 1><<<ng, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
     }
     if (do_down) {
@@ -932,21 +1073,25 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
         g.part_r = (size_t)P * d.H; g.part_s = (size_t)d.n_shared * d.N * d.H;
         const long long grid = (mb_r * kp_r + d.n_shared * mb_s * kp_s) * nb_down;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
-        if (exact) grouped_gemm_exact_kernel<false><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
-        else grouped_gemm_kernel<false><<<(unsigned)grid, 256, kGemmLds, st>>>(g);
+        const unsigned ng = (unsigned)grid;
+        if (mode.layer) grouped_gemm_kernel<false, 2, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else if (exact) grouped_gemm_kernel<false, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<false, 0, 1><<<ng, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
         if (sel.last) {
             float* y32 = d.y_is_fp32 ? static_cast<float*>(y_out) : nullptr;
             uint16_t* y16 = d.y_is_fp32 ? nullptr : static_cast<uint16_t*>(y_out);
             const float* gate = da.shared_gate ? ms.sgate : nullptr;
+            const int32_t* inv = mode.layer ? nullptr : da.inv_perm;
+            const int threads = d.N >= 64 ? 256 : 64;
             if (exact)
-                combine_kernel<float><<<dim3(d.N, (d.H / 4 + 255) / 256), 256, 0, st>>>(
-                    static_cast<const float*>(ms.yp_r), static_cast<const float*>(ms.yp_s), da.inv_perm, da.topk_w, gate, d.H,
-                    d.k, d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
+                combine_kernel<float><<<dim3(d.N, (d.H / 4 + threads - 1) / threads), threads, 0, st>>>(
+                    static_cast<const float*>(ms.yp_r), static_cast<const float*>(ms.yp_s), inv, da.topk_w, gate, d.H, d.k,
+                    d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
             else
-                combine_kernel<__half><<<dim3(d.N, (d.H / 8 + 255) / 256), 256, 0, st>>>(
-                    static_cast<const __half*>(ms.yp_r), static_cast<const __half*>(ms.yp_s), da.inv_perm, da.topk_w, gate, d.H,
-                    d.k, d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
+                combine_kernel<__half><<<dim3(d.N, (d.H / 8 + threads - 1) / threads), threads, 0, st>>>(
+                    static_cast<const __half*>(ms.yp_r), static_cast<const __half*>(ms.yp_s), inv, da.topk_w, gate, d.H, d.k,
+                    d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
         }
         FATE_HIP(hipGetLastError());
     }

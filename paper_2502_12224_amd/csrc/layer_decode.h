@@ -3,6 +3,7 @@
 #pragma once
 #include "common.h"
 #include "route_device.h"
+#include "ffn_internal.h"
 
 namespace fate {
 
@@ -32,6 +33,7 @@ struct LayerArgs {
     const int32_t* hint;           // one-token kernel: k expert ids predicted for this layer, or NULL
     unsigned long long* hq;        // one-token kernel: tagged pairs of h, shared experts [n_shared][I_s_max / 2] then routed slots [k][I_max / 2]
     unsigned long long* yq;        // one-token kernel: [parts - 1][H] tagged partial outputs
+    char* scratch; size_t scratch_bytes;   // host side: the partial rows' part of the workspace (GEMM form)
     int nitems, nwork;             // work items (32-neuron blocks of shared experts, then of routed slots); work blocks in the launch
 };
 
@@ -59,6 +61,14 @@ inline LayerWorkspace layer_workspace(const fate_ffn_desc& d) {
     w.bytes = off;
     return w;
 }
+
+// First launch of a decode layer's GEMM form: the logits of both gates, x as fp16 and the shared experts' gate
+// values.  Everything else of the routing is done in the up GEMM's launch.
+struct RoutePrep {
+    float* z;                  // [gates][N][E]
+    __half* xh; float* sgate; const uint16_t* shared_gate;
+};
+fate_status launch_layer_logits(hipStream_t st, const FusedRouteArgs& r, const RoutePrep& prep);
 
 fate_status launch_layer_decode(hipStream_t st, const fate_ffn_desc& d, LayerArgs a);
 

@@ -57,6 +57,49 @@ __global__ __launch_bounds__(64 * kReduceWaves) void layer_reduce_kernel(LayerAr
     }
 }
 
+// The GEMM form: logits (with the FFN's preparation), up with the selection, down and combination; what
+// stays between them takes the place of the partial rows in the workspace.  Returns false if it does not fit.
+static bool layer_gemm_scratch(const fate_ffn_desc& d, char* base, size_t bytes, DecodeArgs* da, MfmaScratch* ms) {
+    size_t off = 0;
+    auto take = [&](size_t n) {
+        char* p = base + off;
+        off += (n + 255) / 256 * 256;
+        return p;
+    };
+    const size_t P = (size_t)d.N * d.k, SN = (size_t)d.n_shared * d.N;
+    int kp_r = 1, kp_s = 1;
+    mfma_k_parts(d, &kp_r, &kp_s);
+    da->ldh_r = d.I_max;
+    da->ldh_s = d.n_shared ? d.I_shared_max : 0;
+    da->h_r = reinterpret_cast<__half*>(take(P * da->ldh_r * 2));
+    da->h_s = reinterpret_cast<__half*>(take(SN * da->ldh_s * 2));
+    ms->xh = reinterpret_cast<__half*>(take((size_t)d.N * d.H * 2));
+    ms->sgate = reinterpret_cast<float*>(take((size_t)d.N * 4));
+    ms->yp_r = take((size_t)kp_r * P * d.H * 4);
+    ms->yp_s = take((size_t)kp_s * SN * d.H * 4);
+    return off <= bytes;
+}
+
+static fate_status launch_layer_gemm(hipStream_t st, const fate_ffn_desc& d, const LayerArgs& a, DecodeArgs da,
+                                     const MfmaScratch& ms) {
+    float* z = reinterpret_cast<float*>(a.zq);
+    fate_status rc = launch_layer_logits(st, a.r, RoutePrep{z, ms.xh, ms.sgate, a.shared_gate});
+    if (rc != FATE_OK) return rc;
+    da.x = a.r.x; da.N = d.N; da.H = d.H; da.E = d.E; da.k = d.k;
+    da.experts = a.experts; da.shared = a.shared; da.n_shared = d.n_shared;
+    da.counts = a.r.counts; da.offsets = a.r.offsets; da.perm = a.r.perm; da.inv_perm = a.r.inv_perm; da.order = a.r.order;
+    da.topk_w = a.r.w; da.shared_gate = a.shared_gate;
+    da.bits_r = a.bits_r; da.group_r = a.group_r; da.bits_s = a.bits_s; da.group_s = a.group_s;
+    da.status = a.status;
+    MfmaMode mode;
+    const bool pred = a.r.Wg2 != nullptr;
+    const LayerOut lo{z, d.N, d.k, a.r.m, d.E, a.r.renorm, a.r.ids, a.r.w, pred ? a.r.pids : nullptr, a.r.pw, a.r.counts,
+                      a.r.offsets, a.r.perm, a.r.inv_perm, a.r.order, a.r.pop, a.sync};
+    mode.exact = true;
+    mode.layer = &lo;
+    return launch_ffn_mfma(st, d, da, ms, a.y, part_all(), mode);
+}
+
 fate_status launch_layer_decode(hipStream_t st, const fate_ffn_desc& d, LayerArgs a) {
     if (d.N < 1 || d.N > kLayerMaxN || d.N * d.k > kLayerMaxP)
         FATE_FAIL(FATE_ESHAPE, "fused layer: need 1 <= N <= %d and N*k <= %d (N = %d, k = %d)", kLayerMaxN,
@@ -77,6 +120,16 @@ fate_status launch_layer_decode(hipStream_t st, const fate_ffn_desc& d, LayerArg
         B1Args b1;
         int nblocks = 0;
         if (b1_plan(d, a, &b1, &nblocks)) return launch_layer_decode_b1(st, d, b1, nblocks);
+    }
+    // Layers of some size go through the GEMM pipeline in four launches: the kernel below leaves a partial row
+    // of H floats per 32 neurons and pair, as much traffic as the weights, and loops over several items per
+    // workgroup.  Per layer, Qwen shape at 2 / 8 tokens 35.6 -> 32.3 / 61.7 -> 49.1 us, DeepSeek shape at 8
+    // 83 -> 63, Mixtral shape at 1 / 8 61.7 -> 54.4 / 267 -> 151.  Small layers stay with the kernel below (its two
+    // launches against four: E = 66, H = 1024, I = 1152 int8 at one token 20.6 us, 27.3 with the GEMMs).
+    if (decode_by_gemm(d)) {
+        DecodeArgs da{};
+        MfmaScratch ms{};
+        if (layer_gemm_scratch(d, a.scratch, a.scratch_bytes, &da, &ms)) return launch_layer_gemm(st, d, a, da, ms);
     }
     // work items: 32-neuron blocks of the shared experts, then of the routed slots.  With more
     // items than workgroups of the looping kernel fit on the device (asked of the occupancy

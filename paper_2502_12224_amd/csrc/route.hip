@@ -8,6 +8,8 @@
 #include "common.h"
 #include "route_device.h"
 #include "async_lds.h"
+#include "decode_device.h"
+#include "layer_decode.h"
 
 namespace fate {
 
@@ -16,23 +18,23 @@ __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-// Logits of TPW tokens (rows xr) for every expert into z [TPW][E] (LDS), by a whole workgroup of
-// kTokWaves waves; wave w takes experts w, w + kTokWaves, .., four at a time, so that up to 16 rows
+// Logits of TPW tokens (rows of x) for every expert into z [TPW][E], by a whole workgroup of NW
+// waves; wave w takes experts w, w + NW, .., four at a time, so that up to 16 rows
 // of 1 KiB are requested before the first is used.  Rows past the last expert read row 0.
 // A lane sums columns lane*8 + 512*j in order, then the lanes add up: the same bits for a
 // (token, expert) whichever workgroup, batch size or call evaluates it.
 constexpr int kTokWaves = 16;
-template <int TPW>
+template <int TPW, int NW = kTokWaves>
 __device__ __forceinline__ void token_logits(const uint4* __restrict__ x, const uint4* __restrict__ Wg,
                                              const float* __restrict__ bias, int ntok, int nvec, int E, float* z) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int NE = 4, NJ = TPW == 1 ? 4 : 2;       // operands of one batch: within the 128 registers of 16 waves
-    for (int e0 = wave; e0 < E; e0 += kTokWaves * NE) {
+    for (int e0 = wave; e0 < E; e0 += NW * NE) {
         float acc[NE][TPW];
         const uint4* wr[NE];
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
-            const int e = e0 + kTokWaves * i;
+            const int e = e0 + NW * i;
             wr[i] = Wg + (size_t)(e < E ? e : 0) * nvec;
 #pragma unroll
             for (int t = 0; t < TPW; ++t) acc[i][t] = 0.f;
@@ -62,7 +64,7 @@ __device__ __forceinline__ void token_logits(const uint4* __restrict__ x, const 
         }
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
-            const int e = e0 + kTokWaves * i;
+            const int e = e0 + NW * i;
             if (e < E) {
                 const float b = bias ? bias[e] : 0.f;
 #pragma unroll
@@ -364,6 +366,7 @@ __global__ __launch_bounds__(64 * kTokWaves) void route_fused_kernel(FusedRouteA
     const int t = blockIdx.x, g = blockIdx.y, nvec = a.H >> 3, E = a.E;
     token_logits<1>(reinterpret_cast<const uint4*>(a.x) + (size_t)t * nvec, reinterpret_cast<const uint4*>(g ? a.Wg2 : a.Wg),
                     g ? a.bias2 : a.bias, 1, nvec, E, z);
+    for (int i = tid; i < E; i += 64 * kTokWaves) pop[i] = 0;
     __syncthreads();
     const int m = g ? a.m : a.k;
     if (wave == 0) {
@@ -378,15 +381,14 @@ __global__ __launch_bounds__(64 * kTokWaves) void route_fused_kernel(FusedRouteA
     }
     __syncthreads();
     if (!sm_last) return;
-    const int P = a.N * a.k;
-    if (a.Wg2) {
-        for (int i = tid; i < E; i += 64 * kTokWaves) pop[i] = 0;
-        __syncthreads();
-        for (int i = tid; i < a.N * a.m; i += 64 * kTokWaves) atomicAdd(&pop[ld_dev(a.pids + i)], 1);
-    }
-    for (int i = tid; i < P; i += 64 * kTokWaves) all[i] = ld_dev(a.ids + i);
+    const int P = a.N * a.k, Q = a.Wg2 ? a.N * a.m : 0;
+    // (at most 1024 of each: one per thread, requested together)
+    const int id = tid < P ? ld_dev(a.ids + tid) : -1;
+    const int pid = tid < Q ? ld_dev(a.pids + tid) : -1;
+    if (tid < P) all[tid] = id;
+    if (pid >= 0) atomicAdd(&pop[pid], 1);
     __syncthreads();
-    if (a.Wg2)
+    if (Q)
         for (int i = tid; i < E; i += 64 * kTokWaves) a.pop[i] = pop[i];
     if (P <= 64) {
         if (wave == 0) wave_permute_small(all, P, E, a.counts, a.offsets, a.perm, a.inv_perm, a.order);
@@ -394,6 +396,34 @@ __global__ __launch_bounds__(64 * kTokWaves) void route_fused_kernel(FusedRouteA
         block_permute(all, P, E, a.counts, a.offsets, a.perm, a.inv_perm, a.order, sm_perm);
     }
     if (tid == 0) *ticket = 0;
+}
+
+// Logits of a decode layer: a workgroup of four waves per 16 experts, token and gate (a compute unit takes the
+// gate matrix at 64 bytes per cycle; one workgroup for all of 60 experts took 9 us, of which 4 were that); the
+// first gate's first workgroup of a token also writes the token's row as fp16 and its shared gate.
+__global__ __launch_bounds__(256) void layer_logits_kernel(FusedRouteArgs a, RoutePrep prep) {
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t = blockIdx.x, g = blockIdx.y, e0 = blockIdx.z * 16, nvec = a.H >> 3, E = a.E;
+    const uint4* xrow = reinterpret_cast<const uint4*>(a.x) + (size_t)t * nvec;
+    if (e0 >= E) {                                        // the preparation has workgroups of its own
+        if (g) return;
+        uint4* xo = reinterpret_cast<uint4*>(prep.xh) + (size_t)t * nvec;
+        for (int c = tid; c < nvec; c += 256) xo[c] = bf16x8_to_f16x8(xrow[c]);
+        if (wave == 3 && prep.shared_gate != nullptr) {
+            const float v = wave_sigmoid_dot_bf16(xrow, reinterpret_cast<const uint4*>(prep.shared_gate), nvec);
+            if ((tid & 63) == 0) prep.sgate[t] = v;
+        }
+        return;
+    }
+    const float* bias = g ? a.bias2 : a.bias;
+    token_logits<1, 4>(xrow, reinterpret_cast<const uint4*>(g ? a.Wg2 : a.Wg) + (size_t)e0 * nvec, bias ? bias + e0 : nullptr, 1,
+                       nvec, min(16, E - e0), prep.z + ((size_t)g * a.N + t) * E + e0);
+}
+
+fate_status launch_layer_logits(hipStream_t st, const FusedRouteArgs& r, const RoutePrep& prep) {
+    layer_logits_kernel<<<dim3(r.N, r.Wg2 ? 2 : 1, (r.E + 15) / 16 + 1), 256, 0, st>>>(r, prep);
+    FATE_HIP(hipGetLastError());
+    return FATE_OK;
 }
 
 static fate_status check_route_args(const void* x, const void* Wg, const float* bias, int N, int H, int E, int k,
