@@ -237,8 +237,6 @@ static fate_status layer_decode_checked(void* stream, const fate_ffn_desc* d, co
     a.y_is_fp32 = d->y_is_fp32;
     a.status = status ? status : reinterpret_cast<int32_t*>(base + w.status);
     a.sync = reinterpret_cast<int32_t*>(base + w.sync);
-    a.scratch = base + w.part_r;
-    a.scratch_bytes = w.hq - w.part_r;
     return launch_layer_decode(static_cast<hipStream_t>(stream), *d, a);
 }
 

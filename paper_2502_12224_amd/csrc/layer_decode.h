@@ -33,7 +33,6 @@ struct LayerArgs {
     const int32_t* hint;           // one-token kernel: k expert ids predicted for this layer, or NULL
     unsigned long long* hq;        // one-token kernel: tagged pairs of h, shared experts [n_shared][I_s_max / 2] then routed slots [k][I_max / 2]
     unsigned long long* yq;        // one-token kernel: [parts - 1][H] tagged partial outputs
-    char* scratch; size_t scratch_bytes;   // host side: the partial rows' part of the workspace (GEMM form)
     int nitems, nwork;             // work items (32-neuron blocks of shared experts, then of routed slots); work blocks in the launch
 };
 

@@ -129,7 +129,8 @@ fate_status launch_layer_decode(hipStream_t st, const fate_ffn_desc& d, LayerArg
     if (decode_by_gemm(d)) {
         DecodeArgs da{};
         MfmaScratch ms{};
-        if (layer_gemm_scratch(d, a.scratch, a.scratch_bytes, &da, &ms)) return launch_layer_gemm(st, d, a, da, ms);
+        const LayerWorkspace w = layer_workspace(d);
+        if (layer_gemm_scratch(d, reinterpret_cast<char*>(a.part_r), w.hq - w.part_r, &da, &ms)) return launch_layer_gemm(st, d, a, da, ms);
     }
     // work items: 32-neuron blocks of the shared experts, then of the routed slots.  With more
     // items than workgroups of the looping kernel fit on the device (asked of the occupancy
