@@ -60,9 +60,8 @@ static void carve(const fate_ffn_desc& d, void* base, FfnWorkspace* w) {
         w->ms.tab_down = reinterpret_cast<int4*>(p + off); off += align_up(nseg1 * sizeof(int4), 256);
         int kp_r = 1, kp_s = 1;
         mfma_k_parts(d, &kp_r, &kp_s);
-        const size_t osz = exact ? 4 : 2;
-        w->ms.yp_r = p + off; off += align_up((size_t)kp_r * d.N * d.k * d.H * osz, 256);
-        w->ms.yp_s = p + off; off += align_up((size_t)kp_s * d.n_shared * d.N * d.H * osz, 256);
+        w->ms.yp_r = p + off; off += align_up((size_t)kp_r * d.N * d.k * d.H * mfma_out_bytes(exact, kp_r), 256);
+        w->ms.yp_s = p + off; off += align_up((size_t)kp_s * d.n_shared * d.N * d.H * mfma_out_bytes(exact, kp_s), 256);
     }
     w->bytes = off + 256;
 }

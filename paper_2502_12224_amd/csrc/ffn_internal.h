@@ -35,7 +35,7 @@ struct MfmaScratch {
     float* sgate;      // [N] shared gate values
     int4* tab_up;      // [E + n_shared + 1] segments of the up GEMM: first tile, expert, first row, rows
     int4* tab_down;    // same for the down GEMM
-    void* yp_r;        // [kp_r][P,H] per-pair outputs of the down GEMM, fp16 (decode-sized calls: fp32)
+    void* yp_r;        // [kp_r][P,H] per-pair outputs of the down GEMM, mfma_out_bytes() each
     void* yp_s;        // [kp_s][n_shared*N,H]
 };
 
@@ -63,6 +63,8 @@ __host__ __device__ inline PartSel part_all() { return PartSel{{~0ull, ~0ull, ~0
 
 // parts of the reduction dimension of the down GEMM of routed / shared experts
 void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s);
+// bytes per element of its outputs: fp16 only for a whole sum, and not in the decode-sized form
+inline size_t mfma_out_bytes(bool exact, int kp) { return exact || kp > 1 ? 4 : 2; }
 // Routing of a decode layer inside its up GEMM's launch, from the logits (at most 64 pairs): every workgroup
 // selects for itself, the first one writes the outputs.
 struct LayerOut {

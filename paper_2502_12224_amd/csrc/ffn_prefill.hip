@@ -4,7 +4,8 @@
 //   prep     x (bf16) -> fp16 copy, shared-expert gate values, and the tile
 //            tables (prefix sums of tiles per expert segment) of both GEMMs;
 //   up       grouped GEMM  h = silu(X W1^T) * (X W3^T)   -> fp16 [rows, I]
-//   down     grouped GEMM  Yp = h W2^T                     -> fp16 [K parts][rows, H]
+//   down     grouped GEMM  Yp = h W2^T                     -> fp16 [rows, H]; fp32 [K parts][rows, H]
+//            where the reduction dimension is cut into parts
 //   combine  y[t] = sum_j w[t,j] Yp[inv_perm[t*k+j]] + sum_s g_s(t) Yp_s[t]
 // Rows are (token, expert) pairs in the sorted order of the permutation, so
 // an expert's rows are contiguous; shared experts are extra segments of N rows.
@@ -58,11 +59,12 @@ struct GemmArgs {
     int E, n_shared, N, k;
     const int32_t* perm;
     const int4* segs;                  // [E + n_shared + 1]: first tile, expert, first row and rows of a segment
-    void* out_r; int ldo_r;            // routed rows, by sorted position (fp16; the exact down GEMM: fp32)
+    void* out_r; int ldo_r;            // routed rows, by sorted position
     void* out_s; int ldo_s;            // shared rows, s*N + t
     int nb_r, nb_s;                    // column blocks per routed / shared segment
     int kp_r, kp_s;                    // parts of the reduction dimension (down GEMM), each with an output of its own
     size_t part_r, part_s;             // elements between those outputs
+    int f32_r, f32_s;                  // down GEMM: output elements are fp32 (else fp16)
     int bits_r, group_r, bits_s, group_s;              // decode layer: entries of another format, or with zero-points, count as absent
     LayerOut lo;                       // decode layer only
     int32_t* status;
@@ -172,6 +174,7 @@ struct TileCtx {
     int Nout, K, col0, ncol;           // weight rows of the matrix, its columns, this part's columns
     int group;
     void* out; int ldo;                // output row 0 of the tile
+    bool f32;                          // its elements: fp32 or fp16
     const int32_t* orows;              // decode-sized form: output row of tile row r, or NULL: r itself
 };
 
@@ -353,6 +356,7 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
         const int r = mt * 32 + n;
         if (r < c.nrows) {
             __half* o = static_cast<__half*>(c.out) + (size_t)r * c.ldo + 4 * half;
+            float* of = static_cast<float*>(c.out) + (size_t)r * c.ldo + 4 * half;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if constexpr (UP) {
@@ -366,10 +370,16 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
                 } else {
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
-                        __half h[4];
+                        if (!c.wlive[i]) continue;
+                        if (c.f32) {
+                            *reinterpret_cast<float4*>(of + c.wrow[i] + 8 * q) =
+                                make_float4(acc[i][mt][4 * q], acc[i][mt][4 * q + 1], acc[i][mt][4 * q + 2], acc[i][mt][4 * q + 3]);
+                        } else {
+                            __half h[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) h[j] = __float2half(acc[i][mt][4 * q + j]);
-                        if (c.wlive[i]) *reinterpret_cast<uint2*>(o + c.wrow[i] + 8 * q) = *reinterpret_cast<uint2*>(h);
+                            for (int j = 0; j < 4; ++j) h[j] = __float2half(acc[i][mt][4 * q + j]);
+                            *reinterpret_cast<uint2*>(o + c.wrow[i] + 8 * q) = *reinterpret_cast<uint2*>(h);
+                        }
                     }
                 }
             }
@@ -393,7 +403,7 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
                 lds_only_barrier();
                 if (c.rows) p.rows = c.rows + r0;
                 else p.A = c.A + (size_t)r0 * c.lda;
-                p.out = static_cast<__half*>(c.out) + (size_t)r0 * c.ldo;
+                p.out = static_cast<char*>(c.out) + (size_t)r0 * c.ldo * (c.f32 ? sizeof(float) : sizeof(__half));
             }
             p.nrows = min(64, c.nrows - r0);
             if (p.nrows <= 32) gemm_pipe<BITS, ZP, UP, 1>(p, smem);
@@ -823,8 +833,9 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     if (c.nrows <= 0) return;
     const int out_row0 = (is_shared ? e * a.N : sbeg) + row0;      // (MODE 2, routed: 0, rows are pairs)
     c.ldo = is_shared ? a.ldo_s : a.ldo_r;
+    c.f32 = !UP && (EXACT || (is_shared ? a.f32_s : a.f32_r));
     {
-        constexpr size_t osz = EXACT && !UP ? sizeof(float) : sizeof(__half);
+        const size_t osz = c.f32 ? sizeof(float) : sizeof(__half);
         c.out = static_cast<char*>(is_shared ? a.out_s : a.out_r) +
                 ((size_t)part * (is_shared ? a.part_s : a.part_r) + (size_t)out_row0 * c.ldo) * osz;
     }
@@ -849,7 +860,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
                 const int col = nblk * kBNDown + (i % (kBNDown / 4)) * 4;
                 if (MODE == 2 && !is_shared) r = rowlist[r];
                 if (col < a.H) {
-                    if (EXACT) reinterpret_cast<float4*>(static_cast<float*>(c.out) + (size_t)r * c.ldo + col)[0] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (c.f32) reinterpret_cast<float4*>(static_cast<float*>(c.out) + (size_t)r * c.ldo + col)[0] = make_float4(0.f, 0.f, 0.f, 0.f);
                     else reinterpret_cast<uint2*>(static_cast<__half*>(c.out) + (size_t)r * c.ldo + col)[0] = make_uint2(0, 0);
                 }
             }
@@ -905,16 +916,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     grouped_gemm_body<UP, MODE, KW>(a);
 }
 
+// acc += wgt[i] * row i of src, columns c*V .. c*V + V - 1.  With few tokens the rows' latency is all there
+// is, so a thread asks for 128 bytes of rows at once.
+template <class T, int V>
+__device__ __forceinline__ void add_rows(const void* const* src, const float* wgt, int n, int c, float (&acc)[V]) {
+    constexpr int L = V * (int)sizeof(T) / 16, B = 8 / L;  // loads per row, rows per batch
+    for (int i0 = 0; i0 < n; i0 += B) {
+        uint4 v[B][L];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const uint4* q = static_cast<const uint4*>(src[min(i0 + u, n - 1)]);
+#pragma unroll
+            for (int l = 0; l < L; ++l) v[u][l] = q ? q[c * L + l] : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            if (i0 + u >= n) break;
+            const float w = wgt[i0 + u];
+            const T* e = reinterpret_cast<const T*>(v[u]);
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[i] = fmaf(w, (float)e[i], acc[i]);
+        }
+    }
+}
+
 // y[t,:] = sum_j w[t,j] * Yp_r[pos(t,j), :] + sum_s g_s(t) * Yp_s[s*N+t, :], each Yp the sum of its K parts;
-// pos = inv_perm, or the pair itself when that is NULL.  A block of 64 to 256 threads per token and slice of
-// H: with few tokens the rows' latency is all there is, so a thread asks for eight rows at once.
-template <class T>
-__global__ void combine_kernel(const T* __restrict__ yp_r, const T* __restrict__ yp_s, const int32_t* __restrict__ inv_perm,
+// pos = inv_perm, or the pair itself when that is NULL.  TR / TS: elements of the routed / shared outputs.
+// A block of 64 to 256 threads per token and slice of H.
+template <class TR, class TS>
+__global__ void combine_kernel(const TR* __restrict__ yp_r, const TS* __restrict__ yp_s, const int32_t* __restrict__ inv_perm,
                                const float* __restrict__ topk_w, const float* __restrict__ sgate, int H, int k, int n_shared,
                                int N, int kp_r, int kp_s, size_t part_r, size_t part_s, float* __restrict__ y32,
                                uint16_t* __restrict__ y16) {
-    constexpr int V = 16 / sizeof(T);                     // outputs per thread: one 16-byte load of every row
-    __shared__ const T* src[kCombineRows];
+    constexpr bool same = sizeof(TR) == sizeof(TS);
+    constexpr int V = same ? 16 / sizeof(TR) : 8;         // outputs per thread: 16 bytes of the narrower rows
+    __shared__ const void* src[kCombineRows];
     __shared__ float wgt[kCombineRows];
     const int t = blockIdx.x;
     const int c = blockIdx.y * blockDim.x + threadIdx.x;
@@ -941,32 +977,9 @@ __global__ void combine_kernel(const T* __restrict__ yp_r, const T* __restrict__
         }
         __syncthreads();
         if (c * V < H) {
-            for (int i0 = 0; i0 < lim; i0 += 8) {
-                uint4 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const T* q = src[min(i0 + u, lim - 1)];
-                    v[u] = q ? reinterpret_cast<const uint4*>(q)[c] : make_uint4(0, 0, 0, 0);
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (i0 + u >= lim) break;
-                    const float w = wgt[i0 + u];
-                    if constexpr (sizeof(T) == 2) {
-                        const __half2* h = reinterpret_cast<const __half2*>(&v[u]);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            acc[2 * i] = fmaf(w, __low2float(h[i]), acc[2 * i]);
-                            acc[2 * i + 1] = fmaf(w, __high2float(h[i]), acc[2 * i + 1]);
-                        }
-                    } else {
-                        acc[0] = fmaf(w, __uint_as_float(v[u].x), acc[0]);
-                        acc[1] = fmaf(w, __uint_as_float(v[u].y), acc[1]);
-                        acc[2] = fmaf(w, __uint_as_float(v[u].z), acc[2]);
-                        acc[3] = fmaf(w, __uint_as_float(v[u].w), acc[3]);
-                    }
-                }
-            }
+            const int lim_r = same ? lim : max(0, min(lim, nr - r0));
+            add_rows<TR, V>(src, wgt, lim_r, c, acc);
+            if constexpr (!same) add_rows<TS, V>(src + lim_r, wgt + lim_r, lim - lim_r, c, acc);
         }
     }
     if (c * V >= H) return;
@@ -986,7 +999,7 @@ __global__ void combine_kernel(const T* __restrict__ yp_r, const T* __restrict__
 // Parts of the reduction dimension of the down GEMM.  A tile's time is its K; with `tiles` of
 // length K over 2 workgroups per compute unit, a tile longer than the average load of a
 // workgroup would run on after everything else has ended, so it is cut into parts.  Every part
-// has an output of its own, which combine adds up (512 columns at least, 8 parts at most).
+// has an output of its own in fp32, which combine adds up (512 columns at least, 8 parts at most).
 void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s) {
     const long long P = (long long)d.N * d.k, nb = (d.H + kBNDown - 1) / kBNDown;
     const long long tr = (P / kBM + std::min<long long>(d.E, P)) * nb;
@@ -1070,6 +1083,7 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
         g.segs = ms.tab_down; g.nb_r = nb_down; g.nb_s = nb_down;
         g.out_r = ms.yp_r; g.ldo_r = d.H; g.out_s = ms.yp_s; g.ldo_s = d.H;
         g.kp_r = kp_r; g.kp_s = kp_s;
+        g.f32_r = mfma_out_bytes(exact, kp_r) == 4; g.f32_s = d.n_shared && mfma_out_bytes(exact, kp_s) == 4;
         g.part_r = (size_t)P * d.H; g.part_s = (size_t)d.n_shared * d.N * d.H;
         const long long grid = (mb_r * kp_r + d.n_shared * mb_s * kp_s) * nb_down;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
@@ -1084,14 +1098,16 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
             const float* gate = da.shared_gate ? ms.sgate : nullptr;
             const int32_t* inv = mode.layer ? nullptr : da.inv_perm;
             const int threads = d.N >= 64 ? 256 : 64;
-            if (exact)
-                combine_kernel<float><<<dim3(d.N, (d.H / 4 + threads - 1) / threads), threads, 0, st>>>(
-                    static_cast<const float*>(ms.yp_r), static_cast<const float*>(ms.yp_s), inv, da.topk_w, gate, d.H, d.k,
-                    d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
-            else
-                combine_kernel<__half><<<dim3(d.N, (d.H / 8 + threads - 1) / threads), threads, 0, st>>>(
-                    static_cast<const __half*>(ms.yp_r), static_cast<const __half*>(ms.yp_s), inv, da.topk_w, gate, d.H, d.k,
-                    d.n_shared, d.N, kp_r, kp_s, g.part_r, g.part_s, y32, y16);
+#define FATE_COMBINE(TR, TS)                                                                                          \
+    combine_kernel<TR, TS><<<dim3(d.N, (d.H / (sizeof(TR) == sizeof(TS) ? 16 / (int)sizeof(TR) : 8) + threads - 1) / threads), \
+                             threads, 0, st>>>(static_cast<const TR*>(ms.yp_r), static_cast<const TS*>(ms.yp_s), inv,   \
+                                               da.topk_w, gate, d.H, d.k, d.n_shared, d.N, kp_r, kp_s, g.part_r,        \
+                                               g.part_s, y32, y16)
+            if (g.f32_r && (g.f32_s || !d.n_shared)) FATE_COMBINE(float, float);
+            else if (g.f32_r) FATE_COMBINE(float, __half);
+            else if (g.f32_s) FATE_COMBINE(__half, float);
+            else FATE_COMBINE(__half, __half);
+#undef FATE_COMBINE
         }
         FATE_HIP(hipGetLastError());
     }

@@ -1,0 +1,58 @@
+"""The GEMM kernels at the edges of their tiles and the routing kernels at the edges of their row loads.
+Same bars as the other tests: FFN per token row max_i |y - y_ref| / max_i |y_ref| <= 2e-3 (weights and h are rounded
+to fp16 once, 2^-11 relative each), ids and permutations equal."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe as O
+from workloads import SHAPES, gen_gate, gen_hidden
+from helpers import DEV, GpuLayer, f32, ffn_rel_err, gpu_permute, gpu_route, oracle_expert
+from test_gpu_layer_fused import _one_launch_case
+
+pytestmark = pytest.mark.gpu
+
+ROWS = (1, 31, 32, 33, 64, 65, 96, 97, 128, 129)        # rows per expert: both sides of every tile size
+
+
+@pytest.mark.parametrize("H,I,bits,n_shared,I_shared", [
+    (256, 384, 4, 0, 0),                    # whole sums, fp16 outputs
+    (384, 2048, 4, 0, 0),                   # parts of the reduction dimension, fp32 outputs
+    (256, 2048, 8, 1, 384),                 # parts of the routed experts' only, passes of 64 rows
+    (256, 384, 4, 1, 2048),                 # parts of the shared expert's only
+    (256, 1536, 4, 2, 1152),                # parts of both
+])
+def test_prefill_gemm_at_its_tile_edges(H, I, bits, n_shared, I_shared):
+    cfg = dataclasses.replace(SHAPES["tiny"], name="edge", layers=1, H=H, E=len(ROWS), k=1, I=I, bits=bits, group=128,
+                              gate_var=1.0 / H, n_shared=n_shared, I_shared=I_shared)
+    ids = np.repeat(np.arange(cfg.E), ROWS)
+    ids = np.random.default_rng(7).permutation(ids).astype(np.int32)[:, None]
+    N = len(ids)
+    x = gen_hidden(cfg, N, device=DEV)
+    w = torch.rand(N, 1, generator=torch.Generator().manual_seed(3)).to(DEV) + 0.1
+    L = GpuLayer(cfg, 0)
+    y, ws = L.ffn(x, *gpu_permute(torch.from_numpy(ids).to(DEV), cfg.E), w, mode=2, ws_fill=0xff)
+    assert int(ws[:4].view(torch.int32)[0]) == 0
+    sg = None if L.shared_gate is None else f32(L.shared_gate)
+    y_ref = O.moe_ffn_grouped(f32(x), ids, w.cpu().numpy().astype(np.float64),
+                              {e: oracle_expert(L.host[e]) for e in range(cfg.E)},
+                              [oracle_expert(s) for s in L.shared_host], sg)
+    assert ffn_rel_err(f32(y), y_ref).max() <= 2e-3
+
+
+_QWEN = SHAPES["qwen"]
+LAYERS = {
+    "64pairs": (dataclasses.replace(_QWEN, H=1152, E=200, k=8, gate_var=1 / 1152), 8),       # one range of columns, E > 64
+    "int8g64": (dataclasses.replace(_QWEN, H=1024, E=96, I=896, bits=8, group=64, n_shared=2, I_shared=384,
+                                    shared_bits=4, gate_var=1 / 1024), 3),
+    "odd-blocks": (dataclasses.replace(_QWEN, H=768, E=17, k=5, I=1152, n_shared=0, I_shared=0, gate_var=1 / 768), 7),
+    "one-token": (dataclasses.replace(_QWEN, H=1280, E=10, k=4, I=4096, n_shared=0, I_shared=0, gate_var=1 / 1280), 1),
+}
+
+
+@pytest.mark.parametrize("name", list(LAYERS))
+def test_decode_layer_by_gemms_at_its_edges(name):
+    cfg, N = LAYERS[name]
+    _one_launch_case(cfg, name, N, False)
