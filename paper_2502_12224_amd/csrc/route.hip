@@ -45,22 +45,27 @@ __device__ __forceinline__ void token_logits(const uint4* __restrict__ x, const 
             for (int j = 0; j < NJ; ++j) {
                 const int c = c0 + 64 * j;
                 const bool in = c < nvec;
-                const int cc = in ? c : lane;
+                const int cc = in ? c : 0;
 #pragma unroll
                 for (int i = 0; i < NE; ++i) wv[j][i] = wr[i][cc];
 #pragma unroll
                 for (int t = 0; t < TPW; ++t) {
-                    // columns past the row: the activations are zero there, which leaves the sums as they are
+                    // columns past the row read column 0; both operands are zero there, which leaves the sums as they are
                     const uint4 v = x[(size_t)(t < ntok ? t : 0) * nvec + cc];
                     xv[j][t] = in ? v : make_uint4(0, 0, 0, 0);
                 }
             }
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+            for (int j = 0; j < NJ; ++j) {
+                if (c0 - lane + 64 * (j + 1) > nvec && c0 + 64 * j >= nvec) {
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) wv[j][i] = make_uint4(0, 0, 0, 0);
+                }
 #pragma unroll
                 for (int i = 0; i < NE; ++i)
 #pragma unroll
                     for (int t = 0; t < TPW; ++t) acc[i][t] = dot8_bf16(xv[j][t], wv[j][i], acc[i][t]);
+            }
         }
 #pragma unroll
         for (int i = 0; i < NE; ++i) {

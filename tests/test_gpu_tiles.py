@@ -56,3 +56,16 @@ LAYERS = {
 def test_decode_layer_by_gemms_at_its_edges(name):
     cfg, N = LAYERS[name]
     _one_launch_case(cfg, name, N, False)
+
+
+@pytest.mark.parametrize("H", [64, 256, 1024])
+def test_infinite_gate_weight_stays_in_its_column(H):
+    """An infinite gate weight makes its expert's logit infinite (never NaN: lanes past the end of a row must not
+    multiply it by zero), so the expert leads every token's selection."""
+    cfg = dataclasses.replace(SHAPES["tiny"], H=H, E=12, k=2, gate_var=1.0 / H)
+    x = gen_hidden(cfg, 5, device=DEV)
+    x[:, 0] = 1.0
+    Wg, b = gen_gate(cfg, 0, device=DEV)
+    Wg[7, 0] = float("inf")
+    ids, _, _ = gpu_route(x, Wg, b, cfg.k, False, want_probs=False)
+    assert ids[:, 0].tolist() == [7] * 5
