@@ -426,14 +426,16 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
 // more, so two waves per SIMD get through the widening twice as fast as one.  One token of the Mixtral shape:
 // 34 -> 26 us; four ranges gain nothing more).  A stage's scales are one load of 256 bytes per wave: for int4 both
 // blocks' scales of both 64-column halves (groups of 64, or a multiple of 128), with zero-points a second one
-// like it; for the other widths, whose stages lie inside a group, scales in the first half and zero-points in the other.
-template <int BITS, bool ZP, int R, int KW>
+// like it; where a stage lies inside a group (the other widths, int4 stages of 64 columns), scales in the first half and
+// zero-points in the other.  BK: columns of a stage.  int4 takes stages of 128 (the loads of a stage are the cost of its
+// barrier) except for the down projection of an expert whose I is no multiple of 128.
+constexpr int exact_stage(int bits) { return bits == 8 ? 64 : 128; }
+template <int BITS, bool ZP, int R, int KW, int BK>
 struct ExactFmt {
     static constexpr int KT = QFmt<BITS>::KT;
-    static constexpr int BK = BITS == 8 ? 64 : 128;       // columns per stage
     static constexpr int TPS = BK / KT;
-    static constexpr int HS = BITS == 4 ? 2 : 1;          // scales per row and stage
-    static constexpr int SL = BITS == 4 && ZP ? 2 : 1;    // loads of scales and zero-points
+    static constexpr int HS = BITS == 4 && BK == 128 ? 2 : 1;   // scales per row and stage
+    static constexpr int SL = HS == 2 && ZP ? 2 : 1;      // loads of scales and zero-points
     static constexpr int XROW = BK * 2;
     static constexpr int xwave = R * XROW;                // of the waves that share a range of columns
     static constexpr int xbytes = KW * xwave;
@@ -468,10 +470,10 @@ __device__ __forceinline__ uint32_t code_pair(const uint4 (&raw)[TPS], int d, in
 template <int BITS> struct ZpExact { static constexpr float inv_a = 1.0f, c_over_a = 8.0f; };
 template <> struct ZpExact<2> { static constexpr float inv_a = 0.5f, c_over_a = 1.5f; };
 
-template <int BITS, bool ZP, bool UP, int R, int KW>
+template <int BITS, bool ZP, bool UP, int R, int KW, int BK = exact_stage(BITS)>
 __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
-    typedef ExactFmt<BITS, ZP, R, KW> F;
-    constexpr int KT = F::KT, BK = F::BK, TPS = F::TPS, HS = F::HS, SL = F::SL, XROW = F::XROW, RJ = R / 2;
+    typedef ExactFmt<BITS, ZP, R, KW, BK> F;
+    constexpr int KT = F::KT, TPS = F::TPS, HS = F::HS, SL = F::SL, XROW = F::XROW, RJ = R / 2;
     constexpr int SPT = KT / 16, KS = TPS * SPT, KH = KS / HS;
     constexpr int S = F::depth, SB = F::stage;
     constexpr int NX = (F::xwave / 1024 + 4 / KW - 1) / (4 / KW);          // activation loads per wave and stage
@@ -495,7 +497,7 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
         xoff[i] = ((uint32_t)ar * (uint32_t)c.lda + (uint32_t)col0) * 2u + (uint32_t)((q ^ (r & 7)) * 16);
     }
     const char* wbase[2];
-    const char *sbase, *zbase;                            // this lane's scale / zero-point address (int4 with zero-points: zbase)
+    const char *sbase, *zbase;                            // this lane's scale / zero-point address (zbase: two scales per stage)
     {
         const void* wp[2] = {UP ? c.ex->w1 : c.ex->w2, UP ? c.ex->w3 : c.ex->w2};
         const void* sp[2] = {UP ? c.ex->s1 : c.ex->s2, UP ? c.ex->s3 : c.ex->s2};
@@ -505,10 +507,10 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
             wbase[i] = static_cast<const char*>(uniform(wp[i])) + ((size_t)(c.wrow[i] >> 5) * tiles_k + col0 / KT) * 1024;
         const int b = (lane >> 4) & 1;
         const size_t off = (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
-                           (size_t)((col0 + (BITS == 4 ? 64 * half : 0)) / c.group) * c.Nout * 2;
-        const bool zs = ZP && BITS != 4 && half;
+                           (size_t)((col0 + (HS == 2 ? 64 * half : 0)) / c.group) * c.Nout * 2;
+        const bool zs = ZP && HS == 1 && half;
         sbase = static_cast<const char*>(b ? (zs ? zp[1] : sp[1]) : (zs ? zp[0] : sp[0])) + off;
-        zbase = ZP && BITS == 4 ? static_cast<const char*>(b ? zp[1] : zp[0]) + off : nullptr;
+        zbase = ZP && HS == 2 ? static_cast<const char*>(b ? zp[1] : zp[0]) + off : nullptr;
     }
     const uint32_t lane16 = lane * 16;
     int gcol = col0 % c.group;                          // of the next stage to be requested
@@ -526,10 +528,10 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
         }
         if (l == LPS - 1) {                               // on to the next stage's groups (two of them for int4 groups of 64)
             gcol += BK;
-            const size_t adv = gcol >= c.group ? (size_t)(BITS == 4 && c.group == 64 ? 2 : 1) * c.Nout * 2 : 0;
+            const size_t adv = gcol >= c.group ? (size_t)(HS == 2 && c.group == 64 ? 2 : 1) * c.Nout * 2 : 0;
             if (gcol >= c.group) gcol = 0;
             sbase += adv;
-            if (ZP && BITS == 4) zbase += adv;
+            if (ZP && HS == 2) zbase += adv;
         }
     };
     f32x16_t acc[2], sum;
@@ -588,7 +590,7 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
 #pragma unroll
             for (int h = 0; h < HS; ++h) {
                 sv[h][i] = *reinterpret_cast<const _Float16*>(sl + (h * 2 + i) * 64);
-                zv[h][i] = ZP ? *reinterpret_cast<const _Float16*>(sl + (BITS == 4 ? 256 + (h * 2 + i) * 64 : 128 + i * 64)) : (_Float16)0.f;
+                zv[h][i] = ZP ? *reinterpret_cast<const _Float16*>(sl + (HS == 2 ? 256 + (h * 2 + i) * 64 : 128 + i * 64)) : (_Float16)0.f;
             }
         }
         av[0] = *reinterpret_cast<const f16x8_t*>(base + aoff[0]);
@@ -698,6 +700,18 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
             }
         }
     }
+}
+
+// The down projection of an expert whose I is an odd multiple of 64 has half a stage of 128 columns left over.
+template <bool ZP, bool UP, int R, int KW>
+__device__ __forceinline__ void gemm_exact_int4(const TileCtx& c, char* smem) {
+    if constexpr (!UP) {
+        if (c.K % kKQ) {
+            gemm_exact<4, ZP, false, R, 1, 64>(c, smem);
+            return;
+        }
+    }
+    gemm_exact<4, ZP, UP, R, KW>(c, smem);
 }
 
 // The routing outputs of a decode layer, by one workgroup beside the layer's up GEMM: selection, prediction,
@@ -875,11 +889,13 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         c.wlive[i] = wr < c.Nout;
         c.wrow[i] = c.wlive[i] ? wr : 0;
     }
-    // columns of this part: a whole number of 128-column pieces (none is possible: an expert smaller than I_max)
+    // columns of this part: a whole number of 128-column pieces (none is possible: an expert smaller than I_max), with
+    // the last part the 64 columns that an expert's own I may have beyond them
     const int pieces = c.K / kKQ;
     const int p0 = pieces * part / kp, p1 = pieces * (part + 1) / kp;
     c.col0 = p0 * kKQ;
     c.ncol = (p1 - p0) * kKQ;
+    if (!UP && part + 1 == kp) c.ncol += c.K % kKQ;
     c.lda = is_shared ? a.lda_s : a.lda_r;
     c.A = is_shared ? a.A_s : a.A_r;
     c.rows = c.orows = nullptr;
@@ -894,12 +910,12 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         c.A += (size_t)out_row0 * c.lda;
     }
     if constexpr (MODE == 2) {
-        if (bits == 4) gemm_exact<4, false, UP, 8, KW>(c, smem);
+        if (bits == 4) gemm_exact_int4<false, UP, 8, KW>(c, smem);
         else gemm_exact<8, false, UP, 8, KW>(c, smem);
     } else if constexpr (MODE == 1) {
-        if (has_z && bits == 4) gemm_exact<4, true, UP, 16, 1>(c, smem);
+        if (has_z && bits == 4) gemm_exact_int4<true, UP, 16, 1>(c, smem);
         else if (has_z) gemm_exact<2, true, UP, 16, 1>(c, smem);
-        else if (bits == 4) gemm_exact<4, false, UP, 16, 1>(c, smem);
+        else if (bits == 4) gemm_exact_int4<false, UP, 16, 1>(c, smem);
         else if (bits == 2) gemm_exact<2, false, UP, 16, 1>(c, smem);
         else gemm_exact<8, false, UP, 16, 1>(c, smem);
     } else {
