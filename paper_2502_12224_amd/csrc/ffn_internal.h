@@ -88,12 +88,14 @@ struct MfmaMode {
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs da, const MfmaScratch& ms,
                             void* y_out, const PartSel& sel, const MfmaMode& mode);
 
-// Column blocks per segment of the two GEMMs' tile tables, K parts of the down GEMM included.
+// Column blocks per segment of the two GEMMs' tile tables, K parts of the down GEMM included, and the most rows of
+// a tile (1 << rows_log2).
 struct TileBlocks {
-    int r_up, s_up, r_down, s_down;
+    int r_up, s_up, r_down, s_down, rows_log2;
 };
-TileBlocks mfma_tile_blocks(const fate_ffn_desc& d);
-constexpr int kTileRows = 128;      // most rows of a tile
+TileBlocks mfma_tile_blocks(const fate_ffn_desc& d, bool exact);
+constexpr int kTileRowsLog2 = 7;          // prefill: 128 rows
+constexpr int kExactTileRowsLog2 = 4;     // decode-sized form: 16 rows (an expert has more if tokens name it repeatedly)
 
 // The decode kernels' job done by the GEMM's decode-sized form (exact weights, fp32 per-pair outputs):
 // up to 16 tokens, sizes that are multiples of 128, and at least half a device of its 128-neuron

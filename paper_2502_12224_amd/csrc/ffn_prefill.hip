@@ -43,7 +43,7 @@ typedef _Float16 f16x2v_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kBM = kTileRows;      // most rows of a workgroup tile
+constexpr int kBM = 1 << kTileRowsLog2;   // most rows of a workgroup tile
 constexpr int kBNUp = 128;          // weight rows per workgroup tile of the up GEMM (of each matrix)
 constexpr int kBNDown = 256;        // weight rows per workgroup tile of the down GEMM
 constexpr int kCombineRows = 64;    // rows whose addresses and weights a combination block keeps in LDS
@@ -70,7 +70,7 @@ struct GemmArgs {
     int32_t* status;
 };
 
-// Rows of one tile: a segment's rows are cut into as few tiles as hold them, of equal size up to
+// Rows of one prefill tile: a segment's rows are cut into as few tiles as hold them, of equal size up to
 // a whole number of 32-row products.
 __device__ __forceinline__ int tile_rows(int T) {
     const int nt = (T + kBM - 1) / kBM;
@@ -413,8 +413,8 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
 }
 
 // ---- decode-sized form ---------------------------------------------------------------------------
-// At most 16 rows per expert: the codes stream once and everything else is small, so a tile is bounded
-// by the memory path and by the vector instructions of the widening.  The codes enter the matrix
+// At most 16 rows per tile, and with distinct ids per expert: the codes stream once and everything else is small,
+// so a tile is bounded by the memory path and by the vector instructions of the widening.  The codes enter the matrix
 // cores as exact fp16 integers and a group's fp16 scale multiplies the group's fp32 sum: the weights
 // enter exactly, and a pair of codes takes two vector instructions instead of three.  With
 // zero-points the group's sum of activations comes from a third product with ones.
@@ -738,7 +738,7 @@ __device__ __forceinline__ void layer_outputs(const LayerOut& o, char* smem) {
     if (tid == 0) *o.calls += 1;
 }
 
-// MODE 0: prefill.  MODE 1: decode-sized (at most 16 rows per expert), fp32 outputs of the down GEMM.
+// MODE 0: prefill.  MODE 1: decode-sized (tiles of at most 16 rows), fp32 outputs of the down GEMM.
 // MODE 2: the same inside a decode layer (at most 8 tokens, 64 pairs): no tile table; a workgroup finds its
 // expert and rows by itself, the up GEMM's from the logits and the down GEMM's from the selection; rows of h
 // and of the outputs are pairs.  The up GEMM's first workgroup writes the layer's routing outputs.
@@ -837,10 +837,11 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     local -= mb * (nb * kp);
     const int part = local / nb, nblk = local - part * nb;
     const fate_qexpert* ex = (is_shared ? a.shared : a.experts) + e;
-    const int row0 = mb * tile_rows(T);
+    const int trows = EXACT ? 1 << kExactTileRowsLog2 : tile_rows(T);
+    const int row0 = mb * trows;
     TileCtx c;
     c.ex = ex;
-    c.nrows = min(tile_rows(T), T - row0);
+    c.nrows = min(trows, T - row0);
     constexpr int kBN = UP ? kBNUp / KW : kBNDown;
     c.Nout = UP ? uniform(ex->I) : a.H;
     c.K = UP ? a.H : uniform(ex->I);
@@ -1026,12 +1027,12 @@ void mfma_k_parts(const fate_ffn_desc& d, int* kp_r, int* kp_s) {
     *kp_s = d.n_shared ? parts(d.I_shared_max) : 1;
 }
 
-TileBlocks mfma_tile_blocks(const fate_ffn_desc& d) {
+TileBlocks mfma_tile_blocks(const fate_ffn_desc& d, bool exact) {
     int kp_r = 1, kp_s = 1;
     mfma_k_parts(d, &kp_r, &kp_s);
     const int nb_down = (d.H + kBNDown - 1) / kBNDown;
     return TileBlocks{(d.I_max + kBNUp - 1) / kBNUp, d.n_shared ? (d.I_shared_max + kBNUp - 1) / kBNUp : 0, nb_down * kp_r,
-                      nb_down * kp_s};
+                      nb_down * kp_s, exact ? kExactTileRowsLog2 : kTileRowsLog2};
 }
 
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs da, const MfmaScratch& ms,
@@ -1046,12 +1047,14 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
                                      (long long)d.n_shared * d.N * da.ldh_s});
     if (amax >= (1LL << 31))
         FATE_FAIL(FATE_ESHAPE, "the MFMA path needs activation matrices of fewer than 2^31 elements (%lld)", amax);
-    const TileBlocks nb = mfma_tile_blocks(d);
+    const TileBlocks nb = mfma_tile_blocks(d, exact);
     int kp_r = 1, kp_s = 1;
     mfma_k_parts(d, &kp_r, &kp_s);
     const int nb_down = nb.r_down / kp_r;
     // upper bounds of the routed row blocks, and the shared experts' row blocks
-    const long long mb_r = (mode.exact ? 0 : P / kBM) + (d.E < P ? d.E : P), mb_s = (d.N + kBM - 1) / kBM;
+    // (a decode layer has no tile table: its experts have at most 8 rows)
+    const long long mb_r = (mode.layer ? 0 : P >> nb.rows_log2) + (d.E < P ? d.E : P);
+    const long long mb_s = (d.N + (1 << nb.rows_log2) - 1) >> nb.rows_log2;
     const bool do_up = phase != 2, do_down = phase != 1;
     static bool attr_done = false;
     if (!attr_done) {

@@ -116,3 +116,21 @@ def test_decode_layer_of_experts_smaller_than_i_max(bits, E, k, I, sizes, N):
     torch.cuda.synchronize()
     assert buf.status() == 0
     assert ffn_rel_err(f32(buf.y), _oracle_ffn(L, cfg, x, buf.ids, buf.w)).max() <= 2e-3
+
+
+@pytest.mark.parametrize("bits,group,zp,N,k", [(4, 128, False, 16, 4), (4, 64, True, 13, 4), (8, 64, False, 16, 8), (4, 128, False, 9, 3)])
+def test_tokens_that_name_an_expert_more_than_once(bits, group, zp, N, k):
+    """Ids need not be distinct within a token (padding rows name one expert k times): an expert then has up to N * k
+    rows, in calls of up to 16 tokens more than one tile of the decode-sized form."""
+    cfg = _edge(512, 16, k, 2048, bits, group)
+    print(f"case repeated ids bits={bits} group={group} zp={zp} N={N} k={k}", flush=True)
+    ids = torch.randint(0, cfg.E, (N, k), dtype=torch.int32, generator=torch.Generator().manual_seed(N))
+    ids[: N - N // 4] = 5                   # (the rest of the tokens adds the rows that end inside a tile)
+    ids[-1, :] = 9
+    ids = ids.to(DEV)
+    w = (torch.rand(N, k, generator=torch.Generator().manual_seed(3)) + 0.1).to(DEV)
+    x = gen_hidden(cfg, N, device=DEV)
+    L = _layer_of_unequal_experts(cfg, (2048, 1024 + 128), zp)
+    y, ws = L.ffn(x, *gpu_permute(ids, cfg.E), w, ws_fill=0xff)
+    assert int(ws[:4].view(torch.int32)[0]) == 0
+    assert ffn_rel_err(f32(y), _oracle_ffn(L, cfg, x, ids, w)).max() <= 2e-3
