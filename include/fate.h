@@ -195,6 +195,8 @@ typedef struct {
  * Activated experts whose w1 is NULL are skipped and flagged in the int32 at
  * workspace offset 0 (bit 0); an entry whose width / group the kernels cannot
  * read is skipped too (bit 2).
+ * workspace: fate_moe_ffn_q_workspace returns what calls with this descriptor
+ * and any number of tokens up to N need at most.
  * ---------------------------------------------------------------------- */
 typedef struct {
     int32_t N, H, E, k;

@@ -305,3 +305,32 @@ def test_cache_policy_under_address_and_ub_sanitizers(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
     assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
     assert "cache sanitizer driver: ok" in r.stdout
+
+
+def _ffn_need(d, n):
+    """Bytes that a call of n tokens asks for (it is refused for want of a workspace before any GPU work)."""
+    d.N = n
+    z, p16 = C.c_void_p(0), C.c_void_p(0x1000)
+    rc = B.lib().fate_moe_ffn_q(z, C.byref(d), p16, p16, p16, p16, p16, p16, p16, p16, p16, z, p16, z, C.c_size_t(0))
+    assert rc == 4
+    return int(re.search(rb"workspace of (\d+) bytes", B.lib().fate_last_error()).group(1))
+
+
+@pytest.mark.parametrize("H,E,k,I,n_shared,I_shared,mode", [
+    (4096, 8, 2, 14336, 0, 0, 0),           # few large experts: parts of the reduction dimension up to 2047 tokens
+    (2048, 60, 4, 1408, 1, 5632, 0),        # parts of the shared expert
+    (2048, 64, 6, 1408, 2, 1408, 2),
+    (256, 8, 2, 512, 0, 0, 0),              # decode kernels up to 16 tokens
+    (1024, 16, 4, 8192, 2, 2048, 1),
+])
+def test_ffn_workspace_for_n_tokens_serves_every_smaller_call(H, E, k, I, n_shared, I_shared, mode):
+    """A server sizes the workspace once, for its longest prompt: no shorter call may need more."""
+    d = B.make_ffn_desc(1, H, E, k, I, 4, 128, n_shared, I_shared, 4, 128, True, mode)
+    most, asked = 0, {}
+    for n in range(1, 2601):
+        asked[n] = _ffn_need(d, n)
+        most = max(most, asked[n])
+        d.N = n
+        assert B.fate_moe_ffn_q_workspace(d) == most, n
+    if (H, mode) == (4096, 0):
+        assert asked[1535] > asked[2048]    # (the need itself falls there)
