@@ -263,8 +263,8 @@ fate_status fate_moe_ffn_q_part(void* stream, const fate_ffn_desc* d, const void
  *   d->mode must be 0 or 1.
  *   workspace: fate_moe_layer_decode_workspace bytes, 256-byte aligned,
  *        zero-filled once by the caller before the first use (each call
- *        leaves its counters at zero).  Calls that share a workspace must be
- *        ordered on one stream.  The int32 at byte *status_offset of the
+ *        leaves its counters at zero).  Calls that share a workspace, of one
+ *        shape or of several, must be ordered on one stream.  The int32 at byte *status_offset of the
  *        workspace is the status word: bit 0 = an activated expert had NULL
  *        weights, bit 1 = a wait inside the kernel ran out (results invalid).
  * ---------------------------------------------------------------------- */
@@ -300,7 +300,7 @@ fate_status fate_moe_layer_decode(void* stream, const fate_ffn_desc* d, const vo
  * one GPU (different streams, or a graph replayed while another call runs)
  * race and give wrong results; order them on one stream.
  * ---------------------------------------------------------------------- */
-#define FATE_NOALLOC_SCRATCH_BYTES (32u << 20)
+#define FATE_NOALLOC_SCRATCH_BYTES ((32u << 20) + (480u << 10))
 fate_status fate_moe_layer_decode_noalloc(void* stream, const fate_ffn_desc* d, const void* x_bf16,
                                           const void* Wg_bf16, const float* bias,
                                           const void* Wg_next_bf16, const float* bias_next, int m, int renorm,

@@ -38,25 +38,29 @@ struct LayerArgs {
 
 // byte offsets inside the workspace of fate_moe_layer_decode
 struct LayerWorkspace {
-    size_t sync, zq, status, part_r, part_s, hq, yq, bytes;
+    size_t sync, status, zq, hq, yq, part_r, part_s, bytes;
 };
 
+// Words that carry an epoch tag lie in front of everything else, in room of a fixed size for any shape: calls of
+// several shapes share a workspace (always so in the form that allocates nothing), and where one shape keeps
+// untagged data - two fp16 values and a current epoch can be the same bits - no other may poll for a tag.
+constexpr size_t kTagLogits = (size_t)2 * kLayerMaxN * kMaxE * 8;     // every logit of the largest call
+constexpr size_t kTagH = 192 * 1024;         // what b1_plan lets through: 32 pieces of 768 columns of each kind, a word per pair
+constexpr size_t kTagY = 256 * 1024;         // and twice the device's 512 resident blocks, 32 rows each
+
 inline LayerWorkspace layer_workspace(const fate_ffn_desc& d) {
-    const int N = d.N, H = d.H, E = d.E;
+    const int N = d.N, H = d.H;
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     LayerWorkspace w;
     size_t off = 0;
     w.sync = off; off += 256;
-    w.zq = off; off += up((size_t)2 * N * E * sizeof(unsigned long long));
     w.status = off; off += 256;
+    w.zq = off; off += kTagLogits;
+    w.hq = off; off += kTagH;
+    w.yq = off; off += kTagY;
     w.part_r = off; off += up((size_t)N * d.k * (d.I_max / kLayerNeurons) * H * sizeof(float));
     w.part_s = off;
     off += up((size_t)d.n_shared * (d.n_shared ? d.I_shared_max / kLayerNeurons : 0) * N * H * sizeof(float));
-    // one-token kernel: h words and partial outputs of up to kLayerMaxParts down blocks per row block
-    w.hq = off;
-    off += N == 1 ? up(((size_t)d.n_shared * (d.n_shared ? d.I_shared_max : 0) + (size_t)d.k * d.I_max) / 2 * 8) : 0;
-    w.yq = off;
-    off += N == 1 ? up((size_t)kLayerMaxParts * H * 8) : 0;
     w.bytes = off;
     return w;
 }

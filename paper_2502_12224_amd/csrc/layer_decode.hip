@@ -59,7 +59,7 @@ __global__ __launch_bounds__(64 * kReduceWaves) void layer_reduce_kernel(LayerAr
 
 // The GEMM form: logits (with the FFN's preparation), up with the selection, down and combination; what
 // stays between them takes the place of the partial rows in the workspace.  Returns false if it does not fit.
-static bool layer_gemm_scratch(const fate_ffn_desc& d, char* base, size_t bytes, DecodeArgs* da, MfmaScratch* ms) {
+static bool layer_gemm_scratch(const fate_ffn_desc& d, char* base, size_t bytes, DecodeArgs* da, MfmaScratch* ms, float** z) {
     size_t off = 0;
     auto take = [&](size_t n) {
         char* p = base + off;
@@ -77,12 +77,12 @@ static bool layer_gemm_scratch(const fate_ffn_desc& d, char* base, size_t bytes,
     ms->sgate = reinterpret_cast<float*>(take((size_t)d.N * 4));
     ms->yp_r = take((size_t)kp_r * P * d.H * 4);
     ms->yp_s = take((size_t)kp_s * SN * d.H * 4);
+    *z = reinterpret_cast<float*>(take((size_t)2 * d.N * d.E * 4));
     return off <= bytes;
 }
 
 static fate_status launch_layer_gemm(hipStream_t st, const fate_ffn_desc& d, const LayerArgs& a, DecodeArgs da,
-                                     const MfmaScratch& ms) {
-    float* z = reinterpret_cast<float*>(a.zq);
+                                     const MfmaScratch& ms, float* z) {
     fate_status rc = launch_layer_logits(st, a.r, RoutePrep{z, ms.xh, ms.sgate, a.shared_gate});
     if (rc != FATE_OK) return rc;
     da.x = a.r.x; da.N = d.N; da.H = d.H; da.E = d.E; da.k = d.k;
@@ -130,7 +130,9 @@ fate_status launch_layer_decode(hipStream_t st, const fate_ffn_desc& d, LayerArg
         DecodeArgs da{};
         MfmaScratch ms{};
         const LayerWorkspace w = layer_workspace(d);
-        if (layer_gemm_scratch(d, reinterpret_cast<char*>(a.part_r), w.hq - w.part_r, &da, &ms)) return launch_layer_gemm(st, d, a, da, ms);
+        float* z = nullptr;
+        if (layer_gemm_scratch(d, reinterpret_cast<char*>(a.part_r), w.bytes - w.part_r, &da, &ms, &z))
+            return launch_layer_gemm(st, d, a, da, ms, z);
     }
     // work items: 32-neuron blocks of the shared experts, then of the routed slots.  With more
     // items than workgroups of the looping kernel fit on the device (asked of the occupancy

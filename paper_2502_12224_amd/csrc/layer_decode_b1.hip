@@ -687,6 +687,8 @@ bool b1_plan(const fate_ffn_desc& d, const LayerArgs& a, B1Args* b, int* nblocks
         if ((nr = b1_add_items(b->items_r, nr, j, d.I_max / d.group, maxg_r)) < 0) return false;
     b->nparts = (std::max(ns, nr) + kLayerWaves - 1) / kLayerWaves;
     if (b->nparts < 1 || b->nparts > kLayerMaxParts) return false;
+    // room for the tagged words (what passes the other tests fits on this chip)
+    if ((size_t)(b->n_up_s + b->n_up_r) * kLayerNeurons / 2 * 8 > kTagH || (size_t)(b->nparts - 1) * d.H * 8 > kTagY) return false;
     *nblocks = a.nb_route + b->n_up_s + b->n_up_r + b->nparts * b->nrb;
     // The routing blocks and the shared experts' up blocks must be on the device from the start
     // (their requests do not wait for anything); the other blocks have nothing to do before the

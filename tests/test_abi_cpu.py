@@ -334,3 +334,10 @@ def test_ffn_workspace_for_n_tokens_serves_every_smaller_call(H, E, k, I, n_shar
         assert B.fate_moe_ffn_q_workspace(d) == most, n
     if (H, mode) == (4096, 0):
         assert asked[1535] > asked[2048]    # (the need itself falls there)
+
+
+def test_decode_layer_status_word_lies_at_one_place_for_every_shape():
+    """Calls of several shapes may share a workspace: where one keeps its status no other may keep data."""
+    shapes = [(1, 2048, 60, 4, 1408), (8, 2048, 64, 6, 1408), (2, 4096, 8, 2, 14336), (5, 256, 256, 8, 512)]
+    offsets = {B.fate_moe_layer_decode_workspace(B.make_ffn_desc(N, H, E, k, I, 4, 128))[1] for N, H, E, k, I in shapes}
+    assert len(offsets) == 1

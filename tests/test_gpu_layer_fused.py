@@ -272,3 +272,28 @@ def test_one_token_layer_with_prefetch_hints(name):
     sg = None if lw.shared_gate is None else f32(lw.shared_gate)
     y_orc = O.moe_ffn(f32(x), ref.ids.cpu().numpy(), ref.w.cpu().numpy().astype(np.float64), experts, shared, sg)
     assert ffn_rel_err(f32(got.y), y_orc).max() <= 2e-3
+
+
+def test_layers_of_two_shapes_share_a_workspace():
+    """One workspace for calls of two shapes: a call of eight tokens leaves its activations as plain fp16, all of them pairs
+    (1, 0) here, and the one-token call behind it runs at the epoch with those bits (0x3c00).  Its words with an epoch tag
+    lie where no other shape keeps data, so it must not take them for its own: same bits as on a workspace of its own."""
+    tiny = SHAPES["tiny"]
+    a = dataclasses.replace(tiny, layers=1, H=2048, E=8, k=1, I=2048, bits=4, group=128, gate_var=1.0 / 2048)
+    b = dataclasses.replace(tiny, layers=1, H=1024, E=8, k=1, I=384, bits=8, group=128, gate_var=1.0 / 1024)
+    la, lb = LayerWeights(a, 0, DEV), LayerWeights(b, 0, DEV)
+    xa = torch.zeros(8, a.H, dtype=torch.bfloat16, device=DEV)
+    xa[:, 0::2] = 1.0
+    xb = gen_hidden(b, 1, device=DEV)
+    ba, alone, after = LayerBuffers(a, 8, DEV), LayerBuffers(b, 1, DEV), LayerBuffers(b, 1, DEV)
+    layer_forward(b, lb, None, xb, alone, one_launch=True)
+    shared = torch.zeros(max(ba.layer_ws.numel(), after.layer_ws.numel()), dtype=torch.uint8, device=DEV)
+    shared[:4].view(torch.int32).fill_(0x3c00 - 2)
+    ba.layer_ws = after.layer_ws = shared
+    layer_forward(a, la, None, xa, ba, one_launch=True)
+    layer_forward(b, lb, None, xb, after, one_launch=True)
+    torch.cuda.synchronize()
+    assert int(shared[:4].view(torch.int32)[0]) == 0x3c00
+    assert after.status() == 0 and ba.status() == 0
+    for f in ROUTE_FIELDS + ("y",):
+        assert torch.equal(getattr(after, f), getattr(alone, f)), f
