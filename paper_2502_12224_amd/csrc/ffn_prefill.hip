@@ -535,8 +535,8 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
         }
     };
     f32x16_t acc[2], sum;
-    // The up projection adds its groups up in quarters, as the one-call decode layer does (a wave per
-    // quarter there): h is rounded to fp16 and must not depend on which of the two computed it.
+    // The up projection adds its groups up in quarters, whether one wave takes them all or two take two each: h is
+    // rounded to fp16 and must not depend on that.  (The decode kernels have a wave per quarter.)
     float out[2][RJ], tot[2][RJ];
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[0][j] = acc[1][j] = sum[j] = 0.f;
@@ -545,7 +545,8 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
 #pragma unroll
         for (int j = 0; j < RJ; ++j) out[i][j] = tot[i][j] = 0.f;
     const int ngroups = c.K / c.group;
-    int gidx = 0, quarter = ngroups / 4;                  // groups done, end of the current quarter
+    // groups done, end of the current quarter (two waves: of the first one of this wave's two)
+    int gidx = KW == 1 ? 0 : kw * (ngroups / 2), quarter = ngroups * (2 * kw + 1) / 4;
     auto close_quarter = [&]() {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -643,6 +644,8 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
                             while (qn < 4 && ngroups * qn / 4 <= gidx) ++qn;
                             quarter = ngroups * qn / 4;
                         }
+                    } else if constexpr (UP) {
+                        if (++gidx == quarter) close_quarter();
                     }
                 }
             }
@@ -661,28 +664,29 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
             for (int j = 0; j < RJ; ++j) out[i][j] = tot[i][j];
     }
     if constexpr (KW > 1) {
-        // the ranges' sums meet in LDS: the first range's wave of every block adds the others in order
-        static_assert(UP, "the split of the reduction dimension belongs to the up projection");
-        float* red = reinterpret_cast<float*>(smem);      // [range - 1][block of the tile][matrix][row][32]
+        // the quarters' sums meet in LDS: the first range's wave of every block adds the others in order
+        static_assert(UP && KW == 2, "the split of the reduction dimension belongs to the up projection");
+        float* red = reinterpret_cast<float*>(smem);      // [quarter of the second range][block of the tile][matrix][row][32]
         lds_only_barrier();                               // the rings are done with
         const int blk = wave / KW;
-        auto at = [&](int range, int i, int j) {
-            return red + (((range * (4 / KW) + blk) * 2 + i) * RJ * 2 + (j >> 2) * 8 + 4 * half + (j & 3)) * 32 + n;
+        auto at = [&](int q, int i, int j) {
+            return red + (((q * (4 / KW) + blk) * 2 + i) * RJ * 2 + (j >> 2) * 8 + 4 * half + (j & 3)) * 32 + n;
         };
         if (kw > 0) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < RJ; ++j) *at(kw - 1, i, j) = out[i][j];
+                for (int j = 0; j < RJ; ++j) {
+                    *at(0, i, j) = tot[i][j];
+                    *at(1, i, j) = out[i][j];
+                }
         }
         lds_only_barrier();
         if (kw > 0) return;
 #pragma unroll
-        for (int q = 0; q < KW - 1; ++q)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < RJ; ++j) out[i][j] += *at(q, i, j);
+            for (int j = 0; j < RJ; ++j) out[i][j] = ((tot[i][j] + out[i][j]) + *at(0, i, j)) + *at(1, i, j);
     }
 #pragma unroll
     for (int j = 0; j < RJ; ++j) {
@@ -1068,8 +1072,9 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
 #undef FATE_GEMM_ATTR
         attr_done = true;
     }
-    // Decode layer: the columns of the up projection are split over pairs of waves if they can be (whole stages of 128)
-    const int kw = mode.layer && d.H % 256 == 0 ? 2 : 1;
+    // Decode layer: the columns of the up projection are split over pairs of waves if they can be (whole stages of 128,
+    // whole groups)
+    const int kw = mode.layer && d.H % 256 == 0 && (d.H / d.group) % 2 == 0 && (!d.n_shared || (d.H / d.shared_group) % 2 == 0) ? 2 : 1;
     if (do_up && !mode.layer) {
         prefill_prep_kernel<<<sel.first ? d.N : 1, 256, 0, st>>>(da.x, d.N, d.H, d.E, d.n_shared, da.offsets,
                                                                  da.order, da.shared_gate, ms.xh, ms.sgate, ms.tab_up, ms.tab_down,

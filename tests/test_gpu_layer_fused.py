@@ -297,3 +297,27 @@ def test_layers_of_two_shapes_share_a_workspace():
     assert after.status() == 0 and ba.status() == 0
     for f in ROUTE_FIELDS + ("y",):
         assert torch.equal(getattr(after, f), getattr(alone, f)), f
+
+
+@pytest.mark.parametrize("H,E,k,I,bits,group,n_shared,I_shared,N", [
+    (2048, 16, 4, 1408, 4, 128, 2, 512, 5),        # two waves per column range, two quarters each
+    (768, 16, 2, 2048, 4, 128, 0, 0, 8),           # six groups: quarters of one and two
+    (512, 16, 4, 2048, 4, 256, 0, 0, 3),           # two groups: quarters without any
+    (1280, 16, 4, 1280, 4, 256, 0, 0, 6),          # five groups: one wave
+    (1024, 16, 4, 1152, 8, 64, 1, 384, 7),
+])
+def test_layer_by_gemms_gives_the_bits_of_the_separate_calls(H, E, k, I, bits, group, n_shared, I_shared, N):
+    """The two forms of the decode-sized GEMM differ in how many waves share the columns of the up projection, not in the
+    order of any sum (without a shared gate, whose dot product is taken by one wave in one form and by four in the other)."""
+    cfg = dataclasses.replace(SHAPES["tiny"], name="edge", layers=1, H=H, E=E, k=k, I=I, bits=bits, group=group,
+                              gate_var=1.0 / H, n_shared=n_shared, I_shared=I_shared, shared_bits=bits)
+    print(f"case {H} {E} {k} {I} int{bits} g{group} N={N}", flush=True)
+    x = gen_hidden(cfg, N, device=DEV)
+    lw = LayerWeights(cfg, 0, DEV)
+    one, sep = LayerBuffers(cfg, N, DEV), LayerBuffers(cfg, N, DEV)
+    layer_forward(cfg, lw, None, x, one, one_launch=True)
+    layer_forward(cfg, lw, None, x, sep, one_launch=False)
+    torch.cuda.synchronize()
+    assert one.status() == 0
+    for f in ROUTE_FIELDS + ("y",):
+        assert torch.equal(getattr(one, f), getattr(sep, f)), f
