@@ -89,12 +89,16 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
                             void* y_out, const PartSel& sel, const MfmaMode& mode);
 
 // Column blocks per segment of the two GEMMs' tile tables, K parts of the down GEMM included, and the most rows of
-// a tile (1 << rows_log2).
+// a tile of routed / shared experts (1 << rows_r, rows_s).
 struct TileBlocks {
-    int r_up, s_up, r_down, s_down, rows_log2;
+    int r_up, s_up, r_down, s_down, rows_r, rows_s;
 };
 TileBlocks mfma_tile_blocks(const fate_ffn_desc& d, bool exact);
 constexpr int kTileRowsLog2 = 7;          // prefill: 128 rows
+// 64 where the nominal width is not 4 bits: a workgroup takes its rows 64 at a time there, and two workgroups are
+// faster than two passes of one (8-bit, H = 256, I = 512, E = 8, 300 tokens: 32 us with
+// tiles of 128 rows, 24 with these; E = 64, k = 6, H = 2048, I = 1408 with two shared experts, 2048 tokens: 506 and 464).
+constexpr int kTileRowsLog2Wide = 6;
 constexpr int kExactTileRowsLog2 = 4;     // decode-sized form: 16 rows (an expert has more if tokens name it repeatedly)
 
 // The decode kernels' job done by the GEMM's decode-sized form (exact weights, fp32 per-pair outputs):

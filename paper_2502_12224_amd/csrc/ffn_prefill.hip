@@ -10,7 +10,7 @@
 // Rows are (token, expert) pairs in the sorted order of the permutation, so
 // an expert's rows are contiguous; shared experts are extra segments of N rows.
 //
-// GEMM tile: a workgroup of four waves owns up to 128 rows and, per wave, two
+// GEMM tile: a workgroup of four waves owns up to 128 rows (64 of other widths than 4 bits) and, per wave, two
 // 32-row blocks of weights (the same block of W1 and W3, or two neighbouring
 // blocks of W2): 8 accumulators of 32x32, so that a dequantised operand serves
 // four matrix products.  Two workgroups share a compute unit.
@@ -62,6 +62,7 @@ struct GemmArgs {
     void* out_r; int ldo_r;            // routed rows, by sorted position
     void* out_s; int ldo_s;            // shared rows, s*N + t
     int nb_r, nb_s;                    // column blocks per routed / shared segment
+    int rows_r, rows_s;                // most rows of a tile, log2
     int kp_r, kp_s;                    // parts of the reduction dimension (down GEMM), each with an output of its own
     size_t part_r, part_s;             // elements between those outputs
     int f32_r, f32_s;                  // down GEMM: output elements are fp32 (else fp16)
@@ -72,8 +73,8 @@ struct GemmArgs {
 
 // Rows of one prefill tile: a segment's rows are cut into as few tiles as hold them, of equal size up to
 // a whole number of 32-row products.
-__device__ __forceinline__ int tile_rows(int T) {
-    const int nt = (T + kBM - 1) / kBM;
+__device__ __forceinline__ int tile_rows(int T, int most_log2) {
+    const int nt = (T + (1 << most_log2) - 1) >> most_log2;
     return ((T + nt - 1) / nt + 31) & ~31;
 }
 
@@ -841,7 +842,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     local -= mb * (nb * kp);
     const int part = local / nb, nblk = local - part * nb;
     const fate_qexpert* ex = (is_shared ? a.shared : a.experts) + e;
-    const int trows = EXACT ? 1 << kExactTileRowsLog2 : tile_rows(T);
+    const int trows = EXACT ? 1 << kExactTileRowsLog2 : tile_rows(T, is_shared ? a.rows_s : a.rows_r);
     const int row0 = mb * trows;
     TileCtx c;
     c.ex = ex;
@@ -1035,8 +1036,9 @@ TileBlocks mfma_tile_blocks(const fate_ffn_desc& d, bool exact) {
     int kp_r = 1, kp_s = 1;
     mfma_k_parts(d, &kp_r, &kp_s);
     const int nb_down = (d.H + kBNDown - 1) / kBNDown;
+    auto rows = [&](int bits) { return exact ? kExactTileRowsLog2 : (bits == 4 ? kTileRowsLog2 : kTileRowsLog2Wide); };
     return TileBlocks{(d.I_max + kBNUp - 1) / kBNUp, d.n_shared ? (d.I_shared_max + kBNUp - 1) / kBNUp : 0, nb_down * kp_r,
-                      nb_down * kp_s, exact ? kExactTileRowsLog2 : kTileRowsLog2};
+                      nb_down * kp_s, rows(d.bits), rows(d.shared_bits)};
 }
 
 fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs da, const MfmaScratch& ms,
@@ -1057,8 +1059,8 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
     const int nb_down = nb.r_down / kp_r;
     // upper bounds of the routed row blocks, and the shared experts' row blocks
     // (a decode layer has no tile table: its experts have at most 8 rows)
-    const long long mb_r = (mode.layer ? 0 : P >> nb.rows_log2) + (d.E < P ? d.E : P);
-    const long long mb_s = (d.N + (1 << nb.rows_log2) - 1) >> nb.rows_log2;
+    const long long mb_r = (mode.layer ? 0 : P >> nb.rows_r) + (d.E < P ? d.E : P);
+    const long long mb_s = (d.N + (1 << nb.rows_s) - 1) >> nb.rows_s;
     const bool do_up = phase != 2, do_down = phase != 1;
     static bool attr_done = false;
     if (!attr_done) {
@@ -1084,6 +1086,7 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
     GemmArgs g{};
     g.experts = da.experts; g.shared = da.shared; g.E = d.E; g.n_shared = d.n_shared; g.N = d.N; g.k = d.k;
     g.perm = da.perm;
+    g.rows_r = nb.rows_r; g.rows_s = nb.rows_s;
     g.status = da.status;
     if (mode.layer) g.lo = *mode.layer;
     g.bits_r = da.bits_r; g.group_r = da.group_r; g.bits_s = da.bits_s; g.group_s = da.group_s;

@@ -23,8 +23,9 @@ __device__ __forceinline__ void wave_tile_tables(const int32_t* offsets, const i
             const bool mine = s < E ? ((sel.mask[e >> 6] >> (e & 63)) & 1ull) != 0 : sel.first != 0;
             row = s < E ? offsets[e] : 0;
             T = !mine ? 0 : (s < E ? offsets[e + 1] - row : N);
-            cu = ((T + (1 << nb.rows_log2) - 1) >> nb.rows_log2) * (s < E ? nb.r_up : nb.s_up);
-            cd = ((T + (1 << nb.rows_log2) - 1) >> nb.rows_log2) * (s < E ? nb.r_down : nb.s_down);
+            const int rl = s < E ? nb.rows_r : nb.rows_s, nt = (T + (1 << rl) - 1) >> rl;
+            cu = nt * (s < E ? nb.r_up : nb.s_up);
+            cd = nt * (s < E ? nb.r_down : nb.s_down);
         }
         int iu = cu, id = cd;
 #pragma unroll
