@@ -85,18 +85,17 @@ __device__ __forceinline__ void token_logits(const uint4* __restrict__ x, const 
 // A workgroup of 16 waves per TPW tokens.  A decode-sized call is a handful of dependent memory
 // round trips, so a token gets a whole compute unit: the gate matrix (a few hundred KB, from L2
 // after the first workgroup) is requested at once by 16 waves.  48 tokens, E = 64, H = 2048:
-// 9.5 us (one wave per token, rows one after the other: 109 us).
-template <int TPW>
-__global__ __launch_bounds__(64 * kTokWaves) void route_rows_kernel(const uint16_t* __restrict__ x,
-                                                                    const uint16_t* __restrict__ Wg,
-                                                                    const float* __restrict__ bias, int N, int H, int E,
-                                                                    int m, int renorm, int32_t* __restrict__ ids,
-                                                                    float* __restrict__ w, float* __restrict__ probs,
-                                                                    int32_t* __restrict__ pop) {
+// 9.5 us (one wave per token, rows one after the other: 109 us).  NW: waves, 16, or 4 where there are more tokens than the
+// device holds workgroups of 16.
+template <int TPW, int NW>
+__global__ __launch_bounds__(64 * NW) void route_rows_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ Wg,
+                                                           const float* __restrict__ bias, int N, int H, int E, int m,
+                                                           int renorm, int32_t* __restrict__ ids, float* __restrict__ w,
+                                                           float* __restrict__ probs, int32_t* __restrict__ pop) {
     __shared__ float z[TPW * kMaxE];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nvec = H >> 3, tok0 = blockIdx.x * TPW, ntok = min(TPW, N - tok0);
-    token_logits<TPW>(reinterpret_cast<const uint4*>(x) + (size_t)tok0 * nvec, reinterpret_cast<const uint4*>(Wg), bias,
+    token_logits<TPW, NW>(reinterpret_cast<const uint4*>(x) + (size_t)tok0 * nvec, reinterpret_cast<const uint4*>(Wg), bias,
                       ntok, nvec, E, z);
     __syncthreads();
     if (wave < ntok) {
@@ -493,10 +492,17 @@ static fate_status launch_route_rows(hipStream_t st, const void* x, const void* 
     if (N >= 64 && H % 1024 == 0)     // prefill-sized batches: gate GEMM on the matrix cores
         return launch_route_mfma(st, x, Wg, bias, N, H, E, m, renorm, ids, w, probs, pop, RouteSecond{}, 1);
     // four tokens per workgroup share the gate rows once one token each would be several rounds of workgroups
-    if (N >= 1024)
-        route_rows_kernel<4><<<(N + 3) / 4, 64 * kTokWaves, 0, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop);
-    else
-        route_rows_kernel<1><<<N, 64 * kTokWaves, 0, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop);
+#define FATE_ROWS(TPW, NW) \
+    route_rows_kernel<TPW, NW><<<(N + TPW - 1) / TPW, 64 * NW, 0, st>>>(xs, ws, bias, N, H, E, m, renorm, ids, w, probs, pop)
+    // 16 waves while the device holds all workgroups at once (two per compute unit); beyond that workgroups of four waves,
+    // of which none idles while the tokens' selections are taken (E = 60, H = 1920: 1024 tokens 11.9 us with 16 waves, 19.5
+    // with 4; 1023 tokens, a workgroup each, 28.5 and 18.3; 5000 tokens 52 and 41; 20000 tokens 208 and 137)
+    const int groups = N >= 1024 ? (N + 3) / 4 : N;
+    if (N >= 1024 && groups > 512) FATE_ROWS(4, 4);
+    else if (N >= 1024) FATE_ROWS(4, kTokWaves);
+    else if (groups > 512) FATE_ROWS(1, 4);
+    else FATE_ROWS(1, kTokWaves);
+#undef FATE_ROWS
     FATE_HIP(hipGetLastError());
     return FATE_OK;
 }

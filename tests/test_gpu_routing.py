@@ -1,6 +1,8 @@
 """GPU parity of routing, prediction and permutation against the oracle
 (through the C ABI).  Integer outputs must match bit for bit; rows whose
 oracle logits have a top-k gap below 1e-5 are counted apart."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -101,3 +103,15 @@ def test_route_fused_equals_the_three_calls(name, N):
                        inv, order, ws)
     torch.cuda.synchronize()
     assert torch.equal(ids, sid) and torch.equal(w, sw)
+
+
+@pytest.mark.parametrize("H,E,k,N", [(64, 8, 2, 512), (64, 8, 2, 513), (192, 60, 4, 1023), (1920, 16, 2, 2048), (64, 5, 5, 2049), (192, 200, 8, 2051)])
+def test_gates_of_odd_sizes_over_many_tokens_match_oracle(H, E, k, N):
+    """H no multiple of 1024: both sides of the lines between workgroups of 16 waves and of 4, a token and four tokens each."""
+    cfg = dataclasses.replace(SHAPES["tiny"], H=H, E=E, k=k, gate_var=1.0 / H)
+    x = gen_hidden(cfg, N, device=DEV)
+    Wg, b = gen_gate(cfg, 0, device=DEV)
+    ids, w, probs = gpu_route(x, Wg, b, k, False)
+    rid, rw, rp, rz = O.gate_route(f32(x), f32(Wg), bias_np(b), k, False)
+    assert check_routing(ids, w, rid, rw, rz, k, f"H={H} E={E} N={N}") <= max(1, N // 200)
+    assert np.abs(probs.cpu().numpy().astype(np.float64) - rp).max() <= 1e-6
