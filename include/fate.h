@@ -186,10 +186,16 @@ typedef struct {
  * every entry from the table, so a layer may mix copies of different widths
  * (the popularity-aware hybrid of section 4.5: the least popular experts of a
  * prefill arrive as 2-bit copies); a group is a whole number of tile columns
- * (128 / 64 / 32 for int2 / int4 / int8); the decode kernels take groups of
- * 64..256 columns (int4), 64 / 128 (int8), 128 / 256 (int2).
- * mode: 0 = choose (decode kernels if N <= 16, else MFMA), 1 = decode
- * dequant-GEMV kernels, 2 = MFMA grouped GEMM (H and the intermediate sizes
+ * (128 / 64 / 32 for int2 / int4 / int8); in mode 1 the descriptor's groups are
+ * 64, 128 or 256 columns (int4), 64 or 128 (int8), 128 or 256 (int2), and so
+ * are its entries'.  An entry may be of any I up to I_max that is a multiple of
+ * 64 and of the entry's group, in every mode.  A token's ids need not be
+ * distinct.
+ * mode: 0 = choose (1 if N <= 16, else 2); 1 = decode-sized, weights enter the
+ * products exactly: layers whose sizes are multiples of 128 and which make up
+ * 128 workgroups of 128 neurons or more go through the matrix-core GEMM in
+ * tiles of 16 rows (up to 16 tokens), all others through dequant-GEMV kernels;
+ * 2 = MFMA grouped GEMM, weights rounded to fp16 (H, I_max and I_shared_max
  * multiples of 128; N*H, N*k*I_max and n_shared*N*I_shared_max below 2^31;
  * FATE_ESHAPE otherwise).
  * Activated experts whose w1 is NULL are skipped and flagged in the int32 at
@@ -239,17 +245,25 @@ fate_status fate_moe_ffn_q_part(void* stream, const fate_ffn_desc* d, const void
                                 const int32_t* part_experts, int n_part, int flags);
 
 /* ------------------------------------------------------------------------
- * Whole decode-side MoE layer in one call (1 <= N <= 8, N*k <= 64; two
- * launches: the layer kernel and a small reduction): fate_gate_route +
- * fate_cross_layer_predict + fate_permute + fate_moe_ffn_q (section 4.1
- * steps 1-2, 5-6 of one layer), with the same results as those calls:
- * routing outputs bit for bit, y up to the order of its fp32 additions.  The
- * weight stream of the shared experts starts while the gate is still being
- * evaluated; a work group owns 32 intermediate neurons of one expert, does
- * their up projection and multiplies the result into its columns of the down
- * projection, and leaves a partial output row that the reduction adds up.
- * A call with more such items than work groups fit on the device at once
- * launches as many as fit, and each takes every n-th item.
+ * Whole decode-side MoE layer in one call (1 <= N <= 8, N*k <= 64):
+ * fate_gate_route + fate_cross_layer_predict + fate_permute + fate_moe_ffn_q
+ * (section 4.1 steps 1-2, 5-6 of one layer), with the same results as those
+ * calls: routing outputs bit for bit, y up to the order of its fp32 additions
+ * and what that moves in the fp16 roundings of h.  One of three forms:
+ *   one token, one launch: the weight stream of the shared experts starts
+ *     while the gate is still being evaluated, h is handed over between work
+ *     groups through the workspace (4- and 8-bit experts of group 128, layers
+ *     that fit on the device about once);
+ *   four launches - logits, up GEMM with the selection, down GEMM,
+ *     combination - for layers of 128 workgroups of 128 neurons or more with
+ *     sizes that are multiples of 128 (y without a shared gate: the bits of the
+ *     separate calls);
+ *   two launches for the rest: a work group owns 32 intermediate neurons of
+ *     one expert, does their up projection and multiplies the result into its
+ *     columns of the down projection, and leaves a partial output row that the
+ *     second launch adds up.  A call with more such items than work groups fit
+ *     on the device at once launches as many as fit, and each takes every
+ *     n-th item.
  *   hint_ids: NULL, or a device array of k expert ids predicted for THIS layer
  *        by the previous layer's call (the first k entries of its pred_ids; for
  *        N == 1 only, ignored otherwise).  A prefetch hint in the sense of
@@ -287,7 +301,7 @@ fate_status fate_moe_layer_decode(void* stream, const fate_ffn_desc* d, const vo
  * bring a workspace: code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation.  Same arguments, kernels and results as
  * fate_moe_layer_decode, except that the kernels' workspace (call epoch and
- * exit counter, tagged logits, partial output rows) is a device array built
+ * exit counter, tagged words, h, partial outputs) is a device array built
  * into the library, FATE_NOALLOC_SCRATCH_BYTES long, one copy per GPU, held
  * until the process ends; the call allocates nothing and calls no allocating
  * routine.  A shape whose workspace (fate_moe_layer_decode_workspace) exceeds

@@ -21,12 +21,13 @@
 // dequantises its own codes from LDS into the A operand of
 // v_mfma_f32_32x32x16_f16 (exact code, one rounding in code*scale) and
 // multiplies them with the workgroup's activation rows; accumulation is fp32.
-// Full tiles (128 rows) run at what the chip's power limit leaves of the matrix pipe: products
-// issue every 22 ns per SIMD (1.5 PFLOP/s at 1.5 to 1.6 GHz), and a stage of two paired waves is 87 %
-// products.  Measured (before: 64-row tiles, codes in registers): up 1125 -> 835 us and down
-// 645 -> 479 us at 2048 rows of the Mixtral shape (E = 8, H = 4096, I = 14336), 271 -> 200 and
-// 148 -> 119 us at 2048 tokens of the Qwen shape.  Tiles of at most 32 rows are bounded by the
-// wave's own vector instructions (about 1250 cycles per stage).
+// What bounds it, by counters.  Full tiles (2048 tokens of the Mixtral shape, E = 8, H = 4096, I = 14336): the chip
+// holds 1.5 GHz under the up GEMM and the matrix pipe is busy 73 % of the cycles (down 60 %), with 5.6 (4.9) vector
+// instructions per matrix instruction.  Tiles of few rows (48 tokens of the DeepSeek shape, 5 rows each): 2.0 GHz, the
+// matrix pipe busy 24 %, 16.5 vector instructions per matrix instruction, waves waiting for an issue slot 30 % and for
+// memory or a barrier 24 % of their time: a dequantised operand serves one product there instead of four.
+// Measured (before: 64-row tiles, codes in registers): up 1125 -> 867 us and down 645 -> 515 us at 2048 tokens
+// of the Mixtral shape, 271 -> 200 and 148 -> 124 us at 2048 tokens of the Qwen shape.
 #include <hip/hip_fp16.h>
 #include <algorithm>
 #include <type_traits>
@@ -317,9 +318,9 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < 8; ++e) dequant(0, e);
-        // Matrix products of a step with the next step's dequantisation and LDS reads between them: a
-        // wave issues a vector instruction every 5 to 6 cycles and a product occupies the matrix pipe
-        // for 32, so the dequantisation of a step runs beside the products of four row blocks.  (The
+        // Matrix products of a step with the next step's dequantisation and LDS reads between them: a product
+        // occupies the matrix pipe for 32 cycles, so the dequantisation of a step runs beside the products
+        // of four row blocks.  (The
         // fences keep the compiler from collecting the vector instructions in front of the products.)
 #pragma unroll
         for (int d = 0; d < KS; ++d) {
@@ -419,13 +420,14 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
 // cores as exact fp16 integers and a group's fp16 scale multiplies the group's fp32 sum: the weights
 // enter exactly, and a pair of codes takes two vector instructions instead of three.  With
 // zero-points the group's sum of activations comes from a third product with ones.
-// 13 tokens of the Qwen shape: up 45.3 -> 27.8 us (106 MB of codes and scales: 3.8 TB/s), down 45.7 -> 15.9 us
-// against the dequant-GEMV kernels, whose loads sit under branches.
+// 13 tokens of the Qwen shape: up 45.3 -> 28.7 us (106 MB of codes and scales: 3.7 TB/s), down 45.7 -> 17.2 us
+// against the dequant-GEMV kernels, whose loads sit under branches; 16 vector instructions per matrix instruction, waves
+// waiting for memory or a barrier 30 % and for an issue slot 21 % of their time (up).
 // D = activations x codes: lane n holds weight row n, rows 4*half + 0..3 and 8 + 4*half + 0..3.
 // R: rows of the tile (8 or 16).  KW: waves over which the reduction dimension is split (up projection of a
-// decode layer: tiles of 64 neurons instead of 128; a wave issues an instruction every 5 to 6 cycles and no
-// more, so two waves per SIMD get through the widening twice as fast as one.  One token of the Mixtral shape:
-// 34 -> 26 us; four ranges gain nothing more).  A stage's scales are one load of 256 bytes per wave: for int4 both
+// decode layer: tiles of 64 neurons instead of 128; a wave alone on its SIMD issues a widening instruction every 6 to 8
+// cycles, two of them one every 3 to 4.  One token of the Mixtral shape: 34 -> 30 us; four ranges gain nothing
+// more).  A stage's scales are one load of 256 bytes per wave: for int4 both
 // blocks' scales of both 64-column halves (groups of 64, or a multiple of 128), with zero-points a second one
 // like it; where a stage lies inside a group (the other widths, int4 stages of 64 columns), scales in the first half and
 // zero-points in the other.  BK: columns of a stage.  int4 takes stages of 128 (the loads of a stage are the cost of its

@@ -1,4 +1,4 @@
-// Whole decode-side MoE layer in one launch: arguments and workspace layout
+// Whole decode-side MoE layer in one call: arguments and workspace layout
 // shared between the entry point and the kernel's translation unit.
 #pragma once
 #include "common.h"

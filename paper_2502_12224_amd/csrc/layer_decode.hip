@@ -124,7 +124,7 @@ fate_status launch_layer_decode(hipStream_t st, const fate_ffn_desc& d, LayerArg
     // Layers of some size go through the GEMM pipeline in four launches: the kernel below leaves a partial row
     // of H floats per 32 neurons and pair, as much traffic as the weights, and loops over several items per
     // workgroup.  Per layer, Qwen shape at 2 / 8 tokens 35.6 -> 32.3 / 61.7 -> 49.1 us, DeepSeek shape at 8
-    // 83 -> 63, Mixtral shape at 1 / 8 61.7 -> 54.4 / 267 -> 151.  Small layers stay with the kernel below (its two
+    // 80 -> 62, Mixtral shape at 1 / 8 61.3 -> 53.3 / 267 -> 151.  Small layers stay with the kernel below (its two
     // launches against four: E = 66, H = 1024, I = 1152 int8 at one token 20.6 us, 27.3 with the GEMMs).
     if (decode_by_gemm(d)) {
         DecodeArgs da{};

@@ -1,6 +1,6 @@
-// fate_moe_layer_decode: a whole decode-side MoE layer in two launches (1..8
-// tokens): gate logits, softmax / top-k, cross-layer prediction, permutation
-// and the quantised expert FFN.
+// fate_moe_layer_decode, the form of small layers: a whole decode-side MoE
+// layer in two launches (1..8 tokens): gate logits, softmax / top-k,
+// cross-layer prediction, permutation and the quantised expert FFN.
 //
 // Block ids, in order:
 //  routing workgroups: each wave evaluates one gate row (this layer's gate,

@@ -95,13 +95,13 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 // A constant the compiler must keep in a vector register.  (x & mask) | bits with two literal
 // operands cannot be one VOP3 instruction on gfx9 (one scalar or literal operand per
 // instruction), and the compiler then emits v_and + v_or and re-materialises the literals;
-// with both constants in registers it selects v_and_or_b32.
+// with both constants in registers one instruction does it.
 __device__ __forceinline__ uint32_t vgpr_const(uint32_t c) {
     asm("" : "+v"(c));
     return c;
 }
-// (x & mask) | bits.  v_bitop3_b32 issues at twice the rate of v_and_or_b32 when two or more waves share
-// a SIMD (2.9 against 4.7 cycles per instruction on this chip, measured back to back).
+// (x & mask) | bits.  v_bitop3_b32 issues faster than v_and_or_b32 when several waves share a SIMD (back to back, per
+// SIMD: 3.0 against 4.1 cycles with two waves, 1.9 against 2.9 with four; 8 each with one).
 __device__ __forceinline__ uint32_t and_or_b32(uint32_t x, uint32_t mask, uint32_t bits) {
     return __builtin_amdgcn_bitop3_b32(x, vgpr_const(mask), vgpr_const(bits), 0xea);
 }
