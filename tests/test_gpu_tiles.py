@@ -8,7 +8,8 @@ import pytest
 import torch
 
 from oracle import moe as O
-from workloads import SHAPES, gen_gate, gen_hidden
+import paper_2502_12224_amd.binding as B
+from workloads import SHAPES, gen_expert, gen_gate, gen_hidden
 from helpers import DEV, GpuLayer, f32, ffn_rel_err, gpu_permute, gpu_route, oracle_expert
 from test_gpu_layer_fused import _one_launch_case
 
@@ -20,7 +21,7 @@ ROWS = (1, 31, 32, 33, 64, 65, 96, 97, 128, 129)        # rows per expert: both 
 @pytest.mark.parametrize("H,I,bits,n_shared,I_shared", [
     (256, 384, 4, 0, 0),                    # whole sums, fp16 outputs
     (384, 2048, 4, 0, 0),                   # parts of the reduction dimension, fp32 outputs
-    (256, 2048, 8, 1, 384),                 # parts of the routed experts' only, passes of 64 rows
+    (256, 2048, 8, 1, 384),                 # parts of the routed experts' only, tiles of 64 rows
     (256, 384, 4, 1, 2048),                 # parts of the shared expert's only
     (256, 1536, 4, 2, 1152),                # parts of both
 ])
@@ -40,6 +41,31 @@ def test_prefill_gemm_at_its_tile_edges(H, I, bits, n_shared, I_shared):
                               {e: oracle_expert(L.host[e]) for e in range(cfg.E)},
                               [oracle_expert(s) for s in L.shared_host], sg)
     assert ffn_rel_err(f32(y), y_ref).max() <= 2e-3
+
+
+@pytest.mark.parametrize("bits,widths,zp", [(4, (2, 8), False), (4, (2, 4), True), (8, (4, 8, 2), False)])
+def test_prefill_gemm_on_entries_of_other_widths(bits, widths, zp):
+    """Entries of another width than the layer's nominal one: 2- and 8-bit rows in passes of 64 within tiles of 128 rows
+    (4-bit layer), 4-bit rows in tiles of 64 (8-bit layer)."""
+    cfg = dataclasses.replace(SHAPES["tiny"], name="edge", layers=1, H=256, E=len(ROWS), k=1, I=384, bits=bits, group=128,
+                              gate_var=1.0 / 256)
+    ids = np.repeat(np.arange(cfg.E), ROWS)
+    for turn in range(len(widths)):         # every number of rows at every width
+        print(f"case nominal {bits} widths {widths} turn {turn} zp={zp}", flush=True)
+        order = np.random.default_rng(turn).permutation(len(ids))
+        ids_t = ids[order].astype(np.int32)[:, None]
+        x = gen_hidden(cfg, len(ids), device=DEV)
+        w = torch.rand(len(ids), 1, generator=torch.Generator().manual_seed(3)).to(DEV) + 0.1
+        L = GpuLayer(cfg, 0, experts=[])
+        for e in range(cfg.E):
+            L.host[e] = gen_expert(cfg, 0, e, device=DEV, bits=widths[(e + turn) % len(widths)], zero_points=zp)
+            L.packed[e] = B.PackedExpert(L.host[e], DEV)
+        L.table = B.expert_table([L.packed[e].struct() for e in range(cfg.E)], DEV)
+        y, ws = L.ffn(x, *gpu_permute(torch.from_numpy(ids_t).to(DEV), cfg.E), w, mode=2, ws_fill=0xff)
+        assert int(ws[:4].view(torch.int32)[0]) == 0
+        y_ref = O.moe_ffn_grouped(f32(x), ids_t, w.cpu().numpy().astype(np.float64),
+                                  {e: oracle_expert(L.host[e]) for e in range(cfg.E)}, [], None)
+        assert ffn_rel_err(f32(y), y_ref).max() <= 2e-3
 
 
 _QWEN = SHAPES["qwen"]
