@@ -30,8 +30,20 @@ struct DecodeArgs {
     int lds_rows;        // activation rows staged in LDS per pass, plus one zero row
 };
 
+// Pair order of the GEMMs' activations (xh, h_r, h_s) inside every 32 columns: column 8d + 2j + i lies at place
+// 8j + 2d + i.  The 16 bytes of piece j are then columns 2j, 2j + 1 of every 8, which is what one mask takes out of the
+// four dwords (one per 8 columns) of a lane's 4-bit codes.
+__host__ __device__ inline int pair_place(int col) { return (col & ~31) + ((col & 7) >> 1) * 8 + ((col & 31) >> 3) * 2 + (col & 1); }
+#ifdef __HIPCC__
+// the fp16 columns 8c .. 8c + 7 of a row go to their places
+__device__ __forceinline__ void store_pairs(void* row, int c, uint4 v) {
+    uint32_t* o = static_cast<uint32_t*>(row) + (c >> 2) * 16 + (c & 3);
+    o[0] = v.x; o[4] = v.y; o[8] = v.z; o[12] = v.w;
+}
+#endif
+
 struct MfmaScratch {
-    __half* xh;        // [N,H] fp16 copy of x
+    __half* xh;        // [N,H] fp16 copy of x, pair order
     float* sgate;      // [N] shared gate values
     int4* tab_up;      // [E + n_shared + 1] segments of the up GEMM: first tile, expert, first row, rows
     int4* tab_down;    // same for the down GEMM

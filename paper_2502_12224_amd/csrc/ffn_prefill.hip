@@ -23,9 +23,7 @@
 // multiplies them with the workgroup's activation rows; accumulation is fp32.
 // What bounds it, by counters.  Full tiles (2048 tokens of the Mixtral shape, E = 8, H = 4096, I = 14336): the chip
 // holds 1.5 GHz under the up GEMM and the matrix pipe is busy 73 % of the cycles (down 60 %), with 5.6 (4.9) vector
-// instructions per matrix instruction.  Tiles of few rows (48 tokens of the DeepSeek shape, 5 rows each): 2.0 GHz, the
-// matrix pipe busy 24 %, 16.5 vector instructions per matrix instruction, waves waiting for an issue slot 30 % and for
-// memory or a barrier 24 % of their time: a dequantised operand serves one product there instead of four.
+// instructions per matrix instruction.  Tiles of at most 32 rows have a form of their own (below).
 // Measured (before: 64-row tiles, codes in registers): up 1125 -> 867 us and down 645 -> 515 us at 2048 tokens
 // of the Mixtral shape, 271 -> 200 and 148 -> 124 us at 2048 tokens of the Qwen shape.
 #include <hip/hip_fp16.h>
@@ -43,6 +41,7 @@ namespace fate {
 typedef _Float16 f16x2v_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kBM = 1 << kTileRowsLog2;   // most rows of a workgroup tile
 constexpr int kBNUp = 128;          // weight rows per workgroup tile of the up GEMM (of each matrix)
@@ -104,7 +103,7 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
             __half2 h = __floats2half2_rn(bf16_lo(w[i]), bf16_hi(w[i]));
             o[i] = *reinterpret_cast<uint32_t*>(&h);
         }
-        xo[c] = make_uint4(o[0], o[1], o[2], o[3]);
+        store_pairs(xo, c, make_uint4(o[0], o[1], o[2], o[3]));
         if (gv) {
             const uint4 g = gv[c];
             const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
@@ -127,9 +126,9 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
     }
 }
 
-// Two neighbouring columns of one lane: columns 2p, 2p + 1 (p = 0..3) of matrix-core step d of the
-// stage whose raw tile pieces are `raw`, dequantised to a pair of fp16.  The code becomes an exact
-// fp16 integer (its bits OR-ed into the mantissa of a power of two, which is subtracted again) and
+// Pair p (0..3) of the 8 columns that a lane holds of matrix-core step d of the stage whose raw tile pieces are `raw`
+// (the activations' pair order: int4 step d takes columns 2d, 2d + 1 of every dword), dequantised to a pair of fp16.  The
+// code becomes an exact fp16 integer (its bits OR-ed into the mantissa of a power of two, which is subtracted again) and
 // is rounded once in code * scale; with a zero-point (u - z) * s is rounded twice.
 template <int BITS, bool ZP, int TPS>
 __device__ __forceinline__ uint32_t dequant_pair(const uint4 (&raw)[TPS], int d, int p, f16x2v_t s2, f16x2v_t z2) {
@@ -137,22 +136,34 @@ __device__ __forceinline__ uint32_t dequant_pair(const uint4 (&raw)[TPS], int d,
     auto both = [](float v) { return f16x2v_t{(_Float16)v, (_Float16)v}; };
     f16x2v_t w;
     if constexpr (BITS == 2) {
-        // sixteen fields per dword, two steps; signed code 2u - 3 without a zero-point
-        const uint32_t r = dword(0, d >> 1), x = d & 1 ? r >> 8 : r;
-        const uint32_t v = p == 0 ? and_or_b32(x, 0x00030003u, 0x64006400u) : p == 1 ? and_or_b32(x, 0x000c000cu, 0x5c005c00u)
-                         : p == 2 ? and_or_b32(x, 0x00300030u, 0x54005400u) : and_or_b32(x, 0x00c000c0u, 0x4c004c00u);
-        w = __builtin_bit_cast(f16x2v_t, v) - both(p == 0 ? 1024.f : p == 1 ? 256.f : p == 2 ? 64.f : 16.f);
+        // sixteen fields per dword, two dwords per 32 columns; signed code 2u - 3 without a zero-point
+        const uint32_t r = dword(0, 2 * (d >> 2) + (p >> 1)), x = p & 1 ? r >> 8 : r;
+        const int f = d & 3;
+        const uint32_t v = f == 0 ? and_or_b32(x, 0x00030003u, 0x64006400u) : f == 1 ? and_or_b32(x, 0x000c000cu, 0x5c005c00u)
+                         : f == 2 ? and_or_b32(x, 0x00300030u, 0x54005400u) : and_or_b32(x, 0x00c000c0u, 0x4c004c00u);
+        w = __builtin_bit_cast(f16x2v_t, v) - both(f == 0 ? 1024.f : f == 1 ? 256.f : f == 2 ? 64.f : 16.f);
         w = ZP ? w - z2 : w * both(2.f) - both(3.f);
     } else if constexpr (BITS == 4) {
-        const uint32_t r = dword(0, d), x = p < 2 ? r : r >> 8;
-        const uint32_t v = p & 1 ? and_or_b32(x, 0x00f000f0u, 0x54005400u) : and_or_b32(x, 0x000f000fu, 0x64006400u);
-        w = __builtin_bit_cast(f16x2v_t, v) - both((p & 1 ? 64.f : 1024.f) + (ZP ? 0.f : 8.f));
+        const uint32_t r = dword(0, p), x = d < 2 ? r : r >> 8;
+        const uint32_t v = d & 1 ? and_or_b32(x, 0x00f000f0u, 0x54005400u) : and_or_b32(x, 0x000f000fu, 0x64006400u);
+        w = __builtin_bit_cast(f16x2v_t, v) - both((d & 1 ? 64.f : 1024.f) + (ZP ? 0.f : 8.f));
         if constexpr (ZP) w = w - z2;
     } else {
-        const uint32_t v = __builtin_amdgcn_perm(0x64646464u, dword(d >> 1, 2 * (d & 1) + (p >> 1)), p & 1 ? 0x04030402u : 0x04010400u);
+        const uint32_t v = __builtin_amdgcn_perm(0x64646464u, dword(d >> 1, 2 * (p & 1) + (d & 1)), p & 2 ? 0x04030402u : 0x04010400u);
         w = __builtin_bit_cast(f16x2v_t, v) - both(1152.f);       // 1024 + 128
     }
     return __builtin_bit_cast(uint32_t, w * s2);
+}
+
+// Eight activations of a lane: one piece of 16 bytes, or 8 bytes of two pieces.
+template <int N>
+__device__ __forceinline__ f16x8_t load_piece(const char* base, const uint32_t (&off)[N]) {
+    if constexpr (N == 1) {
+        return *reinterpret_cast<const f16x8_t*>(base + off[0]);
+    } else {
+        const uint2 a = *reinterpret_cast<const uint2*>(base + off[0]), b = *reinterpret_cast<const uint2*>(base + off[1]);
+        return __builtin_bit_cast(f16x8_t, u32x4_t{a.x, a.y, b.x, b.y});
+    }
 }
 
 // A value that is the same in all lanes, told to the compiler (it keeps what it loaded from memory
@@ -209,6 +220,7 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
     const int n = lane & 31, half = lane >> 5;
     const int nstage = c.ncol / BK, tiles_k = c.K / KT;
     const uint32_t lds0 = lds_offset(smem);
+    const char* abase = uniform(reinterpret_cast<const char*>(c.A));
 
     // activation loads: load i of this wave fills rows (i*4 + wave)*RPL + lane / (64 / RPL)
     uint32_t xoff[NX];
@@ -246,7 +258,7 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
     auto issue_one = [&](int st, int slot, int l) {
         const uint32_t base = lds0 + slot * SB;
         if (l < NX) {
-            lds_load16(base + (l * 4 + wave) * 1024, reinterpret_cast<const char*>(c.A) + (size_t)st * XROW, xoff[l]);
+            lds_load16(base + (l * 4 + wave) * 1024, abase + (size_t)st * XROW, xoff[l]);
         } else if (l < NX + 2 * TPS) {
             const int i = (l - NX) / TPS, tl = (l - NX) % TPS;
             lds_load16(base + F::xbytes(NMT) + (wave * 2 * TPS + i * TPS + tl) * 1024, wbase[i] + (size_t)(st * TPS + tl) * 1024,
@@ -273,14 +285,18 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[i][mt][j] = 0.f;
     // this lane's activation pieces of a stage, in the order of the weight operands
-    uint32_t aoff[TPS * SPT];
+    // (8-bit tiles: a step's 8 columns are half of two pieces)
+    constexpr int APS = BITS == 8 ? 2 : 1;
+    uint32_t aoff[TPS * SPT][APS];
 #pragma unroll
     for (int tl = 0; tl < TPS; ++tl)
 #pragma unroll
-        for (int d = 0; d < SPT; ++d) {
-            const int piece = (tl * KT + half * (KT / 2)) / 8 + d;
-            aoff[tl * SPT + d] = n * XROW + (piece ^ (n & 7)) * 16;
-        }
+        for (int d = 0; d < SPT; ++d)
+#pragma unroll
+            for (int i = 0; i < APS; ++i) {
+                const int piece = BITS == 8 ? tl * 4 + 2 * d + i : (tl * KT + half * (KT / 2)) / 8 + d;
+                aoff[tl * SPT + d][i] = n * XROW + (piece ^ (n & 7)) * 16 + (BITS == 8 ? half * 8 : 0);
+            }
 
     constexpr int KS = TPS * SPT;                         // matrix-core steps per stage
     int slot = 0, slot_in = S - 1;                        // stage being multiplied, stage being filled
@@ -300,7 +316,7 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
         f16x8_t av[2][NMT];                               // activations of the current and the next step
         u32x4_t b[2][2];                                  // dequantised codes: [step parity][block]
         auto read_av = [&](int d, int mt) {
-            av[d & 1][mt] = *reinterpret_cast<const f16x8_t*>(base + aoff[d] + mt * 32 * XROW);
+            av[d & 1][mt] = load_piece<APS>(base + mt * 32 * XROW, aoff[d]);
         };
         // the e-th of the 8 pairs of a step: 4 of each block
         auto dequant = [&](int d, int e) { b[d & 1][e >> 2][e & 3] = dequant_pair<BITS, ZP>(raw[e >> 2], d, e & 3, s2[e >> 2], z2[e >> 2]); };
@@ -357,19 +373,26 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
     for (int mt = 0; mt < NMT; ++mt) {
         const int r = mt * 32 + n;
         if (r < c.nrows) {
-            __half* o = static_cast<__half*>(c.out) + (size_t)r * c.ldo + 4 * half;
-            float* of = static_cast<float*>(c.out) + (size_t)r * c.ldo + 4 * half;
+            if constexpr (UP) {
+                // in pair order a lane's 16 neurons are two pieces of 16 bytes
+                uint4* o = reinterpret_cast<uint4*>(static_cast<__half*>(c.out) + (size_t)r * c.ldo + c.wrow[0]) + 2 * half;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if constexpr (UP) {
-                    __half h[4];
+                for (int u = 0; u < 2; ++u) {
+                    __half h[8];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float g = acc[0][mt][4 * q + j];
-                        h[j] = __float2half(g / (1.0f + __expf(-g)) * acc[1][mt][4 * q + j]);
-                    }
-                    if (c.wlive[0]) *reinterpret_cast<uint2*>(o + c.wrow[0] + 8 * q) = *reinterpret_cast<uint2*>(h);
-                } else {
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const float g = acc[0][mt][4 * q + 2 * u + j];
+                            h[2 * q + j] = __float2half(g / (1.0f + __expf(-g)) * acc[1][mt][4 * q + 2 * u + j]);
+                        }
+                    if (c.wlive[0]) o[u] = *reinterpret_cast<uint4*>(h);
+                }
+            } else {
+                __half* o = static_cast<__half*>(c.out) + (size_t)r * c.ldo + 4 * half;
+                float* of = static_cast<float*>(c.out) + (size_t)r * c.ldo + 4 * half;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
                         if (!c.wlive[i]) continue;
@@ -383,110 +406,91 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
                             *reinterpret_cast<uint2*>(o + c.wrow[i] + 8 * q) = *reinterpret_cast<uint2*>(h);
                         }
                     }
-                }
             }
         }
     }
 }
 
-// A tile of any number of rows (at most kBM): as many 32-row products as it has rows, in one pass if
-// the stages of that many rows fit into LDS twice (int4), else in passes of 64 rows.
-template <int BITS, bool ZP, bool UP>
-__device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
-    if constexpr (BITS == 4) {
-        if (c.nrows <= 32) gemm_pipe<BITS, ZP, UP, 1>(c, smem);
-        else if (c.nrows <= 64) gemm_pipe<BITS, ZP, UP, 2>(c, smem);
-        else if (c.nrows <= 96) gemm_pipe<BITS, ZP, UP, 3>(c, smem);
-        else gemm_pipe<BITS, ZP, UP, 4>(c, smem);
-    } else {
-        TileCtx p = c;
-        for (int r0 = 0; r0 < c.nrows; r0 += 64) {
-            if (r0) {
-                lds_only_barrier();
-                if (c.rows) p.rows = c.rows + r0;
-                else p.A = c.A + (size_t)r0 * c.lda;
-                p.out = static_cast<char*>(c.out) + (size_t)r0 * c.ldo * (c.f32 ? sizeof(float) : sizeof(__half));
-            }
-            p.nrows = min(64, c.nrows - r0);
-            if (p.nrows <= 32) gemm_pipe<BITS, ZP, UP, 1>(p, smem);
-            else gemm_pipe<BITS, ZP, UP, 2>(p, smem);
-        }
-    }
-}
-
-// ---- decode-sized form ---------------------------------------------------------------------------
-// At most 16 rows per tile, and with distinct ids per expert: the codes stream once and everything else is small,
-// so a tile is bounded by the memory path and by the vector instructions of the widening.  The codes enter the matrix
-// cores as exact fp16 integers and a group's fp16 scale multiplies the group's fp32 sum: the weights
-// enter exactly, and a pair of codes takes two vector instructions instead of three.  With
-// zero-points the group's sum of activations comes from a third product with ones.
-// 13 tokens of the Qwen shape: up 45.3 -> 28.7 us (106 MB of codes and scales: 3.7 TB/s), down 45.7 -> 17.2 us
-// against the dequant-GEMV kernels, whose loads sit under branches; 16 vector instructions per matrix instruction, waves
-// waiting for memory or a barrier 30 % and for an issue slot 21 % of their time (up).
-// D = activations x codes: lane n holds weight row n, rows 4*half + 0..3 and 8 + 4*half + 0..3.
-// R: rows of the tile (8 or 16).  KW: waves over which the reduction dimension is split (up projection of a
-// decode layer: tiles of 64 neurons instead of 128; a wave alone on its SIMD issues a widening instruction every 6 to 8
-// cycles, two of them one every 3 to 4.  One token of the Mixtral shape: 34 -> 30 us; four ranges gain nothing
-// more).  A stage's scales are one load of 256 bytes per wave: for int4 both
-// blocks' scales of both 64-column halves (groups of 64, or a multiple of 128), with zero-points a second one
-// like it; where a stage lies inside a group (the other widths, int4 stages of 64 columns), scales in the first half and
-// zero-points in the other.  BK: columns of a stage.  int4 takes stages of 128 (the loads of a stage are the cost of its
-// barrier) except for the down projection of an expert whose I is no multiple of 128.
-constexpr int exact_stage(int bits) { return bits == 8 ? 64 : 128; }
-template <int BITS, bool ZP, int R, int KW, int BK>
-struct ExactFmt {
+// ---- few rows ------------------------------------------------------------------------------------
+// Tiles of at most 32 rows (decode-sized calls and decode layers: 16 and 8): the codes stream once and everything else is
+// small, so a tile is bounded by the memory path and by the vector instructions that widen the codes.  A 4-bit code enters
+// the matrix cores as u + 16, whose bits are the code's own in the right place and a constant: a shift and an AND-OR per
+// pair of codes.  The fp16 scale multiplies the fp32 sum of a stage's columns (which lie in
+// one group), and the constants' and the zero-point's share, a multiple of the sum of the activations, is what that sum
+// starts from: a product of the activations with a constant.  (Larger constants, or bare
+// bits as denormals, save shifts and lose precision: error of four tokens of the Mixtral shape 2.093e-4, with constants of
+// up to 256 2.099e-4, with denormals 2.5e-4, for no time: the shifts run beside the products.)  Codes of the other
+// widths enter as exact integers.  So weights enter without rounding.  16x16x32 products: 16 rows of activations
+// against 16 rows of weights, whose 16-byte pieces lane (cl = lane / 16, n = lane % 16) reads from the raw tiles in LDS.
+// D: lane (cl, n) holds weight row n, activation rows 4cl .. 4cl + 3.
+// NM: 16-row blocks of activations, R: rows staged (8, or 16 * NM).  KW: waves over which the reduction dimension is split
+// (up projection of a decode layer: tiles of 64 neurons instead of 128).  QT: the columns add up in quarters, whether one
+// wave takes them all or two take two each: h is rounded to fp16 and must not depend on that.
+// Stages: 128 columns for int4 with groups of a multiple of 128 and for int2, 64 for int8 and for int4 otherwise.
+// Against 32x32x16 products of codes made exact by a subtraction (16 rows) or of code * scale (32 rows): 48 tokens of the
+// DeepSeek shape (5 rows a tile) up 51.1 -> 40.7, down 34.1 -> 28.8 us; 13 tokens of the Qwen shape 28.7 -> 24.8 (106 MB
+// of codes and scales: 4.3 TB/s) and 17.2 -> 15.4; one token of the Mixtral shape 30.2 -> 26.3 and 17.5 -> 14.9.
+template <int BITS, int BK, int R, int KW>
+struct RowsFmt {
     static constexpr int KT = QFmt<BITS>::KT;
-    static constexpr int TPS = BK / KT;
-    static constexpr int HS = BITS == 4 && BK == 128 ? 2 : 1;   // scales per row and stage
-    static constexpr int SL = HS == 2 && ZP ? 2 : 1;      // loads of scales and zero-points
+    static constexpr int TPS = BK / KT;                   // weight tiles per stage and block
+    static constexpr int KS = BK / 32;                    // matrix-core steps per stage
+    static constexpr bool split = BITS == 8 || (BITS == 4 && BK == 64); // a step's 8 columns are half of two pieces
     static constexpr int XROW = BK * 2;
     static constexpr int xwave = R * XROW;                // of the waves that share a range of columns
     static constexpr int xbytes = KW * xwave;
     static constexpr int sc0 = xbytes + 4 * 2 * TPS * 1024;
-    static constexpr int stage = sc0 + 4 * SL * 256;
+    static constexpr int stage = sc0 + 4 * 256;
     static constexpr int depth = kGemmLds / stage < 8 ? kGemmLds / stage : 8;
 };
 
-// codes of columns 2p, 2p + 1 of matrix-core step d as exact fp16 integers (int4: u - 8, int8: u - 128, int2: 2u - 3)
-template <int BITS, int TPS>
-__device__ __forceinline__ uint32_t code_pair(const uint4 (&raw)[TPS], int d, int p) {
-    auto dword = [&](int tl, int i) { return i == 0 ? raw[tl].x : i == 1 ? raw[tl].y : i == 2 ? raw[tl].z : raw[tl].w; };
-    auto both = [](float v) { return f16x2v_t{(_Float16)v, (_Float16)v}; };
-    f16x2v_t w;
-    if constexpr (BITS == 2) {
-        const uint32_t r = dword(0, d >> 1), x = d & 1 ? r >> 8 : r;
-        const uint32_t v = p == 0 ? and_or_b32(x, 0x00030003u, 0x64006400u) : p == 1 ? and_or_b32(x, 0x000c000cu, 0x5c005c00u)
-                         : p == 2 ? and_or_b32(x, 0x00300030u, 0x54005400u) : and_or_b32(x, 0x00c000c0u, 0x4c004c00u);
-        w = (__builtin_bit_cast(f16x2v_t, v) - both(p == 0 ? 1024.f : p == 1 ? 256.f : p == 2 ? 64.f : 16.f)) * both(2.f) - both(3.f);
-    } else if constexpr (BITS == 4) {
-        const uint32_t r = dword(d >> 2, d & 3), x = p < 2 ? r : r >> 8;
-        const uint32_t v = p & 1 ? and_or_b32(x, 0x00f000f0u, 0x54005400u) : and_or_b32(x, 0x000f000fu, 0x64006400u);
-        w = __builtin_bit_cast(f16x2v_t, v) - both(p & 1 ? 72.f : 1032.f);
+// the codes of step k of a lane's piece (16 or 8 bytes): int4 u + 16, int8 u - 128, int2 u
+template <int BITS, int BK>
+__device__ __forceinline__ f16x8_t code_step(const uint4& r, int k) {
+    u32x4_t v;
+    if constexpr (BITS == 4) {
+        // pair i of a dword (bits 4i of both halves) to bits 6..9: u + 16
+        auto pair = [](uint32_t r, int i) {
+            return and_or_b32(i < 2 ? r << (6 - 4 * i) : r >> (4 * i - 6), 0x03c003c0u, 0x4c004c00u);
+        };
+        if constexpr (BK == 128) v = u32x4_t{pair(r.x, k), pair(r.y, k), pair(r.z, k), pair(r.w, k)};
+        else v = u32x4_t{pair(r.x, k), pair(r.y, k), pair(r.x, k + 2), pair(r.y, k + 2)};
     } else {
-        const uint32_t v = __builtin_amdgcn_perm(0x64646464u, dword(d >> 1, 2 * (d & 1) + (p >> 1)), p & 1 ? 0x04030402u : 0x04010400u);
-        w = __builtin_bit_cast(f16x2v_t, v) - both(1152.f);
+        uint32_t w[4];
+        float one;
+        if constexpr (BITS == 2) {
+            const uint32_t m = 0x00030003u << (2 * k), o = 0x64006400u - 0x08000800u * k;       // 1024, 256, 64, 16
+            w[0] = and_or_b32(r.x, m, o); w[1] = and_or_b32(r.x >> 8, m, o);
+            w[2] = and_or_b32(r.y, m, o); w[3] = and_or_b32(r.y >> 8, m, o);
+            one = k == 0 ? 1024.f : k == 1 ? 256.f : k == 2 ? 64.f : 16.f;
+        } else {
+            const uint32_t a = k ? r.y : r.x, b = k ? r.w : r.z;
+            w[0] = __builtin_amdgcn_perm(0x64646464u, a, 0x04010400u); w[1] = __builtin_amdgcn_perm(0x64646464u, b, 0x04010400u);
+            w[2] = __builtin_amdgcn_perm(0x64646464u, a, 0x04030402u); w[3] = __builtin_amdgcn_perm(0x64646464u, b, 0x04030402u);
+            one = 1152.f;                                 // 1024 + 128
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2v_t, w[i]) - f16x2v_t{(_Float16)one, (_Float16)one});
     }
-    return __builtin_bit_cast(uint32_t, w);
+    return __builtin_bit_cast(f16x8_t, v);
 }
 
-// (u - z) x summed over a group = (sum of q x, q = a*u - c, plus (c - a z) times the sum of x) / a
-template <int BITS> struct ZpExact { static constexpr float inv_a = 1.0f, c_over_a = 8.0f; };
-template <> struct ZpExact<2> { static constexpr float inv_a = 0.5f, c_over_a = 1.5f; };
-
-template <int BITS, bool ZP, bool UP, int R, int KW, int BK = exact_stage(BITS)>
-__device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
-    typedef ExactFmt<BITS, ZP, R, KW, BK> F;
-    constexpr int KT = F::KT, TPS = F::TPS, HS = F::HS, SL = F::SL, XROW = F::XROW, RJ = R / 2;
-    constexpr int SPT = KT / 16, KS = TPS * SPT, KH = KS / HS;
+template <int BITS, bool ZP, bool UP, int NM, int R, int KW, bool QT, int BK>
+__device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
+    typedef RowsFmt<BITS, BK, R, KW> F;
+    constexpr int KT = F::KT, TPS = F::TPS, KS = F::KS, XROW = F::XROW;
     constexpr int S = F::depth, SB = F::stage;
     constexpr int NX = (F::xwave / 1024 + 4 / KW - 1) / (4 / KW);          // activation loads per wave and stage
-    constexpr int LPS = NX + 2 * TPS + SL;
+    constexpr int LPS = NX + 2 * TPS + 1;
     static_assert(S >= 2, "at least one stage ahead");
+    static_assert(KW == 1 || (KW == 2 && UP && QT && NM == 1), "the split of the reduction dimension belongs to the up projection");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 31, half = lane >> 5;
+    const int n = lane & 15, cl = lane >> 4;
     const int kw = wave & (KW - 1);                       // this wave's range of columns
     const int ncol = c.ncol / KW, col0 = c.col0 + kw * ncol;
-    const int nstage = ncol / BK, tiles_k = c.K / KT;
+    const int nstage = uniform(ncol / BK), tiles_k = c.K / KT;
+    const char* abase = uniform(reinterpret_cast<const char*>(c.A));
     const uint32_t lds0 = lds_offset(smem);
     constexpr int LPR = XROW / 16, RPL = 64 / LPR;        // lanes per row, rows per load
     constexpr int XL = F::xwave / 1024;                   // activation loads of a range; waves beyond them repeat one
@@ -500,73 +504,78 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
         xoff[i] = ((uint32_t)ar * (uint32_t)c.lda + (uint32_t)col0) * 2u + (uint32_t)((q ^ (r & 7)) * 16);
     }
     const char* wbase[2];
-    const char *sbase, *zbase;                            // this lane's scale / zero-point address (zbase: two scales per stage)
+    const char* sbase;                                    // this lane's scale (lanes 0..31) or zero-point address
     {
         const void* wp[2] = {UP ? c.ex->w1 : c.ex->w2, UP ? c.ex->w3 : c.ex->w2};
         const void* sp[2] = {UP ? c.ex->s1 : c.ex->s2, UP ? c.ex->s3 : c.ex->s2};
         const void* zp[2] = {UP ? c.ex->z1 : c.ex->z2, UP ? c.ex->z3 : c.ex->z2};
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            wbase[i] = static_cast<const char*>(uniform(wp[i])) + ((size_t)(c.wrow[i] >> 5) * tiles_k + col0 / KT) * 1024;
+            wbase[i] = uniform(static_cast<const char*>(wp[i]) + ((size_t)(c.wrow[i] >> 5) * tiles_k + col0 / KT) * 1024);
         const int b = (lane >> 4) & 1;
-        const size_t off = (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
-                           (size_t)((col0 + (HS == 2 ? 64 * half : 0)) / c.group) * c.Nout * 2;
-        const bool zs = ZP && HS == 1 && half;
-        sbase = static_cast<const char*>(b ? (zs ? zp[1] : sp[1]) : (zs ? zp[0] : sp[0])) + off;
-        zbase = ZP && HS == 2 ? static_cast<const char*>(b ? zp[1] : zp[0]) + off : nullptr;
+        const void* p0 = ZP && lane >= 32 ? zp[0] : sp[0];
+        const void* p1 = ZP && lane >= 32 ? zp[1] : sp[1];
+        sbase = static_cast<const char*>(b ? p1 : p0) + (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
+                (size_t)(col0 / c.group) * c.Nout * 2;
     }
     const uint32_t lane16 = lane * 16;
-    int gcol = col0 % c.group;                          // of the next stage to be requested
+    int gcol = col0 % c.group;                            // of the next stage to be requested
     auto issue_one = [&](int st, int slot, int l) {
         const uint32_t base = lds0 + slot * SB;
         if (l < NX) {
-            lds_load16(base + kw * F::xwave + xpiece(l) * 1024, reinterpret_cast<const char*>(c.A) + (size_t)st * XROW, xoff[l]);
+            lds_load16(base + kw * F::xwave + xpiece(l) * 1024, abase + (size_t)st * XROW, xoff[l]);
         } else if (l < NX + 2 * TPS) {
             const int i = (l - NX) / TPS, tl = (l - NX) % TPS;
             lds_load16(base + F::xbytes + (wave * 2 * TPS + i * TPS + tl) * 1024, wbase[i] + (size_t)(st * TPS + tl) * 1024, lane16);
-        } else if (l == NX + 2 * TPS) {
-            lds_load4(base + F::sc0 + wave * SL * 256, sbase);
         } else {
-            lds_load4(base + F::sc0 + (wave * SL + 1) * 256, zbase);
-        }
-        if (l == LPS - 1) {                               // on to the next stage's groups (two of them for int4 groups of 64)
+            lds_load4(base + F::sc0 + wave * 256, sbase);
             gcol += BK;
-            const size_t adv = gcol >= c.group ? (size_t)(HS == 2 && c.group == 64 ? 2 : 1) * c.Nout * 2 : 0;
-            if (gcol >= c.group) gcol = 0;
-            sbase += adv;
-            if (ZP && HS == 2) zbase += adv;
+            if (gcol >= c.group) {
+                gcol -= c.group;
+                sbase += (size_t)c.Nout * 2;
+            }
         }
     };
-    f32x16_t acc[2], sum;
-    // The up projection adds its groups up in quarters, whether one wave takes them all or two take two each: h is
-    // rounded to fp16 and must not depend on that.  (The decode kernels have a wave per quarter.)
-    float out[2][RJ], tot[2][RJ];
+    // by block of weight rows (half of the wave's block i) and block of activation rows
+    f32x4_t out[2][2][NM], tot[2][2][NM];
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 16; ++j) acc[0][j] = acc[1][j] = sum[j] = 0.f;
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < RJ; ++j) out[i][j] = tot[i][j] = 0.f;
-    const int ngroups = c.K / c.group;
-    // groups done, end of the current quarter (two waves: of the first one of this wave's two)
-    int gidx = KW == 1 ? 0 : kw * (ngroups / 2), quarter = ngroups * (2 * kw + 1) / 4;
+        for (int mb = 0; mb < NM; ++mb) out[i >> 1][i & 1][mb] = tot[i >> 1][i & 1][mb] = zero;
+    // stages done and the end of the current quarter (two waves: of the first one of this wave's two)
+    const int nq = c.K / BK;
+    int sidx = kw * (nq / 2), quarter = nq * (2 * kw + 1) / 4;
     auto close_quarter = [&]() {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < RJ; ++j) {
-                tot[i][j] += out[i][j];
-                out[i][j] = 0.f;
+            for (int mb = 0; mb < NM; ++mb) {
+                tot[i >> 1][i & 1][mb] += out[i >> 1][i & 1][mb];
+                out[i >> 1][i & 1][mb] = zero;
             }
     };
-    uint32_t aoff[KS];
+    // this lane's piece of a block's raw tiles (rows 0..15 of it; rows 16..31 lie 256 bytes on) and of the activations
+    constexpr bool wide = BITS == 8 || (BITS == 4 && BK == 128);          // the piece: 16 or 8 bytes
+    const uint32_t woff = ((cl & 1) * 32 + n) * 16 + (cl >> 1) * (wide ? 1024 : 8);
+    uint32_t aoff[KS][F::split ? 2 : 1];
 #pragma unroll
-    for (int d = 0; d < KS; ++d) {
-        const int piece = ((d / SPT) * KT + half * (KT / 2)) / 8 + d % SPT;
-        aoff[d] = kw * F::xwave + (n & (R - 1)) * XROW + (piece ^ (n & 7)) * 16;
-    }
-    const f16x8_t ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
-    int gleft = c.group - col0 % c.group;               // columns left of the group being summed
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int i = 0; i < (F::split ? 2 : 1); ++i) {
+            const int piece = BITS == 8 ? (cl >> 1) * 4 + 2 * k + i
+                            : BITS == 2 ? ((cl & 1) * 2 + (cl >> 1)) * 4 + k
+                            : BK == 64 ? (cl & 1) * 4 + k + 2 * i : cl * 4 + k;
+            aoff[k][i] = kw * F::xwave + (n & (R - 1)) * XROW + (piece ^ (n & 7)) * 16 +
+                         (BITS == 8 ? (cl & 1) * 8 : F::split ? (cl >> 1) * 8 : 0);
+        }
+    // What the products of a stage start from: the activations times what the codes carry too much, with the format's own
+    // zero (8; int2: 2u - 3).  A zero-point in memory: its distance to that times the sum of the activations.
+    constexpr bool from_sum = BITS == 4 || (BITS == 2 && !ZP);
+    auto times = [](float v) {
+        const _Float16 h = (_Float16)v;
+        return f16x8_t{h, h, h, h, h, h, h, h};
+    };
     int slot = 0, slot_in = S - 1;
     auto next = [](int i) { return i + 1 == S ? 0 : i + 1; };
 #pragma unroll
@@ -580,145 +589,177 @@ __device__ __forceinline__ void gemm_exact(const TileCtx& c, char* smem) {
         else wait_stages<LPS, S - 2>(nstage - 1 - st);
         lds_only_barrier();                               // stage st is in LDS, everyone is done with stage st - 1
         const char* base = smem + slot * SB;
-        const char* wl = base + F::xbytes + wave * (2 * TPS * 1024) + lane16;
-        const char* sl = base + F::sc0 + wave * SL * 256 + n * 2;
-        uint4 raw[2][TPS];
-        _Float16 sv[HS][2], zv[HS][2];
-        f16x8_t av[2];
-        u32x4_t b[2][2];
-        auto widen = [&](int d, int e) { b[d & 1][e >> 2][e & 3] = code_pair<BITS>(raw[e >> 2], d, e & 3); };
+        const char* wl = base + F::xbytes + wave * (2 * TPS * 1024) + woff;
+        const char* sl = base + F::sc0 + wave * 256 + n * 2;
+        f16x8_t av[NM][KS];
+        uint4 raw[4];
+        float sv[4], zv[4];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int k = 0; k < KS; ++k)
 #pragma unroll
-            for (int tl = 0; tl < TPS; ++tl) raw[i][tl] = *reinterpret_cast<const uint4*>(wl + (i * TPS + tl) * 1024);
+            for (int mb = 0; mb < NM; ++mb) av[mb][k] = load_piece<F::split ? 2 : 1>(base + mb * 16 * XROW, aoff[k]);
 #pragma unroll
-            for (int h = 0; h < HS; ++h) {
-                sv[h][i] = *reinterpret_cast<const _Float16*>(sl + (h * 2 + i) * 64);
-                zv[h][i] = ZP ? *reinterpret_cast<const _Float16*>(sl + (HS == 2 ? 256 + (h * 2 + i) * 64 : 128 + i * 64)) : (_Float16)0.f;
+        for (int q = 0; q < 4; ++q) {
+            const char* p = wl + (q >> 1) * TPS * 1024 + (q & 1) * 256;
+            if constexpr (wide) raw[q] = *reinterpret_cast<const uint4*>(p);
+            else {
+                const uint2 v = *reinterpret_cast<const uint2*>(p);
+                raw[q] = make_uint4(v.x, v.y, 0, 0);
+            }
+            sv[q] = (float)*reinterpret_cast<const _Float16*>(sl + q * 32);
+            zv[q] = ZP ? (BITS == 4 ? 8.f : 0.f) - (float)*reinterpret_cast<const _Float16*>(sl + 128 + q * 32) : 0.f;
+        }
+        f32x4_t start[NM], xsum[NM], acc[4][NM];
+#pragma unroll
+        for (int mb = 0; mb < NM; ++mb) {
+            start[mb] = xsum[mb] = zero;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                if constexpr (from_sum)
+                    start[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        av[mb][k], times(BITS == 2 ? -1.5f : -24.f), start[mb], 0, 0, 0);
+                if constexpr (ZP) xsum[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], times(1.f), xsum[mb], 0, 0, 0);
             }
         }
-        av[0] = *reinterpret_cast<const f16x8_t*>(base + aoff[0]);
-        __builtin_amdgcn_sched_barrier(0);
+        // a block's products, then (behind the next block's) its sums
+        auto products = [&](int q) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) widen(0, e);
+            for (int k = 0; k < KS; ++k) {
+                const f16x8_t b = code_step<BITS, BK>(raw[q], k);
 #pragma unroll
-        for (int d = 0; d < KS; ++d) {
-            __builtin_amdgcn_sched_barrier(0);
+                for (int mb = 0; mb < NM; ++mb)
+                    acc[q][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], b, k ? acc[q][mb] : start[mb], 0, 0, 0);
+            }
+        };
+        auto sums = [&](int q) {
+            const float s = BITS == 2 && !ZP ? 2.0f * sv[q] : sv[q];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[d & 1], __builtin_bit_cast(f16x8_t, b[d & 1][i]), acc[i], 0, 0, 0);
-            if constexpr (ZP) sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[d & 1], ones, sum, 0, 0, 0);
+            for (int mb = 0; mb < NM; ++mb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float t = ZP ? fmaf(zv[q], xsum[mb][j], acc[q][mb][j]) : acc[q][mb][j];
+                    out[q >> 1][q & 1][mb][j] = fmaf(s, t, out[q >> 1][q & 1][mb][j]);
+                }
+        };
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            products(q);
             if constexpr (more) {
 #pragma unroll
-                for (int l = LPS * d / KS; l < LPS * (d + 1) / KS; ++l) issue_one(st + S - 1, slot_in, l);
+                for (int l = LPS * q / 4; l < LPS * (q + 1) / 4; ++l) issue_one(st + S - 1, slot_in, l);
             }
-            if (d + 1 < KS) {
-                av[(d + 1) & 1] = *reinterpret_cast<const f16x8_t*>(base + aoff[d + 1]);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) widen(d + 1, e);
-            }
-            if ((d + 1) % KH == 0) {                      // the end of a scale's columns: the end of its group?
-                gleft -= BK / HS;
-                // (a part of the reduction dimension may end inside a group)
-                bool end = gleft == 0;
-                if constexpr (!more) end = end || (d + 1 == KS && st + 1 == nstage);
-                if (end) {
-                    gleft = c.group;
-                    const int h = d / KH;
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const float s = (float)sv[h][i];
-                        const float dz = ZP ? (ZpExact<BITS>::c_over_a - (float)zv[h][i]) : 0.f;
-#pragma unroll
-                        for (int j = 0; j < RJ; ++j) {
-                            const float v = ZP ? fmaf(ZpExact<BITS>::inv_a, acc[i][j], dz * sum[j]) : acc[i][j];
-                            out[i][j] = fmaf(s, v, out[i][j]);
-                        }
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) sum[j] = 0.f;
-                    if constexpr (UP && KW == 1) {
-                        if (++gidx >= quarter) {
-                            close_quarter();
-                            // the next quarter that holds a group ends at ngroups * q / 4
-                            int qn = 4 * gidx / ngroups + 1;
-                            while (qn < 4 && ngroups * qn / 4 <= gidx) ++qn;
-                            quarter = ngroups * qn / 4;
-                        }
-                    } else if constexpr (UP) {
-                        if (++gidx == quarter) close_quarter();
-                    }
+            if (q) sums(q - 1);
+        }
+        sums(3);
+        if constexpr (QT && UP) {
+            ++sidx;
+            if constexpr (KW == 1) {
+                if (sidx >= quarter) {
+                    close_quarter();
+                    // the next quarter that holds a stage ends at nq * q / 4
+                    int qn = 4 * sidx / nq + 1;
+                    while (qn < 4 && nq * qn / 4 <= sidx) ++qn;
+                    quarter = nq * qn / 4;
                 }
+            } else if (sidx == quarter) {
+                close_quarter();
             }
         }
-        __builtin_amdgcn_sched_barrier(0);
         slot = next(slot);
         slot_in = next(slot_in);
     };
     int st = 0;
     for (; st + S - 1 < nstage; ++st) step(st, std::true_type{});
     for (; st < nstage; ++st) step(st, std::false_type{});
-    if constexpr (UP && KW == 1) {
+    if constexpr (QT && UP && KW == 1) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < RJ; ++j) out[i][j] = tot[i][j];
+            for (int mb = 0; mb < NM; ++mb) out[i >> 1][i & 1][mb] = tot[i >> 1][i & 1][mb];
     }
     if constexpr (KW > 1) {
         // the quarters' sums meet in LDS: the first range's wave of every block adds the others in order
-        static_assert(UP && KW == 2, "the split of the reduction dimension belongs to the up projection");
-        float* red = reinterpret_cast<float*>(smem);      // [quarter of the second range][block of the tile][matrix][row][32]
+        f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);  // [quarter of the second range][block of the tile][4][64 lanes]
         lds_only_barrier();                               // the rings are done with
         const int blk = wave / KW;
-        auto at = [&](int q, int i, int j) {
-            return red + (((q * (4 / KW) + blk) * 2 + i) * RJ * 2 + (j >> 2) * 8 + 4 * half + (j & 3)) * 32 + n;
-        };
+        auto at = [&](int q, int i) { return red + ((q * (4 / KW) + blk) * 4 + i) * 64 + lane; };
         if (kw > 0) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < RJ; ++j) {
-                    *at(0, i, j) = tot[i][j];
-                    *at(1, i, j) = out[i][j];
-                }
+            for (int i = 0; i < 4; ++i) {
+                *at(0, i) = tot[i >> 1][i & 1][0];
+                *at(1, i) = out[i >> 1][i & 1][0];
+            }
         }
         lds_only_barrier();
         if (kw > 0) return;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < RJ; ++j) out[i][j] = ((tot[i][j] + out[i][j]) + *at(0, i, j)) + *at(1, i, j);
+        for (int i = 0; i < 4; ++i)
+            out[i >> 1][i & 1][0] = ((tot[i >> 1][i & 1][0] + out[i >> 1][i & 1][0]) + *at(0, i)) + *at(1, i);
     }
 #pragma unroll
-    for (int j = 0; j < RJ; ++j) {
-        const int r = 8 * (j >> 2) + 4 * half + (j & 3);
-        if (r < c.nrows) {
-            const int ro = c.orows ? c.orows[r] : r;
-            if constexpr (UP) {
-                if (c.wlive[0])
-                    static_cast<__half*>(c.out)[(size_t)ro * c.ldo + c.wrow[0] + n] =
-                        __float2half(out[0][j] / (1.0f + expf(-out[0][j])) * out[1][j]);
-            } else {
+    for (int mb = 0; mb < NM; ++mb)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    if (c.wlive[i]) static_cast<float*>(c.out)[(size_t)ro * c.ldo + c.wrow[i] + n] = out[i][j];
+        for (int j = 0; j < 4; ++j) {
+            const int r = mb * 16 + 4 * cl + j;
+            if (r < c.nrows) {
+                const int ro = c.orows ? c.orows[r] : r;
+                const size_t row = (size_t)ro * c.ldo;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if constexpr (UP) {
+                        const float g = out[0][h][mb][j];
+                        if (c.wlive[0])
+                            static_cast<__half*>(c.out)[row + c.wrow[0] + pair_place(h * 16 + n)] =
+                                __float2half(g / (1.0f + expf(-g)) * (out[1][h][mb][j]));
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            if (c.wlive[i]) {
+                                const float v = out[i][h][mb][j];
+                                if (QT || c.f32) static_cast<float*>(c.out)[row + c.wrow[i] + h * 16 + n] = v;
+                                else static_cast<__half*>(c.out)[row + c.wrow[i] + h * 16 + n] = __float2half(v);
+                            }
+                    }
+                }
             }
         }
+}
+
+template <int BITS, bool ZP, bool UP, int NM, int R, int KW, bool QT>
+__device__ __forceinline__ void rows_tile(const TileCtx& c, char* smem) {
+    if constexpr (BITS == 4) {
+        if (c.group % 128 == 0) gemm_rows<4, ZP, UP, NM, R, KW, QT, 128>(c, smem);
+        else gemm_rows<4, ZP, UP, NM, R, KW, QT, 64>(c, smem);
+    } else {
+        gemm_rows<BITS, ZP, UP, NM, R, KW, QT, BITS == 2 ? 128 : 64>(c, smem);
     }
 }
 
-// The down projection of an expert whose I is an odd multiple of 64 has half a stage of 128 columns left over.
-template <bool ZP, bool UP, int R, int KW>
-__device__ __forceinline__ void gemm_exact_int4(const TileCtx& c, char* smem) {
-    if constexpr (!UP) {
-        if (c.K % kKQ) {
-            gemm_exact<4, ZP, false, R, 1, 64>(c, smem);
-            return;
+// A tile of any number of rows (at most kBM): the few-row form up to 32 rows, else as many 32-row products as it has
+// rows, in one pass if the stages of that many rows fit into LDS twice (int4), else in passes of 64 rows.
+template <int BITS, bool ZP, bool UP>
+__device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
+    if constexpr (BITS == 4) {
+        if (c.nrows <= 16) rows_tile<4, ZP, UP, 1, 16, 1, false>(c, smem);
+        else if (c.nrows <= 32) rows_tile<4, ZP, UP, 2, 32, 1, false>(c, smem);
+        else if (c.nrows <= 64) gemm_pipe<BITS, ZP, UP, 2>(c, smem);
+        else if (c.nrows <= 96) gemm_pipe<BITS, ZP, UP, 3>(c, smem);
+        else gemm_pipe<BITS, ZP, UP, 4>(c, smem);
+    } else {
+        TileCtx p = c;
+        for (int r0 = 0; r0 < c.nrows; r0 += 64) {
+            if (r0) {
+                lds_only_barrier();
+                if (c.rows) p.rows = c.rows + r0;
+                else p.A = c.A + (size_t)r0 * c.lda;
+                p.out = static_cast<char*>(c.out) + (size_t)r0 * c.ldo * (c.f32 ? sizeof(float) : sizeof(__half));
+            }
+            p.nrows = min(64, c.nrows - r0);
+            if (p.nrows <= 16) rows_tile<BITS, ZP, UP, 1, 16, 1, false>(p, smem);
+            else if (p.nrows <= 32) rows_tile<BITS, ZP, UP, 2, 32, 1, false>(p, smem);
+            else gemm_pipe<BITS, ZP, UP, 2>(p, smem);
         }
     }
-    gemm_exact<4, ZP, UP, R, KW>(c, smem);
 }
 
 // The routing outputs of a decode layer, by one workgroup beside the layer's up GEMM: selection, prediction,
@@ -745,7 +786,7 @@ __device__ __forceinline__ void layer_outputs(const LayerOut& o, char* smem) {
     if (tid == 0) *o.calls += 1;
 }
 
-// MODE 0: prefill.  MODE 1: decode-sized (tiles of at most 16 rows), fp32 outputs of the down GEMM.
+// MODE 0: prefill.  MODE 1: decode-sized (tiles of at most 16 rows, all in the few-row form), fp32 outputs of the down GEMM.
 // MODE 2: the same inside a decode layer (at most 8 tokens, 64 pairs): no tile table; a workgroup finds its
 // expert and rows by itself, the up GEMM's from the logits and the down GEMM's from the selection; rows of h
 // and of the outputs are pairs.  The up GEMM's first workgroup writes the layer's routing outputs.
@@ -918,14 +959,14 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         c.A += (size_t)out_row0 * c.lda;
     }
     if constexpr (MODE == 2) {
-        if (bits == 4) gemm_exact_int4<false, UP, 8, KW>(c, smem);
-        else gemm_exact<8, false, UP, 8, KW>(c, smem);
+        if (bits == 4) rows_tile<4, false, UP, 1, 8, KW, true>(c, smem);
+        else rows_tile<8, false, UP, 1, 8, KW, true>(c, smem);
     } else if constexpr (MODE == 1) {
-        if (has_z && bits == 4) gemm_exact_int4<true, UP, 16, 1>(c, smem);
-        else if (has_z) gemm_exact<2, true, UP, 16, 1>(c, smem);
-        else if (bits == 4) gemm_exact_int4<false, UP, 16, 1>(c, smem);
-        else if (bits == 2) gemm_exact<2, false, UP, 16, 1>(c, smem);
-        else gemm_exact<8, false, UP, 16, 1>(c, smem);
+        if (has_z && bits == 4) rows_tile<4, true, UP, 1, 16, 1, true>(c, smem);
+        else if (has_z) rows_tile<2, true, UP, 1, 16, 1, true>(c, smem);
+        else if (bits == 4) rows_tile<4, false, UP, 1, 16, 1, true>(c, smem);
+        else if (bits == 2) rows_tile<2, false, UP, 1, 16, 1, true>(c, smem);
+        else rows_tile<8, false, UP, 1, 16, 1, true>(c, smem);
     } else {
         if (has_z && bits == 4) gemm_tile<4, true, UP>(c, smem);
         else if (has_z) gemm_tile<2, true, UP>(c, smem);

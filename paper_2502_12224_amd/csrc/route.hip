@@ -412,7 +412,7 @@ __global__ __launch_bounds__(256) void layer_logits_kernel(FusedRouteArgs a, Rou
     if (e0 >= E) {                                        // the preparation has workgroups of its own
         if (g) return;
         uint4* xo = reinterpret_cast<uint4*>(prep.xh) + (size_t)t * nvec;
-        for (int c = tid; c < nvec; c += 256) xo[c] = bf16x8_to_f16x8(xrow[c]);
+        for (int c = tid; c < nvec; c += 256) store_pairs(xo, c, bf16x8_to_f16x8(xrow[c]));
         if (wave == 3 && prep.shared_gate != nullptr) {
             const float v = wave_sigmoid_dot_bf16(xrow, reinterpret_cast<const uint4*>(prep.shared_gate), nvec);
             if ((tid & 63) == 0) prep.sgate[t] = v;

@@ -95,3 +95,39 @@ def test_infinite_gate_weight_stays_in_its_column(H):
     Wg[7, 0] = float("inf")
     ids, _, _ = gpu_route(x, Wg, b, cfg.k, False, want_probs=False)
     assert ids[:, 0].tolist() == [7] * 5
+
+
+FEW_ROWS = (1, 15, 16, 17, 31, 32, 33)   # both sides of the few-row forms' blocks of 16 and of their end
+
+
+@pytest.mark.parametrize("bits,group,zp,scale", [
+    (4, 64, False, 1.0),                    # stages of 64 columns
+    (4, 64, True, 1.0),
+    (4, 192, False, 1.0),                   # the same, groups of three stages
+    (4, 128, False, 1.0),                   # stages of 128 columns
+    (4, 256, True, 1.0),                    # groups of two stages
+    (8, 64, False, 1.0),
+    (2, 128, False, 1.0),
+    (2, 256, True, 1.0),
+    (4, 128, False, 2.0 ** -3),             # small and large activations
+    (4, 128, False, 2.0 ** 5),
+])
+def test_tiles_of_few_rows_in_every_format(bits, group, zp, scale):
+    """The forms for tiles of at most 32 rows (and the next larger one) in every format they read.  (With x scaled by
+    2^-3 h is about 2^-9, far above the 2^-14 below which fp16 loses bits; by 2^5 about 2^8.)"""
+    cfg = dataclasses.replace(SHAPES["tiny"], name="few", layers=1, H=768, E=len(FEW_ROWS), k=1, I=768, bits=bits,
+                              group=group, gate_var=1.0 / 768)
+    print(f"case bits={bits} group={group} zp={zp} scale={scale}", flush=True)
+    ids = np.random.default_rng(5).permutation(np.repeat(np.arange(cfg.E), FEW_ROWS)).astype(np.int32)[:, None]
+    x = (gen_hidden(cfg, len(ids), device=DEV).float() * scale).to(torch.bfloat16)
+    w = torch.rand(len(ids), 1, generator=torch.Generator().manual_seed(3)).to(DEV) + 0.1
+    L = GpuLayer(cfg, 0, experts=[])
+    for e in range(cfg.E):
+        L.host[e] = gen_expert(cfg, 0, e, device=DEV, zero_points=zp)
+        L.packed[e] = B.PackedExpert(L.host[e], DEV)
+    L.table = B.expert_table([L.packed[e].struct() for e in range(cfg.E)], DEV)
+    y, ws = L.ffn(x, *gpu_permute(torch.from_numpy(ids).to(DEV), cfg.E), w, mode=2, ws_fill=0xff)
+    assert int(ws[:4].view(torch.int32)[0]) == 0
+    y_ref = O.moe_ffn_grouped(f32(x), ids, w.cpu().numpy().astype(np.float64),
+                              {e: oracle_expert(L.host[e]) for e in range(cfg.E)}, [], None)
+    assert ffn_rel_err(f32(y), y_ref).max() <= 2e-3
