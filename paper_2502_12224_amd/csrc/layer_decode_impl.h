@@ -82,7 +82,7 @@ __device__ __forceinline__ void route_role(const LayerArgs& a, int b, uint32_t t
         if (tid == 0) atomicOr(a.status, 2);
         return;
     }
-    fused_select(r, rsm, nullptr, LdsLoad{zl, r.N, r.E});
+    fused_select(r, rsm, LdsLoad{zl, r.N, r.E});
 }
 
 // ---- Fast body: shapes whose per-wave share is a whole number of register rings ----

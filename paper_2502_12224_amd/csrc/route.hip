@@ -5,6 +5,7 @@
 //
 // fate_route_fused, up to 16 tokens: a workgroup per (token, gate), the last one to leave does
 // popularity and permutation; prefill sizes: both gates in one GEMM launch, then the permutation.
+#include <algorithm>
 #include "common.h"
 #include "route_device.h"
 #include "async_lds.h"
@@ -85,7 +86,7 @@ __device__ __forceinline__ void token_logits(const uint4* __restrict__ x, const 
 // A workgroup of 16 waves per TPW tokens.  A decode-sized call is a handful of dependent memory
 // round trips, so a token gets a whole compute unit: the gate matrix (a few hundred KB, from L2
 // after the first workgroup) is requested at once by 16 waves.  48 tokens, E = 64, H = 2048:
-// 9.5 us (one wave per token, rows one after the other: 109 us).  NW: waves, 16, or 4 where there are more tokens than the
+// 7.8 us, of which the selection is 1.5 (one wave per token, rows one after the other: 109 us).  NW: waves, 16, or 4 where there are more tokens than the
 // device holds workgroups of 16.
 template <int TPW, int NW>
 __global__ __launch_bounds__(64 * NW) void route_rows_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ Wg,
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(64 * NW) void route_rows_kernel(const uint16_t* __r
 // unit.  Every wave brings its own rows and columns to LDS by itself, 64 columns at a time in a ring
 // of stages, whole 128-byte lines per row (read straight into the operand registers, a load
 // touches 32 rows for 32 bytes each); no barrier before the logits meet.  Both gates, E = 60, H = 2048: 131
-// tokens 18.3 -> 10.8 us, 2048 tokens 25.4 -> 16.6 us.
+// tokens 18.3 -> 10.8 us, 2048 tokens 25.4 -> 16.6 us; with the selection by straight-line counting 9.6 and 15.3.
 struct RouteSecond {             // arguments of the second gate (grid.y = 2); unused when grid.y = 1
     const uint16_t* Wg; const float* bias; int m; int32_t* ids; float* w; int32_t* pop;
     int32_t* pop_part;           // [workgroups][E] each: when set, a workgroup leaves its counts of predicted /
@@ -256,7 +257,8 @@ __global__ __launch_bounds__(1024) void permute_kernel(const int32_t* __restrict
 // that those left (cnt_part [nparts][E]) give the place of every expert and, summed up to this
 // workgroup's row, of its pairs among the expert's; the pairs of its own tokens (pairs_wg of them)
 // are ranked by one wave in order.  Same outputs as permute_kernel, which one workgroup works
-// through on its own (131 tokens, k = 4: 8.9 -> 5.5 us, 2048 tokens 21.9 -> 13.2 us).
+// through on its own (131 tokens, k = 4: 8.9 -> 5.0 us, 2048 tokens 21.9 -> 9.7 us; the first workgroup, which also adds
+// up the predictions, asks for eight of their rows at once: 13.9 -> 9.7).
 // The first workgroup writes what is not per pair.
 __global__ __launch_bounds__(256) void permute_parts_kernel(const int32_t* __restrict__ ids, int P, int pairs_wg, int E,
                                                             int nparts, const int32_t* __restrict__ cnt_part,
@@ -287,7 +289,13 @@ __global__ __launch_bounds__(256) void permute_parts_kernel(const int32_t* __res
             }
         }
         if (want_pop)
-            for (int p = tid / Ew; p < nparts; p += rstep) pp += pop_part[(size_t)p * E + e0];
+            for (int p = tid / Ew; p < nparts; p += 8 * rstep) {
+                int v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = p + i * rstep < nparts ? pop_part[(size_t)(p + i * rstep) * E + e0] : 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) pp += v[i];
+            }
         if (rstep == 1) {
             tot[e0] = t; before[e0] = bf; pops[e0] = pp;
         } else {
@@ -356,8 +364,8 @@ __global__ __launch_bounds__(256) void permute_parts_kernel(const int32_t* __res
 // grid (N, gates): a workgroup evaluates one gate for one token as route_rows_kernel does (same
 // bits) and selects; what the permutation and the popularity need goes out with device-scope
 // stores, and the workgroup that leaves last (ticket counter at the start of the workspace, zero
-// between calls) adds them up.  13 tokens, E = 60, H = 2048: 16 us (a wave per gate row for all
-// tokens, then every selection in the last workgroup: 52 us).
+// between calls) adds them up.  13 tokens, E = 60, H = 2048: 11.7 us (selection and
+// permutation entry by entry in loops: 16; a wave per gate row for all tokens, then every selection in the last workgroup: 52).
 __global__ __launch_bounds__(64 * kTokWaves) void route_fused_kernel(FusedRouteArgs a, int32_t* ticket) {
     __shared__ float z[kMaxE];
     __shared__ int32_t sel[kMaxM];
@@ -545,8 +553,10 @@ extern "C" fate_status fate_permute(void* stream, const int32_t* topk_ids, int N
         FATE_FAIL(FATE_EINVAL, "counts, offsets and expert_order must not be NULL");
     if (N > 0 && (topk_ids == nullptr || perm == nullptr || inv_perm == nullptr))
         FATE_FAIL(FATE_EINVAL, "topk_ids, perm and inv_perm must not be NULL when N > 0");
-    permute_kernel<<<1, 1024, 0, static_cast<hipStream_t>(stream)>>>(topk_ids, N * k, E, counts, offsets, perm,
-                                                                    inv_perm, expert_order);
+    // a wave per 64 pairs, at least four for the popularity order of 256 experts (one does everything for 64 pairs)
+    const int waves = N * k <= 64 ? 1 : std::min(kPermMaxWaves, std::max(4, (N * k + 63) / 64));
+    permute_kernel<<<1, 64 * waves, 0, static_cast<hipStream_t>(stream)>>>(topk_ids, N * k, E, counts, offsets, perm,
+                                                                          inv_perm, expert_order);
     FATE_HIP(hipGetLastError());
     return FATE_OK;
 }

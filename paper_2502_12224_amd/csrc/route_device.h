@@ -13,15 +13,94 @@ __device__ __forceinline__ float lane_bcast(float v, int src) {
 }
 __device__ __forceinline__ int lane_bcast(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 
+// Inclusive scan over the 64 lanes: DPP shifts inside rows of 16, then row carries.
+__device__ __forceinline__ int wave_scan(int inc) {
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);   // row_shr:1
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);   // row_shr:2
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);   // row_shr:4
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);   // row_shr:8
+    const int r0 = lane_bcast(inc, 15), r1 = lane_bcast(inc, 31), r2 = lane_bcast(inc, 47);
+    const int row = (threadIdx.x & 63) >> 4;
+    return inc + (row > 0 ? r0 : 0) + (row > 1 ? r1 : 0) + (row > 2 ? r2 : 0);
+}
+
+// rank[i] = how many of the E entries (entry lane + 64 * i in key[i], NS = ceil(E / 64)) have a larger key than entry
+// lane + 64 * i.  One entry at a time goes to all lanes: a lane read, a comparison and an add with carry.
+// The chain is a single wave's, so sixteen entries are straight-line code (as a loop over one entry that also looked
+// at indices, the selection of a token of 60 experts took 3.3 us of a routing kernel's 9 to 16; now 1.5).
+// U: entries per straight-line piece; 1 in the one-launch decode layer, whose chain does not wait for its routing outputs
+// but takes longer with more code around it (Qwen shape, 24 layers: 418 -> 431 us with 16).
+template <int NS, int U>
+__device__ __forceinline__ void wave_count_greater(const int (&key)[NS], int E, int (&rank)[NS]) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) rank[i] = 0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int lim = min(64, E - 64 * s);
+        for (int base = 0; base < lim; base += U) {       // (entries past the last one have the least key: they count for none)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int kj = lane_bcast(key[s], base + u);
+#pragma unroll
+                for (int i = 0; i < NS; ++i) rank[i] += kj > key[i];
+            }
+        }
+    }
+}
+
+// An integer in the order of the float (both zeros alike), above the least one.
+__device__ __forceinline__ int float_order(float v) {
+    const int b = __float_as_int(v + 0.0f);
+    return b ^ ((b >> 31) & 0x7fffffff);
+}
+
+// rank[i] = place of entry lane + 64 * i among the E logits in v, by logit descending, ties to the lower index.
+template <int NS, int U>
+__device__ __forceinline__ void wave_rank_logits(const float (&v)[NS], int E, int (&rank)[NS]) {
+    const int lane = threadIdx.x & 63;
+    int key[NS], sum = 0;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) key[i] = lane + 64 * i < E ? float_order(v[i]) : (int)0x80000000;
+    wave_count_greater<NS, U>(key, E, rank);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) sum += lane + 64 * i < E ? rank[i] : 0;
+    // equal logits have equal counts, and only then do the counts add up to less than 0 + 1 + .. + (E - 1)
+    sum += __builtin_amdgcn_update_dpp(0, sum, 0xB1, 0xf, 0xf, false);
+    sum += __builtin_amdgcn_update_dpp(0, sum, 0x4E, 0xf, 0xf, false);
+    sum += __builtin_amdgcn_update_dpp(0, sum, 0x141, 0xf, 0xf, false);
+    sum += __builtin_amdgcn_update_dpp(0, sum, 0x140, 0xf, 0xf, false);
+    const int all = lane_bcast(sum, 0) + lane_bcast(sum, 16) + lane_bcast(sum, 32) + lane_bcast(sum, 48);
+    if (all == E * (E - 1) / 2) return;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int lim = min(64, E - 64 * s);
+        for (int src = 0; src < lim; ++src) {
+            const int kj = lane_bcast(key[s], src);
+#pragma unroll
+            for (int i = 0; i < NS; ++i) rank[i] += kj == key[i] && src + 64 * s < lane + 64 * i;
+        }
+    }
+}
+
+// Per-lane mask of the lanes in this wave that hold the same key (valid lanes only).
+__device__ __forceinline__ unsigned long long wave_match(int key, bool valid, int nbits) {
+    unsigned long long mask = __ballot(valid);
+    for (int b = 0; b < nbits; ++b) {
+        bool bit = (key >> b) & 1;
+        unsigned long long bb = __ballot(valid && bit);
+        mask &= bit ? bb : ~bb;
+    }
+    return mask;
+}
+
 // One wavefront turns E logits (z, readable by every lane) into the softmax
 // over all experts and the m largest entries, ordered by logit descending
-// with ties to the lower id.  Selection is by rank: every entry counts the
-// entries that precede it in that order (the wave broadcasts one entry at a
-// time), and the entries of rank < m write themselves to position rank.
+// with ties to the lower id.  Selection is by rank: the entries of rank < m
+// write themselves to position rank.
 // NS = ceil(E/64) values per lane.  ids_out/w_out may point to global or LDS
 // memory.  pop (optional) receives +1 per selected expert.  renorm != 0
 // divides the m weights by their sum.
-template <int NS>
+template <int NS, int U>
 __device__ __forceinline__ void wave_softmax_topm_ns(const float* z, int E, int m, int renorm,
                                                      int32_t* ids_out, float* w_out, float* probs_out,
                                                      int32_t* pop) {
@@ -49,19 +128,9 @@ __device__ __forceinline__ void wave_softmax_topm_ns(const float* z, int E, int 
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
         p[i] *= inv;
-        rank[i] = 0;
         if (probs_out && lane + 64 * i < E) probs_out[lane + 64 * i] = p[i];
     }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int lim = min(64, E - 64 * s);
-        for (int src = 0; src < lim; ++src) {
-            const float zj = lane_bcast(v[s], src);
-            const int ej = src + 64 * s;
-#pragma unroll
-            for (int i = 0; i < NS; ++i) rank[i] += (zj > v[i]) || (zj == v[i] && ej < lane + 64 * i);
-        }
-    }
+    wave_rank_logits<NS, U>(v, E, rank);
     float wsel = 0.f;
 #pragma unroll
     for (int i = 0; i < NS; ++i)
@@ -78,17 +147,18 @@ __device__ __forceinline__ void wave_softmax_topm_ns(const float* z, int E, int 
     }
 }
 
+template <int U = 16>
 __device__ __forceinline__ void wave_softmax_topm(const float* z, int E, int m, int renorm,
                                                   int32_t* ids_out, float* w_out, float* probs_out,
                                                   int32_t* pop) {
-    if (E <= 64) wave_softmax_topm_ns<1>(z, E, m, renorm, ids_out, w_out, probs_out, pop);
-    else if (E <= 128) wave_softmax_topm_ns<2>(z, E, m, renorm, ids_out, w_out, probs_out, pop);
-    else wave_softmax_topm_ns<4>(z, E, m, renorm, ids_out, w_out, probs_out, pop);
+    if (E <= 64) wave_softmax_topm_ns<1, U>(z, E, m, renorm, ids_out, w_out, probs_out, pop);
+    else if (E <= 128) wave_softmax_topm_ns<2, U>(z, E, m, renorm, ids_out, w_out, probs_out, pop);
+    else wave_softmax_topm_ns<4, U>(z, E, m, renorm, ids_out, w_out, probs_out, pop);
 }
 
 // Stable grouping of P <= 64 pair indices by expert id, by ONE wavefront, in
 // registers.  Same outputs as block_permute.  Every lane of the wave calls it.
-template <int NS>
+template <int NS, int U>
 __device__ __forceinline__ void wave_permute_small_ns(const int32_t* ids, int P, int E, int32_t* counts,
                                                       int32_t* offsets, int32_t* perm, int32_t* inv_perm,
                                                       int32_t* order) {
@@ -98,29 +168,23 @@ __device__ __forceinline__ void wave_permute_small_ns(const int32_t* ids, int P,
     const int key = valid ? ei : -1;
     int cnt[NS], off[NS], rk[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) cnt[s] = rk[s] = 0;
-    int before = 0;   // earlier pairs of the same expert
-    for (int src = 0; src < P; ++src) {
-        const int ej = lane_bcast(key, src);
-        before += (ej == key) && (src < lane);
+    for (int s = 0; s < NS; ++s) cnt[s] = 0;
+    const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const int before = __popcll(wave_match(key, valid, 6 + (NS > 1) + (NS > 2)) & lt);   // earlier pairs of the same expert
+    for (int b = 0; b < P; b += U) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) cnt[s] += (ej == lane + 64 * s);
+        for (int u = 0; u < U; ++u) {
+            const int ej = lane_bcast(key, b + u);        // (lanes past the last pair: -1)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) cnt[s] += ej == lane + 64 * s;
+        }
     }
     int base = 0;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        // inclusive scan over the 64 lanes: DPP shifts inside rows of 16, then row carries
-        int inc = cnt[s];
-        inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);   // row_shr:1
-        inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);   // row_shr:2
-        inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);   // row_shr:4
-        inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);   // row_shr:8
-        const int r0 = lane_bcast(inc, 15), r1 = lane_bcast(inc, 31), r2 = lane_bcast(inc, 47),
-                  r3 = lane_bcast(inc, 63);
-        const int row = lane >> 4;
-        inc += (row > 0 ? r0 : 0) + (row > 1 ? r1 : 0) + (row > 2 ? r2 : 0);
+        const int inc = wave_scan(cnt[s]);
         off[s] = base + inc - cnt[s];
-        base += r0 + r1 + r2 + r3;
+        base += lane_bcast(inc, 63);
         const int e = lane + 64 * s;
         if (e < E) {
             counts[e] = cnt[s];
@@ -140,27 +204,22 @@ __device__ __forceinline__ void wave_permute_small_ns(const int32_t* ids, int P,
     } else if (lane < P) {
         inv_perm[lane] = -1;
     }
+    int by_count[NS];                                     // count descending, id ascending
 #pragma unroll
-    for (int s2 = 0; s2 < NS; ++s2) {
-        const int lim = min(64, E - 64 * s2);
-        for (int src = 0; src < lim; ++src) {
-            const int cj = lane_bcast(cnt[s2], src);
-            const int ej = src + 64 * s2;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) rk[s] += (cj > cnt[s]) || (cj == cnt[s] && ej < lane + 64 * s);
-        }
-    }
+    for (int s = 0; s < NS; ++s) by_count[s] = lane + 64 * s < E ? cnt[s] * 256 + 255 - (lane + 64 * s) : -1;
+    wave_count_greater<NS, U>(by_count, E, rk);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
         if (lane + 64 * s < E) order[rk[s]] = lane + 64 * s;
 }
 
+template <int U = 16>
 __device__ __forceinline__ void wave_permute_small(const int32_t* ids, int P, int E, int32_t* counts,
                                                    int32_t* offsets, int32_t* perm, int32_t* inv_perm,
                                                    int32_t* order) {
-    if (E <= 64) wave_permute_small_ns<1>(ids, P, E, counts, offsets, perm, inv_perm, order);
-    else if (E <= 128) wave_permute_small_ns<2>(ids, P, E, counts, offsets, perm, inv_perm, order);
-    else wave_permute_small_ns<4>(ids, P, E, counts, offsets, perm, inv_perm, order);
+    if (E <= 64) wave_permute_small_ns<1, U>(ids, P, E, counts, offsets, perm, inv_perm, order);
+    else if (E <= 128) wave_permute_small_ns<2, U>(ids, P, E, counts, offsets, perm, inv_perm, order);
+    else wave_permute_small_ns<4, U>(ids, P, E, counts, offsets, perm, inv_perm, order);
 }
 
 // The m largest of E logits by m rounds of arg-max: same ids, order and
@@ -377,17 +436,6 @@ __device__ __forceinline__ void wave_slot_table(const int32_t* ids, const float*
     }
 }
 
-// Per-lane mask of the lanes in this wave that hold the same key (valid lanes only).
-__device__ __forceinline__ unsigned long long wave_match(int key, bool valid, int nbits) {
-    unsigned long long mask = __ballot(valid);
-    for (int b = 0; b < nbits; ++b) {
-        bool bit = (key >> b) & 1;
-        unsigned long long bb = __ballot(valid && bit);
-        mask &= bit ? bb : ~bb;
-    }
-    return mask;
-}
-
 constexpr int kPermMaxWaves = 16;
 constexpr int kPermSmemInts = (kPermMaxWaves + 2) * kMaxE;
 
@@ -395,7 +443,7 @@ constexpr int kPermSmemInts = (kPermMaxWaves + 2) * kMaxE;
 // blockDim.x = 64*nw threads (nw <= 16).  sm: kPermSmemInts ints of LDS.
 // Every thread of the block must call it.
 __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* counts, int32_t* offsets,
-                                     int32_t* perm, int32_t* inv_perm, int32_t* order, volatile int32_t* sm) {
+                                     int32_t* perm, int32_t* inv_perm, int32_t* order, int32_t* sm) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nthreads = blockDim.x, nw = nthreads >> 6;
     volatile int32_t* wc = sm;                 // [nw][E] per-wave counts, then running bases
@@ -407,6 +455,7 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
     chunk = (chunk + 63) & ~63;
     const int beg = wave * chunk;
     const int end = min(P, beg + chunk);
+    const int nholding = (P + chunk - 1) / max(chunk, 1);  // waves that hold pairs
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
     // the wave's first kPermCache * 64 ids stay in registers for both passes, requested at once
@@ -424,10 +473,14 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
         bool valid = (i < end) && e >= 0 && e < E;
         unsigned long long mk = wave_match(e, valid, nbits);
         if (valid && (mk & lt) == 0) wc[wave * E + e] += __popcll(mk);
+        return mk;
     };
+    unsigned long long mc[kPermCache];                     // (who holds the same id: needed again when the pairs are placed)
 #pragma unroll
-    for (int it = 0; it < kPermCache; ++it)
-        if (beg + 64 * it < end) count_step(beg + 64 * it, ec[it]);
+    for (int it = 0; it < kPermCache; ++it) {
+        mc[it] = 0;
+        if (beg + 64 * it < end) mc[it] = count_step(beg + 64 * it, ec[it]);
+    }
     for (int base = beg + 64 * kPermCache; base < end; base += 64) {
         int i = base + lane;
         count_step(base, (i < end) ? ids[i] : -1);
@@ -435,7 +488,7 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
     __syncthreads();
     for (int e = tid; e < E; e += nthreads) {
         int run = 0;
-        for (int w = 0; w < nw; ++w) {
+        for (int w = 0; w < nholding; ++w) {
             int c = wc[w * E + e];
             wc[w * E + e] = run;
             run += c;
@@ -452,12 +505,7 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
             c[i] = (e < E) ? tot[e] : 0;
             s += c[i];
         }
-        int inc = s;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            int up = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += up;
-        }
+        const int inc = wave_scan(s);
         int run = inc - s;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -472,10 +520,9 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
         if (lane == 63) offsets[E] = inc;
     }
     __syncthreads();
-    auto place_step = [&](int base, int e) {
+    auto place_step = [&](int base, int e, unsigned long long mk) {
         int i = base + lane;
         bool valid = (i < end) && e >= 0 && e < E;
-        unsigned long long mk = wave_match(e, valid, nbits);
         int b = valid ? wc[wave * E + e] : 0;
         if (valid) {
             int pos = excl[e] + b + __popcll(mk & lt);
@@ -488,23 +535,30 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
     };
 #pragma unroll
     for (int it = 0; it < kPermCache; ++it)
-        if (beg + 64 * it < end) place_step(beg + 64 * it, ec[it]);
+        if (beg + 64 * it < end) place_step(beg + 64 * it, ec[it], mc[it]);
     for (int base = beg + 64 * kPermCache; base < end; base += 64) {
         int i = base + lane;
-        place_step(base, (i < end) ? ids[i] : -1);
+        const int e = (i < end) ? ids[i] : -1;
+        place_step(base, e, wave_match(e, i < end && e >= 0 && e < E, nbits));
     }
-    // experts by (count descending, id ascending): lane o holds the totals of experts o, o + 64,
-    // ..; an expert's rank is the number of experts that come before it, counted by ballots
-    int cl[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) cl[g] = (lane + 64 * g < E) ? tot[lane + 64 * g] : -1;
-    for (int e = wave; e < E; e += nw) {
-        const int c = tot[e];
+    // experts by (count descending, id ascending): wave w ranks experts 64w .. 64w + 63
+    const int32_t* totals = sm + nw * E;
+    for (int w = wave; 64 * w < E; w += nw) {
+        const int e = lane + 64 * w, c = e < E ? totals[e] : -1;
         int r = 0;
+        for (int s = 0; 64 * s < E; ++s) {
+            const int v = lane + 64 * s < E ? totals[lane + 64 * s] : -1, lim = min(64, E - 64 * s);
+            // what counts as more: from the blocks before one's own an equal count, too
+            const int least = s < w ? c - 1 : c;
+            for (int b = 0; b < lim; b += 16) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            r += __popcll(__ballot(cl[g] > c || (cl[g] == c && lane + 64 * g < e)));
-        if (lane == 0) order[r] = e;
+                for (int u = 0; u < 16; ++u) {
+                    const int cj = lane_bcast(v, b + u);
+                    r += cj > (s == w && b + u < lane ? c - 1 : least);
+                }
+            }
+        }
+        if (e < E) order[r] = e;
     }
 }
 
@@ -583,12 +637,10 @@ __device__ __forceinline__ void fused_gate_rows(const FusedRouteArgs& a, int rbl
 }
 
 // Run by one whole workgroup (4..8 waves) once every logit has been stored:
-// softmax and selection per token, predicted popularity, permutation.
-// load(g, token, expert) returns a logit.  sm_perm: kPermSmemInts ints, only
-// touched when N*k > 64 (may be NULL otherwise).
+// softmax and selection per token, predicted popularity, permutation (at most 64 pairs).
+// load(g, token, expert) returns a logit.
 template <class Load>
-__device__ __forceinline__ void fused_select(const FusedRouteArgs& a, FusedRouteSmem& sm, int32_t* sm_perm,
-                                             const Load& load) {
+__device__ __forceinline__ void fused_select(const FusedRouteArgs& a, FusedRouteSmem& sm, const Load& load) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nthreads = blockDim.x, nw = nthreads >> 6;
     const int N = a.N, E = a.E, k = a.k, m = a.m;
@@ -602,9 +654,9 @@ __device__ __forceinline__ void fused_select(const FusedRouteArgs& a, FusedRoute
             for (int e = lane; e < E; e += 64) sm.z[wave][e] = load(g, t, e);
             __builtin_amdgcn_wave_barrier();
             if (!g) {
-                wave_softmax_topm(sm.z[wave], E, k, a.renorm, sm.ids + t * k, a.w + (size_t)t * k, nullptr, nullptr);
+                wave_softmax_topm<1>(sm.z[wave], E, k, a.renorm, sm.ids + t * k, a.w + (size_t)t * k, nullptr, nullptr);
             } else {
-                wave_softmax_topm(sm.z[wave], E, m, 0, a.pids + (size_t)t * m, a.pw + (size_t)t * m, nullptr, sm.pop);
+                wave_softmax_topm<1>(sm.z[wave], E, m, 0, a.pids + (size_t)t * m, a.pw + (size_t)t * m, nullptr, sm.pop);
             }
         }
     }
@@ -613,11 +665,7 @@ __device__ __forceinline__ void fused_select(const FusedRouteArgs& a, FusedRoute
     for (int i = threadIdx.x; i < P; i += nthreads) a.ids[i] = sm.ids[i];
     if (a.Wg2)
         for (int i = threadIdx.x; i < E; i += nthreads) a.pop[i] = sm.pop[i];
-    if (P <= 64) {
-        if (wave == 0) wave_permute_small(sm.ids, P, E, a.counts, a.offsets, a.perm, a.inv_perm, a.order);
-    } else {
-        block_permute(sm.ids, P, E, a.counts, a.offsets, a.perm, a.inv_perm, a.order, sm_perm);
-    }
+    if (wave == 0) wave_permute_small<1>(sm.ids, P, E, a.counts, a.offsets, a.perm, a.inv_perm, a.order);
 }
 
 }  // namespace fate

@@ -115,3 +115,47 @@ def test_gates_of_odd_sizes_over_many_tokens_match_oracle(H, E, k, N):
     rid, rw, rp, rz = O.gate_route(f32(x), f32(Wg), bias_np(b), k, False)
     assert check_routing(ids, w, rid, rw, rz, k, f"H={H} E={E} N={N}") <= max(1, N // 200)
     assert np.abs(probs.cpu().numpy().astype(np.float64) - rp).max() <= 1e-6
+
+
+@pytest.mark.parametrize("E,k,N", [(8, 2, 3), (16, 4, 9), (17, 5, 12), (60, 4, 16), (64, 8, 8), (65, 8, 7), (128, 8, 5), (129, 6, 40),
+                                   (200, 8, 64), (256, 8, 130)])
+def test_equal_logits_and_equal_counts_go_to_the_lower_id(E, k, N):
+    """Every third gate row is the row before it (equal logits in every token, whatever the order of summation), the last
+    rows are zero and of both signs; sizes at both sides of the selection's blocks of 16 and 64 entries.  All calls that
+    select agree with the oracle's order, and experts with equal counts are ordered by id."""
+    H = 1024
+    print(f"case E={E} k={k} N={N}", flush=True)
+    cfg = dataclasses.replace(SHAPES["tiny"], H=H, E=E, k=k, gate_var=1.0 / H)
+    x = gen_hidden(cfg, N, device=DEV)
+    Wg, _ = gen_gate(cfg, 0, device=DEV)
+    for e in range(2, E, 3):
+        Wg[e] = Wg[e - 1]
+    Wg[-1], Wg[-2] = 0.0, -0.0
+    m = min(E, k + 3)
+    ids, w, _ = gpu_route(x, Wg, None, k, True, want_probs=False)
+    pid, pw, pop = gpu_predict(x, Wg, None, k, m)
+    z = np.zeros((N, E))
+    z[:] = f32(x).astype(np.float64) @ f32(Wg).astype(np.float64).T
+    for e in range(2, E, 3):
+        if e < E - 2:
+            z[:, e] = z[:, e - 1]
+    z[:, -2:] = 0.0
+    ref = np.argsort(-z, axis=1, kind="stable")
+    gaps = np.sort(z, axis=1)[:, ::-1]
+    d = gaps[:, :-1] - gaps[:, 1:]
+    ok = ~((d[:, : m + 1] > 0) & (d[:, : m + 1] < 1e-5)).any(axis=1)       # (rows that are near-ties by accident)
+    assert ok.sum() >= N - max(1, N // 20)
+    assert np.array_equal(ids.cpu().numpy()[ok], ref[ok, :k]) and np.array_equal(pid.cpu().numpy()[ok], ref[ok, :m])
+    got = gpu_permute(ids, E)
+    for a, r, nm in zip(got, O.permute(ids.cpu().numpy(), E), ("counts", "offsets", "perm", "inv_perm", "expert_order")):
+        assert np.array_equal(a.cpu().numpy(), r), nm
+    assert np.array_equal(pop.cpu().numpy(), np.bincount(pid.cpu().numpy().ravel(), minlength=E))
+    if N <= 16 or N >= 64:
+        ws = torch.zeros(B.fate_route_fused_workspace(N, E), dtype=torch.uint8, device=DEV)
+        mk = lambda *s, dt=torch.int32: torch.full(s, -3, dtype=dt, device=DEV)
+        f = dict(ids=mk(N, k), w=mk(N, k, dt=torch.float32), pid=mk(N, m), pw=mk(N, m, dt=torch.float32), pop=mk(E))
+        perm = (mk(E), mk(E + 1), mk(N * k), mk(N * k), mk(E))
+        B.fate_route_fused(x, Wg, None, Wg, None, k, m, True, f["ids"], f["w"], f["pid"], f["pw"], f["pop"], *perm, ws)
+        torch.cuda.synchronize()
+        for a, r in zip((f["ids"], f["w"], f["pid"], f["pw"], f["pop"], *perm), (ids, w, pid, pw, pop, *got)):
+            assert torch.equal(a, r)
