@@ -5,7 +5,6 @@
 //
 // fate_route_fused, up to 16 tokens: a workgroup per (token, gate), the last one to leave does
 // popularity and permutation; prefill sizes: both gates in one GEMM launch, then the permutation.
-#include <algorithm>
 #include "common.h"
 #include "route_device.h"
 #include "async_lds.h"
@@ -553,10 +552,8 @@ extern "C" fate_status fate_permute(void* stream, const int32_t* topk_ids, int N
         FATE_FAIL(FATE_EINVAL, "counts, offsets and expert_order must not be NULL");
     if (N > 0 && (topk_ids == nullptr || perm == nullptr || inv_perm == nullptr))
         FATE_FAIL(FATE_EINVAL, "topk_ids, perm and inv_perm must not be NULL when N > 0");
-    // a wave per 64 pairs, at least four for the popularity order of 256 experts (one does everything for 64 pairs)
-    const int waves = N * k <= 64 ? 1 : std::min(kPermMaxWaves, std::max(4, (N * k + 63) / 64));
-    permute_kernel<<<1, 64 * waves, 0, static_cast<hipStream_t>(stream)>>>(topk_ids, N * k, E, counts, offsets, perm,
-                                                                          inv_perm, expert_order);
+    permute_kernel<<<1, 64 * perm_waves(N * k), 0, static_cast<hipStream_t>(stream)>>>(topk_ids, N * k, E, counts,
+                                                                                           offsets, perm, inv_perm, expert_order);
     FATE_HIP(hipGetLastError());
     return FATE_OK;
 }

@@ -3,6 +3,7 @@
 // up to 64 pairs, workgroup form for any number).
 #pragma once
 #include "common.h"
+#include "perm_split.h"
 
 namespace fate {
 
@@ -436,7 +437,6 @@ __device__ __forceinline__ void wave_slot_table(const int32_t* ids, const float*
     }
 }
 
-constexpr int kPermMaxWaves = 16;
 constexpr int kPermSmemInts = (kPermMaxWaves + 2) * kMaxE;
 
 // Stable grouping of P pair indices by expert id, by one workgroup of
@@ -451,11 +451,10 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
     volatile int32_t* excl = tot + E;          // [E] exclusive offsets
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
-    int chunk = (P + nw - 1) / nw;
-    chunk = (chunk + 63) & ~63;
+    const int chunk = perm_chunk(P, nw);
     const int beg = wave * chunk;
-    const int end = min(P, beg + chunk);
-    const int nholding = (P + chunk - 1) / max(chunk, 1);  // waves that hold pairs
+    const int end = perm_end(P, beg, chunk);
+    const int nholding = perm_holding(P, chunk);
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
     // the wave's first kPermCache * 64 ids stay in registers for both passes, requested at once
@@ -481,7 +480,8 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
         mc[it] = 0;
         if (beg + 64 * it < end) mc[it] = count_step(beg + 64 * it, ec[it]);
     }
-    for (int base = beg + 64 * kPermCache; base < end; base += 64) {
+    // (the step past the last pairs may pass 2^31 - 1)
+    for (unsigned base = beg + 64 * kPermCache; base < (unsigned)end; base += 64) {
         int i = base + lane;
         count_step(base, (i < end) ? ids[i] : -1);
     }
@@ -536,7 +536,7 @@ __device__ inline void block_permute(const int32_t* ids, int P, int E, int32_t* 
 #pragma unroll
     for (int it = 0; it < kPermCache; ++it)
         if (beg + 64 * it < end) place_step(beg + 64 * it, ec[it], mc[it]);
-    for (int base = beg + 64 * kPermCache; base < end; base += 64) {
+    for (unsigned base = beg + 64 * kPermCache; base < (unsigned)end; base += 64) {
         int i = base + lane;
         const int e = (i < end) ? ids[i] : -1;
         place_step(base, e, wave_match(e, i < end && e >= 0 && e < E, nbits));

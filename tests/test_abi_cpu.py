@@ -307,6 +307,22 @@ def test_cache_policy_under_address_and_ub_sanitizers(tmp_path):
     assert "cache sanitizer driver: ok" in r.stdout
 
 
+def test_permutation_divides_any_number_of_pairs_among_its_waves(tmp_path):
+    """The wave split of the one-workgroup permutation up to 2^31 - 1 pairs, built with -fsanitize=undefined: a sum past
+    2^31 in it took every wave's counts for empty from 2.02e9 pairs on."""
+    import shutil
+    import subprocess
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    exe = str(tmp_path / "perm_split")
+    b = subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+                        os.path.join(root, "tests", "native", "perm_split_driver.cpp"), "-o", exe], capture_output=True, text=True)
+    assert b.returncode == 0, b.stderr[-2000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "perm split driver: ok" in r.stdout, (r.stdout + r.stderr)[-2000:]
+
+
 def _ffn_need(d, n):
     """Bytes that a call of n tokens asks for (it is refused for want of a workspace before any GPU work)."""
     d.N = n
