@@ -202,12 +202,13 @@ struct GemmFmt {
     static constexpr int depth(int nmt) { return kGemmLds / stage(nmt) < 6 ? kGemmLds / stage(nmt) : 6; }
 };
 
-// One tile with NMT 32-row products.  UP: two matrices and SwiGLU; else one matrix, two row blocks.
+// One tile with NMT 32-row products.  UP: two matrices and SwiGLU; else one matrix, two row blocks.  only: rows that are
+// stored (of a single product).
 // Stage layout: activation rows (16-byte pieces of row r permuted by r & 7: conflict-free
 // ds_read_b128), then per wave the raw weight tiles of both blocks, then per wave 256 bytes of
 // scales and zero-points (lanes 0-15 / 16-31: scales of block 0 / 1, 32-47 / 48-63: zero-points).
 template <int BITS, bool ZP, bool UP, int NMT>
-__device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
+__device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem, uint32_t only = ~0u) {
     typedef GemmFmt<BITS> F;
     constexpr int KT = F::KT, BK = F::BK, TPS = F::TPS, XROW = F::XROW;
     constexpr int SPT = KT / 16;                          // matrix-core steps per weight tile
@@ -372,7 +373,7 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
 #pragma unroll
     for (int mt = 0; mt < NMT; ++mt) {
         const int r = mt * 32 + n;
-        if (r < c.nrows) {
+        if (r < c.nrows && (NMT > 1 || (only >> n) & 1)) {
             if constexpr (UP) {
                 // in pair order a lane's 16 neurons are two pieces of 16 bytes
                 uint4* o = reinterpret_cast<uint4*>(static_cast<__half*>(c.out) + (size_t)r * c.ldo + c.wrow[0]) + 2 * half;
@@ -413,14 +414,14 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem) {
 
 // ---- few rows ------------------------------------------------------------------------------------
 // Tiles of at most 32 rows (decode-sized calls and decode layers: 16 and 8): the codes stream once and everything else is
-// small, so a tile is bounded by the memory path and by the vector instructions that widen the codes.  A 4-bit code enters
-// the matrix cores as u + 16, whose bits are the code's own in the right place and a constant: a shift and an AND-OR per
-// pair of codes.  The fp16 scale multiplies the fp32 sum of a stage's columns (which lie in
-// one group), and the constants' and the zero-point's share, a multiple of the sum of the activations, is what that sum
-// starts from: a product of the activations with a constant.  (Larger constants, or bare
-// bits as denormals, save shifts and lose precision: error of four tokens of the Mixtral shape 2.093e-4, with constants of
-// up to 256 2.099e-4, with denormals 2.5e-4, for no time: the shifts run beside the products.)  Codes of the other
-// widths enter as exact integers.  So weights enter without rounding.  16x16x32 products: 16 rows of activations
+// small, so a tile is bounded by the memory path and by the vector instructions that widen the codes.  A code enters the
+// matrix cores as an exact integer counted from the middle of its range (an AND-OR and a subtraction per pair of codes, for
+// int4 half a shift), and the fp16 scale multiplies the fp32 sum of a stage's columns (which lie in one group): weights
+// enter without rounding.  With a zero-point in memory its distance to the middle times the sum of the activations (a
+// product with ones) is added.  (int4 as u + 16, a shift and an AND-OR, with the constant's share taken off the sum,
+// is 0.6 to 1.6 % faster per layer of 1 to 48 tokens - 8 tokens of the DeepSeek shape 470.9 us for 8 layers, now 477.5; 13
+// of the Qwen shape 353.7 for 6, now 359.5 - but makes an infinite activation NaN and sums through terms four times as
+// large as the products.)  16x16x32 products: 16 rows of activations
 // against 16 rows of weights, whose 16-byte pieces lane (cl = lane / 16, n = lane % 16) reads from the raw tiles in LDS.
 // D: lane (cl, n) holds weight row n, activation rows 4cl .. 4cl + 3.
 // NM: 16-row blocks of activations, R: rows staged (8, or 16 * NM).  KW: waves over which the reduction dimension is split
@@ -444,40 +445,47 @@ struct RowsFmt {
     static constexpr int depth = kGemmLds / stage < 8 ? kGemmLds / stage : 8;
 };
 
-// the codes of step k of a lane's piece (16 or 8 bytes): int4 u + 16, int8 u - 128, int2 u
+// What a code is counted from: u - 8, u - 1.5 (2u - 3 of the symmetric format, halved) and u - 128, exact in fp16.
+constexpr float code_mid(int bits) { return bits == 4 ? 8.f : bits == 2 ? 1.5f : 128.f; }
+
+// the codes of step k of a lane's piece (16 or 8 bytes), less code_mid
 template <int BITS, int BK>
 __device__ __forceinline__ f16x8_t code_step(const uint4& r, int k) {
     u32x4_t v;
+    // a pair whose bits are the code's, in the mantissa of a power of two: that and the middle are taken off again
+    auto less = [](uint32_t w, float one) {
+        const _Float16 h = (_Float16)(one + code_mid(BITS));
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2v_t, w) - f16x2v_t{h, h});
+    };
     if constexpr (BITS == 4) {
-        // pair i of a dword (bits 4i of both halves) to bits 6..9: u + 16
-        auto pair = [](uint32_t r, int i) {
-            return and_or_b32(i < 2 ? r << (6 - 4 * i) : r >> (4 * i - 6), 0x03c003c0u, 0x4c004c00u);
+        // pair i of a dword (bits 4i of both halves)
+        auto pair = [&](uint32_t r, int i) {
+            const uint32_t x = i < 2 ? r : r >> 8;
+            return i & 1 ? less(and_or_b32(x, 0x00f000f0u, 0x54005400u), 64.f) : less(and_or_b32(x, 0x000f000fu, 0x64006400u), 1024.f);
         };
         if constexpr (BK == 128) v = u32x4_t{pair(r.x, k), pair(r.y, k), pair(r.z, k), pair(r.w, k)};
         else v = u32x4_t{pair(r.x, k), pair(r.y, k), pair(r.x, k + 2), pair(r.y, k + 2)};
+    } else if constexpr (BITS == 2) {
+        // field k of both bytes of both halves; field 0 is moved up (1024 + 1.5 is no fp16 number)
+        const int f = k ? k : 1;
+        const uint32_t m = 0x00030003u << (2 * f), o = 0x64006400u - 0x08000800u * f;           // 256, 64, 16
+        const float one = f == 1 ? 256.f : f == 2 ? 64.f : 16.f;
+        auto pair = [&](uint32_t r, int hi) {
+            return less(and_or_b32(hi ? (k ? r >> 8 : r >> 6) : (k ? r : r << 2), m, o), one);
+        };
+        v = u32x4_t{pair(r.x, 0), pair(r.x, 1), pair(r.y, 0), pair(r.y, 1)};
     } else {
-        uint32_t w[4];
-        float one;
-        if constexpr (BITS == 2) {
-            const uint32_t m = 0x00030003u << (2 * k), o = 0x64006400u - 0x08000800u * k;       // 1024, 256, 64, 16
-            w[0] = and_or_b32(r.x, m, o); w[1] = and_or_b32(r.x >> 8, m, o);
-            w[2] = and_or_b32(r.y, m, o); w[3] = and_or_b32(r.y >> 8, m, o);
-            one = k == 0 ? 1024.f : k == 1 ? 256.f : k == 2 ? 64.f : 16.f;
-        } else {
-            const uint32_t a = k ? r.y : r.x, b = k ? r.w : r.z;
-            w[0] = __builtin_amdgcn_perm(0x64646464u, a, 0x04010400u); w[1] = __builtin_amdgcn_perm(0x64646464u, b, 0x04010400u);
-            w[2] = __builtin_amdgcn_perm(0x64646464u, a, 0x04030402u); w[3] = __builtin_amdgcn_perm(0x64646464u, b, 0x04030402u);
-            one = 1152.f;                                 // 1024 + 128
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            v[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2v_t, w[i]) - f16x2v_t{(_Float16)one, (_Float16)one});
+        const uint32_t a = k ? r.y : r.x, b = k ? r.w : r.z;
+        auto pair = [&](uint32_t w, uint32_t sel) { return less(__builtin_amdgcn_perm(0x64646464u, w, sel), 1024.f); };
+        v = u32x4_t{pair(a, 0x04010400u), pair(b, 0x04010400u), pair(a, 0x04030402u), pair(b, 0x04030402u)};
     }
     return __builtin_bit_cast(f16x8_t, v);
 }
 
+// Returns, the same in all waves, the rows that are not stored since one of their activations is infinite (or none): with
+// zero-points only, where an infinite activation times a code and times the zero-point's distance can have both signs.
 template <int BITS, bool ZP, bool UP, int NM, int R, int KW, bool QT, int BK>
-__device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
+__device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
     typedef RowsFmt<BITS, BK, R, KW> F;
     constexpr int KT = F::KT, TPS = F::TPS, KS = F::KS, XROW = F::XROW;
     constexpr int S = F::depth, SB = F::stage;
@@ -543,6 +551,9 @@ __device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int mb = 0; mb < NM; ++mb) out[i >> 1][i & 1][mb] = tot[i >> 1][i & 1][mb] = zero;
+    f32x4_t xall[NM];                                     // sums of the activations: the same in all waves
+#pragma unroll
+    for (int mb = 0; mb < NM; ++mb) xall[mb] = zero;
     // stages done and the end of the current quarter (two waves: of the first one of this wave's two)
     const int nq = c.K / BK;
     int sidx = kw * (nq / 2), quarter = nq * (2 * kw + 1) / 4;
@@ -569,13 +580,7 @@ __device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
             aoff[k][i] = kw * F::xwave + (n & (R - 1)) * XROW + (piece ^ (n & 7)) * 16 +
                          (BITS == 8 ? (cl & 1) * 8 : F::split ? (cl >> 1) * 8 : 0);
         }
-    // What the products of a stage start from: the activations times what the codes carry too much, with the format's own
-    // zero (8; int2: 2u - 3).  A zero-point in memory: its distance to that times the sum of the activations.
-    constexpr bool from_sum = BITS == 4 || (BITS == 2 && !ZP);
-    auto times = [](float v) {
-        const _Float16 h = (_Float16)v;
-        return f16x8_t{h, h, h, h, h, h, h, h};
-    };
+    const f16x8_t ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
     int slot = 0, slot_in = S - 1;
     auto next = [](int i) { return i + 1 == S ? 0 : i + 1; };
 #pragma unroll
@@ -607,20 +612,9 @@ __device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
                 raw[q] = make_uint4(v.x, v.y, 0, 0);
             }
             sv[q] = (float)*reinterpret_cast<const _Float16*>(sl + q * 32);
-            zv[q] = ZP ? (BITS == 4 ? 8.f : 0.f) - (float)*reinterpret_cast<const _Float16*>(sl + 128 + q * 32) : 0.f;
+            zv[q] = ZP ? code_mid(BITS) - (float)*reinterpret_cast<const _Float16*>(sl + 128 + q * 32) : 0.f;
         }
-        f32x4_t start[NM], xsum[NM], acc[4][NM];
-#pragma unroll
-        for (int mb = 0; mb < NM; ++mb) {
-            start[mb] = xsum[mb] = zero;
-#pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                if constexpr (from_sum)
-                    start[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                        av[mb][k], times(BITS == 2 ? -1.5f : -24.f), start[mb], 0, 0, 0);
-                if constexpr (ZP) xsum[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], times(1.f), xsum[mb], 0, 0, 0);
-            }
-        }
+        f32x4_t xsum[NM], acc[4][NM];
         // a block's products, then (behind the next block's) its sums
         auto products = [&](int q) {
 #pragma unroll
@@ -628,9 +622,18 @@ __device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
                 const f16x8_t b = code_step<BITS, BK>(raw[q], k);
 #pragma unroll
                 for (int mb = 0; mb < NM; ++mb)
-                    acc[q][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], b, k ? acc[q][mb] : start[mb], 0, 0, 0);
+                    acc[q][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], b, k ? acc[q][mb] : zero, 0, 0, 0);
             }
         };
+        if constexpr (ZP) {
+#pragma unroll
+            for (int mb = 0; mb < NM; ++mb)
+#pragma unroll
+                for (int k = 0; k < KS; ++k)
+                    xsum[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], ones, k ? xsum[mb] : zero, 0, 0, 0);
+#pragma unroll
+            for (int mb = 0; mb < NM; ++mb) xall[mb] += xsum[mb];
+        }
         auto sums = [&](int q) {
             const float s = BITS == 2 && !ZP ? 2.0f * sv[q] : sv[q];
 #pragma unroll
@@ -691,17 +694,28 @@ __device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
             }
         }
         lds_only_barrier();
-        if (kw > 0) return;
+        if (kw > 0) return 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             out[i >> 1][i & 1][0] = ((tot[i >> 1][i & 1][0] + out[i >> 1][i & 1][0]) + *at(0, i)) + *at(1, i);
+    }
+    uint32_t left = 0;
+    if constexpr (ZP) {
+#pragma unroll
+        for (int mb = 0; mb < NM; ++mb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned long long m = __ballot(!__builtin_isfinite(xall[mb][j]));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) left |= (m >> (16 * q)) & 1 ? 1u << (mb * 16 + 4 * q + j) : 0u;
+            }
     }
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int r = mb * 16 + 4 * cl + j;
-            if (r < c.nrows) {
+            if (r < c.nrows && !(ZP && (left >> r) & 1)) {
                 const int ro = c.orows ? c.orows[r] : r;
                 const size_t row = (size_t)ro * c.ldo;
 #pragma unroll
@@ -723,15 +737,25 @@ __device__ __forceinline__ void gemm_rows(const TileCtx& c, char* smem) {
                 }
             }
         }
+    return left;
 }
 
 template <int BITS, bool ZP, bool UP, int NM, int R, int KW, bool QT>
 __device__ __forceinline__ void rows_tile(const TileCtx& c, char* smem) {
+    uint32_t left;
     if constexpr (BITS == 4) {
-        if (c.group % 128 == 0) gemm_rows<4, ZP, UP, NM, R, KW, QT, 128>(c, smem);
-        else gemm_rows<4, ZP, UP, NM, R, KW, QT, 64>(c, smem);
+        if (c.group % 128 == 0) left = gemm_rows<4, ZP, UP, NM, R, KW, QT, 128>(c, smem);
+        else left = gemm_rows<4, ZP, UP, NM, R, KW, QT, 64>(c, smem);
     } else {
-        gemm_rows<BITS, ZP, UP, NM, R, KW, QT, BITS == 2 ? 128 : 64>(c, smem);
+        left = gemm_rows<BITS, ZP, UP, NM, R, KW, QT, BITS == 2 ? 128 : 64>(c, smem);
+    }
+    if constexpr (ZP) {
+        // rows with an infinite activation (an h past the range of fp16): from the weights' own values
+        if (left) {
+            wait_loads<0>();
+            lds_only_barrier();
+            gemm_pipe<BITS, true, UP, 1>(c, smem, left);
+        }
     }
 }
 

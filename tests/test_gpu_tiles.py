@@ -9,6 +9,7 @@ import torch
 
 from oracle import moe as O
 import paper_2502_12224_amd.binding as B
+from paper_2502_12224_amd.stack import LayerBuffers, layer_forward
 from workloads import SHAPES, gen_expert, gen_gate, gen_hidden
 from helpers import DEV, GpuLayer, f32, ffn_rel_err, gpu_permute, gpu_route, oracle_expert
 from test_gpu_layer_fused import _one_launch_case
@@ -131,3 +132,77 @@ def test_tiles_of_few_rows_in_every_format(bits, group, zp, scale):
     y_ref = O.moe_ffn_grouped(f32(x), ids, w.cpu().numpy().astype(np.float64),
                               {e: oracle_expert(L.host[e]) for e in range(cfg.E)}, [], None)
     assert ffn_rel_err(f32(y), y_ref).max() <= 2e-3
+
+
+def _overflowing(ex, how):
+    """h: intermediate neuron 5 leaves the range of fp16 for about every second token.  x: every W1 and W3 weight positive, a
+    row of W2 of one sign, so that an infinite activation makes h infinite and y infinite of the row's sign."""
+    if how == "h":
+        ex.s1[5], ex.s3[5] = 64.0, 64.0
+    else:
+        for w in (ex.w1, ex.w3, ex.w2):
+            w.fill_(0x7f if ex.bits == 8 else 0xff)
+        ex.w2[1::2] = {8: 0x81, 4: 0x11, 2: 0x00}[ex.bits]
+    return ex
+
+
+@pytest.mark.parametrize("bits,group,zp", [(4, 128, False), (4, 64, False), (4, 128, True), (4, 64, True), (8, 64, False),
+                                           (2, 128, False), (2, 128, True)])
+@pytest.mark.parametrize("how", ["h", "x"])
+@pytest.mark.parametrize("form", ["prefill", "decode", "layer"])
+def test_infinite_activations_are_infinite_in_every_form(form, how, bits, group, zp):
+    """A token whose x is infinite, or whose h leaves the range of fp16: every column of y is what IEEE arithmetic on the
+    stored weights gives, +-inf or NaN (a weight of zero), however many rows its expert has; the other tokens of its tile
+    are as precise as ever.  Tiles of 1 to 33 rows, the decode-sized call, the decode layer."""
+    if form == "layer" and (zp or bits == 2):
+        pytest.skip("the decode layer reads symmetric entries of 4 and 8 bits")
+    rows = FEW_ROWS if form == "prefill" else (1, 8, 5, 2) if form == "decode" else (2, 2, 2, 2)
+    H, I = (256, 256) if form == "prefill" else (256, 4096)
+    cfg = dataclasses.replace(SHAPES["tiny"], name="inf", layers=1, H=H, E=len(rows), k=1, I=I, bits=bits, group=group,
+                              gate_var=1.0 / H)
+    print(f"case {form} infinite {how} bits={bits} group={group} zp={zp}", flush=True)
+    ids = np.random.default_rng(5).permutation(np.repeat(np.arange(cfg.E), rows)).astype(np.int32)[:, None]
+    x = gen_hidden(cfg, len(ids), device=DEV)
+    if how == "x":
+        x.abs_()                            # (all neurons have nearly the same h: a negative sum would make them vanish in fp16)
+        x[::3, 77] = float("inf")
+    w = torch.rand(len(ids), 1, generator=torch.Generator().manual_seed(3)).to(DEV) + 0.1
+    L = GpuLayer(cfg, 0, experts=[])
+    for e in range(cfg.E):
+        L.host[e] = _overflowing(gen_expert(cfg, 0, e, device=DEV, zero_points=zp), how)
+        L.packed[e] = B.PackedExpert(L.host[e], DEV)
+    L.table = B.expert_table([L.packed[e].struct() for e in range(cfg.E)], DEV)
+    if form == "layer":
+        L.Wg, L.bias = torch.zeros(cfg.E, H, dtype=torch.bfloat16, device=DEV), None
+        L.Wg[:, :4] = torch.eye(4, device=DEV)
+        x[:, :4] = 0.0                      # (a gate without infinities: column 77 is not in it)
+        x[torch.arange(len(ids)), torch.from_numpy(ids[:, 0].astype(np.int64))] = 8.0
+        L.Wg[:, 77] = 0.0
+        if how == "x":
+            pytest.skip("an infinite x makes the gate's logits NaN")
+        buf = LayerBuffers(cfg, len(ids), DEV)
+        layer_forward(cfg, L, None, x, buf, one_launch=True)
+        torch.cuda.synchronize()
+        assert buf.status() == 0 and torch.equal(buf.ids.cpu(), torch.from_numpy(ids))
+        y, w = f32(buf.y), buf.w
+    else:
+        y, ws = L.ffn(x, *gpu_permute(torch.from_numpy(ids).to(DEV), cfg.E), w, mode=2 if form == "prefill" else 1, ws_fill=0xff)
+        assert int(ws[:4].view(torch.int32)[0]) == 0
+        y = f32(y)
+    x, w = f32(x).astype(np.float64), w.cpu().numpy().astype(np.float64)
+    experts = [oracle_expert(L.host[e]) for e in range(cfg.E)]
+    infinite = 0
+    for t in range(len(ids)):
+        ex = experts[ids[t, 0]]
+        with np.errstate(all="ignore"):
+            g, u = (ex.W1 * x[t]).sum(axis=1), (ex.W3 * x[t]).sum(axis=1)
+            h = g / (1.0 + np.exp(-g)) * u
+            h[np.abs(h) >= 65520.0] = np.copysign(np.inf, h[np.abs(h) >= 65520.0])
+            ref = w[t, 0] * (ex.W2 * h).sum(axis=1)
+        if np.isinf(h).any():
+            infinite += 1
+            assert not np.isfinite(ref).any() and (ref > 0).any() and (ref < 0).any()
+            assert np.array_equal(np.isnan(y[t]), np.isnan(ref)) and np.array_equal(y[t] > 0, ref > 0), (t, rows[ids[t, 0]])
+        else:
+            assert np.abs(y[t] - ref).max() <= 2e-3 * np.abs(ref).max(), t
+    assert 0 < infinite < len(ids)
