@@ -159,3 +159,30 @@ def test_equal_logits_and_equal_counts_go_to_the_lower_id(E, k, N):
         torch.cuda.synchronize()
         for a, r in zip((f["ids"], f["w"], f["pid"], f["pw"], f["pop"], *perm), (ids, w, pid, pw, pop, *got)):
             assert torch.equal(a, r)
+
+
+@pytest.mark.parametrize("E,masked,k,m,N", [(64, 4, 4, 6, 13), (64, 4, 4, 6, 48), (64, 4, 4, 6, 130), (16, 8, 4, 12, 5), (130, 70, 8, 61, 20),
+                                            (12, 11, 1, 2, 70)])
+def test_masked_experts_and_tokens_without_input(E, masked, k, m, N):
+    """Experts masked by a bias of -inf (all of them equal) behind the selection, across its end and inside it, and tokens
+    whose x is zero (all logits equal): equal logits go to the lower id."""
+    H = 1024
+    print(f"case E={E} masked={masked} k={k} m={m} N={N}", flush=True)
+    cfg = dataclasses.replace(SHAPES["tiny"], H=H, E=E, k=k, gate_var=1.0 / H)
+    x = gen_hidden(cfg, N, device=DEV)
+    x[1::3] = 0.0
+    Wg, _ = gen_gate(cfg, 0, device=DEV)
+    bias = torch.zeros(E, device=DEV)
+    bias[torch.randperm(E, generator=torch.Generator().manual_seed(E))[:masked].to(DEV)] = float("-inf")
+    ids, w, _ = gpu_route(x, Wg, bias, k, False, want_probs=False)
+    pid, pw, pop = gpu_predict(x, Wg, bias, k, m)
+    z = f32(x).astype(np.float64) @ f32(Wg).astype(np.float64).T + bias.cpu().numpy()
+    ref = np.argsort(-z, axis=1, kind="stable")
+    top = -np.sort(-z, axis=1)[:, : m + 1]
+    with np.errstate(invalid="ignore"):
+        d = top[:, :-1] - top[:, 1:]
+    ok = ~((d > 0) & (d < 1e-5)).any(axis=1)               # (rows that are near-ties by accident)
+    assert ok.sum() >= N - max(1, N // 20)
+    assert np.array_equal(ids.cpu().numpy()[ok], ref[ok, :k]) and np.array_equal(pid.cpu().numpy()[ok], ref[ok, :m])
+    assert np.array_equal(pop.cpu().numpy(), np.bincount(pid.cpu().numpy().ravel(), minlength=E))
+    assert (pw.cpu().numpy()[np.isneginf(np.take_along_axis(z, pid.cpu().numpy().astype(np.int64), axis=1))] == 0).all()
