@@ -787,7 +787,8 @@ __device__ __forceinline__ void gemm_tile(const TileCtx& c, char* smem) {
 }
 
 // The routing outputs of a decode layer, by one workgroup beside the layer's up GEMM: selection, prediction,
-// permutation and popularity (at most 64 pairs).
+// permutation and popularity (at most 64 pairs).  One entry at a time: nothing waits for this workgroup, and sixteen in
+// straight-line code cost the kernel around it 8 spilled scalar registers.
 __device__ __forceinline__ void layer_outputs(const LayerOut& o, char* smem) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), P = o.N * o.k;
     float* z = reinterpret_cast<float*>(smem);            // [gates][N][E]
@@ -799,14 +800,14 @@ __device__ __forceinline__ void layer_outputs(const LayerOut& o, char* smem) {
     __syncthreads();
     for (int j = wave; j < njobs; j += 4) {
         const int t = j < o.N ? j : j - o.N;
-        if (j < o.N) wave_softmax_topm(z + (size_t)j * o.E, o.E, o.k, o.renorm, ids + t * o.k, o.w + (size_t)t * o.k, nullptr, nullptr);
-        else wave_softmax_topm(z + (size_t)j * o.E, o.E, o.m, 0, o.pids + (size_t)t * o.m, o.pw + (size_t)t * o.m, nullptr, pop);
+        if (j < o.N) wave_softmax_topm<1>(z + (size_t)j * o.E, o.E, o.k, o.renorm, ids + t * o.k, o.w + (size_t)t * o.k, nullptr, nullptr);
+        else wave_softmax_topm<1>(z + (size_t)j * o.E, o.E, o.m, 0, o.pids + (size_t)t * o.m, o.pw + (size_t)t * o.m, nullptr, pop);
     }
     __syncthreads();
     if (tid < P) o.ids[tid] = ids[tid];
     if (o.pids)
         for (int i = tid; i < o.E; i += 256) o.pop[i] = pop[i];
-    if (wave == 0) wave_permute_small(ids, P, o.E, o.counts, o.offsets, o.perm, o.inv_perm, o.order);
+    if (wave == 0) wave_permute_small<1>(ids, P, o.E, o.counts, o.offsets, o.perm, o.inv_perm, o.order);
     if (tid == 0) *o.calls += 1;
 }
 
