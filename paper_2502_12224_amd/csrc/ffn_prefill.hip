@@ -427,29 +427,34 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem, uint32_t
 // NM: 16-row blocks of activations, R: rows staged (8, or 16 * NM).  KW: waves over which the reduction dimension is split
 // (up projection of a decode layer: tiles of 64 neurons instead of 128).  QT: the columns add up in quarters, whether one
 // wave takes them all or two take two each: h is rounded to fp16 and must not depend on that.
-// Stages: 128 columns for int4 with groups of a multiple of 128 and for int2, 64 for int8 and for int4 otherwise.
+// Stages: 128 columns for int4 with groups of a multiple of 128 and for int2, 64 for int8 and for int4 otherwise.  HS = 2:
+// int4 stages of 128 columns with two groups of 64 each, for decode-sized calls and decode layers, where the barrier of a
+// stage counts: lanes 32..63 bring the second group's scales, zero-points are a load of their own.  Groups of 64 against
+// stages of 64: 13 tokens of the Qwen shape 399 -> 379 us (6 layers), 8 of the DeepSeek shape 394 -> 376 (6).
 // Against 32x32x16 products of codes made exact by a subtraction (16 rows) or of code * scale (32 rows): 48 tokens of the
 // DeepSeek shape (5 rows a tile) up 51.1 -> 40.7, down 34.1 -> 28.8 us; 13 tokens of the Qwen shape 28.7 -> 24.8 (106 MB
 // of codes and scales: 4.3 TB/s) and 17.2 -> 15.4; one token of the Mixtral shape 30.2 -> 26.3 and 17.5 -> 14.9.
-template <int BITS, int BK, int R, int KW>
+template <int BITS, bool ZP, int R, int KW, int BK, int HS>
 struct RowsFmt {
     static constexpr int KT = QFmt<BITS>::KT;
     static constexpr int TPS = BK / KT;                   // weight tiles per stage and block
-    static constexpr int KS = BK / 32;                    // matrix-core steps per stage
-    static constexpr bool split = BITS == 8 || (BITS == 4 && BK == 64); // a step's 8 columns are half of two pieces
+    static constexpr int GC = BK / HS;                    // columns of a sum that takes one scale
+    static constexpr int KS = GC / 32;                    // matrix-core steps of it
+    static constexpr bool split = BITS == 8 || (BITS == 4 && GC == 64); // a step's 8 columns are half of two pieces
     static constexpr int XROW = BK * 2;
     static constexpr int xwave = R * XROW;                // of the waves that share a range of columns
     static constexpr int xbytes = KW * xwave;
+    static constexpr int SL = HS == 2 && ZP ? 2 : 1;      // loads of scales and zero-points
     static constexpr int sc0 = xbytes + 4 * 2 * TPS * 1024;
-    static constexpr int stage = sc0 + 4 * 256;
+    static constexpr int stage = sc0 + 4 * SL * 256;
     static constexpr int depth = kGemmLds / stage < 8 ? kGemmLds / stage : 8;
 };
 
 // What a code is counted from: u - 8, u - 1.5 (2u - 3 of the symmetric format, halved) and u - 128, exact in fp16.
 constexpr float code_mid(int bits) { return bits == 4 ? 8.f : bits == 2 ? 1.5f : 128.f; }
 
-// the codes of step k of a lane's piece (16 or 8 bytes), less code_mid
-template <int BITS, int BK>
+// the codes of step k of a lane's piece (16 or 8 bytes; GC: columns of the sum), less code_mid
+template <int BITS, int GC>
 __device__ __forceinline__ f16x8_t code_step(const uint4& r, int k) {
     u32x4_t v;
     // a pair whose bits are the code's, in the mantissa of a power of two: that and the middle are taken off again
@@ -463,7 +468,7 @@ __device__ __forceinline__ f16x8_t code_step(const uint4& r, int k) {
             const uint32_t x = i < 2 ? r : r >> 8;
             return i & 1 ? less(and_or_b32(x, 0x00f000f0u, 0x54005400u), 64.f) : less(and_or_b32(x, 0x000f000fu, 0x64006400u), 1024.f);
         };
-        if constexpr (BK == 128) v = u32x4_t{pair(r.x, k), pair(r.y, k), pair(r.z, k), pair(r.w, k)};
+        if constexpr (GC == 128) v = u32x4_t{pair(r.x, k), pair(r.y, k), pair(r.z, k), pair(r.w, k)};
         else v = u32x4_t{pair(r.x, k), pair(r.y, k), pair(r.x, k + 2), pair(r.y, k + 2)};
     } else if constexpr (BITS == 2) {
         // field k of both bytes of both halves; field 0 is moved up (1024 + 1.5 is no fp16 number)
@@ -484,14 +489,15 @@ __device__ __forceinline__ f16x8_t code_step(const uint4& r, int k) {
 
 // Returns, the same in all waves, the rows that are not stored since one of their activations is infinite (or none): with
 // zero-points only, where an infinite activation times a code and times the zero-point's distance can have both signs.
-template <int BITS, bool ZP, bool UP, int NM, int R, int KW, bool QT, int BK>
+template <int BITS, bool ZP, bool UP, int NM, int R, int KW, bool QT, int BK, int HS = 1>
 __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
-    typedef RowsFmt<BITS, BK, R, KW> F;
-    constexpr int KT = F::KT, TPS = F::TPS, KS = F::KS, XROW = F::XROW;
+    typedef RowsFmt<BITS, ZP, R, KW, BK, HS> F;
+    constexpr int KT = F::KT, TPS = F::TPS, KS = F::KS, GC = F::GC, SL = F::SL, XROW = F::XROW;
     constexpr int S = F::depth, SB = F::stage;
     constexpr int NX = (F::xwave / 1024 + 4 / KW - 1) / (4 / KW);          // activation loads per wave and stage
-    constexpr int LPS = NX + 2 * TPS + 1;
+    constexpr int LPS = NX + 2 * TPS + SL;
     static_assert(S >= 2, "at least one stage ahead");
+    static_assert(HS == 1 || (BITS == 4 && BK == 128), "two groups of 64 columns");
     static_assert(KW == 1 || (KW == 2 && UP && QT && NM == 1), "the split of the reduction dimension belongs to the up projection");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, cl = lane >> 4;
@@ -512,7 +518,8 @@ __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
         xoff[i] = ((uint32_t)ar * (uint32_t)c.lda + (uint32_t)col0) * 2u + (uint32_t)((q ^ (r & 7)) * 16);
     }
     const char* wbase[2];
-    const char* sbase;                                    // this lane's scale (lanes 0..31) or zero-point address
+    // this lane's scale (HS = 1: lanes 0..31) or zero-point address, HS = 2 with zero-points: theirs
+    const char *sbase, *zbase;
     {
         const void* wp[2] = {UP ? c.ex->w1 : c.ex->w2, UP ? c.ex->w3 : c.ex->w2};
         const void* sp[2] = {UP ? c.ex->s1 : c.ex->s2, UP ? c.ex->s3 : c.ex->s2};
@@ -521,10 +528,13 @@ __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
         for (int i = 0; i < 2; ++i)
             wbase[i] = uniform(static_cast<const char*>(wp[i]) + ((size_t)(c.wrow[i] >> 5) * tiles_k + col0 / KT) * 1024);
         const int b = (lane >> 4) & 1;
-        const void* p0 = ZP && lane >= 32 ? zp[0] : sp[0];
-        const void* p1 = ZP && lane >= 32 ? zp[1] : sp[1];
-        sbase = static_cast<const char*>(b ? p1 : p0) + (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
-                (size_t)(col0 / c.group) * c.Nout * 2;
+        const bool zs = ZP && HS == 1 && lane >= 32;
+        const size_t off = (size_t)(b ? c.wrow[1] : c.wrow[0]) * 2 + (lane & 15) * 4 +
+                           (size_t)(col0 / c.group + (HS == 2 && lane >= 32 ? 1 : 0)) * c.Nout * 2;
+        const void* p0 = zs ? zp[0] : sp[0];
+        const void* p1 = zs ? zp[1] : sp[1];
+        sbase = static_cast<const char*>(b ? p1 : p0) + off;
+        zbase = SL == 2 ? static_cast<const char*>(b ? zp[1] : zp[0]) + off : nullptr;
     }
     const uint32_t lane16 = lane * 16;
     int gcol = col0 % c.group;                            // of the next stage to be requested
@@ -535,13 +545,20 @@ __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
         } else if (l < NX + 2 * TPS) {
             const int i = (l - NX) / TPS, tl = (l - NX) % TPS;
             lds_load16(base + F::xbytes + (wave * 2 * TPS + i * TPS + tl) * 1024, wbase[i] + (size_t)(st * TPS + tl) * 1024, lane16);
-        } else {
-            lds_load4(base + F::sc0 + wave * 256, sbase);
-            gcol += BK;
-            if (gcol >= c.group) {
-                gcol -= c.group;
-                sbase += (size_t)c.Nout * 2;
+        } else if (l == NX + 2 * TPS) {
+            lds_load4(base + F::sc0 + wave * SL * 256, sbase);
+            if constexpr (HS == 2) {
+                sbase += (size_t)c.Nout * 4;
+            } else {
+                gcol += BK;
+                if (gcol >= c.group) {
+                    gcol -= c.group;
+                    sbase += (size_t)c.Nout * 2;
+                }
             }
+        } else {
+            lds_load4(base + F::sc0 + (wave * SL + 1) * 256, zbase);
+            zbase += (size_t)c.Nout * 4;
         }
     };
     // by block of weight rows (half of the wave's block i) and block of activation rows
@@ -567,7 +584,7 @@ __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
             }
     };
     // this lane's piece of a block's raw tiles (rows 0..15 of it; rows 16..31 lie 256 bytes on) and of the activations
-    constexpr bool wide = BITS == 8 || (BITS == 4 && BK == 128);          // the piece: 16 or 8 bytes
+    constexpr bool wide = BITS == 8 || (BITS == 4 && GC == 128);          // the piece: 16 or 8 bytes
     const uint32_t woff = ((cl & 1) * 32 + n) * 16 + (cl >> 1) * (wide ? 1024 : 8);
     uint32_t aoff[KS][F::split ? 2 : 1];
 #pragma unroll
@@ -576,7 +593,7 @@ __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
         for (int i = 0; i < (F::split ? 2 : 1); ++i) {
             const int piece = BITS == 8 ? (cl >> 1) * 4 + 2 * k + i
                             : BITS == 2 ? ((cl & 1) * 2 + (cl >> 1)) * 4 + k
-                            : BK == 64 ? (cl & 1) * 4 + k + 2 * i : cl * 4 + k;
+                            : GC == 64 ? (cl & 1) * 4 + k + 2 * i : cl * 4 + k;
             aoff[k][i] = kw * F::xwave + (n & (R - 1)) * XROW + (piece ^ (n & 7)) * 16 +
                          (BITS == 8 ? (cl & 1) * 8 : F::split ? (cl >> 1) * 8 : 0);
         }
@@ -594,66 +611,72 @@ __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
         else wait_stages<LPS, S - 2>(nstage - 1 - st);
         lds_only_barrier();                               // stage st is in LDS, everyone is done with stage st - 1
         const char* base = smem + slot * SB;
-        const char* wl = base + F::xbytes + wave * (2 * TPS * 1024) + woff;
-        const char* sl = base + F::sc0 + wave * 256 + n * 2;
-        f16x8_t av[NM][KS];
-        uint4 raw[4];
-        float sv[4], zv[4];
+        // the columns of one scale (HS = 2: the stage's halves, a weight tile each)
+        auto columns = [&](auto half) {
+            constexpr int h = half;
+            const char* wl = base + F::xbytes + wave * (2 * TPS * 1024) + h * 1024 + woff;
+            const char* sl = base + F::sc0 + wave * SL * 256 + h * 128 + n * 2;
+            f16x8_t av[NM][KS];
+            uint4 raw[4];
+            float sv[4], zv[4];
 #pragma unroll
-        for (int k = 0; k < KS; ++k)
+            for (int k = 0; k < KS; ++k)
 #pragma unroll
-            for (int mb = 0; mb < NM; ++mb) av[mb][k] = load_piece<F::split ? 2 : 1>(base + mb * 16 * XROW, aoff[k]);
+                for (int mb = 0; mb < NM; ++mb) av[mb][k] = load_piece<F::split ? 2 : 1>(base + mb * 16 * XROW + h * 128, aoff[k]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const char* p = wl + (q >> 1) * TPS * 1024 + (q & 1) * 256;
-            if constexpr (wide) raw[q] = *reinterpret_cast<const uint4*>(p);
-            else {
-                const uint2 v = *reinterpret_cast<const uint2*>(p);
-                raw[q] = make_uint4(v.x, v.y, 0, 0);
+            for (int q = 0; q < 4; ++q) {
+                const char* p = wl + (q >> 1) * TPS * 1024 + (q & 1) * 256;
+                if constexpr (wide) raw[q] = *reinterpret_cast<const uint4*>(p);
+                else {
+                    const uint2 v = *reinterpret_cast<const uint2*>(p);
+                    raw[q] = make_uint4(v.x, v.y, 0, 0);
+                }
+                sv[q] = (float)*reinterpret_cast<const _Float16*>(sl + q * 32);
+                zv[q] = ZP ? code_mid(BITS) - (float)*reinterpret_cast<const _Float16*>(sl + (SL == 2 ? 256 : 128) + q * 32) : 0.f;
             }
-            sv[q] = (float)*reinterpret_cast<const _Float16*>(sl + q * 32);
-            zv[q] = ZP ? code_mid(BITS) - (float)*reinterpret_cast<const _Float16*>(sl + 128 + q * 32) : 0.f;
-        }
-        f32x4_t xsum[NM], acc[4][NM];
-        // a block's products, then (behind the next block's) its sums
-        auto products = [&](int q) {
+            f32x4_t xsum[NM], acc[4][NM];
+            // a block's products, then (behind the next block's) its sums
+            auto products = [&](int q) {
 #pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                const f16x8_t b = code_step<BITS, BK>(raw[q], k);
+                for (int k = 0; k < KS; ++k) {
+                    const f16x8_t b = code_step<BITS, GC>(raw[q], k);
+#pragma unroll
+                    for (int mb = 0; mb < NM; ++mb)
+                        acc[q][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], b, k ? acc[q][mb] : zero, 0, 0, 0);
+                }
+            };
+            if constexpr (ZP) {
 #pragma unroll
                 for (int mb = 0; mb < NM; ++mb)
-                    acc[q][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], b, k ? acc[q][mb] : zero, 0, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < KS; ++k)
+                        xsum[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], ones, k ? xsum[mb] : zero, 0, 0, 0);
+#pragma unroll
+                for (int mb = 0; mb < NM; ++mb) xall[mb] += xsum[mb];
             }
-        };
-        if constexpr (ZP) {
+            auto sums = [&](int q) {
+                const float s = BITS == 2 && !ZP ? 2.0f * sv[q] : sv[q];
 #pragma unroll
-            for (int mb = 0; mb < NM; ++mb)
+                for (int mb = 0; mb < NM; ++mb)
 #pragma unroll
-                for (int k = 0; k < KS; ++k)
-                    xsum[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[mb][k], ones, k ? xsum[mb] : zero, 0, 0, 0);
+                    for (int j = 0; j < 4; ++j) {
+                        const float t = ZP ? fmaf(zv[q], xsum[mb][j], acc[q][mb][j]) : acc[q][mb][j];
+                        out[q >> 1][q & 1][mb][j] = fmaf(s, t, out[q >> 1][q & 1][mb][j]);
+                    }
+            };
 #pragma unroll
-            for (int mb = 0; mb < NM; ++mb) xall[mb] += xsum[mb];
-        }
-        auto sums = [&](int q) {
-            const float s = BITS == 2 && !ZP ? 2.0f * sv[q] : sv[q];
+            for (int q = 0; q < 4; ++q) {
+                products(q);
+                if constexpr (more) {
 #pragma unroll
-            for (int mb = 0; mb < NM; ++mb)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float t = ZP ? fmaf(zv[q], xsum[mb][j], acc[q][mb][j]) : acc[q][mb][j];
-                    out[q >> 1][q & 1][mb][j] = fmaf(s, t, out[q >> 1][q & 1][mb][j]);
+                    for (int l = LPS * (4 * h + q) / (4 * HS); l < LPS * (4 * h + q + 1) / (4 * HS); ++l) issue_one(st + S - 1, slot_in, l);
                 }
-        };
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            products(q);
-            if constexpr (more) {
-#pragma unroll
-                for (int l = LPS * q / 4; l < LPS * (q + 1) / 4; ++l) issue_one(st + S - 1, slot_in, l);
+                if (q) sums(q - 1);
             }
-            if (q) sums(q - 1);
-        }
-        sums(3);
+            sums(3);
+        };
+        columns(std::integral_constant<int, 0>{});
+        if constexpr (HS == 2) columns(std::integral_constant<int, 1>{});
         if constexpr (QT && UP) {
             ++sidx;
             if constexpr (KW == 1) {
@@ -745,6 +768,7 @@ __device__ __forceinline__ void rows_tile(const TileCtx& c, char* smem) {
     uint32_t left;
     if constexpr (BITS == 4) {
         if (c.group % 128 == 0) left = gemm_rows<4, ZP, UP, NM, R, KW, QT, 128>(c, smem);
+        else if (QT && c.K % 128 == 0) left = gemm_rows<4, ZP, UP, NM, R, KW, QT, 128, QT ? 2 : 1>(c, smem);
         else left = gemm_rows<4, ZP, UP, NM, R, KW, QT, 64>(c, smem);
     } else {
         left = gemm_rows<BITS, ZP, UP, NM, R, KW, QT, BITS == 2 ? 128 : 64>(c, smem);

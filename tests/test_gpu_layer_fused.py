@@ -305,6 +305,8 @@ def test_layers_of_two_shapes_share_a_workspace():
     (512, 16, 4, 2048, 4, 256, 0, 0, 3),           # two groups: quarters without any
     (1280, 16, 4, 1280, 4, 256, 0, 0, 6),          # five groups: one wave
     (1024, 16, 4, 1152, 8, 64, 1, 384, 7),
+    (1280, 16, 4, 1152, 4, 64, 1, 384, 8),         # two groups per stage, five stages per wave
+    (1152, 16, 4, 1280, 4, 64, 0, 0, 4),           # the same, nine stages: one wave
 ])
 def test_layer_by_gemms_gives_the_bits_of_the_separate_calls(H, E, k, I, bits, group, n_shared, I_shared, N):
     """The two forms of the decode-sized GEMM differ in how many waves share the columns of the up projection, not in the
