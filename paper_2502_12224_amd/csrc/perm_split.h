@@ -12,10 +12,11 @@ namespace fate {
 
 constexpr int kPermMaxWaves = 16;
 
-// Waves of a permutation's workgroup: one per 64 pairs, at least four for the popularity order of 256 experts (64 pairs are
-// one wave's work altogether).
-FATE_PERM_FN int perm_waves(int P) {
+// Waves of a permutation's workgroup: one per 64 pairs, at least four (64 pairs are one wave's work altogether).  More than
+// 64 experts: all of them, for the popularity order, which they divide among themselves.
+FATE_PERM_FN int perm_waves(int P, int E) {
     if (P <= 64) return 1;
+    if (E > 64) return kPermMaxWaves;
     const unsigned n = ((unsigned)P + 63u) / 64u;
     return n < 4u ? 4 : (n > (unsigned)kPermMaxWaves ? kPermMaxWaves : (int)n);
 }
@@ -27,6 +28,6 @@ FATE_PERM_FN int perm_chunk(int P, int nw) { return (int)((((unsigned)P + (unsig
 FATE_PERM_FN int perm_end(int P, int beg, int chunk) { return P - beg < chunk ? P : beg + chunk; }
 
 // Waves that hold pairs.
-FATE_PERM_FN int perm_holding(int P, int chunk) { return chunk > 0 ? P / chunk + (P % chunk != 0) : 0; }
+FATE_PERM_FN int perm_holding(int P, int chunk) { return chunk > 0 ? (int)(((unsigned)P + (unsigned)chunk - 1u) / (unsigned)chunk) : 0; }
 
 }  // namespace fate

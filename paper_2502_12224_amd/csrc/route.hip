@@ -552,7 +552,7 @@ extern "C" fate_status fate_permute(void* stream, const int32_t* topk_ids, int N
         FATE_FAIL(FATE_EINVAL, "counts, offsets and expert_order must not be NULL");
     if (N > 0 && (topk_ids == nullptr || perm == nullptr || inv_perm == nullptr))
         FATE_FAIL(FATE_EINVAL, "topk_ids, perm and inv_perm must not be NULL when N > 0");
-    permute_kernel<<<1, 64 * perm_waves(N * k), 0, static_cast<hipStream_t>(stream)>>>(topk_ids, N * k, E, counts,
+    permute_kernel<<<1, 64 * perm_waves(N * k, E), 0, static_cast<hipStream_t>(stream)>>>(topk_ids, N * k, E, counts,
                                                                                            offsets, perm, inv_perm, expert_order);
     FATE_HIP(hipGetLastError());
     return FATE_OK;

@@ -31,10 +31,10 @@ int main() {
     const int64_t top = INT32_MAX;
     auto at = [&](int64_t P) {
         if (P < 0 || P > top) return;
-        const int waves = fate::perm_waves((int)P);
+        const int waves = fate::perm_waves((int)P, 64);
         const int64_t groups = (P + 63) / 64;
         const int64_t want = P <= 64 ? 1 : groups < 4 ? 4 : groups > fate::kPermMaxWaves ? fate::kPermMaxWaves : groups;
-        if (waves != want) {
+        if (waves != want || fate::perm_waves((int)P, 65) != (P <= 64 ? 1 : fate::kPermMaxWaves)) {
             std::printf("perm split: %d waves for P = %lld\n", waves, (long long)P);
             std::exit(1);
         }

@@ -51,7 +51,9 @@ def test_cross_layer_predict_matches_oracle(name, N):
 
 
 @pytest.mark.parametrize("N,k,E", [(0, 2, 8), (1, 4, 60), (16, 2, 8), (5, 6, 64), (512, 4, 60), (2048, 6, 64),
-                                   (4096, 8, 256), (1000, 1, 3)])
+                                   (4096, 8, 256), (1000, 1, 3),
+                                   # both sides of the popularity order's two forms, and of the ids kept in registers
+                                   (65, 1, 64), (64, 8, 60), (513, 1, 64), (65, 1, 65), (300, 1, 200), (8193, 1, 64)])
 def test_permute_matches_oracle(N, k, E):
     rng = np.random.default_rng(N * 7 + k)
     # skewed draws without repeats inside a row
