@@ -195,9 +195,15 @@ typedef struct {
  * products exactly: layers whose sizes are multiples of 128 and which make up
  * 128 workgroups of 128 neurons or more go through the matrix-core GEMM in
  * tiles of 16 rows (up to 16 tokens), all others through dequant-GEMV kernels;
- * 2 = MFMA grouped GEMM, weights rounded to fp16 (H, I_max and I_shared_max
- * multiples of 128; N*H, N*k*I_max and n_shared*N*I_shared_max below 2^31;
- * FATE_ESHAPE otherwise).
+ * 2 = MFMA grouped GEMM (H, I_max and I_shared_max multiples of 128; N*H,
+ * N*k*I_max and n_shared*N*I_shared_max below 2^31; FATE_ESHAPE otherwise).
+ * An expert's rows are taken in tiles (of 128 rows, 64 where the layer's or the
+ * entry's width is not 4 bits); in tiles of at most 32 rows weights enter exactly
+ * there, too, in larger ones they are rounded to fp16.  So the bits of a token's y
+ * depend on how many other rows its experts have.
+ * x and h are fp16 in the products: larger values become infinite, and a
+ * token's y is then +-inf or NaN as IEEE arithmetic on the stored weights
+ * gives it (the other tokens' are not touched).
  * Activated experts whose w1 is NULL are skipped and flagged in the int32 at
  * workspace offset 0 (bit 0); an entry whose width / group the kernels cannot
  * read is skipped too (bit 2).

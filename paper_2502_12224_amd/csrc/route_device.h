@@ -3,6 +3,7 @@
 // up to 64 pairs, workgroup form for any number).
 #pragma once
 #include "common.h"
+#include "float_order.h"
 #include "perm_split.h"
 
 namespace fate {
@@ -47,12 +48,6 @@ __device__ __forceinline__ void wave_count_greater(const int (&key)[NS], int E, 
             }
         }
     }
-}
-
-// An integer in the order of the float (both zeros alike), above the least one.
-__device__ __forceinline__ int float_order(float v) {
-    const int b = __float_as_int(v + 0.0f);
-    return b ^ ((b >> 31) & 0x7fffffff);
 }
 
 // rank[i] = place of entry lane + 64 * i among the E logits in v, by logit descending, ties to the lower index, for the

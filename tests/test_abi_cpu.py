@@ -307,20 +307,30 @@ def test_cache_policy_under_address_and_ub_sanitizers(tmp_path):
     assert "cache sanitizer driver: ok" in r.stdout
 
 
-def test_permutation_divides_any_number_of_pairs_among_its_waves(tmp_path):
-    """The wave split of the one-workgroup permutation up to 2^31 - 1 pairs, built with -fsanitize=undefined: a sum past
-    2^31 in it took every wave's counts for empty from 2.02e9 pairs on."""
+def _run_native(tmp_path, name):
+    """Compiles tests/native/<name>_driver.cpp with -fsanitize=undefined and runs it."""
     import shutil
     import subprocess
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
-    exe = str(tmp_path / "perm_split")
+    exe = str(tmp_path / name)
     b = subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all",
-                        os.path.join(root, "tests", "native", "perm_split_driver.cpp"), "-o", exe], capture_output=True, text=True)
+                        os.path.join(root, "tests", "native", name + "_driver.cpp"), "-o", exe], capture_output=True, text=True)
     assert b.returncode == 0, b.stderr[-2000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0 and "perm split driver: ok" in r.stdout, (r.stdout + r.stderr)[-2000:]
+    assert r.returncode == 0 and name.replace("_", " ") + " driver: ok" in r.stdout, (r.stdout + r.stderr)[-2000:]
+
+
+def test_permutation_divides_any_number_of_pairs_among_its_waves(tmp_path):
+    """The wave split of the one-workgroup permutation up to 2^31 - 1 pairs: a sum past 2^31 in it took every wave's counts
+    for empty from 2.02e9 pairs on."""
+    _run_native(tmp_path, "perm_split")
+
+
+def test_keys_of_logits_are_in_the_order_of_the_logits(tmp_path):
+    """The integers by which logits are ranked; both zeros are one."""
+    _run_native(tmp_path, "float_order")
 
 
 def _ffn_need(d, n):

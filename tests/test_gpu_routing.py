@@ -123,7 +123,7 @@ def test_gates_of_odd_sizes_over_many_tokens_match_oracle(H, E, k, N):
                                    (200, 8, 64), (256, 8, 130)])
 def test_equal_logits_and_equal_counts_go_to_the_lower_id(E, k, N):
     """Every third gate row is the row before it (equal logits in every token, whatever the order of summation), the last
-    rows are zero and of both signs; sizes at both sides of the selection's blocks of 16 and 64 entries.  All calls that
+    two rows are zero; sizes at both sides of the selection's blocks of 16 and 64 entries.  All calls that
     select agree with the oracle's order, and experts with equal counts are ordered by id."""
     H = 1024
     print(f"case E={E} k={k} N={N}", flush=True)
@@ -132,7 +132,7 @@ def test_equal_logits_and_equal_counts_go_to_the_lower_id(E, k, N):
     Wg, _ = gen_gate(cfg, 0, device=DEV)
     for e in range(2, E, 3):
         Wg[e] = Wg[e - 1]
-    Wg[-1], Wg[-2] = 0.0, -0.0
+    Wg[-2:] = 0.0
     m = min(E, k + 3)
     ids, w, _ = gpu_route(x, Wg, None, k, True, want_probs=False)
     pid, pw, pop = gpu_predict(x, Wg, None, k, m)
