@@ -432,8 +432,10 @@ __device__ __forceinline__ void gemm_pipe(const TileCtx& c, char* smem, uint32_t
 // stage counts: lanes 32..63 bring the second group's scales, zero-points are a load of their own.  Groups of 64 against
 // stages of 64: 13 tokens of the Qwen shape 399 -> 379 us (6 layers), 8 of the DeepSeek shape 394 -> 376 (6).
 // Against 32x32x16 products of codes made exact by a subtraction (16 rows) or of code * scale (32 rows): 48 tokens of the
-// DeepSeek shape (5 rows a tile) up 51.1 -> 40.7, down 34.1 -> 28.8 us; 13 tokens of the Qwen shape 28.7 -> 24.8 (106 MB
-// of codes and scales: 4.3 TB/s) and 17.2 -> 15.4; one token of the Mixtral shape 30.2 -> 26.3 and 17.5 -> 14.9.
+// DeepSeek shape (5 rows a tile) up 51.1 -> 41.0, down 34.1 -> 29.2 us; 13 tokens of the Qwen shape 28.7 -> 24.6 (106 MB
+// of codes and scales: 4.3 TB/s) and 17.2 -> 15.7; one token of the Mixtral shape 30.2 -> 26.8 and 17.5 -> 14.8.  By counters
+// (these three, 1.8 to 2.1 GHz): 13 vector instructions per matrix instruction, the matrix pipe busy 9 to 15 %, waves
+// waiting for memory or a barrier 28 to 40 % and for an issue slot 13 to 34 % of their time.
 template <int BITS, bool ZP, int R, int KW, int BK, int HS>
 struct RowsFmt {
     static constexpr int KT = QFmt<BITS>::KT;
