@@ -28,6 +28,7 @@
 // of the Mixtral shape, 271 -> 200 and 148 -> 124 us at 2048 tokens of the Qwen shape.
 #include <hip/hip_fp16.h>
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include "common.h"
 #include "qformat.h"
@@ -841,7 +842,7 @@ __device__ __forceinline__ void layer_outputs(const LayerOut& o, char* smem) {
 // MODE 2: the same inside a decode layer (at most 8 tokens, 64 pairs): no tile table; a workgroup finds its
 // expert and rows by itself, the up GEMM's from the logits and the down GEMM's from the selection; rows of h
 // and of the outputs are pairs.  The up GEMM's first workgroup writes the layer's routing outputs.
-template <bool UP, int MODE, int KW>
+template <bool UP, int MODE, int KWR, int KWS>
 __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     extern __shared__ uint4 gemm_smem[];
     char* smem = reinterpret_cast<char*>(gemm_smem);
@@ -941,7 +942,8 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     TileCtx c;
     c.ex = ex;
     c.nrows = min(trows, T - row0);
-    constexpr int kBN = UP ? kBNUp / KW : kBNDown;
+    // waves over which the columns are split, weight rows of the tile
+    const int kw = MODE != 2 || !UP ? 1 : KWR == KWS ? KWR : (is_shared ? KWS : KWR), bn = UP ? kBNUp / kw : kBNDown;
     c.Nout = UP ? uniform(ex->I) : a.H;
     c.K = UP ? a.H : uniform(ex->I);
     if (c.nrows <= 0) return;
@@ -981,11 +983,11 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         }
         return;
     }
-    if (UP && nblk * kBN >= c.Nout) return;
+    if (UP && nblk * bn >= c.Nout) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int wr = UP ? nblk * kBN + wave / KW * 32 : nblk * kBNDown + wave * 64 + i * 32;
+        const int wr = UP ? nblk * bn + wave / kw * 32 : nblk * kBNDown + wave * 64 + i * 32;
         c.wlive[i] = wr < c.Nout;
         c.wrow[i] = c.wlive[i] ? wr : 0;
     }
@@ -1010,8 +1012,12 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         c.A += (size_t)out_row0 * c.lda;
     }
     if constexpr (MODE == 2) {
-        if (bits == 4) rows_tile<4, false, UP, 1, 8, KW, true>(c, smem);
-        else rows_tile<8, false, UP, 1, 8, KW, true>(c, smem);
+        auto tile = [&](auto KW) {
+            if (bits == 4) rows_tile<4, false, UP, 1, 8, KW, true>(c, smem);
+            else rows_tile<8, false, UP, 1, 8, KW, true>(c, smem);
+        };
+        if (KWR == KWS || !is_shared) tile(std::integral_constant<int, KWR>{});
+        else tile(std::integral_constant<int, KWS>{});
     } else if constexpr (MODE == 1) {
         if (has_z && bits == 4) rows_tile<4, true, UP, 1, 16, 1, true>(c, smem);
         else if (has_z) rows_tile<2, true, UP, 1, 16, 1, true>(c, smem);
@@ -1027,9 +1033,9 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     }
 }
 
-template <bool UP, int MODE, int KW>
+template <bool UP, int MODE, int KWR, int KWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void grouped_gemm_kernel(GemmArgs a) {
-    grouped_gemm_body<UP, MODE, KW>(a);
+    grouped_gemm_body<UP, MODE, KWR, KWS>(a);
 }
 
 // acc += wgt[i] * row i of src, columns c*V .. c*V + V - 1.  With few tokens the rows' latency is all there
@@ -1158,19 +1164,31 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
     const bool do_up = phase != 2, do_down = phase != 1;
     static bool attr_done = false;
     if (!attr_done) {
-#define FATE_GEMM_ATTR(UP, MODE, KW)                                                                 \
-    FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<UP, MODE, KW>),   \
+#define FATE_GEMM_ATTR(UP, MODE, KWR, KWS)                                                                \
+    FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<UP, MODE, KWR, KWS>),  \
                                  hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        FATE_GEMM_ATTR(true, 0, 1) FATE_GEMM_ATTR(false, 0, 1)
-        FATE_GEMM_ATTR(true, 1, 1) FATE_GEMM_ATTR(false, 1, 1)
-        FATE_GEMM_ATTR(true, 2, 1) FATE_GEMM_ATTR(false, 2, 1)
-        FATE_GEMM_ATTR(true, 2, 2)
+        FATE_GEMM_ATTR(true, 0, 1, 1) FATE_GEMM_ATTR(false, 0, 1, 1)
+        FATE_GEMM_ATTR(true, 1, 1, 1) FATE_GEMM_ATTR(false, 1, 1, 1)
+        FATE_GEMM_ATTR(true, 2, 1, 1) FATE_GEMM_ATTR(false, 2, 1, 1)
+        FATE_GEMM_ATTR(true, 2, 2, 2) FATE_GEMM_ATTR(true, 2, 1, 2)
 #undef FATE_GEMM_ATTR
         attr_done = true;
     }
     // Decode layer: the columns of the up projection are split over pairs of waves if they can be (whole stages of 128,
-    // whole groups)
-    const int kw = mode.layer && d.H % 256 == 0 && (d.H / d.group) % 2 == 0 && (!d.n_shared || (d.H / d.shared_group) % 2 == 0) ? 2 : 1;
+    // whole groups): tiles of 64 neurons instead of 128.  Where those are more than the device holds at once, 4-bit routed
+    // experts keep whole tiles if then all are held: a second round's tiles would start, and select, when the first one's
+    // end (8 tokens of the DeepSeek shape, 814 tiles for 512 places or 429: up projection 33.1 -> 30.0 us; 8 of the Qwen
+    // shape 616 / 352, layer 47.3 -> 45.2 us; 5 of the DeepSeek shape 592 / 318, 51.9 -> 50.2; but with places to spare fewer
+    // tiles read slower: 2 of the Qwen shape 29.5 -> 34.0, 4 36.6 -> 37.6).
+    const bool can_split = mode.layer && d.H % 256 == 0 && (d.H / d.group) % 2 == 0 && (!d.n_shared || (d.H / d.shared_group) % 2 == 0);
+    int kw_r = can_split ? 2 : 1;
+    const int kw_s = kw_r;
+    if (can_split && d.bits == 4) {
+        // distinct experts of N draws of k out of E
+        const double distinct = d.E * (1.0 - std::pow(1.0 - (double)d.k / d.E, d.N));
+        const double routed = distinct * nb.r_up, shared = 2.0 * d.n_shared * nb.s_up;
+        if (2.0 * routed + shared > 1.1 * kGemmSlots && routed + shared <= kGemmSlots) kw_r = 1;
+    }
     if (do_up && !mode.layer) {
         prefill_prep_kernel<<<sel.first ? d.N : 1, 256, 0, st>>>(da.x, d.N, d.H, d.E, d.n_shared, da.offsets,
                                                                  da.order, da.shared_gate, ms.xh, ms.sgate, ms.tab_up, ms.tab_down,
@@ -1188,15 +1206,16 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
     if (do_up) {
         g.A_r = ms.xh; g.lda_r = d.H; g.A_s = ms.xh; g.lda_s = d.H; g.segs = ms.tab_up;
         g.out_r = da.h_r; g.ldo_r = da.ldh_r; g.out_s = da.h_s; g.ldo_s = da.ldh_s;
-        g.nb_r = nb.r_up * kw; g.nb_s = nb.s_up * kw;
+        g.nb_r = nb.r_up * kw_r; g.nb_s = nb.s_up * kw_s;
         g.kp_r = g.kp_s = 1;
-        const long long grid = (mb_r * nb.r_up + d.n_shared * mb_s * nb.s_up) * kw + (mode.layer ? 1 : 0);
+        const long long grid = mb_r * g.nb_r + d.n_shared * mb_s * g.nb_s + (mode.layer ? 1 : 0);
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
         const unsigned ng = (unsigned)grid;
-        if (mode.layer && kw == 2) grouped_gemm_kernel<true, 2, 2><<<ng, 256, kGemmLds, st>>>(g);
-        else if (mode.layer) grouped_gemm_kernel<true, 2, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else if (exact) grouped_gemm_kernel<true, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else grouped_gemm_kernel<true, 0, 1><<<ng, 256, kGemmLds, st>>>(g);
+        if (mode.layer && kw_r == 2) grouped_gemm_kernel<true, 2, 2, 2><<<ng, 256, kGemmLds, st>>>(g);
+        else if (mode.layer && kw_s == 2) grouped_gemm_kernel<true, 2, 1, 2><<<ng, 256, kGemmLds, st>>>(g);
+        else if (mode.layer) grouped_gemm_kernel<true, 2, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else if (exact) grouped_gemm_kernel<true, 1, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<true, 0, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
     }
     if (do_down) {
@@ -1209,9 +1228,9 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
         const long long grid = (mb_r * kp_r + d.n_shared * mb_s * kp_s) * nb_down;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
         const unsigned ng = (unsigned)grid;
-        if (mode.layer) grouped_gemm_kernel<false, 2, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else if (exact) grouped_gemm_kernel<false, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else grouped_gemm_kernel<false, 0, 1><<<ng, 256, kGemmLds, st>>>(g);
+        if (mode.layer) grouped_gemm_kernel<false, 2, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else if (exact) grouped_gemm_kernel<false, 1, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<false, 0, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
         if (sel.last) {
             float* y32 = d.y_is_fp32 ? static_cast<float*>(y_out) : nullptr;

@@ -323,3 +323,13 @@ def test_layer_by_gemms_gives_the_bits_of_the_separate_calls(H, E, k, I, bits, g
     assert one.status() == 0
     for f in ROUTE_FIELDS + ("y",):
         assert torch.equal(getattr(one, f), getattr(sep, f)), f
+
+
+@pytest.mark.parametrize("H,E,k,I,group,n_shared,I_shared,N", [
+    (512, 64, 6, 1408, 128, 2, 384, 8),            # about 35 experts: 814 tiles of 64 neurons, whole routed ones instead
+    (1024, 48, 8, 1152, 64, 0, 0, 7),              # the same in groups of 64
+    (512, 64, 6, 1536, 256, 1, 2048, 8),           # of 256: a group per range of columns
+    (512, 64, 6, 1408, 128, 2, 384, 4),            # fewer tokens: split tiles for both
+])
+def test_layer_of_whole_routed_and_split_shared_tiles_gives_the_bits_of_the_separate_calls(H, E, k, I, group, n_shared, I_shared, N):
+    test_layer_by_gemms_gives_the_bits_of_the_separate_calls(H, E, k, I, 4, group, n_shared, I_shared, N)
