@@ -93,7 +93,7 @@ __device__ __forceinline__ void b1_up_issue(const WorkCtx& c, B1UpRegs<TPG>& R, 
         for (int i = 0; i < 2; ++i) R.scr[i][jg] = ad.sc[i][(size_t)jg * c.I];
 }
 
-template <int BITS, int TPG, class StoreX>
+template <int BITS, int TPG, bool FENCED, class StoreX>
 __device__ __forceinline__ uint32_t b1_up_compute(const WorkCtx& c, B1UpRegs<TPG>& R, StoreX&& store_x) {
     constexpr int KT = QFmt<BITS>::KT, D = kUpRing;
     const int tid = c.tid, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -128,8 +128,8 @@ __device__ __forceinline__ uint32_t b1_up_compute(const WorkCtx& c, B1UpRegs<TPG
     const _Float16* xa = c.xs + arow * c.ldx + half * (KT / 2) + (size_t)wave * tw * KT;
     const float* cxg = c.cx + g_beg * kCxLd;
     for (int r = 0; r + 1 < rounds; ++r)
-        up_round<BITS, TPG, true>(R.raw, R.scr, ad.wt, ad.sc, I, r, xa, cxg, ctok, bc, out, [] {});
-    up_round<BITS, TPG, false>(R.raw, R.scr, ad.wt, ad.sc, I, rounds - 1, xa, cxg, ctok, bc, out, [] {});
+        up_round<BITS, TPG, true, FENCED>(R.raw, R.scr, ad.wt, ad.sc, I, r, xa, cxg, ctok, bc, out, [] {});
+    up_round<BITS, TPG, false, FENCED>(R.raw, R.scr, ad.wt, ad.sc, I, rounds - 1, xa, cxg, ctok, bc, out, [] {});
     if (half == 0) {
         c.red[(wave * 2 + 0) * 32 + n] = out[0][0];
         c.red[(wave * 2 + 1) * 32 + n] = out[1][0];
@@ -242,7 +242,23 @@ __device__ __forceinline__ bool b1_entry_usable(const fate_qexpert& ex, int bits
            ex.z1 == nullptr;
 }
 
-template <int BR, int TR, int BS, int TS, bool HINTED>
+// A table entry read from LDS is the same in every lane.  The kernel of three waves keeps it in
+// scalar registers: its vector registers have no room for the pointers.
+template <int WPE>
+__device__ __forceinline__ fate_qexpert b1_entry(const fate_qexpert& e) {
+    if constexpr (WPE == 2) return e;
+    constexpr int kWords = sizeof(fate_qexpert) / 4;
+    static_assert(sizeof(fate_qexpert) % 4 == 0, "whole words");
+    struct Words {
+        uint32_t w[kWords];
+    };
+    Words v = __builtin_bit_cast(Words, e);
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) v.w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v.w[i]);
+    return __builtin_bit_cast(fate_qexpert, v);
+}
+
+template <int BR, int TR, int BS, int TS, int WPE, bool HINTED>
 __device__ __forceinline__ void b1_up_role(const B1Args& A, int ub, bool is_shared, uint32_t tag, char* dyn) {
     const LayerArgs& a = A.a;
     const int tid = threadIdx.x;
@@ -289,7 +305,7 @@ __device__ __forceinline__ void b1_up_role(const B1Args& A, int ub, bool is_shar
             cx.I = ex.I; cx.kb = kb; cx.ex = ex;
             B1UpRegs<TS> R;
             b1_up_issue<BS, TS>(cx, R, load_x);
-            hbits = b1_up_compute<BS, TS>(cx, R, store_x);
+            hbits = b1_up_compute<BS, TS, WPE == 3>(cx, R, store_x);
         }
         b1_publish_h(hq_dst, tag, hbits);
         return;
@@ -327,7 +343,7 @@ __device__ __forceinline__ void b1_up_role(const B1Args& A, int ub, bool is_shar
     }
     bool ready = in_flight && e_true == e_cur;
     if (!ready && e_true >= 0) {
-        const fate_qexpert ex = reinterpret_cast<const fate_qexpert*>(tab)[e_true];
+        const fate_qexpert ex = b1_entry<WPE>(reinterpret_cast<const fate_qexpert*>(tab)[e_true]);
         const bool usable = b1_entry_usable(ex, a.bits_r, a.group_r);
         if (!usable && tid == 0) atomicOr(a.status, 1);
         if (usable && kb * kLayerNeurons < ex.I) {
@@ -337,7 +353,7 @@ __device__ __forceinline__ void b1_up_role(const B1Args& A, int ub, bool is_shar
         }
     }
     uint32_t hbits = 0;
-    if (ready) hbits = b1_up_compute<BR, TR>(cx, R, store_x);
+    if (ready) hbits = b1_up_compute<BR, TR, WPE == 3>(cx, R, store_x);
     b1_publish_h(hq_dst, tag, hbits);
 }
 
@@ -371,7 +387,7 @@ __device__ __forceinline__ int b1_down_request(const fate_qexpert& ex, int H, in
 // u + C (one v_and_or_b32 per pair); the constant's share, C + zero times the sum of the group's h,
 // leaves per group - every lane holds one tagged word of a group of 128, so that sum is one wave
 // reduction per group.  Returns the item's contribution to output row rb*32 + n in lanes 0..31.
-template <int BITS, int TPG>
+template <int BITS, int TPG, int CHAINS>
 __device__ __forceinline__ float b1_down_product(const uint4 (&raw)[kB1MaxTiles], const uint32_t (&sc)[kB1MaxTiles / TPG],
                                                  int ng, const unsigned long long* hq_src, uint32_t tag, _Float16* hl,
                                                  const _Float16* zrow, bool* failed,
@@ -418,12 +434,12 @@ __device__ __forceinline__ float b1_down_product(const uint4 (&raw)[kB1MaxTiles]
     const BiasConst bc = bias_const();
     const f32x16_t zero = f32x16_zero();
     float out = 0.f;
-    // two groups at a time, each with an accumulator of its own: the dependent matrix-core steps
-    // of one group run under those of the other
+    // CHAINS groups at a time, each with an accumulator of its own: with two, the dependent
+    // matrix-core steps of one group run under those of the other; one needs fewer registers
 #pragma unroll
-    for (int jg = 0; jg < MAXG; jg += 2) {
+    for (int jg = 0; jg < MAXG; jg += CHAINS) {
         constexpr bool kOdd = MAXG % 2 != 0;
-        const bool pair = !kOdd || jg + 1 < MAXG;
+        const bool pair = CHAINS == 2 && (!kOdd || jg + 1 < MAXG);
         f32x16_t acc0, acc1 = zero;
 #pragma unroll
         for (int tl = 0; tl < TPG; ++tl) {
@@ -442,6 +458,7 @@ __device__ __forceinline__ float b1_down_product(const uint4 (&raw)[kB1MaxTiles]
                 if (pair)
                     acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[st], b1[st], (tl == 0 && st == 0) ? zero : acc1, 0, 0, 0);
             }
+            if constexpr (CHAINS == 1) __builtin_amdgcn_sched_barrier(0);
         }
         // groups past the item's end multiply stale h with repeated tiles: they do not count
         if (jg < ng) out = fmaf(half_bits_to_float(sc[jg]), acc0[0] - ch[jg], out);
@@ -450,7 +467,7 @@ __device__ __forceinline__ float b1_down_product(const uint4 (&raw)[kB1MaxTiles]
     return out;
 }
 
-template <int BR, int TR, int BS, int TS>
+template <int BR, int TR, int BS, int TS, int WPE>
 __device__ __forceinline__ void b1_down_role(const B1Args& A, int part, int rb, uint32_t tag, char* dyn) {
     const LayerArgs& a = A.a;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -522,7 +539,7 @@ __device__ __forceinline__ void b1_down_role(const B1Args& A, int part, int rb, 
         if (itr.ng > 0 && e_true != e_cur) {
             ng_r = 0;
             if (e_true >= 0) {
-                const fate_qexpert ex = reinterpret_cast<const fate_qexpert*>(tab)[e_true];
+                const fate_qexpert ex = b1_entry<WPE>(reinterpret_cast<const fate_qexpert*>(tab)[e_true]);
                 ng_r = b1_down_request<BR, TR>(ex, H, rb, itr.g0, itr.ng, raw_r, sc_r);
             }
         }
@@ -532,9 +549,9 @@ __device__ __forceinline__ void b1_down_role(const B1Args& A, int part, int rb, 
         wsrc = wv[rank];
     }
     // the shared piece first: its h exists long before the routed one
-    if (ng_s > 0) out_s = b1_down_product<BS, TS>(raw_s, sc_s, ng_s, hq_s, tag, hl, zrow, &failed);
+    if (ng_s > 0) out_s = b1_down_product<BS, TS, WPE == 2 ? 2 : 1>(raw_s, sc_s, ng_s, hq_s, tag, hl, zrow, &failed);
     if (ng_r > 0 && !failed)
-        out_r = b1_down_product<BR, TR>(raw_r, sc_r, ng_r, hq_r, tag, hl, zrow, &failed, side, &side_val);
+        out_r = b1_down_product<BR, TR, WPE == 2 ? 2 : 1>(raw_r, sc_r, ng_r, hq_r, tag, hl, zrow, &failed, side, &side_val);
     if (failed && lane == 0) atomicOr(a.status, 2);
     if (lane < 32) {
         red_s[wave * 32 + lane] = out_s;
@@ -577,8 +594,9 @@ __device__ __forceinline__ void b1_down_role(const B1Args& A, int part, int rb, 
     }
 }
 
-template <int BR, int TR, int BS, int TS>
-__global__ __launch_bounds__(kLayerThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void moe_layer_decode_b1_kernel(B1Args A) {
+// WPE: waves per SIMD, 2 or 3 (see the launch).
+template <int BR, int TR, int BS, int TS, int WPE>
+__global__ __launch_bounds__(kLayerThreads) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void moe_layer_decode_b1_kernel(B1Args A) {
     extern __shared__ uint4 smem[];
     __shared__ FusedRouteSmem rsm;
     char* dyn = reinterpret_cast<char*>(smem);
@@ -590,13 +608,13 @@ __global__ __launch_bounds__(kLayerThreads) __attribute__((amdgpu_waves_per_eu(2
     if (b < a.nb_route) {
         route_role(a, b, tag, dyn, rsm);
     } else if ((b -= a.nb_route) < A.n_up_s) {
-        b1_up_role<BR, TR, BS, TS, false>(A, b, true, tag, dyn);
+        b1_up_role<BR, TR, BS, TS, WPE, false>(A, b, true, tag, dyn);
     } else if ((b -= A.n_up_s) < A.n_up_r) {
         // (two copies of the routed up block: without a hint there is one place that asks for weights)
-        if (a.hint != nullptr) b1_up_role<BR, TR, BS, TS, true>(A, b, false, tag, dyn);
-        else b1_up_role<BR, TR, BS, TS, false>(A, b, false, tag, dyn);
+        if (a.hint != nullptr) b1_up_role<BR, TR, BS, TS, WPE, true>(A, b, false, tag, dyn);
+        else b1_up_role<BR, TR, BS, TS, WPE, false>(A, b, false, tag, dyn);
     } else if ((b -= A.n_up_r) < nd) {
-        b1_down_role<BR, TR, BS, TS>(A, b / A.nrb, b % A.nrb, tag, dyn);
+        b1_down_role<BR, TR, BS, TS, WPE>(A, b / A.nrb, b % A.nrb, tag, dyn);
     }
     // the workgroup that leaves last opens the next epoch
     __syncthreads();
@@ -617,7 +635,7 @@ template <int BR, int TR, int BS, int TS>
 static int b1_occupancy(int lds) {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, reinterpret_cast<const void*>(moe_layer_decode_b1_kernel<BR, TR, BS, TS>), kLayerThreads,
+            &nb, reinterpret_cast<const void*>(moe_layer_decode_b1_kernel<BR, TR, BS, TS, 2>), kLayerThreads,
             (size_t)lds) != hipSuccess)
         return 0;
     return nb;
@@ -647,7 +665,7 @@ int b1_resident_blocks(const fate_ffn_desc& d) {
 #define FATE_B1_OCC(BR, TR, BS, TS) per_cu = b1_occupancy<BR, TR, BS, TS>(lds);
         FATE_B1_SWITCH(d.bits, bits_s, FATE_B1_OCC)
 #undef FATE_B1_OCC
-        val[key] = per_cu;
+        val[key] = std::min(per_cu, 2);       // (the kernel of two waves per SIMD)
         key_lds[key] = lds;
     }
     return val[key] * cached_cu;
@@ -703,8 +721,16 @@ bool b1_plan(const fate_ffn_desc& d, const LayerArgs& a, B1Args* b, int* nblocks
 fate_status launch_layer_decode_b1(hipStream_t st, const fate_ffn_desc& d, const B1Args& b, int nblocks) {
     const int bits_s = d.n_shared ? d.shared_bits : d.bits;
     const int lds = b1_lds_bytes(d);
+    // Workgroups beyond two per compute unit would start as earlier ones leave, and the down blocks
+    // among them would ask for their weights only then: such launches take the kernel of three waves
+    // per SIMD.  64 experts, 6 selected, H 2048, 576 workgroups: 22.1 us a layer with two, 18.1 with
+    // three.  It has 168 registers instead of 256 and therefore multiplies tile by tile, one
+    // accumulator at a time, which costs where nothing has to wait: 60 experts, 4 selected, 496
+    // workgroups: 17.3 us with two, 17.5 with three.  Same sums, same order, same bits.
+    const bool three = nblocks > b1_resident_blocks(d);
 #define FATE_B1_LAUNCH(BR, TR, BS, TS) \
-    moe_layer_decode_b1_kernel<BR, TR, BS, TS><<<nblocks, kLayerThreads, lds, st>>>(b);
+    if (!three) moe_layer_decode_b1_kernel<BR, TR, BS, TS, 2><<<nblocks, kLayerThreads, lds, st>>>(b); \
+    else moe_layer_decode_b1_kernel<BR, TR, BS, TS, 3><<<nblocks, kLayerThreads, lds, st>>>(b);
     FATE_B1_SWITCH(d.bits, bits_s, FATE_B1_LAUNCH)
 #undef FATE_B1_LAUNCH
     FATE_HIP(hipGetLastError());

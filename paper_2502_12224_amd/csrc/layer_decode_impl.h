@@ -155,8 +155,9 @@ constexpr int kCxLd = kTokPass + 1;      // bias sums per group: tokens 0..7 and
 
 // one ring of the up projection: D tiles of both matrices, straight-line so that the compiler
 // can wait for exactly the tile it needs
-// (mid: called once half of the ring's registers are free again)
-template <int BITS, int TPG, bool REFILL, class Mid>
+// (mid: called once half of the ring's registers are free again; FENCED: the compiler does not work
+// on two tiles at once, for kernels whose registers for that would be spilled)
+template <int BITS, int TPG, bool REFILL, bool FENCED = false, class Mid>
 __device__ __forceinline__ void up_round(uint4 (&raw)[2][kUpRing], uint32_t (&scr)[2][kUpRing / TPG], const gu4_t* wt,
                                          const gu16_t* sc, int srows, int round, const _Float16* xa, const float* cxg,
                                          const int (&ctok)[4], const BiasConst& bc, float (&out)[2][4], Mid&& mid) {
@@ -192,6 +193,7 @@ __device__ __forceinline__ void up_round(uint4 (&raw)[2][kUpRing], uint32_t (&sc
                 for (int st = 0; st < S; ++st)
                     acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[st], b[st], (tl == 0 && st == 0) ? zero : acc[i],
                                                                     0, 0, 0);
+                if constexpr (FENCED) __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll

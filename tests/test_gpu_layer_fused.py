@@ -45,6 +45,25 @@ def test_one_launch_layer_on_other_formats_and_without_shared_experts(name, N):
     _one_launch_case(VARIANTS[name], name, N, False)
 
 
+# one-token layers of more workgroups than two per compute unit hold (604 and 664 with five and six of the
+# Qwen-shaped experts) run the kernel of three waves per SIMD; one instantiation per pair of formats
+@pytest.mark.parametrize("bits,shared_bits,k", [(4, 4, 5), (4, 4, 6), (4, 8, 6), (8, 4, 6), (8, 8, 6)])
+def test_one_token_layer_of_more_workgroups_than_two_per_compute_unit(bits, shared_bits, k):
+    cfg = dataclasses.replace(_QWEN, name=f"qwen-k{k}-{bits}-{shared_bits}", k=k, bits=bits, shared_bits=shared_bits)
+    one, (x, lw, ln) = _one_launch_case(cfg, cfg.name, 1, False)
+    # hints: all right, one wrong, all wrong; y differs at most in the order of its fp32 sums
+    true = one.ids.cpu().numpy()[0].tolist()
+    others = [e for e in range(cfg.E) if e not in true]
+    y_ref = f32(one.y).astype(np.float64)
+    for h in (true, true[:1] + [others[0]] + true[2:], others[:k]):
+        print(f"  hint {h}", flush=True)
+        one.y.fill_(float("nan"))
+        layer_forward(cfg, lw, ln, x, one, one_launch=True, hint_ids=torch.tensor(h, dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        assert one.status() == 0
+        assert ffn_rel_err(f32(one.y), y_ref).max() <= 1e-5, h
+
+
 def _one_launch_case(cfg, name, N, last):
     print(f"case {name} N={N} last={last}", flush=True)
     x = gen_hidden(cfg, N, device=DEV)
@@ -93,6 +112,7 @@ def _one_launch_case(cfg, name, N, last):
     err = ffn_rel_err(f32(one.y), y_ref).max()
     print(f"  max row error vs oracle {err:.2e}")
     assert err <= 2e-3
+    return one, (x, lw, ln)
 
 
 def test_one_launch_layer_rejects_large_batches():
