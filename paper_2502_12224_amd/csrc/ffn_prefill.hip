@@ -79,6 +79,11 @@ __device__ __forceinline__ int tile_rows(int T, int most_log2) {
     return ((T + nt - 1) / nt + 31) & ~31;
 }
 
+// x to fp16 and the shared experts' gate, one workgroup per token, and before them one for the tile
+// tables: a serial chain of its own, it starts first and runs beside the conversion instead of after
+// that of token 0 (Qwen shape, whole passes: 13 tokens 367 -> 362 us for 6 layers, 131 tokens
+// 355 -> 352 and 512 tokens 559 -> 555 for 4).  A later piece of a layer processed in pieces finds x
+// and the gate values in place: it launches the tables' workgroup only.
 __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __restrict__ x, int N, int H, int E,
                                                            int n_shared, const int32_t* __restrict__ offsets,
                                                            const int32_t* __restrict__ order,
@@ -87,10 +92,12 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
                                                            int4* __restrict__ tab_up, int4* __restrict__ tab_down,
                                                            TileBlocks nb, PartSel sel) {
     __shared__ float red[4];
-    const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t = (int)blockIdx.x - 1, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nvec = H >> 3;
-    // (a later piece of a layer processed in pieces finds x and the gate values in place: only the tables change)
-    if (sel.first) {
+    if (t < 0) {
+        if (wave == 0) wave_tile_tables(offsets, order, E, n_shared, N, nb, sel, tab_up, tab_down);
+        return;
+    }
     const uint4* xr = reinterpret_cast<const uint4*>(x) + (size_t)t * nvec;
     uint4* xo = reinterpret_cast<uint4*>(xh) + (size_t)t * nvec;
     const uint4* gv = reinterpret_cast<const uint4*>(shared_gate);
@@ -120,10 +127,6 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
         if (lane == 0) red[wave] = acc;
         __syncthreads();
         if (tid == 0) sgate[t] = 1.0f / (1.0f + expf(-((red[0] + red[1]) + (red[2] + red[3]))));
-    }
-    }
-    if (t == 0 && wave == 0) {
-        wave_tile_tables(offsets, order, E, n_shared, N, nb, sel, tab_up, tab_down);
     }
 }
 
@@ -1190,7 +1193,7 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
         if (2.0 * routed + shared > 1.1 * kGemmSlots && routed + shared <= kGemmSlots) kw_r = 1;
     }
     if (do_up && !mode.layer) {
-        prefill_prep_kernel<<<sel.first ? d.N : 1, 256, 0, st>>>(da.x, d.N, d.H, d.E, d.n_shared, da.offsets,
+        prefill_prep_kernel<<<sel.first ? d.N + 1 : 1, 256, 0, st>>>(da.x, d.N, d.H, d.E, d.n_shared, da.offsets,
                                                                  da.order, da.shared_gate, ms.xh, ms.sgate, ms.tab_up, ms.tab_down,
                                                                  nb, sel);
         FATE_HIP(hipGetLastError());
