@@ -493,6 +493,15 @@ __device__ __forceinline__ f16x8_t code_step(const uint4& r, int k) {
     return __builtin_bit_cast(f16x8_t, v);
 }
 
+// a * b rounded to fp16 once.  Spelled out: from the plain expression the compiler makes this instruction in most copies
+// of the code below and, where it joins the ends of two copies, a product and a conversion, which round twice (about one
+// value in 2^15 differs) - the bits of h would hang on which kernels a copy is compiled into.
+__device__ __forceinline__ uint16_t half_of_product(float a, float b) {
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b));
+    return (uint16_t)r;
+}
+
 // Returns, the same in all waves, the rows that are not stored since one of their activations is infinite (or none): with
 // zero-points only, where an infinite activation times a code and times the zero-point's distance can have both signs.
 template <int BITS, bool ZP, bool UP, int NM, int R, int KW, bool QT, int BK, int HS = 1>
@@ -752,8 +761,8 @@ __device__ __forceinline__ uint32_t gemm_rows(const TileCtx& c, char* smem) {
                     if constexpr (UP) {
                         const float g = out[0][h][mb][j];
                         if (c.wlive[0])
-                            static_cast<__half*>(c.out)[row + c.wrow[0] + pair_place(h * 16 + n)] =
-                                __float2half(g / (1.0f + expf(-g)) * (out[1][h][mb][j]));
+                            static_cast<uint16_t*>(c.out)[row + c.wrow[0] + pair_place(h * 16 + n)] =
+                                half_of_product(g / (1.0f + expf(-g)), out[1][h][mb][j]);
                     } else {
 #pragma unroll
                         for (int i = 0; i < 2; ++i)

@@ -345,6 +345,24 @@ def test_layer_by_gemms_gives_the_bits_of_the_separate_calls(H, E, k, I, bits, g
         assert torch.equal(getattr(one, f), getattr(sep, f)), f
 
 
+@pytest.mark.parametrize("bits,shared_bits,group", [(4, 8, 128), (8, 4, 128), (8, 8, 128), (4, 4, 128), (4, 4, 64)])
+def test_layer_and_separate_calls_round_h_alike(bits, shared_bits, group):
+    """Both forms round h to fp16 once, in every copy of the code.  A row whose copy rounds to fp32 in between differs in
+    about one value of 2^15: eight tokens, 13312 values of h each, eight inputs."""
+    cfg = dataclasses.replace(SHAPES["tiny"], name="rounding", layers=1, H=512, E=16, k=2, I=1024, bits=bits, group=group,
+                              gate_var=1.0 / 512, n_shared=2, I_shared=5632, shared_bits=shared_bits)
+    lw = LayerWeights(cfg, 0, DEV)
+    one, sep = LayerBuffers(cfg, 8, DEV), LayerBuffers(cfg, 8, DEV)
+    for step in range(8):
+        print(f"int{bits} int{shared_bits} g{group} input {step}", flush=True)
+        x = gen_hidden(cfg, 8, step=step, device=DEV)
+        layer_forward(cfg, lw, None, x, one, one_launch=True)
+        layer_forward(cfg, lw, None, x, sep, one_launch=False)
+        torch.cuda.synchronize()
+        assert one.status() == 0
+        assert torch.equal(one.y, sep.y), (one.y != sep.y).any(1).nonzero().flatten().tolist()
+
+
 @pytest.mark.parametrize("H,E,k,I,group,n_shared,I_shared,N", [
     (512, 64, 6, 1408, 128, 2, 384, 8),            # about 35 experts: 814 tiles of 64 neurons, whole routed ones instead
     (1024, 48, 8, 1152, 64, 0, 0, 7),              # the same in groups of 64
