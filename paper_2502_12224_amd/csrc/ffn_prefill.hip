@@ -28,13 +28,13 @@
 // of the Mixtral shape, 271 -> 200 and 148 -> 124 us at 2048 tokens of the Qwen shape.
 #include <hip/hip_fp16.h>
 #include <algorithm>
-#include <cmath>
 #include <type_traits>
 #include "common.h"
 #include "qformat.h"
 #include "ffn_internal.h"
 #include "async_lds.h"
 #include "tile_table.h"
+#include "up_tiles.h"
 #include "route_device.h"
 
 namespace fate {
@@ -853,15 +853,16 @@ __device__ __forceinline__ void layer_outputs(const LayerOut& o, char* smem) {
 // MODE 0: prefill.  MODE 1: decode-sized (tiles of at most 16 rows, all in the few-row form), fp32 outputs of the down GEMM.
 // MODE 2: the same inside a decode layer (at most 8 tokens, 64 pairs): no tile table; a workgroup finds its
 // expert and rows by itself, the up GEMM's from the logits and the down GEMM's from the selection; rows of h
-// and of the outputs are pairs.  The up GEMM's first workgroup writes the layer's routing outputs.
-template <bool UP, int MODE, int KWR, int KWS>
+// and of the outputs are pairs.  The up GEMM's first workgroup writes the layer's routing outputs.  KW: waves over which its
+// columns are split; CHOOSE: routed tiles are whole where the number of named experts asks for it.
+template <bool UP, int MODE, int KW, bool CHOOSE>
 __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     extern __shared__ uint4 gemm_smem[];
     char* smem = reinterpret_cast<char*>(gemm_smem);
     __shared__ int32_t rowlist[MODE == 2 ? 8 : 1];
     constexpr bool EXACT = MODE != 0;
     const int lane = threadIdx.x & 63;
-    bool is_shared;
+    bool is_shared, whole = false;
     int local, e = 0, sbeg = 0, T = 0;
     if constexpr (MODE == 2) {
         int b = (int)blockIdx.x;
@@ -869,7 +870,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
             layer_outputs(a.lo, smem);
             return;
         }
-        const int kr = a.nb_r * (UP ? 1 : a.kp_r), ks = a.nb_s * (UP ? 1 : a.kp_s);
+        const int ks = a.nb_s * (UP ? 1 : a.kp_s);
         is_shared = b < a.n_shared * ks;
         if (is_shared) {
             e = b / ks;
@@ -877,8 +878,6 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
             T = a.N;
         } else {
             b -= a.n_shared * ks;
-            const int slot = b / kr;
-            local = b - slot * kr;
             // slot s is the s-th pair, in pair order, whose expert no earlier pair has
             const int P = a.N * a.k;
             int key;
@@ -902,6 +901,10 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
             const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
             const bool lead = key >= 0 && (same & lt) == 0;
             const unsigned long long leads = __ballot(lead);
+            if constexpr (CHOOSE) whole = up_tiles_whole(__popcll(leads), a.nb_r >> 1, a.n_shared * ks, kGemmSlots, a.H);
+            const int kr = CHOOSE && whole ? a.nb_r >> 1 : a.nb_r * (UP ? 1 : a.kp_r);
+            const int slot = __popcll(__ballot(lane * kr <= b)) - 1;      // b / kr (at most 64 slots)
+            local = b - slot * kr;
             const unsigned long long mine = __ballot(lead && __popcll(leads & lt) == slot);
             if (mine == 0) return;                        // fewer activated experts than slots
             const int l = __ffsll((long long)mine) - 1;
@@ -945,9 +948,9 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         local = b - first;
     }
     const int nb = is_shared ? a.nb_s : a.nb_r, kp = UP ? 1 : (is_shared ? a.kp_s : a.kp_r);
-    const int mb = local / (nb * kp);
+    const int mb = MODE == 2 ? 0 : local / (nb * kp);       // (a decode layer's experts have at most 8 rows)
     local -= mb * (nb * kp);
-    const int part = local / nb, nblk = local - part * nb;
+    const int part = MODE == 2 && UP ? 0 : local / nb, nblk = local - part * nb;
     const fate_qexpert* ex = (is_shared ? a.shared : a.experts) + e;
     const int trows = EXACT ? 1 << kExactTileRowsLog2 : tile_rows(T, is_shared ? a.rows_s : a.rows_r);
     const int row0 = mb * trows;
@@ -955,7 +958,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     c.ex = ex;
     c.nrows = min(trows, T - row0);
     // waves over which the columns are split, weight rows of the tile
-    const int kw = MODE != 2 || !UP ? 1 : KWR == KWS ? KWR : (is_shared ? KWS : KWR), bn = UP ? kBNUp / kw : kBNDown;
+    const int kw = whole ? 1 : KW, bn = UP ? kBNUp / kw : kBNDown;
     c.Nout = UP ? uniform(ex->I) : a.H;
     c.K = UP ? a.H : uniform(ex->I);
     if (c.nrows <= 0) return;
@@ -1024,12 +1027,9 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
         c.A += (size_t)out_row0 * c.lda;
     }
     if constexpr (MODE == 2) {
-        auto tile = [&](auto KW) {
-            if (bits == 4) rows_tile<4, false, UP, 1, 8, KW, true>(c, smem);
-            else rows_tile<8, false, UP, 1, 8, KW, true>(c, smem);
-        };
-        if (KWR == KWS || !is_shared) tile(std::integral_constant<int, KWR>{});
-        else tile(std::integral_constant<int, KWS>{});
+        if (CHOOSE && whole) rows_tile<4, false, UP, 1, 8, 1, true>(c, smem);       // (routed, of the layer's width: 4 bits)
+        else if (bits == 4) rows_tile<4, false, UP, 1, 8, KW, true>(c, smem);
+        else rows_tile<8, false, UP, 1, 8, KW, true>(c, smem);
     } else if constexpr (MODE == 1) {
         if (has_z && bits == 4) rows_tile<4, true, UP, 1, 16, 1, true>(c, smem);
         else if (has_z) rows_tile<2, true, UP, 1, 16, 1, true>(c, smem);
@@ -1045,9 +1045,9 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     }
 }
 
-template <bool UP, int MODE, int KWR, int KWS>
+template <bool UP, int MODE, int KW, bool CHOOSE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void grouped_gemm_kernel(GemmArgs a) {
-    grouped_gemm_body<UP, MODE, KWR, KWS>(a);
+    grouped_gemm_body<UP, MODE, KW, CHOOSE>(a);
 }
 
 // acc += wgt[i] * row i of src, columns c*V .. c*V + V - 1.  With few tokens the rows' latency is all there
@@ -1176,31 +1176,27 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
     const bool do_up = phase != 2, do_down = phase != 1;
     static bool attr_done = false;
     if (!attr_done) {
-#define FATE_GEMM_ATTR(UP, MODE, KWR, KWS)                                                                \
-    FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<UP, MODE, KWR, KWS>),  \
+#define FATE_GEMM_ATTR(...)                                                                 \
+    FATE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<__VA_ARGS__>),  \
                                  hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        FATE_GEMM_ATTR(true, 0, 1, 1) FATE_GEMM_ATTR(false, 0, 1, 1)
-        FATE_GEMM_ATTR(true, 1, 1, 1) FATE_GEMM_ATTR(false, 1, 1, 1)
-        FATE_GEMM_ATTR(true, 2, 1, 1) FATE_GEMM_ATTR(false, 2, 1, 1)
-        FATE_GEMM_ATTR(true, 2, 2, 2) FATE_GEMM_ATTR(true, 2, 1, 2)
+        FATE_GEMM_ATTR(true, 0, 1) FATE_GEMM_ATTR(false, 0, 1)
+        FATE_GEMM_ATTR(true, 1, 1) FATE_GEMM_ATTR(false, 1, 1)
+        FATE_GEMM_ATTR(true, 2, 1) FATE_GEMM_ATTR(false, 2, 1)
+        FATE_GEMM_ATTR(true, 2, 2) FATE_GEMM_ATTR(true, 2, 2, true)
 #undef FATE_GEMM_ATTR
         attr_done = true;
     }
     // Decode layer: the columns of the up projection are split over pairs of waves if they can be (whole stages of 128,
-    // whole groups): tiles of 64 neurons instead of 128.  Where those are more than the device holds at once, 4-bit routed
-    // experts keep whole tiles if then all are held: a second round's tiles would start, and select, when the first one's
-    // end (8 tokens of the DeepSeek shape, 814 tiles for 512 places or 429: up projection 33.1 -> 30.0 us; 8 of the Qwen
-    // shape 616 / 352, layer 47.3 -> 45.2 us; 5 of the DeepSeek shape 592 / 318, 51.9 -> 50.2; but with places to spare fewer
-    // tiles read slower: 2 of the Qwen shape 29.5 -> 34.0, 4 36.6 -> 37.6).
-    const bool can_split = mode.layer && d.H % 256 == 0 && (d.H / d.group) % 2 == 0 && (!d.n_shared || (d.H / d.shared_group) % 2 == 0);
-    int kw_r = can_split ? 2 : 1;
-    const int kw_s = kw_r;
-    if (can_split && d.bits == 4) {
-        // distinct experts of N draws of k out of E
-        const double distinct = d.E * (1.0 - std::pow(1.0 - (double)d.k / d.E, d.N));
-        const double routed = distinct * nb.r_up, shared = 2.0 * d.n_shared * nb.s_up;
-        if (2.0 * routed + shared > 1.1 * kGemmSlots && routed + shared <= kGemmSlots) kw_r = 1;
-    }
+    // whole groups), tiles of 64 neurons instead of 128; 4-bit routed experts go back to whole tiles where the workgroups
+    // count more experts than split ones have places for (up_tiles.h).  Where no count can ask for that: the kernel that
+    // does not choose.  Per layer, always split / chosen from an expected count of uniform routing / now: 8 tokens of the
+    // DeepSeek shape 60.8 / 57.0 / 56.9 us, of the Qwen shape 47.6 / 45.4 / 44.4, of that with a Zipf gate (13 experts
+    // instead of 22) 38.4 / 39.8 / 38.2; 2 of the Mixtral shape 76.7 / 80.0 / 76.7.
+    const int kw = mode.layer && d.H % 256 == 0 && (d.H / d.group) % 2 == 0 && (!d.n_shared || (d.H / d.shared_group) % 2 == 0) ? 2 : 1;
+    const unsigned shared_tiles = (unsigned)(kw * d.n_shared * nb.s_up);
+    bool choose = false;
+    long long tiles_r = mb_r * nb.r_up * kw;
+    if (kw == 2 && d.bits == 4) tiles_r = up_tiles_most((int)mb_r, nb.r_up, shared_tiles, kGemmSlots, d.H, &choose);
     if (do_up && !mode.layer) {
         prefill_prep_kernel<<<sel.first ? d.N + 1 : 1, 256, 0, st>>>(da.x, d.N, d.H, d.E, d.n_shared, da.offsets,
                                                                  da.order, da.shared_gate, ms.xh, ms.sgate, ms.tab_up, ms.tab_down,
@@ -1218,16 +1214,16 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
     if (do_up) {
         g.A_r = ms.xh; g.lda_r = d.H; g.A_s = ms.xh; g.lda_s = d.H; g.segs = ms.tab_up;
         g.out_r = da.h_r; g.ldo_r = da.ldh_r; g.out_s = da.h_s; g.ldo_s = da.ldh_s;
-        g.nb_r = nb.r_up * kw_r; g.nb_s = nb.s_up * kw_s;
+        g.nb_r = nb.r_up * kw; g.nb_s = nb.s_up * kw;
         g.kp_r = g.kp_s = 1;
-        const long long grid = mb_r * g.nb_r + d.n_shared * mb_s * g.nb_s + (mode.layer ? 1 : 0);
+        const long long grid = tiles_r + d.n_shared * mb_s * g.nb_s + (mode.layer ? 1 : 0);
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
         const unsigned ng = (unsigned)grid;
-        if (mode.layer && kw_r == 2) grouped_gemm_kernel<true, 2, 2, 2><<<ng, 256, kGemmLds, st>>>(g);
-        else if (mode.layer && kw_s == 2) grouped_gemm_kernel<true, 2, 1, 2><<<ng, 256, kGemmLds, st>>>(g);
-        else if (mode.layer) grouped_gemm_kernel<true, 2, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else if (exact) grouped_gemm_kernel<true, 1, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else grouped_gemm_kernel<true, 0, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        if (choose) grouped_gemm_kernel<true, 2, 2, true><<<ng, 256, kGemmLds, st>>>(g);
+        else if (mode.layer && kw == 2) grouped_gemm_kernel<true, 2, 2><<<ng, 256, kGemmLds, st>>>(g);
+        else if (mode.layer) grouped_gemm_kernel<true, 2, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else if (exact) grouped_gemm_kernel<true, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<true, 0, 1><<<ng, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
     }
     if (do_down) {
@@ -1240,9 +1236,9 @@ fate_status launch_ffn_mfma(hipStream_t st, const fate_ffn_desc& d, DecodeArgs d
         const long long grid = (mb_r * kp_r + d.n_shared * mb_s * kp_s) * nb_down;
         if (grid > 0x7fffffffLL) FATE_FAIL(FATE_ESHAPE, "too many tiles");
         const unsigned ng = (unsigned)grid;
-        if (mode.layer) grouped_gemm_kernel<false, 2, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else if (exact) grouped_gemm_kernel<false, 1, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
-        else grouped_gemm_kernel<false, 0, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        if (mode.layer) grouped_gemm_kernel<false, 2, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else if (exact) grouped_gemm_kernel<false, 1, 1><<<ng, 256, kGemmLds, st>>>(g);
+        else grouped_gemm_kernel<false, 0, 1><<<ng, 256, kGemmLds, st>>>(g);
         FATE_HIP(hipGetLastError());
         if (sel.last) {
             float* y32 = d.y_is_fp32 ? static_cast<float*>(y_out) : nullptr;

@@ -328,6 +328,12 @@ def test_permutation_divides_any_number_of_pairs_among_its_waves(tmp_path):
     _run_native(tmp_path, "perm_split")
 
 
+def test_tiles_of_the_decode_layer_follow_the_experts_that_are_named(tmp_path):
+    """Whole routed tiles are for layers whose split ones are more than the device holds at once; taken from the number of
+    experts that a uniform gate would name, they were chosen for skewed gates too, where they are slower."""
+    _run_native(tmp_path, "up_tiles")
+
+
 def test_keys_of_logits_are_in_the_order_of_the_logits(tmp_path):
     """The integers by which logits are ranked; both zeros are one."""
     _run_native(tmp_path, "float_order")

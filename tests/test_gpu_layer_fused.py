@@ -363,6 +363,40 @@ def test_layer_and_separate_calls_round_h_alike(bits, shared_bits, group):
         assert torch.equal(one.y, sep.y), (one.y != sep.y).any(1).nonzero().flatten().tolist()
 
 
+@pytest.mark.parametrize("H,E,k,I,bits,shared_bits,group,n_shared,I_shared,N,distinct,zipf,whole", [
+    (512, 64, 6, 1408, 4, 8, 128, 2, 384, 8, 8, 0.0, True),        # about 35 experts of 11 tiles
+    (512, 64, 6, 1408, 4, 8, 128, 2, 384, 8, 2, 0.0, False),       # the same call, tokens equal but for two: about 11
+    (1024, 48, 8, 1152, 4, 4, 64, 0, 0, 7, 7, 0.0, True),          # groups of 64
+    (512, 64, 6, 1536, 4, 4, 256, 1, 2048, 8, 8, 0.0, True),       # of 256: a group per range of columns
+    (512, 60, 4, 1408, 4, 4, 128, 1, 5632, 8, 8, 0.0, True),       # 88 shared tiles, a uniform gate ...
+    (512, 60, 4, 1408, 4, 4, 128, 1, 5632, 8, 8, 1.5, False),      # ... and a Zipf gate
+    (512, 64, 8, 2816, 4, 4, 128, 0, 0, 8, 8, 0.0, True),          # whole tiles beyond a round too
+    (4096, 64, 6, 1408, 4, 8, 128, 2, 384, 8, 8, 0.0, True),       # long rows: two rounds of split tiles, one of whole ones
+    (4096, 64, 6, 1408, 4, 8, 128, 2, 384, 8, 4, 0.0, False),
+])
+def test_layer_of_chosen_tiles_gives_the_bits_of_the_separate_calls(H, E, k, I, bits, shared_bits, group, n_shared, I_shared, N,
+                                                                    distinct, zipf, whole):
+    """Whole or split routed tiles by the number of experts that the tokens name: the same bits, and both are met."""
+    cfg = dataclasses.replace(SHAPES["tiny"], name="tiles", layers=1, H=H, E=E, k=k, I=I, bits=bits, group=group,
+                              gate_var=1.0 / H, n_shared=n_shared, I_shared=I_shared, shared_bits=shared_bits, zipf_s=zipf)
+    print(f"case {H} {E} {k} {I} g{group} N={N} distinct {distinct} zipf {zipf}", flush=True)
+    x = gen_hidden(cfg, N, device=DEV)
+    x = x[:distinct].repeat(N // distinct + 1, 1)[:N].contiguous()
+    lw = LayerWeights(cfg, 0, DEV)
+    one, sep = LayerBuffers(cfg, N, DEV), LayerBuffers(cfg, N, DEV)
+    layer_forward(cfg, lw, None, x, one, one_launch=True)
+    layer_forward(cfg, lw, None, x, sep, one_launch=False)
+    torch.cuda.synchronize()
+    assert one.status() == 0
+    # the side of the line that this case is meant for
+    named = int((one.counts > 0).sum())
+    tiles, shared = (I + 127) // 128, 2 * n_shared * ((I_shared + 127) // 128)
+    split, whole_tiles = 2 * named * tiles + shared, named * tiles + shared
+    assert (split > 512 if H <= 3072 else split > 768 and whole_tiles <= 512) == whole, (named, split, whole_tiles)
+    for f in ROUTE_FIELDS + ("y",):
+        assert torch.equal(getattr(one, f), getattr(sep, f)), f
+
+
 @pytest.mark.parametrize("H,E,k,I,group,n_shared,I_shared,N", [
     (512, 64, 6, 1408, 128, 2, 384, 8),            # about 35 experts: 814 tiles of 64 neurons, whole routed ones instead
     (1024, 48, 8, 1152, 64, 0, 0, 7),              # the same in groups of 64
