@@ -598,7 +598,6 @@ __device__ __forceinline__ void b1_down_role(const B1Args& A, int part, int rb, 
 template <int BR, int TR, int BS, int TS, int WPE>
 __global__ __launch_bounds__(kLayerThreads) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void moe_layer_decode_b1_kernel(B1Args A) {
     extern __shared__ uint4 smem[];
-    __shared__ FusedRouteSmem rsm;
     char* dyn = reinterpret_cast<char*>(smem);
     const LayerArgs& a = A.a;
     uint32_t tag = (uint32_t)ld_dev(a.sync) + 1u;
@@ -606,7 +605,7 @@ __global__ __launch_bounds__(kLayerThreads) __attribute__((amdgpu_waves_per_eu(W
     int b = blockIdx.x;
     const int nd = A.nparts * A.nrb;
     if (b < a.nb_route) {
-        route_role(a, b, tag, dyn, rsm);
+        route_role(a, b, tag, dyn + sizeof(FusedRouteSmem), *reinterpret_cast<FusedRouteSmem*>(dyn));
     } else if ((b -= a.nb_route) < A.n_up_s) {
         b1_up_role<BR, TR, BS, TS, WPE, false>(A, b, true, tag, dyn);
     } else if ((b -= A.n_up_s) < A.n_up_r) {
@@ -628,7 +627,8 @@ __global__ __launch_bounds__(kLayerThreads) __attribute__((amdgpu_waves_per_eu(W
 static bool b1_format(int bits, int group) { return (bits == 4 && group == 128) || (bits == 8 && group == 128); }
 
 static int b1_lds_bytes(const fate_ffn_desc& d) {
-    return std::max(work_lds(1, d.H, d.E, d.k).bytes, b1_down_lds(d.E, d.k).bytes);
+    return std::max({work_lds(1, d.H, d.E, d.k).bytes, b1_down_lds(d.E, d.k).bytes,
+                     (int)sizeof(FusedRouteSmem) + 2 * d.E * 4});      // (a routing block: its selection, the logits of both gates)
 }
 
 template <int BR, int TR, int BS, int TS>
@@ -710,9 +710,10 @@ bool b1_plan(const fate_ffn_desc& d, const LayerArgs& a, B1Args* b, int* nblocks
     *nblocks = a.nb_route + b->n_up_s + b->n_up_r + b->nparts * b->nrb;
     // The routing blocks and the shared experts' up blocks must be on the device from the start
     // (their requests do not wait for anything); the other blocks have nothing to do before the
-    // logits exist and may start as earlier blocks leave (a block only waits for lower ids) - the
-    // down blocks then ask for their shared W2 pieces later, nothing else changes.  A launch
-    // several times larger than the device is left to the general kernel.
+    // logits exist and may start as earlier blocks leave (a block only waits for lower ids).  What
+    // that costs the down blocks, which ask for their W2 pieces only then, is why larger launches
+    // run three blocks per compute unit (see the launch).  A launch several times larger than the
+    // device is left to the general kernel.
     const int resident = b1_resident_blocks(d);
     const int early = a.nb_route + b->n_up_s;
     return resident > 0 && early <= resident && *nblocks <= 2 * resident;
@@ -723,10 +724,20 @@ fate_status launch_layer_decode_b1(hipStream_t st, const fate_ffn_desc& d, const
     const int lds = b1_lds_bytes(d);
     // Workgroups beyond two per compute unit would start as earlier ones leave, and the down blocks
     // among them would ask for their weights only then: such launches take the kernel of three waves
-    // per SIMD.  64 experts, 6 selected, H 2048, 576 workgroups: 22.1 us a layer with two, 18.1 with
-    // three.  It has 168 registers instead of 256 and therefore multiplies tile by tile, one
-    // accumulator at a time, which costs where nothing has to wait: 60 experts, 4 selected, 496
-    // workgroups: 17.3 us with two, 17.5 with three.  Same sums, same order, same bits.
+    // per SIMD (155 to 168 registers).  It multiplies tile by tile, one accumulator at a time, which
+    // costs where nothing has to wait.  Same sums, same order, same bits.  us a layer with two / with
+    // three, H 2048, routed / shared widths:
+    //   422 to 510 workgroups    4/4 16.8 / 16.9, 17.2 / 17.4; 8/4 16.4 / 16.5
+    //   550 to 576               4/8 20.3 / 18.3, 21.2 / 18.5; 8/8 21.2 / 18.2
+    //   638 to 662               4/4 28.8 / 20.0; 4/8 27.4 / 19.3; 8/4 23.8 / 19.0; 8/8 29.8 / 22.2
+    //   726 to 854               4/4 36.0 / 25.4; 4/8 33.5 / 22.3; 8/4 35.6 / 27.8; 8/8 40.0 / 32.0
+    // With hints: 422 to 510 17.8 / 18.0, 19.0 / 19.2; 576 22.0 / 20.7; 638 23.3 / 20.0 to 29.2 / 23.6.  Where LDS has room
+    // for two only (more than about 53 KB each: E = 256 from H = 6144, E = 128 from 8192) three waves are
+    // no slower, since they spill nothing: H 6144, E 256, 640 workgroups 31.9 / 32.1; E 192, 672: 39.1 / 38.6; H 8192,
+    // E 128, 704: 39.7 / 38.4.  So the line is the number of workgroups alone.
+    // The selection's LDS of the one block that needs it (13.5 KB) lies in the others' room; as static LDS it kept
+    // the third workgroup out from H = 4096 or E = 256 on: H 4096, E 128, 8 selected, I 1152, 952 workgroups 49.4 -> 41.9;
+    // H 8192, E 16, 648: 37.6 -> 31.3; H 4096, E 192, 544: 25.9 -> 24.9 (two: 24.9, 25.5 with static LDS).
     const bool three = nblocks > b1_resident_blocks(d);
 #define FATE_B1_LAUNCH(BR, TR, BS, TS) \
     if (!three) moe_layer_decode_b1_kernel<BR, TR, BS, TS, 2><<<nblocks, kLayerThreads, lds, st>>>(b); \

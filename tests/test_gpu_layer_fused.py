@@ -45,11 +45,38 @@ def test_one_launch_layer_on_other_formats_and_without_shared_experts(name, N):
     _one_launch_case(VARIANTS[name], name, N, False)
 
 
-# one-token layers of more workgroups than two per compute unit hold (604 and 664 with five and six of the
-# Qwen-shaped experts) run the kernel of three waves per SIMD; one instantiation per pair of formats
+def _one_token_workgroups(cfg):
+    """Workgroups of a one-token layer with both gates: the gates' rows, 32 neurons of every expert, 32 outputs of every
+    part of the down projection (pieces of at most 768 columns of int4 or 384 of int8, four a workgroup).  The kernel of
+    three waves per SIMD takes launches of more than 512."""
+    pieces = lambda I, bits: -(-I // (768 if bits == 4 else 384))
+    parts = -(-max(cfg.n_shared * pieces(cfg.I_shared, cfg.shared_bits), cfg.k * pieces(cfg.I, cfg.bits)) // 4)
+    return 2 * cfg.E // 4 + cfg.n_shared * cfg.I_shared // 32 + cfg.k * cfg.I // 32 + parts * cfg.H // 32
+
+
+# one-token layers of more workgroups than two per compute unit hold (618 and 662 with five and six of the
+# Qwen-shaped experts, 726 to 854 with 8-bit ones) run the kernel of three waves per SIMD; one instantiation per pair of formats
 @pytest.mark.parametrize("bits,shared_bits,k", [(4, 4, 5), (4, 4, 6), (4, 8, 6), (8, 4, 6), (8, 8, 6)])
 def test_one_token_layer_of_more_workgroups_than_two_per_compute_unit(bits, shared_bits, k):
     cfg = dataclasses.replace(_QWEN, name=f"qwen-k{k}-{bits}-{shared_bits}", k=k, bits=bits, shared_bits=shared_bits)
+    assert _one_token_workgroups(cfg) > 512
+    _one_token_case_with_hints(cfg)
+
+
+# the kernel of two waves per SIMD, of every pair of formats; with three, the largest tables and selections
+@pytest.mark.parametrize("bits,shared_bits,k,I_shared,E,workgroups", [
+    (4, 4, 4, 5632, 60, 510), (4, 8, 2, 1408, 60, 226), (8, 4, 2, 1408, 60, 290), (8, 8, 4, 1408, 60, 506),
+    (4, 4, 8, 1408, 256, 780),
+])
+def test_one_token_layer_on_both_sides_of_two_workgroups_per_compute_unit(bits, shared_bits, k, I_shared, E, workgroups):
+    cfg = dataclasses.replace(_QWEN, name=f"qwen-{bits}-{shared_bits}-k{k}-{I_shared}-{E}", k=k, bits=bits, shared_bits=shared_bits,
+                              I_shared=I_shared, E=E)
+    assert _one_token_workgroups(cfg) == workgroups
+    _one_token_case_with_hints(cfg)
+
+
+def _one_token_case_with_hints(cfg):
+    k = cfg.k
     one, (x, lw, ln) = _one_launch_case(cfg, cfg.name, 1, False)
     # hints: all right, one wrong, all wrong; y differs at most in the order of its fp32 sums
     true = one.ids.cpu().numpy()[0].tolist()
