@@ -183,12 +183,14 @@ def test_one_launch_layer_with_outlier_activations(name, N):
     assert err <= 2e-3
 
 @pytest.mark.parametrize("name,N,how", [("qwen", 1, "null"), ("qwen", 6, "null"), ("mixtral", 1, "null"),
-                                        ("qwen", 1, "zero_points"), ("qwen", 6, "zero_points")])
+                                        ("qwen", 1, "zero_points"), ("qwen", 6, "zero_points"),
+                                        ("deepseek", 1, "null"), ("deepseek", 1, "zero_points")])
 def test_one_launch_layer_with_an_expert_that_is_not_resident(name, N, how):
     """An activated expert whose table entry holds NULL pointers, or is stored in a format the one-launch
     layer does not read (here: with zero-points): status bit 0 is raised, its pairs contribute nothing,
-    everything else is as usual (one-item and looping kernels)."""
+    everything else is as usual (one-token kernels of two and three waves per SIMD, GEMMs)."""
     cfg = SHAPES[name]
+    assert N > 1 or name == "mixtral" or (_one_token_workgroups(cfg) > 512) == (name == "deepseek")
     print(f"case {name} N={N} one expert absent ({how})", flush=True)
     x = gen_hidden(cfg, N, device=DEV)
     lw = LayerWeights(cfg, 0, DEV)
