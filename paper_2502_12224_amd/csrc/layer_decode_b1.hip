@@ -713,8 +713,12 @@ bool b1_plan(const fate_ffn_desc& d, const LayerArgs& a, B1Args* b, int* nblocks
     // logits exist and may start as earlier blocks leave (a block only waits for lower ids).  What
     // that costs the down blocks, which ask for their W2 pieces only then, is why larger launches
     // run three blocks per compute unit (see the launch).  A launch several times larger than the
-    // device is left to the general kernel.
-    const int resident = b1_resident_blocks(d);
+    // device is left to the general kernel, and so is one of more than 66 KB of LDS per block that
+    // two per compute unit do not hold (H 8192, E 256, 4 selected, I 1024, 768 blocks: 40.7 us a layer, 38.7 by
+    // the general path; 8-bit, I 768: 42.1 and 40.6).
+    int resident = b1_resident_blocks(d);
+    const int lds = b1_lds_bytes(d);
+    if (lds > 66 * 1024 && lds <= 80 * 1024) resident /= 2;
     const int early = a.nb_route + b->n_up_s;
     return resident > 0 && early <= resident && *nblocks <= 2 * resident;
 }
