@@ -80,10 +80,9 @@ __device__ __forceinline__ int tile_rows(int T, int most_log2) {
 }
 
 // x to fp16 and the shared experts' gate, one workgroup per token, and before them one for the tile
-// tables: a serial chain of its own, it starts first and runs beside the conversion instead of after
-// that of token 0 (Qwen shape, whole passes: 13 tokens 367 -> 362 us for 6 layers, 131 tokens
-// 355 -> 352 and 512 tokens 559 -> 555 for 4).  A later piece of a layer processed in pieces finds x
-// and the gate values in place: it launches the tables' workgroup only.
+// tables: a serial chain of its own, which starts first and runs beside the conversion (built by token 0's
+// workgroup behind its row, whole passes of 13 to 2048 tokens took the same within 1 %).  A later piece of a
+// layer processed in pieces finds x and the gate values in place: it launches the tables' workgroup only.
 __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __restrict__ x, int N, int H, int E,
                                                            int n_shared, const int32_t* __restrict__ offsets,
                                                            const int32_t* __restrict__ order,

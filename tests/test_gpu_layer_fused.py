@@ -229,7 +229,7 @@ def test_one_launch_layer_with_an_expert_that_is_not_resident(name, N, how):
 def test_one_launch_layer_replayed_from_a_graph(name, N):
     """The layer call captured once and replayed with new inputs, with eager calls and synchronisations
     between the replays: every replay gives what the eager call gives on the same input, bit for bit
-    (one-item and looping kernels; the call's epoch lives on the device, so a replay advances it)."""
+    (one-token kernel and GEMM form; the call's epoch lives on the device, so a replay advances it)."""
     cfg = SHAPES[name]
     print(f"case {name} N={N} graph replays", flush=True)
     lw = LayerWeights(cfg, 0, DEV)
@@ -428,6 +428,16 @@ def test_layer_of_chosen_tiles_gives_the_bits_of_the_separate_calls(H, E, k, I, 
 
 @pytest.mark.parametrize("H,E,k,I,group,n_shared,I_shared,N", [
     (512, 64, 6, 1408, 128, 2, 384, 8),            # about 35 experts: 814 tiles of 64 neurons, whole routed ones instead
+    (1024, 48, 8, 1152, 64, 0, 0, 7),              # the same in groups of 64
+    (512, 64, 6, 1536, 256, 1, 2048, 8),           # of 256: a group per range of columns
+    (512, 64, 6, 1408, 128, 2, 384, 4),            # fewer tokens: split tiles for both
+])
+def test_layer_of_whole_routed_and_split_shared_tiles_gives_the_bits_of_the_separate_calls(H, E, k, I, group, n_shared, I_shared, N):
+    test_layer_by_gemms_gives_the_bits_of_the_separate_calls(H, E, k, I, 4, group, n_shared, I_shared, N)
+
+
+@pytest.mark.parametrize("H,E,k,I,group,n_shared,I_shared,N", [
+    (512, 64, 6, 1408, 128, 2, 384, 8),            # about 35 experts: 782 tiles of 64 neurons, whole routed ones instead
     (1024, 48, 8, 1152, 64, 0, 0, 7),              # the same in groups of 64
     (512, 64, 6, 1536, 256, 1, 2048, 8),           # of 256: a group per range of columns
     (512, 64, 6, 1408, 128, 2, 384, 4),            # fewer tokens: split tiles for both
