@@ -14,7 +14,7 @@ Workloads (all synthetic, seeded):
                          experts in pinned host memory, a fraction cached on the
                          device: one prefill pass, then decode steps with the cache
                          step issuing H2D copies on a side stream.
-Prints one JSON line (see the design doc for the fields).
+Prints one JSON line.
 """
 import argparse
 import ctypes as C
@@ -347,20 +347,20 @@ def bench_decode(args):
 
 DECODE_WORKLOADS = {
     # name: (shape, batch, decode steps cycled, description); every expert resident on the device
-    "qwen_decode": ("qwen", 1, 128, "configs[1]: Qwen1.5-MoE-shaped decode, 24 layers chained, batch 1, "
+    "qwen_decode": ("qwen", 1, 128, "Qwen1.5-MoE-shaped decode, 24 layers chained, batch 1, "
                                     "60 experts top-4 (I=1408) + gated shared expert (I=5632), int4 g128"),
-    "deepseek_decode8": ("deepseek", 8, 64, "configs[3]: DeepSeek-MoE-16B-shaped decode, 28 layers chained, batch 8, "
+    "deepseek_decode8": ("deepseek", 8, 64, "DeepSeek-MoE-16B-shaped decode, 28 layers chained, batch 8, "
                                             "all experts resident"),
-    "mixtral_decode": ("mixtral", 1, 128, "configs[4]: Mixtral-8x7B-shaped decode, 32 layers chained, batch 1, "
+    "mixtral_decode": ("mixtral", 1, 128, "Mixtral-8x7B-shaped decode, 32 layers chained, batch 1, "
                                           "all experts resident"),
 }
 
 PREFILL_WORKLOADS = {
     # name: (shape, tokens, description)
-    "qwen_prefill512": ("qwen_prefill", 512, "configs[2]: Qwen1.5-MoE-shaped prefill, 512 tokens, Zipf(1.1) routing"),
-    "qwen_prefill2048": ("qwen_prefill", 2048, "configs[2]: Qwen1.5-MoE-shaped prefill, 2048 tokens, Zipf(1.1) routing"),
-    "deepseek_prefill1024": ("deepseek", 1024, "configs[3]: DeepSeek-MoE-16B-shaped prefill, 1024 tokens, all experts resident"),
-    "mixtral_prefill2048": ("mixtral", 2048, "configs[4]: Mixtral-8x7B-shaped prefill, 2048 tokens, all experts resident"),
+    "qwen_prefill512": ("qwen_prefill", 512, "Qwen1.5-MoE-shaped prefill, 512 tokens, Zipf(1.1) routing"),
+    "qwen_prefill2048": ("qwen_prefill", 2048, "Qwen1.5-MoE-shaped prefill, 2048 tokens, Zipf(1.1) routing"),
+    "deepseek_prefill1024": ("deepseek", 1024, "DeepSeek-MoE-16B-shaped prefill, 1024 tokens, all experts resident"),
+    "mixtral_prefill2048": ("mixtral", 2048, "Mixtral-8x7B-shaped prefill, 2048 tokens, all experts resident"),
 }
 
 
@@ -534,10 +534,10 @@ def bench_prefill(args, emit=True):
 OFFLOAD_WORKLOADS = {
     # name: (shape, prefill tokens, decode batch, decode steps, description)
     "deepseek_offload": ("deepseek", 1024, 8, 64,
-                         "configs[3]: DeepSeek-MoE-16B-shaped, routed experts in pinned host memory, 30% of them "
+                         "DeepSeek-MoE-16B-shaped, routed experts in pinned host memory, 30% of them "
                          "cached on the device (3 shallow layers full); prefill 1024 tokens, then decode batch 8"),
     "mixtral_offload": ("mixtral", 2048, 1, 128,
-                        "configs[4]: Mixtral-8x7B-shaped, experts in pinned host memory, 25% cached on the device; "
+                        "Mixtral-8x7B-shaped, experts in pinned host memory, 25% cached on the device; "
                         "prefill 2048 tokens, then decode batch 1"),
 }
 

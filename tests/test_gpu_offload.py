@@ -116,14 +116,14 @@ def _offload_case(cfg, L, cache_total, L_shallow, n_max, N, steps, check_steps):
 
 
 def test_offloaded_deepseek_shape_against_both_oracles():
-    """configs[3] geometry on five layers: one fully cached shallow layer and four deep layers with the
+    """The DeepSeek shape on five layers: one fully cached shallow layer and four deep layers with the
     14 / 13 slots the 30 % budget gives the real 28-layer stack; 4.46 MB experts, batch 8."""
     cfg = SHAPES["deepseek"]
     _offload_case(cfg, L=5, cache_total=64 + 14 + 14 + 13 + 13, L_shallow=1, n_max=8, N=8, steps=5, check_steps=2)
 
 
 def test_offloaded_mixtral_shape_against_both_oracles():
-    """configs[4] geometry on three layers: 90.8 MB experts, one shallow layer full and two of eight
+    """The Mixtral shape on three layers: 90.8 MB experts, one shallow layer full and two of eight
     experts cached in each deep layer (25 %), batch 1."""
     cfg = SHAPES["mixtral"]
     _offload_case(cfg, L=3, cache_total=8 + 2 + 2, L_shallow=1, n_max=1, N=1, steps=6, check_steps=2)

@@ -47,21 +47,17 @@ def default_m(E: int, k: int) -> int:
 
 
 SHAPES = {
-    # configs[0]
     "tiny": MoEShape("tiny", layers=2, H=256, E=8, k=2, I=512, bits=8, group=64,
                      renorm=True, gate_var=1.0 / 256, seed=0),
-    # configs[1] / configs[2]
     "qwen": MoEShape("qwen", layers=24, H=2048, E=60, k=4, I=1408, bits=4, group=128,
                      n_shared=1, I_shared=5632, shared_bits=4, shared_gate=True,
                      renorm=False, gate_var=1.0 / 2048, bias_std=0.5, seed=1),
     "qwen_prefill": MoEShape("qwen_prefill", layers=24, H=2048, E=60, k=4, I=1408, bits=4, group=128,
                              n_shared=1, I_shared=5632, shared_bits=4, shared_gate=True,
                              renorm=False, gate_var=1.0 / 2048, zipf_s=1.1, seed=2),
-    # configs[3]
     "deepseek": MoEShape("deepseek", layers=28, H=2048, E=64, k=6, I=1408, bits=4, group=128,
                          n_shared=2, I_shared=1408, shared_bits=8, shared_gate=False,
                          renorm=False, gate_var=1.0 / 2048, seed=3, cache_frac=0.30),
-    # configs[4]
     "mixtral": MoEShape("mixtral", layers=32, H=4096, E=8, k=2, I=14336, bits=4, group=128,
                         renorm=True, gate_var=1.0 / 4096, seed=4, cache_frac=0.25),
 }
