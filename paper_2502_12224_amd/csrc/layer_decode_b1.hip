@@ -605,7 +605,12 @@ __global__ __launch_bounds__(kLayerThreads) __attribute__((amdgpu_waves_per_eu(W
     int b = blockIdx.x;
     const int nd = A.nparts * A.nrb;
     if (b < a.nb_route) {
-        route_role(a, b, tag, dyn + sizeof(FusedRouteSmem), *reinterpret_cast<FusedRouteSmem*>(dyn));
+        if constexpr (WPE == 2) {
+            __shared__ FusedRouteSmem rsm;
+            route_role(a, b, tag, dyn, rsm);
+        } else {
+            route_role(a, b, tag, dyn + sizeof(FusedRouteSmem), *reinterpret_cast<FusedRouteSmem*>(dyn));
+        }
     } else if ((b -= a.nb_route) < A.n_up_s) {
         b1_up_role<BR, TR, BS, TS, WPE, false>(A, b, true, tag, dyn);
     } else if ((b -= A.n_up_s) < A.n_up_r) {
@@ -712,13 +717,10 @@ bool b1_plan(const fate_ffn_desc& d, const LayerArgs& a, B1Args* b, int* nblocks
     // (their requests do not wait for anything); the other blocks have nothing to do before the
     // logits exist and may start as earlier blocks leave (a block only waits for lower ids).  What
     // that costs the down blocks, which ask for their W2 pieces only then, is why larger launches
-    // run three blocks per compute unit (see the launch).  A launch several times larger than the
-    // device is left to the general kernel, and so is one of more than 66 KB of LDS per block that
-    // two per compute unit do not hold (H 8192, E 256, 4 selected, I 1024, 768 blocks: 40.7 us a layer, 38.7 by
-    // the general path; 8-bit, I 768: 42.1 and 40.6).
-    int resident = b1_resident_blocks(d);
-    const int lds = b1_lds_bytes(d);
-    if (lds > 66 * 1024 && lds <= 80 * 1024) resident /= 2;
+    // run three blocks per compute unit (see the launch).  A launch several times larger than what the
+    // kernel of two holds is left to the general kernel (H 8192, E 256, 4 selected, I 1024, 768 blocks of 85 KB: 40.7 us a layer
+    // here, 38.7 there; 8-bit, I 768: 42.1 and 40.6).
+    const int resident = b1_resident_blocks(d);
     const int early = a.nb_route + b->n_up_s;
     return resident > 0 && early <= resident && *nblocks <= 2 * resident;
 }
@@ -737,11 +739,11 @@ fate_status launch_layer_decode_b1(hipStream_t st, const fate_ffn_desc& d, const
     //   726 to 854               4/4 36.0 / 25.4; 4/8 33.5 / 22.3; 8/4 35.6 / 27.8; 8/8 40.0 / 32.0
     // With hints: 422 to 510 17.8 / 18.0, 19.0 / 19.2; 576 22.0 / 20.7; 638 23.3 / 20.0 to 29.2 / 23.6.  Where LDS has room
     // for two only (more than about 53 KB each: E = 256 from H = 6144, E = 128 from 8192) three waves are
-    // no slower, since they spill nothing: H 6144, E 256, 640 workgroups 31.9 / 32.1; E 192, 672: 39.1 / 38.6; H 8192,
-    // E 128, 704: 39.7 / 38.4.  So the line is the number of workgroups alone.
-    // The selection's LDS of the one block that needs it (13.5 KB) lies in the others' room; as static LDS it kept
+    // no slower, since they spill nothing: H 6144, E 256, 640 workgroups 33.4 / 32.1; E 192, 672: 39.3 / 38.6; H 8192,
+    // E 128, 704: 40.5 / 38.4.  So the line is the number of workgroups alone.
+    // There the selection's LDS of the one block that needs it (13.5 KB) lies in the others' room; as static LDS it kept
     // the third workgroup out from H = 4096 or E = 256 on: H 4096, E 128, 8 selected, I 1152, 952 workgroups 49.4 -> 41.9;
-    // H 8192, E 16, 648: 37.6 -> 31.3; H 4096, E 192, 544: 25.9 -> 24.9 (two: 24.9, 25.5 with static LDS).
+    // H 8192, E 16, 648: 37.6 -> 31.3; H 4096, E 192, 544: 25.9 -> 24.9 (two: 25.5).
     const bool three = nblocks > b1_resident_blocks(d);
 #define FATE_B1_LAUNCH(BR, TR, BS, TS) \
     if (!three) moe_layer_decode_b1_kernel<BR, TR, BS, TS, 2><<<nblocks, kLayerThreads, lds, st>>>(b); \
