@@ -741,7 +741,7 @@ fate_status launch_layer_decode_b1(hipStream_t st, const fate_ffn_desc& d, const
     // for two only (more than about 53 KB each: E = 256 from H = 6144, E = 128 from 8192) three waves are
     // no slower, since they spill nothing: H 6144, E 256, 640 workgroups 33.4 / 32.1; E 192, 672: 39.3 / 38.6; H 8192,
     // E 128, 704: 40.5 / 38.4.  So the line is the number of workgroups alone.
-    // There the selection's LDS of the one block that needs it (13.5 KB) lies in the others' room; as static LDS it kept
+    // In the kernel of three the selection's LDS of the one block that needs it (13.5 KB) lies in the others' room; as static LDS it kept
     // the third workgroup out from H = 4096 or E = 256 on: H 4096, E 128, 8 selected, I 1152, 952 workgroups 49.4 -> 41.9;
     // H 8192, E 16, 648: 37.6 -> 31.3; H 4096, E 192, 544: 25.9 -> 24.9 (two: 25.5).
     const bool three = nblocks > b1_resident_blocks(d);
